@@ -49,12 +49,8 @@ struct StencilArgs {
   T omega;
   double* part;  // sums at [0, np), maxima at [np, 2 np)
   int np;
-  // exchange list, read by group tiles (levels whose launch finishes shared DoFs)
-  const int32_t* xptr;
-  const Copy* xcopies;
-  const int64_t* xcidx;
-  const double* xinv;
-  const float* xinvf;
+  const FaceDev* faces;   // 3D face and edge tiles
+  const EdgeCopy* edges;
 };
 
 // exchange_kernel / iface_kernel: groups of copies of macro-boundary DoFs.
@@ -257,11 +253,8 @@ StencilArgs<T> stencil_args(const Level& L, const void* x, void* y, const void* 
   a.omega = (T)omega;
   a.part = part;
   a.np = (int)L.n_partials(dt);
-  a.xptr = L.dev.xgrp_ptr;
-  a.xcopies = L.dev.xcopies;
-  a.xcidx = L.dev.xcpidx;
-  a.xinv = L.dev.xgrp_invdiag;
-  a.xinvf = L.dev.xgrp_invdiagf;
+  a.faces = L.dev.faces;
+  a.edges = L.dev.edges;
   return a;
 }
 
@@ -285,7 +278,7 @@ GroupArgs<T> exchange_args(const Level& L, const void* x, void* y, const void* b
   return g;
 }
 inline int exchange_blocks(const Level& L) { return (int)L.xgroup_blocks(); }
-// stencil passes of levels whose launch finishes shared DoFs need no exchange launch
+// 3D stencil passes finish shared DoFs themselves: no exchange launch
 inline bool exchange_in_launch(const Level& L) { return L.xfused; }
 
 template <typename T>
@@ -442,7 +435,7 @@ struct BatchOp {
   int kind, dtype, dim, mode;
   int nseg, nwg;
   int64_t args_off, wg0_off;
-  int variant;  // stencil ops: 3D tile shape of the members' levels (kPenZ or kPenSeg); tail ops: dynamic LDS bytes
+  int variant;  // 3D stencil ops: rows per band (shape3); tail ops: dynamic LDS bytes
   int pad_;
 };
 

@@ -13,6 +13,30 @@
 
 namespace mf {
 
+// A launch of one request (nwg workgroups), and one over a batch op's table.
+template <class A>
+Launch<A> single(const A& a, int nwg) {
+  Launch<A> l{};
+  l.one = a;
+  l.nseg = 0;
+  l.nwg = nwg;
+  return l;
+}
+template <class A>
+Launch<A> batched(const BatchOp& op, const char* table) {
+  Launch<A> l{};
+  l.many = (const A*)(table + op.args_off);
+  l.wg0 = (const int32_t*)(table + op.wg0_off);
+  l.nseg = op.nseg;
+  l.nwg = op.nwg;
+  return l;
+}
+
+// 3D stencil launch (stencil3d_kernels.hip): every row of the level in one
+// launch.  mode as launch_stencil; R: rows per band (shape3).
+int launch_stencil3(int mode, int R, const Launch<StencilArgs<double>>& l, hipStream_t s);
+int launch_stencil3(int mode, int R, const Launch<StencilArgs<float>>& l, hipStream_t s);
+
 // One launch of the whole operator: interior rows of every macro (wave
 // tiles) and macro-boundary rows (interface groups).  mode: kApply, kJacobi,
 // kResidual, kNormB.  part (nullable; kResidual / kNormB) receives sums of

@@ -21,6 +21,8 @@ struct LevelDev {
   MacroDev* md = nullptr;
   Tile* tiles = nullptr;       // interior wave tiles, padded to a multiple of kWavesPerWG
   Tile* tiles_f32 = nullptr;   // 2D FP32 wave tiles
+  FaceDev* faces = nullptr;    // 3D macro faces
+  EdgeCopy* edges = nullptr;   // 3D copies of macro edge and vertex DoFs
   Tile* segs = nullptr;        // row segments of 64 points covering every storage point
   Tile* psegs = nullptr;       // slice segments: 64 consecutive storage points of one slice
   int32_t* sbase = nullptr;    // first macro-local index of each slice z = 0 .. N + 1 (3D)
@@ -50,13 +52,14 @@ struct LevelDev {
 struct Level {
   int level = 0;
   int N = 0;
-  int pen_z = 0;  // 3D tile shape: pencils of kPenZ slices, or runs of slice segments (kPenSeg)
-  bool xfused = false;  // the stencil launch finishes shared DoFs (group tiles; slice-run levels): no exchange launch
+  bool xfused = false;  // 3D: the stencil launch finishes shared DoFs, no exchange launch follows
   int64_t storage = 0, unique = 0;
   std::vector<int64_t> base;    // per macro storage offset
   std::vector<MacroDev> md;
   std::vector<Tile> tiles;      // interior wave tiles (natural order, padded)
   std::vector<Tile> tiles_f32;  // 2D FP32 wave tiles (kTileH2F rows); empty in 3D (same as tiles)
+  std::vector<FaceDev> faces;   // 3D: macro faces, and the copies of the edge and vertex DoFs, that tiles name
+  std::vector<EdgeCopy> edges;
   std::vector<Tile> segs;       // per-point row segments
   // per-point slice segments {macro, first slice-local index, 0, z}: a
   // slice (the whole macro in 2D) is contiguous in storage, so its points

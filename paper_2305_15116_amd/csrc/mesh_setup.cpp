@@ -254,6 +254,124 @@ static int build_topology(mf_mesh* m) {
   return MF_OK;
 }
 
+// ---------------------------------------------------------------- 3D tiles
+// Tiles of a 3D level: the interior walk's slabs of every macro, the inner
+// points of every macro face, and the copies of the edge and vertex DoFs.
+static void build_tiles3(const mf_mesh* m, Level& L) {
+  const int N = L.N;
+  const Shape3 sh = shape3(N);
+  std::vector<Tile> bnd;
+  for (int64_t c = 0; c < m->nc; ++c)
+    for (int z0 = 1; z0 <= N - 2; z0 += sh.PZ) {
+      // columns of the slab: band b has N - z0 - R b of them, as long as its first row has two
+      int Q = 0;
+      for (int b = 0; N - z0 - sh.R * b >= 2; ++b) Q += N - z0 - sh.R * b;
+      const int nz = std::min(sh.PZ, N - 1 - z0);
+      for (int q0 = -1; q0 + 1 < Q; q0 += kTileW) L.tiles.push_back({(int32_t)c, q0, Q, z0 | nz << 16});
+    }
+  // faces: weights a and b run over two of the face's vertices, with a along
+  // the first macro's x where its face holds vertices 0 and 1 (contiguous storage)
+  const StencilTable ST = stencil_table(3);
+  for (const Prim& P : m->prims) {
+    if (P.v.size() != 3 || N < kMinFaceN) continue;
+    int pa = 0, pb = 1, pc = 2;
+    for (int j = 0; j < 3; ++j) {
+      if (P.local[0][j] == 1) pa = j;
+      if (P.local[0][j] == 0) pc = j;
+    }
+    const bool lined = P.local[0][pa] == 1 && P.local[0][pc] == 0;
+    if (!lined) {  // the far face or x = 0: a along y
+      for (int j = 0; j < 3; ++j) {
+        if (P.local[0][j] == 2) pa = j;
+        if (P.local[0][j] == 3) pb = j;
+      }
+      pc = 3 - pa - pb;
+    }
+    pb = 3 - pa - pc;
+    FaceDev F{};
+    F.N = N;
+    F.copies = (int16_t)P.cell.size();
+    F.dirichlet = P.dirichlet ? 1 : 0;
+    double diag = 0.0;
+    for (int i = 0; i < 2; ++i) {
+      const size_t k = std::min<size_t>(i, P.cell.size() - 1);
+      FaceCopy& C = F.cp[i];
+      C.macro = (int32_t)P.cell[k];
+      int mask = 0;
+      for (int j = 0; j < 3; ++j) {
+        const int l = P.local[k][j];
+        mask |= 1 << l;
+        if (l == 0) continue;
+        if (j == pa) C.a[l - 1] = 1;
+        else if (j == pb) C.b[l - 1] = 1;
+        else C.n[l - 1] = 1, C.a[l - 1] = C.b[l - 1] = -1;
+      }
+      for (int f = 0; f < 4; ++f)
+        if (!((mask >> f) & 1)) C.face = (int8_t)f;
+      if (k == (size_t)i) diag += L.md[C.macro].wm[mask][ST.centre];
+    }
+    if (F.dirichlet && F.cp[0].face <= 1) continue;  // written by the walk
+    F.inv = diag != 0.0 ? 1.0 / diag : 0.0;
+    F.invf = (float)F.inv;
+    const int id = (int)L.faces.size(), n = (N - 1) * (N - 2) / 2, run = F.dirichlet ? kFaceRun0 : (F.copies == 1 ? kFaceRun1 : kFaceRun2);
+    L.faces.push_back(F);
+    for (int i = 0; i < n; i += run) bnd.push_back({kFaceTile, i, std::min(run, n - i), id});
+  }
+  // edge and vertex DoFs (the all-groups list's other groups; all of them on the smallest levels, except those
+  // that the walk writes)
+  int32_t first = 0;  // of the open tile
+  auto close = [&] {
+    const int32_t n = (int32_t)L.edges.size() - first;
+    if (n > 0) bnd.push_back({kEdgeTile, first, n, 0});
+    first = (int32_t)L.edges.size();
+  };
+  for (int64_t g = 0; g < L.ngroups(); ++g) {
+    const int c0 = L.grp_ptr[g], n = L.grp_ptr[g + 1] - c0;
+    const Copy& k0 = L.copies[c0];
+    const int m0 = support_mask(3, N, k0.x, k0.y, k0.z);
+    if (__builtin_popcount(m0) == 3 && N >= kMinFaceN) continue;  // a face point
+    if ((m0 == 13 || m0 == 14) && (L.grp_flag[g] & 1)) continue;
+    double diag = 0.0;
+    for (int c = c0; c < c0 + n; ++c) {
+      const Copy& k = L.copies[c];
+      diag += L.md[k.macro].wm[support_mask(3, N, k.x, k.y, k.z)][ST.centre];
+    }
+    if (n > kWave || (int32_t)L.edges.size() - first + n > kWave) close();
+    const int head = (int)L.edges.size() - first;
+    for (int c = c0; c < c0 + n; ++c) {
+      const Copy& k = L.copies[c];
+      EdgeCopy e{};
+      e.idx = L.base[k.macro] + idx3(N, k.x, k.y, k.z);
+      e.inv = diag != 0.0 ? 1.0 / diag : 0.0;
+      e.macro = k.macro;
+      e.x = (int16_t)k.x, e.y = (int16_t)k.y, e.z = (int16_t)k.z;
+      e.mask = (uint8_t)support_mask(3, N, k.x, k.y, k.z);
+      e.head = (uint8_t)(n > kWave ? 0 : head);
+      e.copies = (uint8_t)(n > kWave ? 0 : n);
+      e.dirichlet = L.grp_flag[g] & 1;
+      L.edges.push_back(e);
+    }
+    if (n > kWave) {
+      bnd.push_back({kEdgeBigTile, first, n, 0});
+      first = (int32_t)L.edges.size();
+    }
+  }
+  close();
+  while (L.tiles.size() % kWavesPerWG) L.tiles.push_back({-1, 0, 0, 0});
+  while (bnd.size() % kWavesPerWG) bnd.push_back({-1, 0, 0, 0});
+  // the boundary's workgroups are spread evenly among the walk's (each XCD
+  // takes a contiguous chunk of workgroups, so appended ones would all land on one)
+  const size_t nr = L.tiles.size() / kWavesPerWG, nb = bnd.size() / kWavesPerWG;
+  std::vector<Tile> all;
+  all.reserve(L.tiles.size() + bnd.size());
+  for (size_t ir = 0, ib = 0; ir < nr || ib < nb;) {
+    const bool take = ib < nb && (ir == nr || ib * nr <= ir * nb);
+    const Tile* src = take ? &bnd[ib++ * kWavesPerWG] : &L.tiles[ir++ * kWavesPerWG];
+    all.insert(all.end(), src, src + kWavesPerWG);
+  }
+  L.tiles.swap(all);
+}
+
 // ---------------------------------------------------------------- per level
 static int build_level(mf_mesh* m, int level, Level& L) {
   const int dim = m->dim, d1 = dim + 1;
@@ -472,56 +590,19 @@ static int build_level(mf_mesh* m, int level, Level& L) {
       L.xcpidx[i] = storage_index(L.xcopies[i]);
   });
 
-  // wave tiles over every point of every macro, natural order: macro,
-  // (slice chunk,) strip, band; on small 3D levels runs of slice segments
-  // (macro, slice, index)
+  // wave tiles, natural order: 2D over every point of every macro (macro,
+  // band, strip); 3D over the interior points (macro, slab, columns), then the
+  // macro faces and the edge and vertex copies
   L.tiles.clear();
-  L.pen_z = dim == 3 && N <= kSegUpToN ? kPenSeg : kPenZ;
-  if (L.pen_z == kPenSeg)
-    L.tiles.reserve((size_t)m->nc * (macro_points(dim, N) / (kWave * seg_run(N)) + N + 2) + 64);
-  else
-    L.tiles.reserve((size_t)m->nc * (macro_points(dim, N) / (kTileW * (dim == 2 ? kTileH2 : kPenR * L.pen_z)) * 2 + 64));
-  for (int64_t c = 0; c < m->nc; ++c) {
-    if (L.pen_z == kPenSeg) {
-      for (int z = 0; z <= N; ++z) {
-        const int64_t S = N - z, P = (S + 1) * (S + 2) / 2;
-        const int64_t run = kWave * seg_run(N);
-        for (int64_t r0 = 0; r0 < P; r0 += run)
-          L.tiles.push_back({(int32_t)c, (int32_t)r0, (int32_t)std::min<int64_t>(run, P - r0), z});
-      }
-    } else if (dim == 2) {
+  L.xfused = dim == 3;
+  if (dim == 2) {
+    L.tiles.reserve((size_t)m->nc * (macro_points(dim, N) / (kTileW * kTileH2) * 2 + 64));
+    for (int64_t c = 0; c < m->nc; ++c)
       for (int y0 = 0; y0 <= N; y0 += kTileH2)
         for (int x0 = 0; x0 + y0 <= N; x0 += kTileW) L.tiles.push_back({(int32_t)c, x0, y0, 0});
-    } else {
-      for (int z0 = 0; z0 <= N; z0 += L.pen_z)
-        for (int y0 = 0; y0 + z0 <= N; y0 += kPenR)
-          for (int x0 = 0; x0 + y0 + z0 <= N; x0 += kTileW) L.tiles.push_back({(int32_t)c, x0, y0, z0});
-    }
-  }
-  while (L.tiles.size() % kWavesPerWG) L.tiles.push_back({-1, 0, 0, 0});
-  // (measured: on pencil levels the group work lengthens the launch more than
-  // the exchange launch costs, cube level 8 FP64 apply 96 -> 109 us)
-  L.xfused = L.pen_z == kPenSeg && dim == 3;
-  if (L.xfused) {
-    // group tiles: the shared DoFs, finished in the same launch.  Their
-    // workgroups are spread evenly among the runs' (each XCD takes a
-    // contiguous chunk of workgroups, so appended ones would all land on one)
-    std::vector<Tile> grp;
-    const int64_t ng = L.nxgroups();
-    for (int64_t g0 = 0; g0 < ng; g0 += kWave)
-      grp.push_back({kGroupTile, (int32_t)g0, (int32_t)std::min<int64_t>(kWave, ng - g0), 0});
-    while (grp.size() % kWavesPerWG) grp.push_back({-1, 0, 0, 0});
-    const size_t nr = L.tiles.size() / kWavesPerWG, ngw = grp.size() / kWavesPerWG;
-    std::vector<Tile> all;
-    all.reserve(L.tiles.size() + grp.size());
-    size_t ir = 0, ig = 0;
-    while (ir < nr || ig < ngw) {
-      // next: a group workgroup while the groups lag the runs proportionally
-      const bool take_g = ig < ngw && (ir == nr || ig * nr <= ir * ngw);
-      const Tile* src = take_g ? &grp[ig++ * kWavesPerWG] : &L.tiles[ir++ * kWavesPerWG];
-      all.insert(all.end(), src, src + kWavesPerWG);
-    }
-    L.tiles.swap(all);
+    while (L.tiles.size() % kWavesPerWG) L.tiles.push_back({-1, 0, 0, 0});
+  } else {
+    build_tiles3(m, L);
   }
   L.tiles_f32.clear();
   if (dim == 2) {
@@ -578,6 +659,8 @@ int upload_level(mf_mesh* m, Level& L) {
   if ((rc = dev_upload(&D.md, L.md))) return rc;
   if ((rc = dev_upload(&D.tiles, L.tiles))) return rc;
   if ((rc = dev_upload(&D.tiles_f32, L.tiles_f32))) return rc;
+  if ((rc = dev_upload(&D.faces, L.faces))) return rc;
+  if ((rc = dev_upload(&D.edges, L.edges))) return rc;
   if ((rc = dev_upload(&D.segs, L.segs))) return rc;
   if ((rc = dev_upload(&D.psegs, L.psegs))) return rc;
   if ((rc = dev_upload(&D.sbase, L.sbase))) return rc;
@@ -759,7 +842,7 @@ int build_mesh(mf_mesh* m) {
 void free_device(mf_mesh* m) {
   for (auto& L : m->levels) {
     LevelDev& D = L.dev;
-    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
+    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.faces, D.edges, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
                     D.xgrp_invdiagf,
                     D.part, D.result, D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.own_bits, D.p2_tiles};
     for (void* p : ptrs)

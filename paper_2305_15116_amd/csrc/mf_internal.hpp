@@ -28,40 +28,32 @@ constexpr int kTileH2 = MF_TILE_H2;   // rows per 2D wave tile (FP64)
 // as many bytes in flight per wave.
 constexpr int kTileH2F = 16;
 constexpr int kRingU2F = 8;
-// 3D: a wave walks a "pencil" of kPenR rows upward through kPenZ slices,
-// keeping the rows of slices z-1, z, z+1 in registers.
-#ifndef MF_PEN_R
-#define MF_PEN_R 4
-#endif
-#ifndef MF_PEN_Z
-#define MF_PEN_Z 8
-#endif
-constexpr int kPenR = MF_PEN_R;
-constexpr int kPenZ = MF_PEN_Z;
-// Small 3D levels: instead of pencils, a wave takes a run of up to kSegRun
-// slice segments (64 consecutive storage points of one slice each, across
-// row ends), one point per lane, and gathers each point's 15 neighbours.
-// A pencil's walk is a chain of dependent slice loads, and with few waves in
-// flight that chain sets a small level's kernel time; a run has no chain, so
-// a launch costs about one round of loads (measured on the 6-tet cube: 11-14
-// us per FP64 apply at N = 16..64 against 18 us with pencils).  From N = 256
-// on, the 15 gathered loads per point cost more than the walk (FP64 apply at
-// N = 256: 169 us against 96).  kPenSeg marks a level whose tile list holds
-// such runs.
-constexpr int kPenSeg = 1;
-#ifndef MF_SEG3D_UPTO_N
-#define MF_SEG3D_UPTO_N 128
-#endif
-constexpr int kSegUpToN = MF_SEG3D_UPTO_N;  // runs of slice segments when N <= this
-constexpr int kSegRun = 4;
-// segments per run at side N: fewer on the smallest levels, for more waves
-MF_HD constexpr int seg_run(int N) { return N >= 128 ? 4 : (N >= 64 ? 2 : 1); }
-// On slice-run levels the stencil launch also finishes the shared DoFs: among
-// the runs, the tile list holds group tiles (macro = kGroupTile,
-// x0 = first exchange group, y0 = groups, at most 64), whose lanes compute
-// each shared DoF's whole row from its copies' partial stencils, so no
-// exchange launch follows.
-constexpr int kGroupTile = -2;
+// 3D: a wave takes 64 consecutive columns of a slab of PZ slices, cut into
+// bands of R rows, and walks them upward through the slices (walk3d.hpp).
+// Measured on the 6-tet cube (us per launch, FP64 apply / Jacobi / residual):
+// large bands read fewer rows twice and win where memory bounds the launch
+// (N = 256: R = 4 74 / 96 / 96, R = 2 86 / 102 / 101), short slabs keep the
+// launch's front compact (PZ = 4 / 6 / 8: 73 / 75 / 75; 8 from N = 512 on, for
+// fewer norm partials); small levels need waves instead (N = 128: R = 3
+// 11.7 / 12.9 / 12.8, R = 4 12.6 / 15.8 / 15.6; N = 64: R = 2 4.9 / 5.5 / 5.3, R = 1
+// 5.5 / 6.0 / 5.7; N = 32: R = 1 4.4 / 5.0 / 4.5, R = 2 4.5 / 5.1 / 5.0).
+struct Shape3 {
+  int R, PZ;  // rows per band, slices per slab
+};
+MF_HD constexpr Shape3 shape3(int N) {
+  return N >= 512 ? Shape3{4, 8} : N >= 256 ? Shape3{4, 6} : N >= 128 ? Shape3{3, 4} : N >= 64 ? Shape3{2, 4} : Shape3{1, 2};
+}
+constexpr int kMaxR3 = 4;
+// Kinds of a 3D tile list's other tiles (Tile::macro): inner points of a macro
+// face, copies of macro edge and vertex DoFs.
+constexpr int kFaceTile = -2;
+constexpr int kEdgeTile = -3;
+constexpr int kEdgeBigTile = -4;
+// From this side on the inner points of a face have tiles of their own; below
+// (at most 21 points) they are listed with the edge and vertex copies.
+constexpr int kMinFaceN = 16;
+// points per face tile: Dirichlet faces (copies), faces of one and of two macros
+constexpr int kFaceRun0 = 2048, kFaceRun1 = 1536, kFaceRun2 = 128;
 // 3D prolongations walk runs of up to kTransferRun 64-point slice segments
 // (single segments below N = 256).
 constexpr int kTransferRun = 4;
@@ -73,11 +65,10 @@ constexpr int kWG = kWave * kWavesPerWG;
 constexpr int kIfaceWG = 256;  // groups per interface workgroup
 constexpr int kXCD = 8;        // MI355X: 8 accelerator complex dies, workgroups dealt round-robin
 
-// A wave tile: columns [x0, x0+62) of rows [y0, y0+H) of `macro` (2D), or of
-// rows [y0, y0+kPenR) in slices [z, z+kPenZ) (3D).  For per-point kernels the same record names a row segment
-// of 64 points starting at x0 of row y0 in slice z; in the tile list of a kPenSeg level, y0 points of slice z
-// from slice-local index x0 (a run of at most kSegRun segments), then group tiles (kGroupTile).  macro = -1:
-// padding.
+// A wave tile: columns [x0, x0+62) of rows [y0, y0+H) of `macro` (2D); the
+// columns from x0 on of the slab's y0 at slices z & 0xffff on, z >> 16 of them (3D); y0 points of face z from point x0 on (kFaceTile);
+// y0 copies from copy x0 on (kEdgeTile, kEdgeBigTile).  For per-point kernels the same record names a row
+// segment of 64 points starting at x0 of row y0 in slice z.  macro = -1: padding.
 struct Tile {
   int32_t macro, x0, y0, z;
 };
@@ -85,6 +76,33 @@ struct Tile {
 // A copy of a macro-boundary DoF: macro id and its index-space point.
 struct Copy {
   int32_t macro, x, y, z;
+};
+
+// A macro face (3D): the one or two macros that contain it.  An inner point has
+// face weights wa, wb >= 1 and wc = N - wa - wb >= 1; in macro cp[i] it is the
+// point n N + a wa + b wb (per coordinate).
+struct FaceCopy {
+  int32_t macro;
+  int8_t face;  // the macro's face: 0: x + y + z = N, 1..3: x, y, z = 0
+  int8_t n[3], a[3], b[3];
+};
+struct FaceDev {
+  int32_t N;
+  int16_t copies, dirichlet;
+  FaceCopy cp[2];  // (one macro: repeated)
+  double inv;      // 1 / assembled diagonal of an inner point
+  float invf;
+};
+
+// A copy of a macro edge or vertex DoF (3D).
+struct EdgeCopy {
+  int64_t idx;  // storage index
+  double inv;   // 1 / assembled diagonal
+  int32_t macro;
+  int16_t x, y, z;
+  uint8_t mask;          // support mask in its macro
+  uint8_t head, copies;  // lane of the DoF's first copy in its tile, number of copies (kEdgeTile)
+  uint8_t dirichlet;
 };
 
 // Per-macro, per-level constants.  wm[s] is the (partial) stencil of a point

@@ -76,11 +76,9 @@ __device__ __forceinline__ void accum(double& ss, double& mx, T out, T xc) {
 // Finish the row of one point.  acc is its (partial) stencil value, xc and bv
 // its x and b entries.  Interior points, Dirichlet points (identity rows) and
 // points no other macro shares are finished here; shared non-Dirichlet points
-// get their partial row for the exchange (KEEP_SHARED), or nothing where the
-// same launch computes their whole rows (group_rows3).  Norm partials count
-// each unique DoF once (Dirichlet DoFs on shared primitives only in their
-// owner).
-template <typename T, int DIM, int MODE, bool KEEP_SHARED = true>
+// get their partial row for the exchange.  Norm partials count each unique DoF
+// once (Dirichlet DoFs on shared primitives only in their owner).
+template <typename T, int DIM, int MODE>
 __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int mask, T acc, T xc, T bv, T omega,
                                        T* yp, double& ss, double& mx) {
   constexpr int FM = full_mask(DIM);
@@ -100,8 +98,44 @@ __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int m
     else out = bv;
     if (MODE != kNormB) st(yp, out);
     accum<T, MODE>(ss, mx, out, xc);
-  } else if (MODE != kNormB && KEEP_SHARED) {
+  } else if (MODE != kNormB) {
     st(yp, acc);
+  }
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+  return v;
+}
+
+// One (sum, maximum) partial per workgroup of NW waves, summed in a fixed
+// order, into slot n of part (maxima at np).  Called by every thread.
+template <int NW>
+__device__ __forceinline__ void wg_partial(double ss, double mx, double* part, int np, int n) {
+  __shared__ double s_ss[NW], s_mx[NW];
+  ss = wave_sum(ss);
+  mx = wave_max(mx);
+  const int wv = (int)threadIdx.x / kWave;
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    s_ss[wv] = ss;
+    s_mx[wv] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double p = s_ss[0], q = s_mx[0];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) {
+      p += s_ss[k];
+      q = fmax(q, s_mx[k]);
+    }
+    part[n] = p;
+    part[np + n] = q;
   }
 }
 

@@ -1,0 +1,69 @@
+// 3D constant-stencil kernels (gfx950): one launch finishes every row of a
+// level (apply, weighted Jacobi, residual and norms).  Its tile list holds the
+// interior walk's columns, the macro faces and the macro edge and vertex
+// copies (walk3d.hpp), spread among each other.
+
+#include <hip/hip_runtime.h>
+
+#include "launch.hpp"
+#include "walk3d.hpp"
+
+namespace mf {
+
+namespace {
+
+// Fine levels (R = 4) deal runs of 16 workgroups to the XCDs in turn: N = 256,
+// FP64 apply / Jacobi / residual 73.6 / 94.0 / 93.2 us against 75.3 / 96 / 96 with
+// one chunk per XCD (runs of 4: 74.8 / 94.3 / 93.7, of 64: 76.8 / 98.9 / 98.7);
+// levels that fit the caches gain nothing from it.
+constexpr int kXcdRun = 16;
+
+template <typename T, int MODE, int R>
+__global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<T>> L) {
+  const int g = R == kMaxR3 ? wave::xcd_wg_run<kXcdRun>(L.nwg) : wave::xcd_wg(L.nwg);
+  if (g < 0) return;
+  StencilArgs<T> a;
+  const int n = resolve(L, g, a);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Tile t = load_seg(a.tiles, n * kWavesPerWG + wv);
+  double ss = 0.0, mx = 0.0;
+  if (t.macro >= 0) walk3<T, MODE, R>(t, a.md[t.macro], a.X, a.Y, a.B, a.omega, ss, mx);
+  else if (t.macro == kFaceTile) face_rows<T, MODE>(a, t, ss, mx);
+  else if (t.macro != -1) edge_rows<T, MODE>(a, t, ss, mx);
+  if (has_partials(MODE) && a.part != nullptr) wg_partial<kWavesPerWG>(ss, mx, a.part, a.np, n);
+}
+
+template <typename T, int MODE>
+void run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+  const dim3 grid(R == kMaxR3 ? wave::xcd_grid_run(l.nwg, kXcdRun) : wave::xcd_grid(l.nwg)), wg(kWG);
+  static_assert(kMaxR3 == 4, "one instance per band height");
+  if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, 0, s, l);
+  else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, 0, s, l);
+  else if (R == 2) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 2>), grid, wg, 0, s, l);
+  else hipLaunchKernelGGL((stencil3_kernel<T, MODE, 1>), grid, wg, 0, s, l);
+}
+
+template <typename T>
+int dispatch(int mode, int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+  if (l.nwg <= 0) return MF_OK;
+  switch (mode) {
+    case kApply: run<T, kApply>(R, l, s); break;
+    case kJacobi: run<T, kJacobi>(R, l, s); break;
+    case kResidual: run<T, kResidual>(R, l, s); break;
+    case kNormB: run<T, kNormB>(R, l, s); break;
+    default: run<T, kApplyDot>(R, l, s); break;
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
+}
+
+}  // namespace
+
+int launch_stencil3(int mode, int R, const Launch<StencilArgs<double>>& l, hipStream_t s) {
+  return dispatch(mode, R, l, s);
+}
+int launch_stencil3(int mode, int R, const Launch<StencilArgs<float>>& l, hipStream_t s) {
+  return dispatch(mode, R, l, s);
+}
+
+}  // namespace mf

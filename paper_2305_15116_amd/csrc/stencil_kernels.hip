@@ -1,4 +1,4 @@
-// Constant-stencil kernels for CDNA4 (gfx950): the operator's rows for every
+// Constant-stencil kernels for CDNA4 (gfx950): the 2D operator's rows for every
 // point of every macro (apply, weighted Jacobi, residual + norm partials),
 // the exchange that completes rows of DoFs shared by several macros, and the
 // deterministic norm reduction.
@@ -8,11 +8,11 @@
 // weights; on a CPU its speed depends on whether three source rows plus the
 // destination row fit in a cache level (the layer condition).  Here the same
 // reuse is kept in registers: a 64-lane wavefront owns 64 consecutive
-// columns and walks rows upward (2D), or walks a pencil of rows upward
-// through the slices (3D), holding the rows the stencil needs and taking the
-// x+-1 neighbours from adjacent lanes through DPP shifts, so each source
+// columns and walks rows upward, holding the rows the stencil needs and taking
+// the x+-1 neighbours from adjacent lanes through DPP shifts, so each source
 // value is read from memory once per tile; future rows are loaded ahead to
-// keep enough bytes in flight for HBM3E.  No matrix cores: the path is
+// keep enough bytes in flight for HBM3E (the 3D walk: walk3d.hpp and
+// stencil3d_kernels.hip).  No matrix cores: the path is
 // HBM-bound.
 //
 // Macro-boundary DoFs are handled in the same walk (the paper leaves them to
@@ -38,17 +38,6 @@ using wave::dn1;
 using wave::up1;
 using wave::xcd_wg;
 
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-  return v;
-}
 
 #ifndef MF_RING_U2
 #define MF_RING_U2 8
@@ -92,48 +81,46 @@ __device__ __forceinline__ void finish_interior(const MacroDev& M, T acc, T xc, 
   accum<T, MODE>(ss, mx, out, xc);
 }
 
-// Support masks of the boundary lanes of rows off the y = 0 (and, in 3D,
-// z = 0) faces: the row's first point (x = 0), its last (far face) or both.
-template <int DIM>
+// Support masks of the boundary lanes of rows off the y = 0 edge: the row's
+// first point (x = 0), its last (far edge) or both.
 struct RowMasks {
-  static constexpr int L = full_mask(DIM) & ~2;   // x = 0
-  static constexpr int F = full_mask(DIM) & ~1;   // far face
-  static constexpr int LF = full_mask(DIM) & ~3;  // both
+  static constexpr int L = full_mask(2) & ~2;   // x = 0
+  static constexpr int F = full_mask(2) & ~1;   // far edge
+  static constexpr int LF = full_mask(2) & ~3;  // both
 };
 
 // Row of one point from its neighbour values v (xc = its x, bv = its b).
-// may_face (a compile-time constant after unrolling) marks the rows that can
-// lie on the y = 0 / z = 0 faces: those go through the general per-lane
-// path.  In other rows a boundary lane is the row's first point (x = 0, only
-// in tiles starting at x0 = 0, tile_left), its last (on the far face
-// x + y + z = N), or both.  A row without such a lane takes the interior
-// stencil from scalar registers, and so does a row whose boundary lanes are
-// all Dirichlet points (they copy x).  Any other row takes, in every lane,
-// the partial stencil of the lane's own support mask from the LDS table
-// (interior lanes read the full stencil there, the same weights); the
-// neighbours such a lane lacks (x - 1 for x = 0, the offsets of coordinate
-// sum +1 on the far face) have weight 0 in its table row, and their
-// stand-in values are replaced by 0 so that those terms add exactly nothing.
-// The terms are summed in table order in every case, so a boundary row is
-// the sum over the neighbours it has, in that order.  Jacobi needs bid =
-// 1 / centre weight of the L, F and LF masks.
-template <typename T, int DIM, int MODE, bool KEEP_SHARED = true>
+// may_edge (a compile-time constant after unrolling) marks the rows that can
+// lie on the y = 0 edge: those go through the general per-lane path.  In other
+// rows a boundary lane is the row's first point (x = 0, only in tiles starting
+// at x0 = 0, tile_left), its last (on the far edge x + y = N), or both.  A row
+// without such a lane takes the interior stencil from scalar registers, and so
+// does a row whose boundary lanes are all Dirichlet points (they copy x).  Any
+// other row takes, in every lane, the partial stencil of the lane's own
+// support mask from the LDS table (interior lanes read the full stencil there,
+// the same weights); the neighbours such a lane lacks (x - 1 for x = 0, the
+// offsets of coordinate sum +1 on the far edge) have weight 0 in its table
+// row, and their stand-in values are replaced by 0 so that those terms add
+// exactly nothing.  The terms are summed in table order in every case, so a
+// boundary row is the sum over the neighbours it has, in that order.  Jacobi
+// needs bid = 1 / centre weight of the L, F and LF masks.
+template <typename T, int MODE>
 __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, const T* wi, bool inside, int N, int x,
-                                          int y, int z, const T* v, T xc, T bv, T omega, T* yp, double& ss,
-                                          double& mx, bool may_face, bool tile_left, const T* bid) {
-  constexpr StencilTable ST = stencil_table(DIM);
-  constexpr int FM = full_mask(DIM);
+                                          int y, const T* v, T xc, T bv, T omega, T* yp, double& ss, double& mx,
+                                          bool may_edge, bool tile_left, const T* bid) {
+  constexpr StencilTable ST = stencil_table(2);
+  constexpr int FM = full_mask(2);
   constexpr int NO = ST.n;
-  if (may_face && (y == 0 || (DIM == 3 && z == 0))) {
-    // a row on the y = 0 or z = 0 face: every lane is a boundary point
+  if (may_edge && y == 0) {
+    // the row on the y = 0 edge: every lane is a boundary point
     if (__builtin_amdgcn_ballot_w64(inside)) {
-      const int mask = support_mask(DIM, N, x, y, z);
-      const T acc = partial_sum<T, DIM>(W, inside ? mask : FM, N, x, y, z, v);
-      if (inside) finish<T, DIM, MODE, KEEP_SHARED>(M, W, mask, acc, xc, bv, omega, yp, ss, mx);
+      const int mask = support_mask(2, N, x, y, 0);
+      const T acc = partial_sum<T, 2>(W, inside ? mask : FM, N, x, y, 0, v);
+      if (inside) finish<T, 2, MODE>(M, W, mask, acc, xc, bv, omega, yp, ss, mx);
     }
     return;
   }
-  const bool far = inside && x + y + z == N;
+  const bool far = inside && x + y == N;
   const bool left = tile_left && inside && x == 0;
   if (!__builtin_amdgcn_ballot_w64(far || left)) {
     T acc = wi[0] * v[0];
@@ -157,7 +144,7 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
       T vo = v[o];
-      if (ST.off[o][0] + ST.off[o][1] + ST.off[o][2] > 0) vo = far ? T(0) : vo;
+      if (ST.off[o][0] + ST.off[o][1] > 0) vo = far ? T(0) : vo;
       if (ST.off[o][0] < 0) vo = left ? T(0) : vo;
       a = o == 0 ? wr[0] * vo : fma(wr[o], vo, a);
     }
@@ -176,7 +163,7 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
     out = bv;
   }
   if (inside) {
-    if (MODE != kNormB && (KEEP_SHARED || !shared)) st(yp, out);
+    if (MODE != kNormB) st(yp, out);
     if (dir ? own : !shared) accum<T, MODE>(ss, mx, out, xc);
   }
 }
@@ -221,9 +208,9 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
   T bid[3] = {T(0), T(0), T(0)};
   if (MODE == kJacobi) {
     constexpr int c = stencil_table(2).centre;
-    bid[0] = T(1) / W[RowMasks<2>::L][c];
-    bid[1] = T(1) / W[RowMasks<2>::F][c];
-    bid[2] = T(1) / W[RowMasks<2>::LF][c];
+    bid[0] = T(1) / W[RowMasks::L][c];
+    bid[1] = T(1) / W[RowMasks::F][c];
+    bid[2] = T(1) / W[RowMasks::LF][c];
   }
 
   const int xc = max(x, 0);
@@ -254,8 +241,8 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
     const T ap_l = up1(ap), ap_r = dn1(ap);
     const T v[7] = {am, am_r, a0_l, a0, a0_r, ap_l, ap};
     const bool inside = lane >= 1 && lane <= kTileW && x + yy <= N;
-    point_row<T, 2, MODE>(M, W, wi, inside, N, x, yy, 0, v, a0, bv, omega, Y + rs32(N, yy) + (unsigned)xc, ss, mx,
-                          k == 0, x0 == 0, bid);
+    point_row<T, MODE>(M, W, wi, inside, N, x, yy, v, a0, bv, omega, Y + rs32(N, yy) + (unsigned)xc, ss, mx, k == 0,
+                       x0 == 0, bid);
     am = a0;
     am_r = a0_r;
     a0 = ap;
@@ -336,225 +323,15 @@ __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const Ma
   }
 }
 
-// ------------------------------------------------------------------ 3D pencil
-// Slice z of a tetrahedral macro is a triangle of side S = N - z.  Output row
-// y of slice z reads rows y, y+1 of slice z-1, rows y-1..y+1 of slice z and
-// rows y-1, y of slice z+1.  A wave keeps rows y0-1 .. y0+kPenR of five
-// consecutive slices in registers (z-1, z, z+1 and two in flight) and walks
-// z upward, so each value is loaded once per pencil.  Rows, columns and
-// slices outside the macro are clamped to a valid point (values never used).
-template <typename T, int MODE, int PZ>
-__device__ __forceinline__ void pencil3d(const int x0, const int y0, const int z0, const MacroDev& M, WTab<T> W,
-                                         const T* __restrict__ X, T* __restrict__ Y, const T* __restrict__ B,
-                                         T omega, double& ss, double& mx) {
-  constexpr int FM = full_mask(3);
-  constexpr int NS = 5;
-  constexpr int NR = kPenR + 2;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int N = M.N;
-  const int x = x0 - 1 + lane;
-  const int nz = min(PZ, N + 1 - x0 - y0 - z0);  // output slices z0 .. z0+nz-1
-  X += M.base;
-  Y += M.base;
-  if (MODE != kApply) B += M.base;
-  T wi[15];
-#pragma unroll
-  for (int o = 0; o < 15; ++o) wi[o] = Prec<T>::w(M, FM, o);
-  T bid[3] = {T(0), T(0), T(0)};
-  if (MODE == kJacobi) {
-    constexpr int c = stencil_table(3).centre;
-    bid[0] = T(1) / W[RowMasks<3>::L][c];
-    bid[1] = T(1) / W[RowMasks<3>::F][c];
-    bid[2] = T(1) / W[RowMasks<3>::LF][c];
-  }
-  const int xc = max(x, 0);
-  // Slice z of a macro starts at sum_{k<z} (S_k+1)(S_k+2)/2, S_k = N - k;
-  // bases are advanced incrementally (slices past N are clamped to slice N).
-  auto next_base = [&](int64_t zb, int zp) -> int64_t {  // base of slice zp+1 given base of zp
-    const int S = N - zp;
-    return zp >= N ? zb : zb + ((int64_t)(S + 1) * (S + 2) >> 1);
-  };
-  auto ld = [&](const T* __restrict__ base, int64_t zb, int zp, int y) -> T {
-    const int S = N - min(zp, N);
-    return ldrow(base + zb, S, y, S, xc);
-  };
-  T s[NS][NR];
-  int64_t lb = z0 > 0 ? slice_base(N, z0 - 1) : 0;  // base of the next slice to load
-  int lz = max(z0 - 1, 0);                          // its (clamped) index
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-#pragma unroll
-    for (int j = 0; j < NR; ++j) s[i][j] = ld(X, lb, lz, y0 - 1 + j);
-    if (z0 - 1 + i >= 0) {
-      lb = next_base(lb, lz);
-      lz = min(lz + 1, N);
-    }
-  }
-  int64_t zb = slice_base(N, z0);  // output slice base
-  T bq[2][kPenR];
-  if (MODE != kApply) {
-#pragma unroll
-    for (int j = 0; j < kPenR; ++j) bq[0][j] = ld(B, zb, z0, y0 + j);
-  }
-#pragma unroll
-  for (int k = 0; k < PZ; ++k) {
-    const int z = z0 + k;
-    const int64_t zb1 = next_base(zb, min(z, N));
-    if (MODE != kApply && k + 1 < PZ) {
-#pragma unroll
-      for (int j = 0; j < kPenR; ++j) bq[(k + 1) % 2][j] = ld(B, zb1, z + 1, y0 + j);
-    }
-    const T* A = s[k % NS];
-    const T* Bs = s[(k + 1) % NS];
-    const T* C = s[(k + 2) % NS];
-    if (k < nz) {
-      const int S = N - z;
-      T* Yz = Y + zb;
-#pragma unroll
-      for (int j = 1; j <= kPenR; ++j) {
-        const int y = y0 + j - 1;
-        const T v[15] = {A[j],      dn1(A[j]),  A[j + 1],      up1(A[j + 1]), Bs[j - 1],
-                         dn1(Bs[j - 1]), up1(Bs[j]), Bs[j],     dn1(Bs[j]),    up1(Bs[j + 1]),
-                         Bs[j + 1], C[j - 1],   dn1(C[j - 1]), up1(C[j]),     C[j]};
-        const bool inside = lane >= 1 && lane <= kTileW && x + y + z <= N;
-        const T bv = MODE != kApply ? bq[k % 2][j - 1] : T(0);
-        point_row<T, 3, MODE>(M, W, wi, inside, N, x, y, z, v, Bs[j], bv, omega, Yz + rs32(S, y) + (unsigned)xc, ss,
-                              mx, j == 1 || k == 0, x0 == 0, bid);
-      }
-    }
-    // slice z-1 is done: its slot takes the next slice (z+4)
-#pragma unroll
-    for (int j = 0; j < NR; ++j) s[k % NS][j] = ld(X, lb, lz, y0 - 1 + j);
-    lb = next_base(lb, lz);
-    lz = min(lz + 1, N);
-    zb = zb1;
-  }
-}
-
-
-
-
-// ------------------------------------------------------------ 3D slice runs
-// A run of t.y0 consecutive points of slice z from slice-local index t.x0,
-// one point per lane, 64 at a time.  Relative to the point's own index p in
-// slice z (side S = N - z; row y holds d = S + 1 - y points): row y + 1 of
-// the slice starts d after p's column, row y - 1 ends d + 1 before it; the
-// point (x, y, z + 1) lies T(S) - y after p and (x, y, z - 1) lies
-// T(S + 1) - y before it, T(s) = (s + 1)(s + 2) / 2 being the points of a
-// slice of side s.  The 15 neighbours are therefore seven row positions and
-// their +-1 columns.  Indices are formed relative to the first point of
-// slice z - 1 (of slice 0 at z = 0), so every offset is a non-negative
-// 32-bit value.  Lattice points outside the macro map to some index of the
-// neighbouring slices; for 1 <= z <= N - 2 every such index stays inside
-// the macro, elsewhere the indices are clamped into it.  Those values are
-// stand-ins that the boundary rows never use (point_row).
-template <typename T, int MODE>
-__device__ __forceinline__ void seg3d(const Tile& t, const MacroDev& M, WTab<T> W, const T* __restrict__ X,
-                                      T* __restrict__ Y, const T* __restrict__ B, T omega, double& ss, double& mx) {
-  constexpr int FM = full_mask(3);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int N = M.N, z = t.z, S = N - z;
-  T wi[15];
-#pragma unroll
-  for (int o = 0; o < 15; ++o) wi[o] = Prec<T>::w(M, FM, o);
-  T bid[3] = {T(0), T(0), T(0)};
-  if (MODE == kJacobi) {
-    constexpr int c = stencil_table(3).centre;
-    bid[0] = T(1) / W[RowMasks<3>::L][c];
-    bid[1] = T(1) / W[RowMasks<3>::F][c];
-    bid[2] = T(1) / W[RowMasks<3>::LF][c];
-  }
-  const int za = max(z - 1, 0);
-  const int64_t ab = M.base + slice_base(N, za);
-  const T* Xa = X + ab;
-  const int Ts = (S + 1) * (S + 2) / 2;                 // points of slice z
-  const int Tb = z > 0 ? (S + 2) * (S + 3) / 2 : 0;     // points of slice z - 1: offset of slice z
-  const bool safe = z >= 1 && z + 2 <= N;
-  // highest index of the three slices around z, inside the macro
-  const int hi = (int)min(tet_count_small(N + 1) - slice_base(N, za) - 1, (int64_t)Tb + 2 * (int64_t)Ts);
-  auto ld = [&](int i) -> T {
-    if (!safe) i = min(max(i, 0), hi);
-    return *(const T*)((const char*)Xa + (unsigned)i * (unsigned)sizeof(T));
-  };
-#pragma unroll
-  for (int k = 0; k < kSegRun; ++k) {
-    if (k * kWave >= t.y0) break;  // wave-uniform
-    int r = t.x0 + k * kWave + lane;
-    const bool live = k * kWave + lane < t.y0;
-    if (!live) r = 0;
-    int x, y;
-    slice_xy3(S, r, x, y);
-    const int d = S + 1 - y;
-    const int p = Tb + r;
-    const int pu = p + Ts - y;
-    const int pd = r + y;
-    const T v[15] = {ld(pd),         ld(pd + 1),     ld(pd + d + 1), ld(pd + d), ld(p - d - 1),
-                     ld(p - d),      ld(p - 1),      ld(p),          ld(p + 1),  ld(p + d - 1),
-                     ld(p + d),      ld(pu - d),     ld(pu - d + 1), ld(pu - 1), ld(pu)};
-    const T bv = MODE != kApply ? B[ab + p] : T(0);
-    point_row<T, 3, MODE, false>(M, W, wi, live, N, x, y, z, v, v[7], bv, omega, Y + ab + p, ss, mx, true, true, bid);
-  }
-}
-
-// A group tile of a slice-run level: lane i finishes shared DoF t.x0 + i of
-// the exchange list.  Each copy's partial row is formed as the walk forms it
-// at a boundary point (the partial stencil of the copy's support mask in its
-// own macro, neighbours outside that macro dropped, table order), the copies
-// are summed in the list's fixed macro order and the row is finished as the
-// exchange kernel finishes it, so the values are those of the run and
-// exchange launches; the runs leave these DoFs alone (point_row with
-// KEEP_SHARED = false).
-template <typename T, int MODE>
-__device__ __forceinline__ void group_rows3(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
-  constexpr StencilTable ST = stencil_table(3);
-  const int lane = threadIdx.x & (kWave - 1);
-  if (lane >= t.y0) return;
-  const int g = t.x0 + lane;
-  const int c0 = a.xptr[g], c1 = a.xptr[g + 1];
-  const int64_t i0 = a.xcidx[c0];
-  T out;
-  if (MODE == kNormB) {
-    out = a.B[i0];
-  } else {
-    T acc = T(0);
-    for (int c = c0; c < c1; ++c) {
-      const Copy k = a.xcopies[c];
-      const MacroDev& M = a.md[k.macro];
-      const int N = M.N;
-      const int64_t i = a.xcidx[c];
-      int off[15];
-      nbr_offsets3(N, k.y, k.z, off);
-      const int mask = support_mask(3, N, k.x, k.y, k.z);
-      T p = T(0);
-#pragma unroll
-      for (int o = 0; o < ST.n; ++o) {
-        const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
-        const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
-        const T v = a.X[in ? i + off[o] : i];
-        p = fma(Prec<T>::w(M, mask, o), in ? v : T(0), p);
-      }
-      acc += p;
-    }
-    if (MODE == kApply || MODE == kApplyDot) out = acc;
-    else if (MODE == kJacobi) out = fma(a.omega * Prec<T>::ginv(a.xinv, a.xinvf, g), a.B[i0] - acc, a.X[i0]);
-    else out = a.B[i0] - acc;
-    for (int c = c0; c < c1; ++c) a.Y[a.xcidx[c]] = out;
-  }
-  accum<T, MODE>(ss, mx, out, MODE == kApplyDot ? a.X[i0] : T(0));
-}
-
-// Whether a wave tile has output points on its macro's boundary (x = 0,
-// y = 0, z = 0 or the far face x + y + z = N).
-template <typename T, int DIM, int PZ>
+// Whether a wave tile has output points on its macro's boundary (x = 0, y = 0
+// or the far edge x + y = N).
+template <typename T>
 __device__ __forceinline__ bool tile_on_boundary(const Tile& t, int N) {
-  if (DIM == 2) return t.x0 == 0 || t.y0 == 0 || t.x0 + t.y0 + (kTileW - 1) + (Tile2<T>::H - 1) >= N;
-  if (PZ == kPenSeg) return true;  // a run of 64 points or more reaches a row end
-  return t.x0 == 0 || t.y0 == 0 || t.z == 0 || t.x0 + t.y0 + t.z + (kTileW - 1) + (kPenR - 1) + (PZ - 1) >= N;
+  return t.x0 == 0 || t.y0 == 0 || t.x0 + t.y0 + (kTileW - 1) + (Tile2<T>::H - 1) >= N;
 }
 
-template <typename T, int DIM, int MODE, int PZ>
+template <typename T, int MODE>
 __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T>> L) {
-  constexpr bool kPart = has_partials(MODE);
   const int g = xcd_wg(L.nwg);
   if (g < 0) return;
   StencilArgs<T> a;
@@ -575,13 +352,13 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
     if (m0 >= 0) {
       const int N0 = a.md[m0].N;
 #pragma unroll
-      for (int k = 0; k < kWavesPerWG; ++k) need = need || tile_on_boundary<T, DIM, PZ>(a.tiles[n * kWavesPerWG + k], N0);
+      for (int k = 0; k < kWavesPerWG; ++k) need = need || tile_on_boundary<T>(a.tiles[n * kWavesPerWG + k], N0);
     }
     if (need) {
       load_wtab<T>(a.md[m0], wtab[0], 0, kWG);
       __syncthreads();
     }
-  } else if (t.macro >= 0 && tile_on_boundary<T, DIM, PZ>(t, a.md[t.macro].N)) {
+  } else if (t.macro >= 0 && tile_on_boundary<T>(t, a.md[t.macro].N)) {
     load_wtab<T>(a.md[t.macro], wtab[wv], wv * kWave, kWave);
     __builtin_amdgcn_wave_barrier();
   }
@@ -589,38 +366,10 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (t.macro >= 0) {
     const MacroDev& M = a.md[t.macro];
     WTab<T> W = wtab[same ? 0 : wv];
-    if (DIM == 2 && tile2d_inner<T>(t.x0, t.y0, M.N))
-      tile2d_fast<T, MODE>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
-    else if (DIM == 2)
-      tile2d<T, MODE>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
-    else if (PZ == kPenSeg)
-      seg3d<T, MODE>(t, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
-    else
-      pencil3d<T, MODE, PZ>(t.x0, t.y0, t.z, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
-  } else if (DIM == 3 && PZ == kPenSeg && t.macro == kGroupTile) {
-    group_rows3<T, MODE>(a, t, ss, mx);
+    if (tile2d_inner<T>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
+    else tile2d<T, MODE>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
   }
-  if (kPart && a.part != nullptr) {
-    // one partial per workgroup: its four waves summed in a fixed order
-    ss = wave_sum(ss);
-    mx = wave_max(mx);
-    __shared__ double s_ss[kWavesPerWG], s_mx[kWavesPerWG];
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-      s_ss[wv] = ss;
-      s_mx[wv] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double p = s_ss[0], q = s_mx[0];
-#pragma unroll
-      for (int k = 1; k < kWavesPerWG; ++k) {
-        p += s_ss[k];
-        q = fmax(q, s_mx[k]);
-      }
-      a.part[n] = p;
-      a.part[a.np + n] = q;
-    }
-  }
+  if (has_partials(MODE) && a.part != nullptr) wg_partial<kWavesPerWG>(ss, mx, a.part, a.np, n);
 }
 
 // ------------------------------------------------------------------ exchange
@@ -639,26 +388,7 @@ __global__ __launch_bounds__(kIfaceWG) void exchange_kernel(const Launch<GroupAr
     const T out = exchange_row<T, DIM, MODE>(a, g, i0);
     accum<T, MODE>(ss, mx, out, MODE == kApplyDot ? a.X[i0] : T(0));
   }
-  if (has_partials(MODE) && a.part != nullptr) {
-    __shared__ double s_ss[kIfaceWG / kWave], s_mx[kIfaceWG / kWave];
-    ss = wave_sum(ss);
-    mx = wave_max(mx);
-    const int w = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-      s_ss[w] = ss;
-      s_mx[w] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double p = 0.0, q = 0.0;
-      for (int i = 0; i < kIfaceWG / kWave; ++i) {
-        p += s_ss[i];
-        q = fmax(q, s_mx[i]);
-      }
-      a.part[blk] = p;
-      a.part[a.np + blk] = q;
-    }
-  }
+  if (has_partials(MODE) && a.part != nullptr) wg_partial<kIfaceWG / kWave>(ss, mx, a.part, a.np, blk);
 }
 
 // Every macro-boundary DoF: kExchangeSum (y = sum of x over the copies,
@@ -728,45 +458,15 @@ int check_launch() {
   return MF_OK;
 }
 
-inline int stencil_grid(int nwg) { return wave::xcd_grid(nwg); }
-
-template <class A>
-Launch<A> single(const A& a, int nwg) {
-  Launch<A> l{};
-  l.one = a;
-  l.nseg = 0;
-  l.nwg = nwg;
-  return l;
-}
-
-template <class A>
-Launch<A> batched(const BatchOp& op, const char* table) {
-  Launch<A> l{};
-  l.many = (const A*)(table + op.args_off);
-  l.wg0 = (const int32_t*)(table + op.wg0_off);
-  l.nseg = op.nseg;
-  l.nwg = op.nwg;
-  return l;
-}
-
-template <typename T, int DIM, int MODE>
+template <typename T, int MODE>
 void run_stencil(const Level& L, const void* x, void* y, const void* b, double omega, double* part,
                  hipStream_t s) {
   const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
-  if (a.nwg > 0) {
-    // the tile shape is a 3D notion: 2D uses one instance
-    if (DIM == 3 && L.pen_z == kPenSeg) {
-      if constexpr (DIM == 3)
-        hipLaunchKernelGGL((stencil_kernel<T, DIM, MODE, kPenSeg>), dim3(stencil_grid(a.nwg)), dim3(kWG), 0, s,
-                           single(a, a.nwg));
-    } else {
-      hipLaunchKernelGGL((stencil_kernel<T, DIM, MODE, kPenZ>), dim3(stencil_grid(a.nwg)), dim3(kWG), 0, s,
-                         single(a, a.nwg));
-    }
-  }
-  const int nblk = exchange_in_launch(L) ? 0 : exchange_blocks(L);
+  if (a.nwg > 0)
+    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid(a.nwg)), dim3(kWG), 0, s, single(a, a.nwg));
+  const int nblk = exchange_blocks(L);
   if (nblk == 0) return;
-  hipLaunchKernelGGL((exchange_kernel<T, DIM, MODE>), dim3(nblk), dim3(kIfaceWG), 0, s,
+  hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(nblk), dim3(kIfaceWG), 0, s,
                      single(exchange_args<T>(L, x, y, b, omega, part), nblk));
 }
 
@@ -778,65 +478,74 @@ void run_iface(const Level& L, const void* x, void* y, const void* b, hipStream_
                      single(iface_args<T>(L, x, y, b), nblk));
 }
 
-template <typename T, int DIM>
-void dispatch(int mode, const Level& L, const void* x, void* y, const void* b, double omega, double* part,
-              hipStream_t s) {
-  switch (mode) {
-    case kApply: run_stencil<T, DIM, kApply>(L, x, y, b, omega, part, s); break;
-    case kJacobi: run_stencil<T, DIM, kJacobi>(L, x, y, b, omega, part, s); break;
-    case kResidual: run_stencil<T, DIM, kResidual>(L, x, y, b, omega, part, s); break;
-    case kNormB: run_stencil<T, DIM, kNormB>(L, x, y, b, omega, part, s); break;
-    case kApplyDot: run_stencil<T, DIM, kApplyDot>(L, x, y, b, omega, part, s); break;
-    case kExchangeSum: run_iface<T, DIM, kExchangeSum>(L, x, y, b, s); break;
-    default: run_iface<T, DIM, kDirichletSet>(L, x, y, b, s); break;
-  }
-}
-
-int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
-           double omega, double* part, hipStream_t s) {
-  if (dtype == MF_F64) {
-    if (m->dim == 2) dispatch<double, 2>(mode, L, x, y, b, omega, part, s);
-    else dispatch<double, 3>(mode, L, x, y, b, omega, part, s);
+template <typename T>
+int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const void* b, double omega, double* part,
+             hipStream_t s) {
+  if (mode == kExchangeSum) {
+    if (dim == 2) run_iface<T, 2, kExchangeSum>(L, x, y, b, s);
+    else run_iface<T, 3, kExchangeSum>(L, x, y, b, s);
+  } else if (mode == kDirichletSet) {
+    if (dim == 2) run_iface<T, 2, kDirichletSet>(L, x, y, b, s);
+    else run_iface<T, 3, kDirichletSet>(L, x, y, b, s);
+  } else if (dim == 3) {
+    const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
+    return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
   } else {
-    if (m->dim == 2) dispatch<float, 2>(mode, L, x, y, b, omega, part, s);
-    else dispatch<float, 3>(mode, L, x, y, b, omega, part, s);
+    switch (mode) {
+      case kApply: run_stencil<T, kApply>(L, x, y, b, omega, part, s); break;
+      case kJacobi: run_stencil<T, kJacobi>(L, x, y, b, omega, part, s); break;
+      case kResidual: run_stencil<T, kResidual>(L, x, y, b, omega, part, s); break;
+      case kNormB: run_stencil<T, kNormB>(L, x, y, b, omega, part, s); break;
+      default: run_stencil<T, kApplyDot>(L, x, y, b, omega, part, s); break;
+    }
   }
   return check_launch();
 }
 
+int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
+           double omega, double* part, hipStream_t s) {
+  return dtype == MF_F64 ? dispatch<double>(m->dim, mode, L, x, y, b, omega, part, s)
+                         : dispatch<float>(m->dim, mode, L, x, y, b, omega, part, s);
+}
+
 // ---------------------------------------------------------------- batched
-template <typename T, int DIM, int MODE>
+template <typename T, int MODE>
 void batch_stencil(const BatchOp& op, const char* table, hipStream_t s) {
-  if (op.kind == kOpStencil && DIM == 3 && op.variant == kPenSeg) {
-    if constexpr (DIM == 3)
-      hipLaunchKernelGGL((stencil_kernel<T, DIM, MODE, kPenSeg>), dim3(stencil_grid(op.nwg)), dim3(kWG), 0, s,
-                         batched<StencilArgs<T>>(op, table));
-  } else if (op.kind == kOpStencil)
-    hipLaunchKernelGGL((stencil_kernel<T, DIM, MODE, kPenZ>), dim3(stencil_grid(op.nwg)), dim3(kWG), 0, s,
+  if (op.kind == kOpStencil)
+    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid(op.nwg)), dim3(kWG), 0, s,
                        batched<StencilArgs<T>>(op, table));
   else
-    hipLaunchKernelGGL((exchange_kernel<T, DIM, MODE>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
+    hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
                        batched<GroupArgs<T>>(op, table));
 }
 
 template <typename T, int DIM>
-void batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
+void batch_iface(const BatchOp& op, const char* table, hipStream_t s) {
+  if (op.mode == kExchangeSum)
+    hipLaunchKernelGGL((iface_kernel<T, DIM, kExchangeSum>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
+                       batched<GroupArgs<T>>(op, table));
+  else
+    hipLaunchKernelGGL((iface_kernel<T, DIM, kDirichletSet>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
+                       batched<GroupArgs<T>>(op, table));
+}
+
+template <typename T>
+int batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
   if (op.kind == kOpIface) {
-    if (op.mode == kExchangeSum)
-      hipLaunchKernelGGL((iface_kernel<T, DIM, kExchangeSum>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
-                         batched<GroupArgs<T>>(op, table));
-    else
-      hipLaunchKernelGGL((iface_kernel<T, DIM, kDirichletSet>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
-                         batched<GroupArgs<T>>(op, table));
-    return;
+    if (op.dim == 2) batch_iface<T, 2>(op, table, s);
+    else batch_iface<T, 3>(op, table, s);
+  } else if (op.dim == 3) {
+    return launch_stencil3(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
+  } else {
+    switch (op.mode) {
+      case kApply: batch_stencil<T, kApply>(op, table, s); break;
+      case kJacobi: batch_stencil<T, kJacobi>(op, table, s); break;
+      case kResidual: batch_stencil<T, kResidual>(op, table, s); break;
+      case kNormB: batch_stencil<T, kNormB>(op, table, s); break;
+      default: batch_stencil<T, kApplyDot>(op, table, s); break;
+    }
   }
-  switch (op.mode) {
-    case kApply: batch_stencil<T, DIM, kApply>(op, table, s); break;
-    case kJacobi: batch_stencil<T, DIM, kJacobi>(op, table, s); break;
-    case kResidual: batch_stencil<T, DIM, kResidual>(op, table, s); break;
-    case kNormB: batch_stencil<T, DIM, kNormB>(op, table, s); break;
-    default: batch_stencil<T, DIM, kApplyDot>(op, table, s); break;
-  }
+  return check_launch();
 }
 
 }  // namespace
@@ -881,14 +590,7 @@ int launch_stencil_batch(const BatchOp& op, const char* table, hipStream_t s) {
     hipLaunchKernelGGL(reduce_kernel, dim3(op.nwg), dim3(kRedT), 0, s, batched<ReduceArgs>(op, table));
     return check_launch();
   }
-  if (op.dtype == MF_F64) {
-    if (op.dim == 2) batch_dispatch<double, 2>(op, table, s);
-    else batch_dispatch<double, 3>(op, table, s);
-  } else {
-    if (op.dim == 2) batch_dispatch<float, 2>(op, table, s);
-    else batch_dispatch<float, 3>(op, table, s);
-  }
-  return check_launch();
+  return op.dtype == MF_F64 ? batch_dispatch<double>(op, table, s) : batch_dispatch<float>(op, table, s);
 }
 
 }  // namespace mf

@@ -277,25 +277,6 @@ void run_tail(int dim, const Launch<TailArgs<T>>& l, int lds, hipStream_t s) {
   else hipLaunchKernelGGL((vcycle_tail_kernel<T, 3>), dim3(l.nwg), dim3(kTailWG), lds, s, l);
 }
 
-template <class A>
-Launch<A> single(const A& a, int nwg) {
-  Launch<A> l{};
-  l.one = a;
-  l.nseg = 0;
-  l.nwg = nwg;
-  return l;
-}
-
-template <class A>
-Launch<A> batched(const BatchOp& op, const char* table) {
-  Launch<A> l{};
-  l.many = (const A*)(table + op.args_off);
-  l.wg0 = (const int32_t*)(table + op.wg0_off);
-  l.nseg = op.nseg;
-  l.nwg = op.nwg;
-  return l;
-}
-
 }  // namespace
 
 template <typename T>

@@ -245,17 +245,6 @@ __global__ __launch_bounds__(256) void vector_kernel(const Launch<VecArgs> L) {
 }
 
 // ---------------------------------------------------------------- PCG
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-__device__ __forceinline__ double wmax(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-
 // Grid-stride over the storage index, nblk blocks of 256 threads.  KIND
 // kOpPcgZDot: z = s e with s = res[sslot] for FP32 e (the preconditioner
 // solved for r / s) and 1 for FP64 e, partials of r . z.  KIND kOpPcgUpdate:
@@ -328,8 +317,8 @@ __global__ __launch_bounds__(256) void pcg_lin_kernel(const Launch<PcgArgs> L) {
       }
     }
   }
-  ss = wsum(ss);
-  mx = wmax(mx);
+  ss = wave_sum(ss);
+  mx = wave_max(mx);
   __shared__ double s_ss[4], s_mx[4];
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & (kWave - 1)) == 0) {
@@ -363,25 +352,6 @@ __global__ __launch_bounds__(256) void pcg_dir_kernel(const Launch<VecArgs> L) {
   }
   const double beta = a.res[2] / a.res[3];
   for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < a.n; i += stride) p[i] = fma(beta, p[i], z(i));
-}
-
-template <class A>
-Launch<A> single(const A& a, int nwg) {
-  Launch<A> l{};
-  l.one = a;
-  l.nseg = 0;
-  l.nwg = nwg;
-  return l;
-}
-
-template <class A>
-Launch<A> batched(const BatchOp& op, const char* table) {
-  Launch<A> l{};
-  l.many = (const A*)(table + op.args_off);
-  l.wg0 = (const int32_t*)(table + op.wg0_off);
-  l.nseg = op.nseg;
-  l.nwg = op.nwg;
-  return l;
 }
 
 template <int KIND>
@@ -562,7 +532,7 @@ __global__ __launch_bounds__(256) void lin3_kernel(const Lin3Args a) {
     mx = fmax(mx, fabs(v));
   }
   if (!a.part) return;
-  mx = wmax(mx);
+  mx = wave_max(mx);
   __shared__ double s_mx[4];
   if ((threadIdx.x & (kWave - 1)) == 0) s_mx[threadIdx.x >> 6] = mx;
   __syncthreads();

@@ -1,0 +1,393 @@
+// Device code of the 3D stencil launches (gfx950): the interior walk of the
+// tetrahedral macros, the macro faces and the macro edges and vertices.  A
+// launch's tile list mixes the three kinds, so that every row of the level,
+// shared DoFs included, is finished by one launch.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rows.hpp"
+#include "wave.hpp"
+
+namespace mf {
+
+// ------------------------------------------------------------------ buffers
+// Bounds-checked accesses relative to a base: a load past the end gives 0, a
+// store past it is dropped, so neither needs a clamp or a branch.  Offsets
+// are bytes; kDrop is past every buffer (sizes are capped below it).
+namespace buf {
+
+using Rsrc = __amdgpu_buffer_rsrc_t;
+constexpr unsigned kDrop = 0x80000000u;
+
+template <typename T>
+__device__ __forceinline__ Rsrc make(const T* p, int64_t n) {
+  const int64_t bytes = n * (int64_t)sizeof(T);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff),
+                                           0x00027000);
+}
+
+typedef unsigned U2 __attribute__((ext_vector_type(2)));
+
+template <typename T>
+__device__ __forceinline__ T ld(Rsrc r, unsigned off) {
+  if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+template <typename T>
+__device__ __forceinline__ void st(Rsrc r, unsigned off, T v) {
+  if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
+}
+
+}  // namespace buf
+
+// Row value of a macro-boundary DoF that is not Dirichlet, from its assembled
+// sum acc; inv = 1 / assembled diagonal.
+template <typename T, int MODE>
+__device__ __forceinline__ T boundary_row(T acc, T xc, T bv, T omega, T inv) {
+  if (MODE == kApply || MODE == kApplyDot) return acc;
+  if (MODE == kJacobi) return fma(omega * inv, bv - acc, xc);
+  if (MODE == kResidual) return bv - acc;
+  return bv;
+}
+template <typename T, int MODE>
+__device__ __forceinline__ T dirichlet_row(T xc, T bv) {
+  return MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : xc);
+}
+
+// ------------------------------------------------------------------ interior
+// Rows off the y = 0 and z = 0 faces, in a slab of nz slices from z0: the
+// interior points, and the x = 0 and far-face (x + y + z = N) points where
+// those faces are Dirichlet (they copy x), so that such rows are written
+// without holes.  The slab's rows are taken in bands of R (band b: rows
+// R b + 1 .. R b + R); a band's columns are those of its first row in slice z0
+// (x = 0 .. N - z0 - R b - 1), so every output's x +- 1 neighbours are columns
+// of the same band.  The bands' columns are numbered one after the other and
+// a wave takes 64 consecutive ones (62 outputs), so that short rows fill the
+// lanes as long ones do.
+//
+// Each lane walks its column upward through the slices with the rows
+// R b .. R b + R + 1 of four slices in registers.  Storage offsets are per lane
+// and advance by additions: in a slice of side S, row y + 1 starts S + 1 - y
+// after row y, and (x, y, z + 1) lies T(S) - y after (x, y, z), T(S) being
+// the slice's points.  Rows and slices past the macro's far face give values
+// that no output uses; offsets past the macro's end are outside the buffer.
+//
+// Bound: memory.  Against pencils of 62 columns x 4 rows x 8 slices whose lanes
+// past a row's end idled and whose boundary rows took per-lane weights from
+// LDS, this needs 8.2 million wave instructions instead of 23 at N = 256 (cube,
+// FP64 apply) and no exchange launch: 94.0 -> 72.4 us per apply (3.8 TB/s of x
+// and y; a copy that walks the same way runs at 4.0, a straight one at 6.1);
+// two FP32 sweeps 160 -> 96 us; N = 128 FP64 apply 28 -> 11.7 us.  Rows written
+// with holes (boundary points left to other tiles) cost 6 us more: a line
+// that leaves the cache half written is written twice.
+struct Column {
+  int x, y0;  // column, row below the band's first output row
+};
+
+// q-th column of the slab of side A = N - z0: band b starts at
+// b A - R b (b - 1) / 2, so b is the smaller root of
+// R b^2 - (2 A + R) b + 2 q = 0, rounded down and corrected by one step either
+// way (FP32: the discriminant is within an ulp and the root within an ulp).
+template <int R>
+__device__ __forceinline__ Column column_of(int A, int q) {
+  const float c = (float)(2 * A + R);
+  int b = (int)((c - __builtin_amdgcn_sqrtf(fmaxf(c * c - (float)(8 * R) * (float)q, 0.0f))) * (0.5f / R));
+  auto start = [&](int k) { return k * A - R * ((k * (k - 1)) >> 1); };
+  b = max(b, 0);
+  if (start(b) > q) --b;
+  else if (start(b + 1) <= q) ++b;
+  return Column{q - start(b), R * b};
+}
+
+template <typename T, int MODE, int R>
+__device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T* __restrict__ X, T* __restrict__ Y,
+                                      const T* __restrict__ B, T omega, double& ss, double& mx) {
+  using wave::dn1;
+  using wave::up1;
+  constexpr bool kX = MODE != kNormB;                      // reads x
+  constexpr bool kB = MODE != kApply && MODE != kApplyDot;  // reads b
+  constexpr unsigned E = sizeof(T);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int N = M.N, z0 = t.z & 0xffff, nz = t.z >> 16, Q = t.y0, A = N - z0;
+  T w[15];
+#pragma unroll
+  for (int o = 0; o < 15; ++o) w[o] = Prec<T>::w(M, full_mask(3), o);
+  const int qi = t.x0 + lane;
+  const Column col = column_of<R>(A, min(max(qi, 0), Q - 1));
+  // this lane's output (j, k) — row y0 + j, slice z0 + k — is written iff key + j + k < lim:
+  // interior points, with copy_far also the far face's; x = 0 only with copy_left (off the far face)
+  constexpr int kFarBit = full_mask(3) & ~1, kLeftBit = full_mask(3) & ~2;
+  const int copy_far = (M.dir_mask >> kFarBit) & 1, copy_left = (M.dir_mask >> kLeftBit) & 1;
+  const int lim = A + copy_far;
+  const bool left = col.x == 0;
+  const bool mine = (unsigned)(lane - 1) < (unsigned)kTileW && (unsigned)qi < (unsigned)Q && (!left || copy_left);
+  const int key = mine ? col.x + col.y0 + (left ? copy_far : 0) : N + 1;
+  const int64_t sb = M.base + slice_base(N, z0 - 1);
+  const int64_t rest = tet_count_small(N + 1) - slice_base(N, z0 - 1);
+  const buf::Rsrc bx = buf::make(X + sb, rest), by = buf::make(Y + sb, rest);
+  const buf::Rsrc bb = kB ? buf::make(B + sb, rest) : bx;
+
+  // cursor of the next slice to load: offset of row y0, points of row y0 (both in bytes), side
+  const unsigned yb = (unsigned)col.y0 * E;
+  unsigned o = (unsigned)(row_start(A + 1, col.y0) + col.x) * E, D = (unsigned)(A + 2 - col.y0) * E;
+  int S = A + 1;
+  auto next_slice = [&](unsigned& off, unsigned& d, int side) {
+    off += (unsigned)(((side + 1) * (side + 2)) >> 1) * E - yb;
+    d -= E;
+  };
+  unsigned oo = o, Do = D;  // cursor of the output slices
+  next_slice(oo, Do, S);
+  int So = S - 1;
+  constexpr int NS = 4;  // slices in registers: the three an output slice reads, and the next
+  T s[NS][R + 2];
+  auto load_slice = [&](T* v) {
+    unsigned r = o;
+#pragma unroll
+    for (int j = 0; j < R + 2; ++j) {
+      v[j] = buf::ld<T>(bx, r);
+      r += D - (unsigned)j * E;
+    }
+    next_slice(o, D, S);
+    --S;
+  };
+  unsigned oq[2][R];  // offsets of the output rows
+  T bq[2][R];
+  auto out_rows = [&](unsigned* off, T* v) {
+    unsigned r = oo;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      r += Do - (unsigned)j * E;
+      off[j] = r;
+      if (kB) v[j] = buf::ld<T>(bb, r);
+    }
+    next_slice(oo, Do, So);
+    --So;
+  };
+  if (kX) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) load_slice(s[i]);
+  }
+  out_rows(oq[0], bq[0]);
+  for (int k0 = 0; k0 < nz; k0 += NS) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int k = k0 + i;
+      if (k >= nz) break;
+      out_rows(oq[(i + 1) % 2], bq[(i + 1) % 2]);
+      const T* a0 = s[i];
+      const T* a1 = s[(i + 1) % NS];
+      const T* a2 = s[(i + 2) % NS];
+#pragma unroll
+      for (int j = 1; j <= R; ++j) {
+        T acc = T(0);
+        if (kX) {
+          // the terms with dx = -1 and dx = +1 are summed in the neighbour's
+          // lane and shifted once each (a shift is two moves in FP64)
+          T l = w[3] * a0[j + 1], r = w[1] * a0[j];
+          acc = w[0] * a0[j];
+          acc = fma(w[2], a0[j + 1], acc);
+          acc = fma(w[4], a1[j - 1], acc);
+          l = fma(w[6], a1[j], l);
+          r = fma(w[5], a1[j - 1], r);
+          acc = fma(w[7], a1[j], acc);
+          l = fma(w[9], a1[j + 1], l);
+          r = fma(w[8], a1[j], r);
+          acc = fma(w[10], a1[j + 1], acc);
+          l = fma(w[13], a2[j], l);
+          r = fma(w[12], a2[j - 1], r);
+          acc = fma(w[11], a2[j - 1], acc);
+          acc = fma(w[14], a2[j], acc);
+          acc = (acc + up1(l)) + dn1(r);
+        }
+        const T bv = bq[i % 2][j - 1], xc = a1[j];
+        const bool in = key < lim - j - k;
+        const bool dir = left || key == A - j - k;  // (of the lanes written)
+        T out;
+        if (MODE == kApply || MODE == kApplyDot) out = acc;
+        else if (MODE == kJacobi) out = fma(omega * Prec<T>::invd(M), bv - acc, xc);
+        else if (MODE == kResidual) out = bv - acc;
+        else out = bv;
+        out = dir ? dirichlet_row<T, MODE>(xc, bv) : out;
+        if (MODE != kNormB) buf::st<T>(by, in ? oq[i % 2][j - 1] : buf::kDrop, out);
+        if (has_partials(MODE)) accum<T, MODE>(ss, mx, in ? out : T(0), in ? xc : T(0));
+      }
+      if (kX && k + NS < nz + 2) load_slice(s[i]);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ faces
+// Whether offset o of the 3D stencil stays in the macro at an inner point of
+// its face f (f = 0: x + y + z = N, f = 1..3: x, y, z = 0).
+__host__ __device__ constexpr bool on_side(int f, int o) {
+  constexpr StencilTable ST = stencil_table(3);
+  return f == 0 ? ST.off[o][0] + ST.off[o][1] + ST.off[o][2] <= 0 : ST.off[o][f - 1] >= 0;
+}
+
+// Partial row of an inner point of face F of macro M (X points at it): its 11
+// neighbours in the macro, in table order.
+template <typename T, int F>
+__device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int y, int z) {
+  constexpr int mask = full_mask(3) & ~(1 << F);
+  int off[15];
+  nbr_offsets3(M.N, y, z, off);
+  T v[15], acc = T(0);
+#pragma unroll
+  for (int o = 0; o < 15; ++o)
+    if (on_side(F, o)) v[o] = X[off[o]];
+#pragma unroll
+  for (int o = 0; o < 15; ++o)
+    if (on_side(F, o)) acc = fma(Prec<T>::w(M, mask, o), v[o], acc);
+  return acc;
+}
+
+// Storage index in copy C of the face point with weights wa, wb (and its y, z).
+__device__ __forceinline__ int64_t face_index(const MacroDev* md, const FaceCopy& C, int N, int wa, int wb, int& y,
+                                              int& z) {
+  const int x = C.n[0] * N + C.a[0] * wa + C.b[0] * wb;
+  y = C.n[1] * N + C.a[1] * wa + C.b[1] * wb;
+  z = C.n[2] * N + C.a[2] * wa + C.b[2] * wb;
+  return md[C.macro].base + idx3(N, x, y, z);
+}
+
+// t.y0 inner points of the Dirichlet face t.z from its t.x0-th on (they copy
+// x), four at a time per lane: their loads are issued before any store.
+template <typename T, int MODE>
+__device__ __forceinline__ void face_copies(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
+  constexpr bool kX = MODE != kNormB;
+  constexpr bool kB = MODE == kResidual || MODE == kNormB;
+  constexpr int U = 4;
+  const FaceDev& F = a.faces[t.z];
+  for (int i0 = threadIdx.x & (kWave - 1); i0 < t.y0; i0 += U * kWave) {
+    int64_t at[U];
+    T xc[U], bv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int ia, ib, y, z;
+      slice_xy3(F.N - 3, t.x0 + min(i0 + u * kWave, t.y0 - 1), ia, ib);
+      at[u] = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, y, z);
+      xc[u] = kX ? a.X[at[u]] : T(0);
+      bv[u] = kB ? a.B[at[u]] : T(0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * kWave >= t.y0) break;
+      const T out = dirichlet_row<T, MODE>(xc[u], bv[u]);
+      if (MODE != kNormB) a.Y[at[u]] = out;
+      accum<T, MODE>(ss, mx, out, xc[u]);
+    }
+  }
+}
+
+// t.y0 inner points of macro face t.z (not Dirichlet) from its t.x0-th on:
+// whole rows, summed over the face's one or two macros in the face's order,
+// written to every copy.  Macro, face and weights are the same for all lanes
+// (scalar registers), so a copy's row is 11 gathers and as many FMAs.
+template <typename T, int MODE>
+__device__ __forceinline__ void face_rows(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
+  constexpr bool kX = MODE != kNormB;
+  constexpr bool kB = MODE != kApply && MODE != kApplyDot;
+  const FaceDev& F = a.faces[t.z];
+  if (F.dirichlet) return face_copies<T, MODE>(a, t, ss, mx);
+  const int N = F.N;
+  for (int i = threadIdx.x & (kWave - 1); i < t.y0; i += kWave) {
+    int ia, ib;
+    slice_xy3(N - 3, t.x0 + i, ia, ib);
+    int64_t at[2];
+    int y[2], z[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) at[c] = face_index(a.md, F.cp[c], N, ia + 1, ib + 1, y[c], z[c]);
+    const T xc = kX ? a.X[at[0]] : T(0), bv = kB ? a.B[at[0]] : T(0);
+    T acc = T(0);
+    if (kX) {
+      for (int c = 0; c < F.copies; ++c) {
+        const MacroDev& M = a.md[F.cp[c].macro];
+        const T* Xc = a.X + (c == 0 ? at[0] : at[1]);
+        const int yc = c == 0 ? y[0] : y[1], zc = c == 0 ? z[0] : z[1];
+        switch (F.cp[c].face) {
+          case 0: acc += face_partial<T, 0>(M, Xc, yc, zc); break;
+          case 1: acc += face_partial<T, 1>(M, Xc, yc, zc); break;
+          case 2: acc += face_partial<T, 2>(M, Xc, yc, zc); break;
+          default: acc += face_partial<T, 3>(M, Xc, yc, zc); break;
+        }
+      }
+    }
+    const T out = boundary_row<T, MODE>(acc, xc, bv, a.omega, sizeof(T) == 8 ? (T)F.inv : (T)F.invf);
+    if (MODE != kNormB) {
+      a.Y[at[0]] = out;
+      if (F.copies == 2) a.Y[at[1]] = out;
+    }
+    accum<T, MODE>(ss, mx, out, xc);
+  }
+}
+
+// ------------------------------------------------------------------ edges, vertices
+// Partial row of one copy of a macro edge or vertex DoF: the partial stencil
+// of its support mask, neighbours outside the macro dropped, table order.
+template <typename T>
+__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X) {
+  constexpr StencilTable ST = stencil_table(3);
+  const MacroDev& M = md[k.macro];
+  const int N = M.N;
+  int off[15];
+  nbr_offsets3(N, k.y, k.z, off);
+  T p = T(0);
+#pragma unroll
+  for (int o = 0; o < ST.n; ++o) {
+    const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
+    const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
+    const T v = X[in ? k.idx + off[o] : k.idx];
+    p = fma(Prec<T>::w(M, k.mask, o), in ? v : T(0), p);
+  }
+  return p;
+}
+
+// t.y0 copies of macro edge and vertex DoFs, one per lane; the copies of a
+// DoF sit in consecutive lanes from its head (kEdgeTile), or, with more than
+// 64 copies, one DoF fills the tile in steps of 64 (kEdgeBigTile).  The
+// copies' partial rows are summed in list order by every lane of the DoF.
+template <typename T, int MODE>
+__device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
+  constexpr bool kX = MODE != kNormB;
+  constexpr bool kB = MODE != kApply && MODE != kApplyDot;
+  const int lane = threadIdx.x & (kWave - 1);
+  const EdgeCopy* L = a.edges + t.x0;
+  if (t.macro == kEdgeBigTile) {
+    T acc = T(0);
+    if (kX && !L[0].dirichlet)
+      for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+        const int n = min(kWave, t.y0 - c0);
+        const T p = lane < n ? copy_partial<T>(a.md, L[c0 + lane], a.X) : T(0);
+        for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
+      }
+    const T xh = kX ? a.X[L[0].idx] : T(0), bh = kB ? a.B[L[0].idx] : T(0);
+    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : boundary_row<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
+    if (MODE != kNormB)
+      for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
+    if (lane == 0) accum<T, MODE>(ss, mx, out, xh);
+    return;
+  }
+  const bool live = lane < t.y0;
+  const EdgeCopy k = L[live ? lane : 0];
+  T p = T(0);
+  if (kX && live && !k.dirichlet) p = copy_partial<T>(a.md, k, a.X);
+  T acc = T(0);
+  if (kX) {
+    const int n = live ? k.copies : 0;
+    for (int i = 0; __builtin_amdgcn_ballot_w64(i < n); ++i) {
+      const T v = __shfl(p, (k.head + i) & (kWave - 1), kWave);
+      acc += i < n ? v : T(0);
+    }
+  }
+  const T xo = kX ? a.X[k.idx] : T(0), bo = kB ? a.B[k.idx] : T(0);
+  const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
+  const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : boundary_row<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
+  if (live) {
+    if (MODE != kNormB) a.Y[k.idx] = out;
+    if (lane == k.head) accum<T, MODE>(ss, mx, out, xo);
+  }
+}
+
+}  // namespace mf

@@ -48,5 +48,16 @@ __device__ __forceinline__ int xcd_wg(int nwg) {
 // Grid of an XCD-mapped launch of nwg workgroups.
 inline int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
 
+// The same with runs of RUN consecutive workgroups dealt to the XCDs in turn:
+// neighbours still share an L2, and the launch as a whole moves through
+// memory in one front instead of eight.
+template <int RUN>
+__device__ __forceinline__ int xcd_wg_run(int nwg) {
+  const int k = blockIdx.x % kXCD, j = blockIdx.x / kXCD;
+  const int n = ((j / RUN) * kXCD + k) * RUN + j % RUN;
+  return n < nwg ? n : -1;
+}
+inline int xcd_grid_run(int nwg, int run) { return kXCD * run * ((nwg + kXCD * run - 1) / (kXCD * run)); }
+
 }  // namespace wave
 }  // namespace mf
