@@ -189,7 +189,7 @@ __device__ __forceinline__ void p2_tile(int x0, int y0, const MacroDev& Md, cons
 template <typename T>
 __global__ __launch_bounds__(kWG) void p2_kernel(const Tile* __restrict__ tiles, int nwg, const MacroDev* md,
                                                  const P2Macro* p2, const T* __restrict__ X, T* __restrict__ Y) {
-  const int g = wave::xcd_wg(nwg);
+  const int g = wave::xcd_wg_runs(nwg, wave::kRuns2);
   if (g < 0) return;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Tile t = tiles[g * kWavesPerWG + wv];
@@ -258,7 +258,7 @@ template <typename T>
 int run_p2(const mf_mesh* m, const Level& F, const void* x, void* y, hipStream_t s) {
   const int nwg = (int)(F.p2_tiles.size() / kWavesPerWG);
   if (nwg > 0)
-    hipLaunchKernelGGL(p2_kernel<T>, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s, F.dev.p2_tiles, nwg, F.dev.md,
+    hipLaunchKernelGGL(p2_kernel<T>, dim3(wave::xcd_grid_runs(nwg, wave::kRuns2)), dim3(kWG), 0, s, F.dev.p2_tiles, nwg, F.dev.md,
                        m->p2_dev, (const T*)x, (T*)y);
   const int64_t nb = (int64_t)m->nc * 3 * F.N;
   hipLaunchKernelGGL(p2_boundary_kernel<T>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, F.dev.md, m->p2_dev,

@@ -16,11 +16,11 @@ namespace {
 // FP64 apply / Jacobi / residual 73.6 / 94.0 / 93.2 us against 75.3 / 96 / 96 with
 // one chunk per XCD (runs of 4: 74.8 / 94.3 / 93.7, of 64: 76.8 / 98.9 / 98.7);
 // levels that fit the caches gain nothing from it.
-constexpr int kXcdRun = 16;
+constexpr wave::XcdRuns kRuns3{1000, 4};
 
 template <typename T, int MODE, int R>
 __global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<T>> L) {
-  const int g = R == kMaxR3 ? wave::xcd_wg_run<kXcdRun>(L.nwg) : wave::xcd_wg(L.nwg);
+  const int g = R == kMaxR3 ? wave::xcd_wg_runs(L.nwg, kRuns3) : wave::xcd_wg(L.nwg);
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<
 
 template <typename T, int MODE>
 void run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
-  const dim3 grid(R == kMaxR3 ? wave::xcd_grid_run(l.nwg, kXcdRun) : wave::xcd_grid(l.nwg)), wg(kWG);
+  const dim3 grid(R == kMaxR3 ? wave::xcd_grid_runs(l.nwg, kRuns3) : wave::xcd_grid(l.nwg)), wg(kWG);
   static_assert(kMaxR3 == 4, "one instance per band height");
   if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, 0, s, l);
   else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, 0, s, l);

@@ -36,7 +36,6 @@ namespace {
 
 using wave::dn1;
 using wave::up1;
-using wave::xcd_wg;
 
 
 #ifndef MF_RING_U2
@@ -332,7 +331,7 @@ __device__ __forceinline__ bool tile_on_boundary(const Tile& t, int N) {
 
 template <typename T, int MODE>
 __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T>> L) {
-  const int g = xcd_wg(L.nwg);
+  const int g = wave::xcd_wg_runs(L.nwg, wave::kRuns2);
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
@@ -463,7 +462,7 @@ void run_stencil(const Level& L, const void* x, void* y, const void* b, double o
                  hipStream_t s) {
   const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
   if (a.nwg > 0)
-    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid(a.nwg)), dim3(kWG), 0, s, single(a, a.nwg));
+    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(a.nwg, wave::kRuns2)), dim3(kWG), 0, s, single(a, a.nwg));
   const int nblk = exchange_blocks(L);
   if (nblk == 0) return;
   hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(nblk), dim3(kIfaceWG), 0, s,
@@ -512,7 +511,7 @@ int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x,
 template <typename T, int MODE>
 void batch_stencil(const BatchOp& op, const char* table, hipStream_t s) {
   if (op.kind == kOpStencil)
-    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid(op.nwg)), dim3(kWG), 0, s,
+    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(op.nwg, wave::kRuns2)), dim3(kWG), 0, s,
                        batched<StencilArgs<T>>(op, table));
   else
     hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(op.nwg), dim3(kIfaceWG), 0, s,

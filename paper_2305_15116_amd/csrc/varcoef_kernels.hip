@@ -147,7 +147,7 @@ template <typename T>
 __global__ __launch_bounds__(kWG) void varcoef_kernel(const Tile* __restrict__ tiles, int nwg, const MacroDev* md,
                                                       const T* __restrict__ K, const T* __restrict__ X,
                                                       T* __restrict__ Y) {
-  const int g = wave::xcd_wg(nwg);
+  const int g = wave::xcd_wg_runs(nwg, wave::kRuns2);
   if (g < 0) return;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Tile t = tiles[g * kWavesPerWG + wv];
@@ -165,7 +165,7 @@ int run_varcoef(const Level& L, const void* k, const void* x, void* y, hipStream
   const Tile* tiles = f32 ? L.dev.tiles_f32 : L.dev.tiles;
   const int nwg = (int)((f32 ? L.tiles_f32.size() : L.tiles.size()) / kWavesPerWG);
   if (nwg > 0)
-    hipLaunchKernelGGL(varcoef_kernel<T>, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s, tiles, nwg, L.dev.md,
+    hipLaunchKernelGGL(varcoef_kernel<T>, dim3(wave::xcd_grid_runs(nwg, wave::kRuns2)), dim3(kWG), 0, s, tiles, nwg, L.dev.md,
                        (const T*)k, (const T*)x, (T*)y);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));

@@ -48,16 +48,31 @@ __device__ __forceinline__ int xcd_wg(int nwg) {
 // Grid of an XCD-mapped launch of nwg workgroups.
 inline int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
 
-// The same with runs of RUN consecutive workgroups dealt to the XCDs in turn:
-// neighbours still share an L2, and the launch as a whole moves through
-// memory in one front instead of eight.
-template <int RUN>
-__device__ __forceinline__ int xcd_wg_run(int nwg) {
+// The same for launches of at least `from` workgroups with runs of 2^shift
+// consecutive workgroups dealt to the XCDs in turn: neighbours still share an
+// L2, and the launch as a whole moves through memory in one front instead of
+// eight.  Smaller launches (whose data the caches hold) keep one chunk per XCD.
+struct XcdRuns {
+  int from, shift;
+};
+__device__ __forceinline__ int xcd_wg_runs(int nwg, XcdRuns r) {
+  if (nwg < r.from) return xcd_wg(nwg);
   const int k = blockIdx.x % kXCD, j = blockIdx.x / kXCD;
-  const int n = ((j / RUN) * kXCD + k) * RUN + j % RUN;
+  const int n = (((j >> r.shift) * kXCD + k) << r.shift) + (j & ((1 << r.shift) - 1));
   return n < nwg ? n : -1;
 }
-inline int xcd_grid_run(int nwg, int run) { return kXCD * run * ((nwg + kXCD * run - 1) / (kXCD * run)); }
+inline int xcd_grid_runs(int nwg, XcdRuns r) {
+  if (nwg < r.from) return xcd_grid(nwg);
+  const int per = kXCD << r.shift;
+  return (nwg + per - 1) / per * per;
+}
+// The 2D walks: runs of 32.  Level 14, FP64 apply / Jacobi: 380.7 / 565.6 us
+// with runs of 32, 399 / 586 with one chunk per XCD, 384.8 / 566 and 377 / 564
+// with 16 and 64 (two triangles at level 12: 58.0 / 82.3, 62.1 / 86.9, 58.3 /
+// 82.2, 57.8 / 82.5); variable coefficient at level 14 604 -> 578, P2 at level 13
+// 424 -> 415.  13 triangles at level 10: FP64 (3,600 workgroups) 31.6 -> 31.1,
+// FP32 (1,900) 19.4 -> 20.4, one triangle at level 10 5.5 -> 5.7.
+constexpr XcdRuns kRuns2{3000, 5};
 
 }  // namespace wave
 }  // namespace mf
