@@ -260,6 +260,7 @@ static int build_topology(mf_mesh* m) {
 static void build_tiles3(const mf_mesh* m, Level& L) {
   const int N = L.N;
   const Shape3 sh = shape3(N);
+  const FaceRuns runs = face_runs(N);
   std::vector<Tile> bnd;
   for (int64_t c = 0; c < m->nc; ++c)
     for (int z0 = 1; z0 <= N - 2; z0 += sh.PZ) {
@@ -313,7 +314,7 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
     if (F.dirichlet && F.cp[0].face <= 1) continue;  // written by the walk
     F.inv = diag != 0.0 ? 1.0 / diag : 0.0;
     F.invf = (float)F.inv;
-    const int id = (int)L.faces.size(), n = (N - 1) * (N - 2) / 2, run = F.dirichlet ? kFaceRun0 : (F.copies == 1 ? kFaceRun1 : kFaceRun2);
+    const int id = (int)L.faces.size(), n = (N - 1) * (N - 2) / 2, run = F.dirichlet ? runs.dirichlet : (F.copies == 1 ? runs.one : runs.two);
     L.faces.push_back(F);
     for (int i = 0; i < n; i += run) bnd.push_back({kFaceTile, i, std::min(run, n - i), id});
   }

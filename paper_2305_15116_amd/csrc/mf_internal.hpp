@@ -52,8 +52,14 @@ constexpr int kEdgeBigTile = -4;
 // From this side on the inner points of a face have tiles of their own; below
 // (at most 21 points) they are listed with the edge and vertex copies.
 constexpr int kMinFaceN = 16;
-// points per face tile: Dirichlet faces (copies), faces of one and of two macros
-constexpr int kFaceRun0 = 2048, kFaceRun1 = 1536, kFaceRun2 = 128;
+// Points per face tile: Dirichlet faces (copies), faces of one and of two
+// macros.  Up to N = 128 a launch is a few latencies long, and a tile that takes
+// a second step lengthens it (N = 32, FP64 apply 4.5 us with 64 points, 6.6
+// with 128); above, larger tiles keep the norm partials few.
+struct FaceRuns {
+  int dirichlet, one, two;
+};
+MF_HD constexpr FaceRuns face_runs(int N) { return N >= 256 ? FaceRuns{2048, 1536, 128} : FaceRuns{256, 64, 64}; }
 // 3D prolongations walk runs of up to kTransferRun 64-point slice segments
 // (single segments below N = 256).
 constexpr int kTransferRun = 4;

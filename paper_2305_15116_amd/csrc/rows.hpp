@@ -16,7 +16,8 @@ struct Prec;
 template <>
 struct Prec<double> {
   static __device__ __forceinline__ double w(const MacroDev& M, int mask, int i) { return M.wm[mask][i]; }
-  static __device__ __forceinline__ double invd(const MacroDev& M) { return M.inv_diag; }
+  static __device__ __forceinline__ const double* row(const MacroDev& M, int mask) { return M.wm[mask]; }
+  static __device__ __forceinline__ const double& invd(const MacroDev& M) { return M.inv_diag; }
   static __device__ __forceinline__ double ginv(const double* d, const float*, int g) { return d[g]; }
   static __device__ __forceinline__ const double* K(const MacroDev& M, int t) { return M.K[t]; }
 };
@@ -24,7 +25,8 @@ struct Prec<double> {
 template <>
 struct Prec<float> {
   static __device__ __forceinline__ float w(const MacroDev& M, int mask, int i) { return M.wmf[mask][i]; }
-  static __device__ __forceinline__ float invd(const MacroDev& M) { return M.inv_diagf; }
+  static __device__ __forceinline__ const float* row(const MacroDev& M, int mask) { return M.wmf[mask]; }
+  static __device__ __forceinline__ const float& invd(const MacroDev& M) { return M.inv_diagf; }
   static __device__ __forceinline__ float ginv(const double*, const float* f, int g) { return f[g]; }
   static __device__ __forceinline__ const float* K(const MacroDev& M, int t) { return M.Kf[t]; }
 };
@@ -145,6 +147,17 @@ __device__ __forceinline__ void wg_partial(double ss, double mx, double* part, i
 template <class T>
 __device__ __forceinline__ const __attribute__((address_space(4))) T* as_const(const T* p) {
   return (const __attribute__((address_space(4))) T*)p;
+}
+
+// A record or a value of one at a wave-uniform address: a scalar load, whatever
+// the compiler can prove about the kernel's stores.
+template <class V>
+__device__ __forceinline__ V uniform(const V& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return *as_const(&v);
+#else
+  return v;  // the host pass only type-checks device code
+#endif
 }
 
 __device__ __forceinline__ int find_seg_c(const int32_t* wg0, int nseg, int g) {

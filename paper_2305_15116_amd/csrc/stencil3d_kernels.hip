@@ -12,15 +12,9 @@ namespace mf {
 
 namespace {
 
-// Fine levels (R = 4) deal runs of 16 workgroups to the XCDs in turn: N = 256,
-// FP64 apply / Jacobi / residual 73.6 / 94.0 / 93.2 us against 75.3 / 96 / 96 with
-// one chunk per XCD (runs of 4: 74.8 / 94.3 / 93.7, of 64: 76.8 / 98.9 / 98.7);
-// levels that fit the caches gain nothing from it.
-constexpr wave::XcdRuns kRuns3{1000, 4};
-
 template <typename T, int MODE, int R>
 __global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<T>> L) {
-  const int g = R == kMaxR3 ? wave::xcd_wg_runs(L.nwg, kRuns3) : wave::xcd_wg(L.nwg);
+  const int g = R == kMaxR3 ? wave::xcd_wg_runs(L.nwg, wave::kRuns3) : wave::xcd_wg(L.nwg);
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
@@ -33,14 +27,25 @@ __global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<
   if (has_partials(MODE) && a.part != nullptr) wg_partial<kWavesPerWG>(ss, mx, a.part, a.np, n);
 }
 
+// Workgroups per CU of the fine levels' launches.  Cube at N = 256 / 512, us
+// without a cap, then with 4 / 3 / 2: FP64 apply 72.9 / 507, 71.3 / 497, 70.6 /
+// 474, 72.8 / 472; FP64 Jacobi 96.8 / 706, -, 94.5 / 682, 92.8 / 643; FP32 apply
+// 41.0 / 274, 38.9 / 248, 39.7 / 255, -; FP32 Jacobi 47.8 / 374, 46.2 / 347, 46.8
+// / 340, 51.3 / 367.
+template <typename T, int MODE>
+constexpr int wgs_per_cu() {
+  return sizeof(T) == 4 ? 4 : (MODE == kApply ? 3 : 2);
+}
+
 template <typename T, int MODE>
 void run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
-  const dim3 grid(R == kMaxR3 ? wave::xcd_grid_runs(l.nwg, kRuns3) : wave::xcd_grid(l.nwg)), wg(kWG);
+  const dim3 grid(R == kMaxR3 ? wave::xcd_grid_runs(l.nwg, wave::kRuns3) : wave::xcd_grid(l.nwg)), wg(kWG);
+  const int lds = R == kMaxR3 ? wave::lds_cap(l.nwg, wave::kRuns3, wgs_per_cu<T, MODE>()) : 0;
   static_assert(kMaxR3 == 4, "one instance per band height");
-  if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, 0, s, l);
-  else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, 0, s, l);
-  else if (R == 2) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 2>), grid, wg, 0, s, l);
-  else hipLaunchKernelGGL((stencil3_kernel<T, MODE, 1>), grid, wg, 0, s, l);
+  if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, lds, s, l);
+  else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, lds, s, l);
+  else if (R == 2) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 2>), grid, wg, lds, s, l);
+  else hipLaunchKernelGGL((stencil3_kernel<T, MODE, 1>), grid, wg, lds, s, l);
 }
 
 template <typename T>

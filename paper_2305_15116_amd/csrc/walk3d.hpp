@@ -22,9 +22,14 @@ constexpr unsigned kDrop = 0x80000000u;
 
 template <typename T>
 __device__ __forceinline__ Rsrc make(const T* p, int64_t n) {
+  // address and size are the same for all lanes, but part of their 64-bit
+  // arithmetic is vector instructions: without the moves back to scalar
+  // registers every access would loop over the lanes' descriptors
+  const uint64_t u = (uint64_t)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)u), hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
   const int64_t bytes = n * (int64_t)sizeof(T);
-  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff),
-                                           0x00027000);
+  const int size = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)hi << 32 | lo), (short)0, size, 0x00027000);
 }
 
 typedef unsigned U2 __attribute__((ext_vector_type(2)));
@@ -42,10 +47,10 @@ __device__ __forceinline__ void st(Rsrc r, unsigned off, T v) {
 
 }  // namespace buf
 
-// Row value of a macro-boundary DoF that is not Dirichlet, from its assembled
-// sum acc; inv = 1 / assembled diagonal.
+// Row value of a DoF that is not Dirichlet, from its assembled sum acc; inv = 1
+// / assembled diagonal.
 template <typename T, int MODE>
-__device__ __forceinline__ T boundary_row(T acc, T xc, T bv, T omega, T inv) {
+__device__ __forceinline__ T row_value(T acc, T xc, T bv, T omega, T inv) {
   if (MODE == kApply || MODE == kApplyDot) return acc;
   if (MODE == kJacobi) return fma(omega * inv, bv - acc, xc);
   if (MODE == kResidual) return bv - acc;
@@ -77,9 +82,9 @@ __device__ __forceinline__ T dirichlet_row(T xc, T bv) {
 // Bound: memory.  Against pencils of 62 columns x 4 rows x 8 slices whose lanes
 // past a row's end idled and whose boundary rows took per-lane weights from
 // LDS, this needs 8.2 million wave instructions instead of 23 at N = 256 (cube,
-// FP64 apply) and no exchange launch: 94.0 -> 72.4 us per apply (3.8 TB/s of x
+// FP64 apply) and no exchange launch: 94.0 -> 70.5 us per apply (3.9 TB/s of x
 // and y; a copy that walks the same way runs at 4.0, a straight one at 6.1);
-// two FP32 sweeps 160 -> 96 us; N = 128 FP64 apply 28 -> 11.7 us.  Rows written
+// two FP32 sweeps 160 -> 92 us; N = 128 FP64 apply 28 -> 10.3 us.  Rows written
 // with holes (boundary points left to other tiles) cost 6 us more: a line
 // that leaves the cache half written is written twice.
 struct Column {
@@ -101,6 +106,51 @@ __device__ __forceinline__ Column column_of(int A, int q) {
   return Column{q - start(b), R * b};
 }
 
+// What a lane writes: output (j, k) — row y0 + j, slice z0 + k, j >= 1 — where
+// key + j + k < lim: interior points, and the far face's where it is
+// Dirichlet; x = 0 only where that face is (off the far face).
+struct WalkLane {
+  Column col;
+  int key, lim, A;
+  bool left;
+  __device__ __forceinline__ bool writes(int jk) const { return key < lim - jk; }
+  // (of the points written) on the Dirichlet boundary
+  __device__ __forceinline__ bool copies(int jk) const { return left || key == A - jk; }
+};
+template <int R>
+__device__ __forceinline__ WalkLane walk_lane(const Tile& t, const MacroDev& M) {
+  constexpr int kFarBit = full_mask(3) & ~1, kLeftBit = full_mask(3) & ~2;
+  const int lane = threadIdx.x & (kWave - 1), q = t.x0 + lane, Q = t.y0;
+  WalkLane w;
+  const int N = uniform(M.N), dir_mask = uniform(M.dir_mask);
+  w.A = N - (t.z & 0xffff);
+  w.col = column_of<R>(w.A, min(max(q, 0), Q - 1));
+  const int copy_far = (dir_mask >> kFarBit) & 1, copy_left = (dir_mask >> kLeftBit) & 1;
+  w.lim = w.A + copy_far;
+  w.left = w.col.x == 0;
+  const bool mine = (unsigned)(lane - 1) < (unsigned)kTileW && (unsigned)q < (unsigned)Q && (!w.left || copy_left);
+  w.key = mine ? w.col.x + w.col.y0 + (w.left ? copy_far : 0) : N + 1;
+  return w;
+}
+
+// A column's place in the slices of its slab, from slice z0 - 1 upward.
+template <typename T>
+struct Cursor {
+  unsigned off, row;  // bytes: offset of row y0's point from the first point of slice z0 - 1, length of row y0
+  unsigned yb;
+  int S;  // side of the slice
+  __device__ __forceinline__ Cursor(int A, const Column& c)
+      : off((unsigned)(row_start(A + 1, c.y0) + c.x) * (unsigned)sizeof(T)),
+        row((unsigned)(A + 2 - c.y0) * (unsigned)sizeof(T)),
+        yb((unsigned)c.y0 * (unsigned)sizeof(T)),
+        S(A + 1) {}
+  __device__ __forceinline__ void next() {
+    off += (unsigned)(((S + 1) * (S + 2)) >> 1) * (unsigned)sizeof(T) - yb;
+    row -= (unsigned)sizeof(T);
+    --S;
+  }
+};
+
 template <typename T, int MODE, int R>
 __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T* __restrict__ X, T* __restrict__ Y,
                                       const T* __restrict__ B, T omega, double& ss, double& mx) {
@@ -109,61 +159,42 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
   constexpr bool kX = MODE != kNormB;                      // reads x
   constexpr bool kB = MODE != kApply && MODE != kApplyDot;  // reads b
   constexpr unsigned E = sizeof(T);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int N = M.N, z0 = t.z & 0xffff, nz = t.z >> 16, Q = t.y0, A = N - z0;
+  const int N = uniform(M.N), z0 = t.z & 0xffff, nz = t.z >> 16;
+  const T* wrow = Prec<T>::row(M, full_mask(3));
   T w[15];
 #pragma unroll
-  for (int o = 0; o < 15; ++o) w[o] = Prec<T>::w(M, full_mask(3), o);
-  const int qi = t.x0 + lane;
-  const Column col = column_of<R>(A, min(max(qi, 0), Q - 1));
-  // this lane's output (j, k) — row y0 + j, slice z0 + k — is written iff key + j + k < lim:
-  // interior points, with copy_far also the far face's; x = 0 only with copy_left (off the far face)
-  constexpr int kFarBit = full_mask(3) & ~1, kLeftBit = full_mask(3) & ~2;
-  const int copy_far = (M.dir_mask >> kFarBit) & 1, copy_left = (M.dir_mask >> kLeftBit) & 1;
-  const int lim = A + copy_far;
-  const bool left = col.x == 0;
-  const bool mine = (unsigned)(lane - 1) < (unsigned)kTileW && (unsigned)qi < (unsigned)Q && (!left || copy_left);
-  const int key = mine ? col.x + col.y0 + (left ? copy_far : 0) : N + 1;
-  const int64_t sb = M.base + slice_base(N, z0 - 1);
+  for (int o = 0; o < 15; ++o) w[o] = uniform(wrow[o]);
+  const T invd = kB ? uniform(Prec<T>::invd(M)) : T(0);
+  const WalkLane wl = walk_lane<R>(t, M);
+  const int64_t sb = uniform(M.base) + slice_base(N, z0 - 1);
   const int64_t rest = tet_count_small(N + 1) - slice_base(N, z0 - 1);
   const buf::Rsrc bx = buf::make(X + sb, rest), by = buf::make(Y + sb, rest);
   const buf::Rsrc bb = kB ? buf::make(B + sb, rest) : bx;
 
-  // cursor of the next slice to load: offset of row y0, points of row y0 (both in bytes), side
-  const unsigned yb = (unsigned)col.y0 * E;
-  unsigned o = (unsigned)(row_start(A + 1, col.y0) + col.x) * E, D = (unsigned)(A + 2 - col.y0) * E;
-  int S = A + 1;
-  auto next_slice = [&](unsigned& off, unsigned& d, int side) {
-    off += (unsigned)(((side + 1) * (side + 2)) >> 1) * E - yb;
-    d -= E;
-  };
-  unsigned oo = o, Do = D;  // cursor of the output slices
-  next_slice(oo, Do, S);
-  int So = S - 1;
+  Cursor<T> in(wl.A, wl.col), out(wl.A, wl.col);
+  out.next();
   constexpr int NS = 4;  // slices in registers: the three an output slice reads, and the next
   T s[NS][R + 2];
   auto load_slice = [&](T* v) {
-    unsigned r = o;
+    unsigned r = in.off;
 #pragma unroll
     for (int j = 0; j < R + 2; ++j) {
       v[j] = buf::ld<T>(bx, r);
-      r += D - (unsigned)j * E;
+      r += in.row - (unsigned)j * E;
     }
-    next_slice(o, D, S);
-    --S;
+    in.next();
   };
   unsigned oq[2][R];  // offsets of the output rows
   T bq[2][R];
   auto out_rows = [&](unsigned* off, T* v) {
-    unsigned r = oo;
+    unsigned r = out.off;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      r += Do - (unsigned)j * E;
+      r += out.row - (unsigned)j * E;
       off[j] = r;
       if (kB) v[j] = buf::ld<T>(bb, r);
     }
-    next_slice(oo, Do, So);
-    --So;
+    out.next();
   };
   if (kX) {
 #pragma unroll
@@ -202,16 +233,11 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
           acc = (acc + up1(l)) + dn1(r);
         }
         const T bv = bq[i % 2][j - 1], xc = a1[j];
-        const bool in = key < lim - j - k;
-        const bool dir = left || key == A - j - k;  // (of the lanes written)
-        T out;
-        if (MODE == kApply || MODE == kApplyDot) out = acc;
-        else if (MODE == kJacobi) out = fma(omega * Prec<T>::invd(M), bv - acc, xc);
-        else if (MODE == kResidual) out = bv - acc;
-        else out = bv;
-        out = dir ? dirichlet_row<T, MODE>(xc, bv) : out;
-        if (MODE != kNormB) buf::st<T>(by, in ? oq[i % 2][j - 1] : buf::kDrop, out);
-        if (has_partials(MODE)) accum<T, MODE>(ss, mx, in ? out : T(0), in ? xc : T(0));
+        const bool wr = wl.writes(j + k);
+        T v = row_value<T, MODE>(acc, xc, bv, omega, invd);
+        v = wl.copies(j + k) ? dirichlet_row<T, MODE>(xc, bv) : v;
+        if (MODE != kNormB) buf::st<T>(by, wr ? oq[i % 2][j - 1] : buf::kDrop, v);
+        if (has_partials(MODE)) accum<T, MODE>(ss, mx, wr ? v : T(0), wr ? xc : T(0));
       }
       if (kX && k + NS < nz + 2) load_slice(s[i]);
     }
@@ -229,17 +255,17 @@ __host__ __device__ constexpr bool on_side(int f, int o) {
 // Partial row of an inner point of face F of macro M (X points at it): its 11
 // neighbours in the macro, in table order.
 template <typename T, int F>
-__device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int y, int z) {
-  constexpr int mask = full_mask(3) & ~(1 << F);
+__device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int N, int y, int z) {
+  const T* w = Prec<T>::row(M, full_mask(3) & ~(1 << F));
   int off[15];
-  nbr_offsets3(M.N, y, z, off);
+  nbr_offsets3(N, y, z, off);
   T v[15], acc = T(0);
 #pragma unroll
   for (int o = 0; o < 15; ++o)
     if (on_side(F, o)) v[o] = X[off[o]];
 #pragma unroll
   for (int o = 0; o < 15; ++o)
-    if (on_side(F, o)) acc = fma(Prec<T>::w(M, mask, o), v[o], acc);
+    if (on_side(F, o)) acc = fma(uniform(w[o]), v[o], acc);
   return acc;
 }
 
@@ -249,7 +275,7 @@ __device__ __forceinline__ int64_t face_index(const MacroDev* md, const FaceCopy
   const int x = C.n[0] * N + C.a[0] * wa + C.b[0] * wb;
   y = C.n[1] * N + C.a[1] * wa + C.b[1] * wb;
   z = C.n[2] * N + C.a[2] * wa + C.b[2] * wb;
-  return md[C.macro].base + idx3(N, x, y, z);
+  return uniform(md[C.macro].base) + idx3(N, x, y, z);
 }
 
 // t.y0 inner points of the Dirichlet face t.z from its t.x0-th on (they copy
@@ -307,14 +333,14 @@ __device__ __forceinline__ void face_rows(const StencilArgs<T>& a, const Tile& t
         const T* Xc = a.X + (c == 0 ? at[0] : at[1]);
         const int yc = c == 0 ? y[0] : y[1], zc = c == 0 ? z[0] : z[1];
         switch (F.cp[c].face) {
-          case 0: acc += face_partial<T, 0>(M, Xc, yc, zc); break;
-          case 1: acc += face_partial<T, 1>(M, Xc, yc, zc); break;
-          case 2: acc += face_partial<T, 2>(M, Xc, yc, zc); break;
-          default: acc += face_partial<T, 3>(M, Xc, yc, zc); break;
+          case 0: acc += face_partial<T, 0>(M, Xc, N, yc, zc); break;
+          case 1: acc += face_partial<T, 1>(M, Xc, N, yc, zc); break;
+          case 2: acc += face_partial<T, 2>(M, Xc, N, yc, zc); break;
+          default: acc += face_partial<T, 3>(M, Xc, N, yc, zc); break;
         }
       }
     }
-    const T out = boundary_row<T, MODE>(acc, xc, bv, a.omega, sizeof(T) == 8 ? (T)F.inv : (T)F.invf);
+    const T out = row_value<T, MODE>(acc, xc, bv, a.omega, sizeof(T) == 8 ? (T)F.inv : (T)F.invf);
     if (MODE != kNormB) {
       a.Y[at[0]] = out;
       if (F.copies == 2) a.Y[at[1]] = out;
@@ -363,7 +389,7 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
         for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
       }
     const T xh = kX ? a.X[L[0].idx] : T(0), bh = kB ? a.B[L[0].idx] : T(0);
-    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : boundary_row<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
+    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
     if (MODE != kNormB)
       for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
     if (lane == 0) accum<T, MODE>(ss, mx, out, xh);
@@ -383,7 +409,7 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
   }
   const T xo = kX ? a.X[k.idx] : T(0), bo = kB ? a.B[k.idx] : T(0);
   const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
-  const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : boundary_row<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
+  const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
   if (live) {
     if (MODE != kNormB) a.Y[k.idx] = out;
     if (lane == k.head) accum<T, MODE>(ss, mx, out, xo);
