@@ -60,7 +60,7 @@ int launch_exchange_apply(const Level& L, int dtype, void* y, hipStream_t s);
 // matrices (identity at Dirichlet DoFs), then the exchange.
 int launch_p2_apply(const mf_mesh* m, int level, int dtype, const void* x, void* y, hipStream_t s);
 
-// Variable-coefficient 2D apply y = A(k) x (k: nodal coefficient, same
+// Variable-coefficient apply y = A(k) x (k: nodal coefficient, same
 // layout as x), including the exchange of shared DoFs.
 int launch_varcoef_apply(const mf_mesh* m, const Level& L, int dtype, const void* k, const void* x, void* y,
                          hipStream_t s);

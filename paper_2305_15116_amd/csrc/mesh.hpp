@@ -21,6 +21,8 @@ struct LevelDev {
   MacroDev* md = nullptr;
   Tile* tiles = nullptr;       // interior wave tiles, padded to a multiple of kWavesPerWG
   Tile* tiles_f32 = nullptr;   // 2D FP32 wave tiles
+  Tile* btiles = nullptr;      // 3D face and edge tiles
+  Tile* vtiles[2] = {nullptr, nullptr};  // variable-coefficient column tiles (FP64, FP32)
   FaceDev* faces = nullptr;    // 3D macro faces
   EdgeCopy* edges = nullptr;   // 3D copies of macro edge and vertex DoFs
   Tile* segs = nullptr;        // row segments of 64 points covering every storage point
@@ -58,6 +60,8 @@ struct Level {
   std::vector<MacroDev> md;
   std::vector<Tile> tiles;      // interior wave tiles (natural order, padded)
   std::vector<Tile> tiles_f32;  // 2D FP32 wave tiles (kTileH2F rows); empty in 3D (same as tiles)
+  std::vector<Tile> btiles;     // 3D: the face and edge tiles by themselves, one per workgroup (kFaceRunsWG)
+  std::vector<Tile> vtiles[2];  // 3D: column tiles of the variable-coefficient walk (FP64, FP32)
   std::vector<FaceDev> faces;   // 3D: macro faces, and the copies of the edge and vertex DoFs, that tiles name
   std::vector<EdgeCopy> edges;
   std::vector<Tile> segs;       // per-point row segments

@@ -255,21 +255,28 @@ static int build_topology(mf_mesh* m) {
 }
 
 // ---------------------------------------------------------------- 3D tiles
-// Tiles of a 3D level: the interior walk's slabs of every macro, the inner
-// points of every macro face, and the copies of the edge and vertex DoFs.
-static void build_tiles3(const mf_mesh* m, Level& L) {
-  const int N = L.N;
-  const Shape3 sh = shape3(N);
-  const FaceRuns runs = face_runs(N);
-  std::vector<Tile> bnd;
-  for (int64_t c = 0; c < m->nc; ++c)
+// Column tiles of every macro's slabs, padded to whole workgroups.
+static std::vector<Tile> column_tiles(int N, int64_t nc, const Shape3& sh) {
+  std::vector<Tile> out;
+  for (int64_t c = 0; c < nc; ++c)
     for (int z0 = 1; z0 <= N - 2; z0 += sh.PZ) {
       // columns of the slab: band b has N - z0 - R b of them, as long as its first row has two
       int Q = 0;
       for (int b = 0; N - z0 - sh.R * b >= 2; ++b) Q += N - z0 - sh.R * b;
       const int nz = std::min(sh.PZ, N - 1 - z0);
-      for (int q0 = -1; q0 + 1 < Q; q0 += kTileW) L.tiles.push_back({(int32_t)c, q0, Q, z0 | nz << 16});
+      for (int q0 = -1; q0 + 1 < Q; q0 += kTileW) out.push_back({(int32_t)c, q0, Q, z0 | nz << 16});
     }
+  while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
+  return out;
+}
+
+// Tiles of a 3D level: the interior walk's slabs of every macro, the inner
+// points of every macro face, and the copies of the edge and vertex DoFs.
+static void build_tiles3(const mf_mesh* m, Level& L) {
+  const int N = L.N;
+  std::vector<Tile> bnd;
+  L.tiles = column_tiles(N, m->nc, shape3(N));
+  for (int f32 = 0; f32 < 2; ++f32) L.vtiles[f32] = column_tiles(N, m->nc, shape3_varcoef(N, f32));
   // faces: weights a and b run over two of the face's vertices, with a along
   // the first macro's x where its face holds vertices 0 and 1 (contiguous storage)
   const StencilTable ST = stencil_table(3);
@@ -314,16 +321,24 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
     if (F.dirichlet && F.cp[0].face <= 1) continue;  // written by the walk
     F.inv = diag != 0.0 ? 1.0 / diag : 0.0;
     F.invf = (float)F.inv;
-    const int id = (int)L.faces.size(), n = (N - 1) * (N - 2) / 2, run = F.dirichlet ? runs.dirichlet : (F.copies == 1 ? runs.one : runs.two);
+    const int id = (int)L.faces.size(), n = (N - 1) * (N - 2) / 2;
     L.faces.push_back(F);
-    for (int i = 0; i < n; i += run) bnd.push_back({kFaceTile, i, std::min(run, n - i), id});
+    auto cut = [&](std::vector<Tile>& to, const FaceRuns& r) {
+      const int run = F.dirichlet ? r.dirichlet : (F.copies == 1 ? r.one : r.two);
+      for (int i = 0; i < n; i += run) to.push_back({kFaceTile, i, std::min(run, n - i), id});
+    };
+    cut(bnd, face_runs(N));
+    cut(L.btiles, kFaceRunsWG);
   }
   // edge and vertex DoFs (the all-groups list's other groups; all of them on the smallest levels, except those
   // that the walk writes)
   int32_t first = 0;  // of the open tile
   auto close = [&] {
     const int32_t n = (int32_t)L.edges.size() - first;
-    if (n > 0) bnd.push_back({kEdgeTile, first, n, 0});
+    if (n > 0) {
+      bnd.push_back({kEdgeTile, first, n, 0});
+      L.btiles.push_back(bnd.back());
+    }
     first = (int32_t)L.edges.size();
   };
   for (int64_t g = 0; g < L.ngroups(); ++g) {
@@ -354,11 +369,11 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
     }
     if (n > kWave) {
       bnd.push_back({kEdgeBigTile, first, n, 0});
+      L.btiles.push_back(bnd.back());
       first = (int32_t)L.edges.size();
     }
   }
   close();
-  while (L.tiles.size() % kWavesPerWG) L.tiles.push_back({-1, 0, 0, 0});
   while (bnd.size() % kWavesPerWG) bnd.push_back({-1, 0, 0, 0});
   // the boundary's workgroups are spread evenly among the walk's (each XCD
   // takes a contiguous chunk of workgroups, so appended ones would all land on one)
@@ -660,6 +675,9 @@ int upload_level(mf_mesh* m, Level& L) {
   if ((rc = dev_upload(&D.md, L.md))) return rc;
   if ((rc = dev_upload(&D.tiles, L.tiles))) return rc;
   if ((rc = dev_upload(&D.tiles_f32, L.tiles_f32))) return rc;
+  if ((rc = dev_upload(&D.btiles, L.btiles))) return rc;
+  for (int i = 0; i < 2; ++i)
+    if ((rc = dev_upload(&D.vtiles[i], L.vtiles[i]))) return rc;
   if ((rc = dev_upload(&D.faces, L.faces))) return rc;
   if ((rc = dev_upload(&D.edges, L.edges))) return rc;
   if ((rc = dev_upload(&D.segs, L.segs))) return rc;
@@ -843,7 +861,7 @@ int build_mesh(mf_mesh* m) {
 void free_device(mf_mesh* m) {
   for (auto& L : m->levels) {
     LevelDev& D = L.dev;
-    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.faces, D.edges, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
+    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.btiles, D.vtiles[0], D.vtiles[1], D.faces, D.edges, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
                     D.xgrp_invdiagf,
                     D.part, D.result, D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.own_bits, D.p2_tiles};
     for (void* p : ptrs)

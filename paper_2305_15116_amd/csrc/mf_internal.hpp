@@ -44,6 +44,14 @@ MF_HD constexpr Shape3 shape3(int N) {
   return N >= 512 ? Shape3{4, 8} : N >= 256 ? Shape3{4, 6} : N >= 128 ? Shape3{3, 4} : N >= 64 ? Shape3{2, 4} : Shape3{1, 2};
 }
 constexpr int kMaxR3 = 4;
+// The variable-coefficient walk's: it forms R + 1 rows and PZ + 1 layers of
+// cells for the R x PZ points of a column, and holds the rows of two vectors
+// (FP64 R = 3 spills).  Cube, us per apply: N = 256 FP64 R = 2, PZ = 8 / 12 / 6
+// 145 / 143 / 154, R = 1 159; FP32 R = 3, PZ = 12 / 8 77.0 / 78.5, R = 4, PZ = 8 81.3, R = 2
+// 79.5; N = 128 FP64 R = 2 29.8, R = 3 47.
+MF_HD constexpr Shape3 shape3_varcoef(int N, bool f32) {
+  return N >= 256 ? (f32 ? Shape3{3, 12} : Shape3{2, 12}) : N >= 64 ? Shape3{2, 4} : Shape3{1, 2};
+}
 // Kinds of a 3D tile list's other tiles (Tile::macro): inner points of a macro
 // face, copies of macro edge and vertex DoFs.
 constexpr int kFaceTile = -2;
@@ -59,6 +67,7 @@ constexpr int kMinFaceN = 16;
 struct FaceRuns {
   int dirichlet, one, two;
 };
+constexpr FaceRuns kFaceRunsWG{1024, 256, 128};  // where a workgroup takes a tile
 MF_HD constexpr FaceRuns face_runs(int N) { return N >= 256 ? FaceRuns{2048, 1536, 128} : FaceRuns{256, 64, 64}; }
 // 3D prolongations walk runs of up to kTransferRun 64-point slice segments
 // (single segments below N = 256).

@@ -1,4 +1,4 @@
-// Variable-coefficient 2D P1 apply (gfx950): y = A(k) x with A(k) the
+// Variable-coefficient P1 apply (gfx950): y = A(k) x with A(k) the
 // stiffness matrix of -div(k grad u), k the P1 interpolant of nodal values
 // k_i (a vector in storage layout).  On a P1 element grad u . grad v is
 // constant, so each element matrix is exactly mean_T(k) times the
@@ -22,6 +22,7 @@
 
 #include "launch.hpp"
 #include "rows.hpp"
+#include "walk3d.hpp"
 #include "wave.hpp"
 
 namespace mf {
@@ -175,17 +176,176 @@ int run_varcoef(const Level& L, const void* k, const void* x, void* y, hipStream
   return launch_exchange_apply(L, dtype_of<T>(), y, s);
 }
 
-
 // ---------------------------------------------------------------- 3D
-// Tetrahedral macros: a point's row sums over the micro-tets of its macro
-// that contain it (24 for an interior point: each of the 6 element types
-// with the point at each of its 4 vertices), each tet contributing
-// mean_T(k) times its row of the constant-coefficient element matrix.  Every
-// vertex of such a tet is the point itself or one of its 15 stencil
-// neighbours, so one lane loads k and x at those 15 points (gathers within a
-// few rows of 3 slices, served by L1/L2) and forms all contributions in
-// registers.  One wave takes a 64-point slice segment (consecutive storage
-// points of one slice, across row ends), so short rows leave no lane idle.
+template <typename T>
+struct VarcoefArgs {
+  const Tile* tiles;
+  const Tile* btiles;  // the boundary tiles alone
+  const MacroDev* md;
+  const FaceDev* faces;
+  const EdgeCopy* edges;
+  const T* K;
+  const T* X;
+  T* Y;
+};
+
+// Tetrahedral macros: columns as in the constant-coefficient walk (walk3d.hpp),
+// and one launch for the macro faces, edges and vertices.
+//
+// Interior points.  The micro-tets come six to a lattice cell (x, y, z) ..
+// (x + 1, y + 1, z + 1), types t0 .. t5, and an element matrix has zero row
+// sums, so a row is sum_j w_ij (x_j - x_i) over its 14 lattice edges, w_ij
+// summing (coefficient sum of the tet) x (entry ij of its matrix) over the
+// tets around the edge: 36 products per cell for the seven edges per point,
+// each then used by both of its ends, instead of 24 element rows per point.
+// The reflection of a cell through its centre maps t0, t1, t2 to t5, t3, t4,
+// so 18 entries serve all six.
+//
+// A lane walks its column layer by layer (the cells between two slices).  A
+// layer completes the weights of the edges inside its lower slice (begun by
+// the layer below), forms those of the edges across it, and adds every edge's
+// flux to its two ends: the lower slice's rows are then complete, the upper
+// slice's begun.  Ends and cells in the lane to the left are reached by
+// shifting sums.  The 1/4 of the coefficient means is applied once to the row
+// (a power of two: exact).
+//
+// Bound: vector issue and memory about equally.  Cube, against a lane per
+// point that gathers 30 values and forms 24 element rows: N = 256 FP64 301 -> 138
+// us, FP32 143 -> 75 (24 and 12 B/DoF: 3.0 and 2.7 TB/s), N = 128 46 -> 30 and 27 ->
+// 20; of these the boundary launch takes 25 and 12 us.  More than two
+// workgroups per CU (launch bound 3) spill.
+template <typename T, int R>
+__device__ __forceinline__ void vc_walk3(const Tile& t, const MacroDev& M, const T* __restrict__ K,
+                                         const T* __restrict__ X, T* __restrict__ Y) {
+  constexpr unsigned E = sizeof(T);
+  constexpr int NS = 3;  // slices in registers: a layer's two, and the next
+  const int N = uniform(M.N), z0 = t.z & 0xffff, nz = t.z >> 16, A = N - z0;
+  const T* P0 = Prec<T>::K(M, 0);
+  const T* P1 = Prec<T>::K(M, 1);
+  const T* P2 = Prec<T>::K(M, 2);
+  const T a01 = uniform(P0[1]), a02 = uniform(P0[2]), a03 = uniform(P0[3]), a12 = uniform(P0[6]), a13 = uniform(P0[7]), a23 = uniform(P0[11]);
+  const T b01 = uniform(P1[1]), b02 = uniform(P1[2]), b03 = uniform(P1[3]), b12 = uniform(P1[6]), b13 = uniform(P1[7]), b23 = uniform(P1[11]);
+  const T c01 = uniform(P2[1]), c02 = uniform(P2[2]), c03 = uniform(P2[3]), c12 = uniform(P2[6]), c13 = uniform(P2[7]), c23 = uniform(P2[11]);
+  const WalkLane wl = walk_lane<R>(t, M);
+  const int64_t sb = uniform(M.base) + slice_base(N, z0 - 1);
+  const int64_t rest = tet_count_small(N + 1) - slice_base(N, z0 - 1);
+  const buf::Rsrc bk = buf::make(K + sb, rest), bx = buf::make(X + sb, rest), by = buf::make(Y + sb, rest);
+  Cursor<T> in(A, wl.col), out(A, wl.col);
+  out.next();
+  T k[NS][R + 2], x[NS][R + 2];  // rows y0 .. y0 + R + 1
+  auto load = [&](T* kv, T* xv) {
+    unsigned r = in.off;
+#pragma unroll
+    for (int j = 0; j < R + 2; ++j) {
+      kv[j] = buf::ld<T>(bk, r);
+      xv[j] = buf::ld<T>(bx, r);
+      r += in.row - (unsigned)j * E;
+    }
+    in.next();
+  };
+#pragma unroll
+  for (int i = 0; i < NS; ++i) load(k[i], x[i]);
+  T kr[NS][R + 2], xr[NS][R + 2];  // the same at x + 1
+#pragma unroll
+  for (int j = 0; j < R + 2; ++j) {
+    kr[0][j] = dn1(k[0][j]);
+    xr[0][j] = dn1(x[0][j]);
+  }
+  // begun by the layer below: weights of the lower slice's edges along x, y and x - y, and its rows
+  T w1[R + 1], w2[R + 1], w12[R + 1], ys[R + 1];
+#pragma unroll
+  for (int j = 0; j <= R; ++j) w1[j] = w2[j] = w12[j] = ys[j] = T(0);
+  for (int i0 = 0; i0 <= nz; i0 += NS) {
+#pragma unroll
+    for (int ii = 0; ii < NS; ++ii) {
+      const int i = i0 + ii;  // layer between slices z0 - 1 + i and z0 + i
+      if (i > nz) break;
+      const T *k0 = k[ii], *q0 = kr[ii], *x0 = x[ii], *v0 = xr[ii];
+      const T *k1 = k[(ii + 1) % NS], *x1 = x[(ii + 1) % NS];
+      T *q1 = kr[(ii + 1) % NS], *v1 = xr[(ii + 1) % NS];
+#pragma unroll
+      for (int j = 0; j < R + 2; ++j) {
+        q1[j] = dn1(k1[j]);
+        v1[j] = dn1(x1[j]);
+      }
+      T lo[R + 2], up[R + 2];  // the layer's share of the lower and of the upper rows
+#pragma unroll
+      for (int j = 0; j < R + 2; ++j) lo[j] = up[j] = T(0);
+      // of the cells one row below: shares of the edges along x (lower and upper slice), z, x - z, and the left lane's z
+      T pB = T(0), pD = T(0), pK = T(0), pP = T(0), pL = T(0);
+#pragma unroll
+      for (int j = 0; j <= R; ++j) {
+        // coefficient sums of the cell's tets
+        const T body = k0[j + 1] + q1[j], s100_001 = q0[j] + k1[j], s110_011 = q0[j + 1] + k1[j + 1];
+        const T t0 = (k0[j] + k0[j + 1]) + s100_001;
+        const T t1 = body + (q0[j] + q0[j + 1]);
+        const T t2 = body + s110_011;
+        const T t3 = body + (k1[j + 1] + k1[j]);
+        const T t4 = body + s100_001;
+        const T t5 = (q1[j] + q1[j + 1]) + s110_011;
+        const bool row = j >= 1;  // (row 0 only feeds row 1)
+        // edges of the lower slice, complete with this layer
+        const T W2 = w2[j] + (a02 * t0 + up1(b23 * t1));
+        const T W12 = w12[j] + fma(c13, t4, fma(b02, t1, a12 * t0));
+        // edges across the layer
+        const T W23 = fma(c12, t4, fma(b13, t3, a23 * t0)) + up1(fma(a23, t5, fma(c12, t2, b13 * t1)));
+        const T Wb = fma(c01, t2 + t4, b01 * (t1 + t3));
+        const T d2 = x0[j + 1] - x0[j], d12 = v0[j] - x0[j + 1], d23 = x0[j + 1] - x1[j], db = v1[j] - x0[j + 1];
+        T left = T(0);
+        if (row) {
+          const T W1 = w1[j] + fma(a01, t0, pB);
+          const T W3 = (fma(a03, t0, pK)) + up1(fma(c03, t4, fma(b12, t1, pL)));
+          const T W13 = fma(c23, t4, fma(a13, t0, pP));
+          const T d1 = v0[j] - x0[j], d3 = x1[j] - x0[j], d13 = v0[j] - x1[j];
+          lo[j] = fma(W1, d1, lo[j]);
+          lo[j] = fma(W2, d2, lo[j]);
+          lo[j] = fma(W3, d3, lo[j]);
+          left = fma(W13, d13, fma(W12, d12, W1 * d1));
+          lo[j] -= up1(left);
+          up[j] = fma(W13, d13, up[j]);
+          up[j] = fma(-W3, d3, up[j]);
+          up[j] = fma(W23, d23, up[j]);
+          up[j] -= up1(Wb * db);
+        }
+        lo[j + 1] = fma(-W2, d2, lo[j + 1]);
+        lo[j + 1] = fma(W12, d12, lo[j + 1]);
+        lo[j + 1] = fma(-W23, d23, lo[j + 1]);
+        lo[j + 1] = fma(Wb, db, lo[j + 1]);
+        // edges of the upper slice, begun
+        if (row) w1[j] = fma(c02, t4, fma(b03, t3, pD));
+        w2[j] = fma(b23, t3, up1(a02 * t5));
+        w12[j] = fma(a12, t5, fma(b02, t3, c13 * t2));
+        pB = fma(c02, t2, b03 * t1);
+        pD = a01 * t5;
+        pK = fma(b12, t3, c03 * t2);
+        pP = fma(a13, t5, c23 * t2);
+        pL = a03 * t5;
+      }
+      if (i > 0) {
+        unsigned r = out.off;
+        const int kk = i - 1;
+#pragma unroll
+        for (int j = 1; j <= R; ++j) {
+          r += out.row - (unsigned)(j - 1) * E;
+          const T v = wl.copies(j + kk) ? x0[j] : (ys[j] + lo[j]) * T(0.25);
+          buf::st<T>(by, wl.writes(j + kk) ? r : buf::kDrop, v);
+        }
+        out.next();
+      }
+#pragma unroll
+      for (int j = 1; j <= R; ++j) ys[j] = up[j];
+      if (i + NS <= nz + 1) load(k[ii], x[ii]);
+    }
+  }
+}
+
+// Macro-boundary points: one lane per point and copy, 24 element rows at most,
+// each the coefficient sum of its tet times its row of the element matrix.
+// Every vertex of a tet around a point is the point or one of its 15 stencil
+// neighbours.  Bound: the latency of the gathers (rows of a face lie a slice or
+// a row apart).  A workgroup per tile, with a face's two copies in two waves,
+// beside the walk's launch: in one kernel with it, the boundary's registers
+// made the walk spill.
 
 // Index into the 15 stencil offsets of lattice offset d (-1 if none).
 __host__ __device__ constexpr int stencil_slot(int dx, int dy, int dz) {
@@ -211,88 +371,185 @@ __host__ __device__ constexpr bool tet_slots_valid() {
 }
 static_assert(tet_slots_valid(), "every edge of a micro-tet is a stencil offset");
 
-template <typename T>
-__device__ __forceinline__ void vc3_point(const MacroDev& M, const T* __restrict__ K, const T* __restrict__ X,
-                                          T* __restrict__ Y, int x, int y, int z) {
-  constexpr StencilTable ST = stencil_table(3);
+// Whether that tet lies in the macro when the point is an inner point of face f.
+__host__ __device__ constexpr bool tet_on_side(int f, int t, int v) {
+  for (int u = 0; u < 4; ++u)
+    if (!on_side(f, tet_slot(t, v, u))) return false;
+  return true;
+}
+
+// Four times the row of a point from the coefficients and values of its
+// stencil neighbours; in(t, v): its type-t tet with the point as vertex v is
+// in the macro; UNIFORM: all lanes have the same macro.
+template <bool UNIFORM, typename T, class In>
+__device__ __forceinline__ T vc3_row(const MacroDev& M, const T* kv, const T* xv, In in) {
+  auto entry = [](const T& v) { return UNIFORM ? uniform(v) : v; };
   constexpr ElemTable E = elem_table(3);
-  const int N = M.N;
-  const int S = N - z;
-  // neighbours by offsets from the point's index, all taken relative to the
-  // first point of slice z - 1 (slice 0 at z = 0) as 32-bit offsets
-  const int za = z > 0 ? z - 1 : 0;
-  const int64_t ab = M.base + slice_base(N, za);
-  const int c = (z > 0 ? (S + 2) * (S + 3) / 2 : 0) + row_start(S, y) + x;
-  int off[15];
-  nbr_offsets3(N, y, z, off);
-  const T* __restrict__ Ka = K + ab;
-  const T* __restrict__ Xa = X + ab;
-  T kv[ST.n], xv[ST.n];
-#pragma unroll
-  for (int o = 0; o < ST.n; ++o) {
-    const int nx = x + ST.off[o][0], ny = y + ST.off[o][1], nz = z + ST.off[o][2];
-    const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
-    // neighbours outside the macro read the point itself; no tet uses them
-    const unsigned byte = (unsigned)(in ? c + off[o] : c) * (unsigned)sizeof(T);
-    kv[o] = *(const T*)((const char*)Ka + byte);
-    xv[o] = *(const T*)((const char*)Xa + byte);
-  }
-  const int mask = support_mask(3, N, x, y, z);
-  if (mask != full_mask(3) && ((M.dir_mask >> mask) & 1)) {
-    Y[ab + c] = xv[ST.centre];  // identity row
-    return;
-  }
-  // the sums of the four vertex coefficients are used unscaled and the row
-  // scaled by 1/4 once at the end: scaling by powers of two is exact, so this
-  // equals summing mean_T(k) times the element rows.  The element matrices
-  // are read in the kernel's precision (FP32 kernels: the macro's FP32 copy).
   T acc = T(0);
 #pragma unroll
   for (int t = 0; t < E.ntypes; ++t) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int ax = x - E.off[t][v][0], ay = y - E.off[t][v][1], az = z - E.off[t][v][2];
-      const bool exists = ax >= 0 && ay >= 0 && az >= 0 && ax + ay + az <= N - E.slack[t];
       const int s0 = tet_slot(t, v, 0), s1 = tet_slot(t, v, 1), s2 = tet_slot(t, v, 2), s3 = tet_slot(t, v, 3);
       const T ks = kv[s0] + kv[s1] + kv[s2] + kv[s3];
       const T* Kt = Prec<T>::K(M, t) + 4 * v;
-      T r = Kt[0] * xv[s0];
-      r = fma(Kt[1], xv[s1], r);
-      r = fma(Kt[2], xv[s2], r);
-      r = fma(Kt[3], xv[s3], r);
-      acc = exists ? fma(ks, r, acc) : acc;
+      T r = entry(Kt[0]) * xv[s0];
+      r = fma(entry(Kt[1]), xv[s1], r);
+      r = fma(entry(Kt[2]), xv[s2], r);
+      r = fma(entry(Kt[3]), xv[s3], r);
+      acc = in(t, v) ? fma(ks, r, acc) : acc;
     }
+    // per-lane matrices: one type's entries in registers at a time
+    if (!UNIFORM) __builtin_amdgcn_sched_barrier(0);
   }
-  // interior, unshared and shared points alike store their (partial) row;
-  // the exchange kernel completes shared DoFs
-  Y[ab + c] = acc * T(0.25);
+  return acc;
+}
+
+template <typename T, int F>
+__device__ __forceinline__ T vc3_face(const MacroDev& M, const T* K, const T* X, int N, int y, int z) {
+  int off[15];
+  nbr_offsets3(N, y, z, off);
+  T kv[15], xv[15];
+#pragma unroll
+  for (int o = 0; o < 15; ++o) {
+    kv[o] = on_side(F, o) ? K[off[o]] : T(0);
+    xv[o] = on_side(F, o) ? X[off[o]] : T(0);
+  }
+  return vc3_row<true>(M, kv, xv, [](int t, int v) { return tet_on_side(F, t, v); });
+}
+
+// One tile of the macro boundary per workgroup.  Faces of two macros: waves 2 c
+// and 2 c + 1 take the two copies of the tile's c-th 64 points and add their
+// rows through LDS, so no wave waits for one copy's gathers before the
+// other's.
+template <typename T>
+__device__ __forceinline__ void vc3_faces(const VarcoefArgs<T>& a, const Tile& t, int wv, T* part) {
+  const FaceDev& F = a.faces[t.z];
+  const int lane = threadIdx.x & (kWave - 1);
+  if (F.dirichlet) {
+    for (int i = threadIdx.x; i < t.y0; i += kWG) {
+      int ia, ib, y, z;
+      slice_xy3(F.N - 3, t.x0 + i, ia, ib);
+      const int64_t p = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, y, z);
+      a.Y[p] = a.X[p];
+    }
+    return;
+  }
+  const bool two = F.copies == 2;
+  const int c = two ? wv & 1 : 0, step = two ? kWG / 2 : kWG;
+  const FaceCopy& C = F.cp[c];
+  const MacroDev& M = a.md[C.macro];
+  for (int i0 = 0; i0 < t.y0; i0 += step) {
+    const int i = i0 + (two ? wv >> 1 : wv) * kWave + lane;
+    int ia, ib, y, z;
+    slice_xy3(F.N - 3, t.x0 + min(i, t.y0 - 1), ia, ib);
+    const int64_t p = face_index(a.md, C, F.N, ia + 1, ib + 1, y, z);
+    T acc;
+    switch (C.face) {
+      case 0: acc = vc3_face<T, 0>(M, a.K + p, a.X + p, F.N, y, z); break;
+      case 1: acc = vc3_face<T, 1>(M, a.K + p, a.X + p, F.N, y, z); break;
+      case 2: acc = vc3_face<T, 2>(M, a.K + p, a.X + p, F.N, y, z); break;
+      default: acc = vc3_face<T, 3>(M, a.K + p, a.X + p, F.N, y, z); break;
+    }
+    if (two) {
+      part[threadIdx.x] = acc;
+      __syncthreads();
+      acc = part[(wv & ~1) * kWave + lane] + part[(wv | 1) * kWave + lane];
+      __syncthreads();
+    }
+    if (i < t.y0) a.Y[p] = acc * T(0.25);
+  }
 }
 
 template <typename T>
-__global__ __launch_bounds__(kWG) void varcoef3d_kernel(const Tile* __restrict__ segs, int nwg, const MacroDev* md,
-                                                        const T* __restrict__ K, const T* __restrict__ X,
-                                                        T* __restrict__ Y) {
-  const int g = wave::xcd_wg(nwg);
+__device__ __forceinline__ T vc3_copy(const VarcoefArgs<T>& a, const EdgeCopy& e) {
+  constexpr StencilTable ST = stencil_table(3);
+  constexpr ElemTable E = elem_table(3);
+  const MacroDev& M = a.md[e.macro];
+  const int N = M.N;
+  int off[15];
+  nbr_offsets3(N, e.y, e.z, off);
+  T kv[15], xv[15];
+#pragma unroll
+  for (int o = 0; o < 15; ++o) {
+    const int nx = e.x + ST.off[o][0], ny = e.y + ST.off[o][1], nz = e.z + ST.off[o][2];
+    const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
+    const int64_t i = in ? e.idx + off[o] : e.idx;  // (no tet uses the neighbours outside)
+    kv[o] = a.K[i];
+    xv[o] = a.X[i];
+  }
+  return vc3_row<false>(M, kv, xv, [&](int t, int v) {
+    const int ax = e.x - E.off[t][v][0], ay = e.y - E.off[t][v][1], az = e.z - E.off[t][v][2];
+    return ax >= 0 && ay >= 0 && az >= 0 && ax + ay + az <= N - E.slack[t];
+  });
+}
+
+template <typename T>
+__device__ __forceinline__ void vc3_edges(const VarcoefArgs<T>& a, const Tile& t) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const EdgeCopy* L = a.edges + t.x0;
+  if (t.macro == kEdgeBigTile) {
+    T acc = T(0);
+    if (!L[0].dirichlet)
+      for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+        const int n = min(kWave, t.y0 - c0);
+        const T p = lane < n ? vc3_copy<T>(a, L[c0 + lane]) : T(0);
+        for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
+      }
+    for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = L[0].dirichlet ? a.X[L[c].idx] : acc * T(0.25);
+    return;
+  }
+  const bool live = lane < t.y0;
+  const EdgeCopy e = L[live ? lane : 0];
+  T p = T(0), acc = T(0);
+  if (live && !e.dirichlet) p = vc3_copy<T>(a, e);
+  const int n = live ? e.copies : 0;
+  for (int i = 0; __builtin_amdgcn_ballot_w64(i < n); ++i) {
+    const T v = __shfl(p, (e.head + i) & (kWave - 1), kWave);
+    acc += i < n ? v : T(0);
+  }
+  if (live) a.Y[e.idx] = e.dirichlet ? a.X[e.idx] : acc * T(0.25);
+}
+
+template <typename T, int R>
+__global__ __launch_bounds__(kWG, 2) void varcoef3d_kernel(const VarcoefArgs<T> a, int nwg) {
+  const int g = wave::xcd_wg_runs(nwg, wave::kRuns3);
   if (g < 0) return;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Tile sg = load_seg(segs, g * kWavesPerWG + wv);
-  if (sg.macro < 0) return;
-  const MacroDev& M = md[sg.macro];
-  int x, y, z;
-  slice_point<3>(sg, M.N, x, y, z);
-  if (x + y + z > M.N) return;  // lanes past the slice's last point
-  vc3_point<T>(M, K, X, Y, x, y, z);
+  const Tile t = load_seg(a.tiles, g * kWavesPerWG + wv);
+  if (t.macro >= 0) vc_walk3<T, R>(t, a.md[t.macro], a.K, a.X, a.Y);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kWG) void varcoef3d_boundary_kernel(const VarcoefArgs<T> a) {
+  __shared__ T part[kWG];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Tile t = load_seg(a.btiles, blockIdx.x);
+  if (t.macro == kFaceTile) vc3_faces<T>(a, t, wv, part);
+  else if (t.macro != -1 && wv == 0) vc3_edges<T>(a, t);
+}
+
+template <typename T, int R>
+void run_vc3(const VarcoefArgs<T>& a, int nwg, hipStream_t s) {
+  hipLaunchKernelGGL((varcoef3d_kernel<T, R>), dim3(wave::xcd_grid_runs(nwg, wave::kRuns3)), dim3(kWG), 0, s, a, nwg);
 }
 
 template <typename T>
 int run_varcoef3d(const Level& L, const void* k, const void* x, void* y, hipStream_t s) {
-  const int nwg = (int)(L.psegs.size() / kWavesPerWG);
-  if (nwg > 0)
-    hipLaunchKernelGGL(varcoef3d_kernel<T>, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s, L.dev.psegs, nwg, L.dev.md,
-                       (const T*)k, (const T*)x, (T*)y);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));
-  return launch_exchange_apply(L, dtype_of<T>(), y, s);
+  constexpr int i = sizeof(T) == 8 ? 0 : 1;
+  const int nwg = (int)(L.vtiles[i].size() / kWavesPerWG), R = shape3_varcoef(L.N, i == 1).R;
+  const VarcoefArgs<T> a{L.dev.vtiles[i], L.dev.btiles, L.dev.md, L.dev.faces, L.dev.edges,
+                         (const T*)k,      (const T*)x,   (T*)y};
+  if (nwg > 0) {
+    if (R == 4) run_vc3<T, 4>(a, nwg, s);
+    else if (R == 3) run_vc3<T, 3>(a, nwg, s);
+    else if (R == 2) run_vc3<T, 2>(a, nwg, s);
+    else run_vc3<T, 1>(a, nwg, s);
+  }
+  const int nb = (int)L.btiles.size();
+  if (nb > 0) hipLaunchKernelGGL((varcoef3d_boundary_kernel<T>), dim3(nb), dim3(kWG), 0, s, a);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }
 
 }  // namespace
