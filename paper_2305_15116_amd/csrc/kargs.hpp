@@ -436,7 +436,7 @@ struct BatchOp {
   int nseg, nwg;
   int64_t args_off, wg0_off;
   int variant;  // 3D stencil ops: rows per band (shape3); tail ops: dynamic LDS bytes
-  int pad_;
+  int side;     // launched on the batch's second stream
 };
 
 }  // namespace mf
