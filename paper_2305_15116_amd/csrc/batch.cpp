@@ -202,11 +202,22 @@ void jacobi_stage(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int v
     });
     return;
   }
-  if (from_zero) {
+  const bool two = from_zero && two_from_zero(dim, sweeps);
+  if (two) {
+    stencil_op(P, ms, dim, vdt, kJacobi2, o.omega, [&](const Member& M, Pass& p) {
+      const int l = lof(M);
+      if (l < 0) return false;
+      p.level = l;
+      p.x = p.b = M.w.b[l];
+      p.y = M.w.x[l];
+      p.part = nullptr;
+      return true;
+    });
+  } else if (from_zero) {
     if (vdt == MF_F64) jacobi0_op<double>(P, ms, dim, o, lof);
     else jacobi0_op<float>(P, ms, dim, o, lof);
   }
-  for (int i = from_zero ? 1 : 0; i < sweeps; ++i) {
+  for (int i = two ? 2 : (from_zero ? 1 : 0); i < sweeps; ++i) {
     stencil_op(P, ms, dim, vdt, kJacobi, o.omega, [&](const Member& M, Pass& p) {
       const int l = lof(M);
       if (l < 0) return false;

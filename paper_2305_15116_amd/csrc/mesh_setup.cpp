@@ -275,11 +275,25 @@ static std::vector<Tile> column_tiles(int N, int64_t nc, const Shape3& sh) {
 static void build_tiles3(const mf_mesh* m, Level& L) {
   const int N = L.N;
   std::vector<Tile> bnd;
+  const StencilTable ST = stencil_table(3);
+  for (int64_t c = 0; c < m->nc; ++c) L.md[c].zinv[full_mask(3)] = L.md[c].inv_diag;
+  for (const Prim& P : m->prims) {
+    auto mask = [&](size_t k) {
+      int s = 0;
+      for (size_t j = 0; j < P.v.size(); ++j) s |= 1 << P.local[k][j];
+      return s;
+    };
+    double diag = 0.0;
+    for (size_t k = 0; k < P.cell.size(); ++k) diag += L.md[P.cell[k]].wm[mask(k)][ST.centre];
+    for (size_t k = 0; k < P.cell.size(); ++k)
+      L.md[P.cell[k]].zinv[mask(k)] = P.dirichlet || diag == 0.0 ? 0.0 : 1.0 / diag;
+  }
+  for (int64_t c = 0; c < m->nc; ++c)
+    for (int s = 0; s < 16; ++s) L.md[c].zinvf[s] = (float)L.md[c].zinv[s];
   L.tiles = column_tiles(N, m->nc, shape3(N));
   for (int f32 = 0; f32 < 2; ++f32) L.vtiles[f32] = column_tiles(N, m->nc, shape3_varcoef(N, f32));
   // faces: weights a and b run over two of the face's vertices, with a along
   // the first macro's x where its face holds vertices 0 and 1 (contiguous storage)
-  const StencilTable ST = stencil_table(3);
   for (const Prim& P : m->prims) {
     if (P.v.size() != 3 || N < kMinFaceN) continue;
     int pa = 0, pb = 1, pc = 2;

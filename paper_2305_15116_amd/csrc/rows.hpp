@@ -15,6 +15,7 @@ struct Prec;
 
 template <>
 struct Prec<double> {
+  static __device__ __forceinline__ double zinv(const MacroDev& M, int mask) { return M.zinv[mask]; }
   static __device__ __forceinline__ double w(const MacroDev& M, int mask, int i) { return M.wm[mask][i]; }
   static __device__ __forceinline__ const double* row(const MacroDev& M, int mask) { return M.wm[mask]; }
   static __device__ __forceinline__ const double& invd(const MacroDev& M) { return M.inv_diag; }
@@ -24,6 +25,7 @@ struct Prec<double> {
 
 template <>
 struct Prec<float> {
+  static __device__ __forceinline__ float zinv(const MacroDev& M, int mask) { return M.zinvf[mask]; }
   static __device__ __forceinline__ float w(const MacroDev& M, int mask, int i) { return M.wmf[mask][i]; }
   static __device__ __forceinline__ const float* row(const MacroDev& M, int mask) { return M.wmf[mask]; }
   static __device__ __forceinline__ const float& invd(const MacroDev& M) { return M.inv_diagf; }

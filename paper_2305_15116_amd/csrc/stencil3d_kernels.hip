@@ -54,6 +54,7 @@ int dispatch(int mode, int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   switch (mode) {
     case kApply: run<T, kApply>(R, l, s); break;
     case kJacobi: run<T, kJacobi>(R, l, s); break;
+    case kJacobi2: run<T, kJacobi2>(R, l, s); break;
     case kResidual: run<T, kResidual>(R, l, s); break;
     case kNormB: run<T, kNormB>(R, l, s); break;
     default: run<T, kApplyDot>(R, l, s); break;

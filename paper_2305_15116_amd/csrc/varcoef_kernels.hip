@@ -428,9 +428,9 @@ __device__ __forceinline__ void vc3_faces(const VarcoefArgs<T>& a, const Tile& t
   const int lane = threadIdx.x & (kWave - 1);
   if (F.dirichlet) {
     for (int i = threadIdx.x; i < t.y0; i += kWG) {
-      int ia, ib, y, z;
+      int ia, ib, x, y, z;
       slice_xy3(F.N - 3, t.x0 + i, ia, ib);
-      const int64_t p = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, y, z);
+      const int64_t p = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, x, y, z);
       a.Y[p] = a.X[p];
     }
     return;
@@ -441,9 +441,9 @@ __device__ __forceinline__ void vc3_faces(const VarcoefArgs<T>& a, const Tile& t
   const MacroDev& M = a.md[C.macro];
   for (int i0 = 0; i0 < t.y0; i0 += step) {
     const int i = i0 + (two ? wv >> 1 : wv) * kWave + lane;
-    int ia, ib, y, z;
+    int ia, ib, x, y, z;
     slice_xy3(F.N - 3, t.x0 + min(i, t.y0 - 1), ia, ib);
-    const int64_t p = face_index(a.md, C, F.N, ia + 1, ib + 1, y, z);
+    const int64_t p = face_index(a.md, C, F.N, ia + 1, ib + 1, x, y, z);
     T acc;
     switch (C.face) {
       case 0: acc = vc3_face<T, 0>(M, a.K + p, a.X + p, F.N, y, z); break;

@@ -52,13 +52,21 @@ __device__ __forceinline__ void st(Rsrc r, unsigned off, T v) {
 template <typename T, int MODE>
 __device__ __forceinline__ T row_value(T acc, T xc, T bv, T omega, T inv) {
   if (MODE == kApply || MODE == kApplyDot) return acc;
-  if (MODE == kJacobi) return fma(omega * inv, bv - acc, xc);
+  if (MODE == kJacobi || MODE == kJacobi2) return fma(omega * inv, bv - acc, xc);
   if (MODE == kResidual) return bv - acc;
   return bv;
 }
 template <typename T, int MODE>
 __device__ __forceinline__ T dirichlet_row(T xc, T bv) {
+  if (MODE == kJacobi2) return T(0);
   return MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : xc);
+}
+
+// The iterate at a point with support `mask` whose stored value is v: v, or
+// (kJacobi2, whose X is b) the first sweep's omega D^-1 b.
+template <typename T, int MODE>
+__device__ __forceinline__ T iterate(const MacroDev& M, int mask, T omega, T v) {
+  return MODE == kJacobi2 ? (omega * Prec<T>::zinv(M, mask)) * v : v;
 }
 
 // ------------------------------------------------------------------ interior
@@ -158,6 +166,7 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
   using wave::up1;
   constexpr bool kX = MODE != kNormB;                      // reads x
   constexpr bool kB = MODE != kApply && MODE != kApplyDot;  // reads b
+  constexpr bool kZ = MODE == kJacobi2;                     // as X: scaled to the iterate when its slice is first used
   constexpr unsigned E = sizeof(T);
   const int N = uniform(M.N), z0 = t.z & 0xffff, nz = t.z >> 16;
   const T* wrow = Prec<T>::row(M, full_mask(3));
@@ -192,7 +201,7 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
     for (int j = 0; j < R; ++j) {
       r += out.row - (unsigned)j * E;
       off[j] = r;
-      if (kB) v[j] = buf::ld<T>(bb, r);
+      if (kB && !kZ) v[j] = buf::ld<T>(bb, r);
     }
     out.next();
   };
@@ -201,6 +210,26 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
     for (int i = 0; i < NS; ++i) load_slice(s[i]);
   }
   out_rows(oq[0], bq[0]);
+  // kJacobi2: omega / diagonal of the column's points inside and on the far face, of rows y > 0 and (zy) of the
+  // row below the band where that is y = 0; slice i of the slab, b of the outputs kept in v
+  T zi = T(0), zf = T(0), zyi = T(0), zyf = T(0);
+  auto iterate_slice = [&](T* a, int i, T ci, T cf, T cyi, T cyf, T* v) {
+    if (v) {
+#pragma unroll
+      for (int j = 1; j <= R; ++j) v[j - 1] = a[j];
+    }
+    const int far = wl.A + 1 - i - wl.col.x - wl.col.y0;  // its row on the far face
+#pragma unroll
+    for (int j = 0; j < R + 2; ++j) a[j] *= far == j ? (j == 0 ? cyf : cf) : (j == 0 ? cyi : ci);
+  };
+  if (kZ) {
+    const int mx = wl.left ? 0 : 2, my = wl.col.y0 == 0 ? 0 : 4;
+    auto c = [&](int mask) { return omega * Prec<T>::zinv(M, mask); };
+    zi = c(13 | mx), zf = c(12 | mx), zyi = c(9 | mx | my), zyf = c(8 | mx | my);
+    if (z0 == 1) iterate_slice(s[0], 0, c(5 | mx), c(4 | mx), c(1 | mx | my), c(mx | my), nullptr);
+    else iterate_slice(s[0], 0, zi, zf, zyi, zyf, nullptr);
+    iterate_slice(s[1], 1, zi, zf, zyi, zyf, bq[0]);
+  }
   for (int k0 = 0; k0 < nz; k0 += NS) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
@@ -209,6 +238,7 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
       out_rows(oq[(i + 1) % 2], bq[(i + 1) % 2]);
       const T* a0 = s[i];
       const T* a1 = s[(i + 1) % NS];
+      if (kZ) iterate_slice(s[(i + 2) % NS], k + 2, zi, zf, zyi, zyf, bq[(i + 1) % 2]);
       const T* a2 = s[(i + 2) % NS];
 #pragma unroll
       for (int j = 1; j <= R; ++j) {
@@ -254,8 +284,9 @@ __host__ __device__ constexpr bool on_side(int f, int o) {
 
 // Partial row of an inner point of face F of macro M (X points at it): its 11
 // neighbours in the macro, in table order.
-template <typename T, int F>
-__device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int N, int y, int z) {
+template <typename T, int F, int MODE>
+__device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int N, int x, int y, int z, T omega) {
+  constexpr StencilTable ST = stencil_table(3);
   const T* w = Prec<T>::row(M, full_mask(3) & ~(1 << F));
   int off[15];
   nbr_offsets3(N, y, z, off);
@@ -265,14 +296,18 @@ __device__ __forceinline__ T face_partial(const MacroDev& M, const T* X, int N, 
     if (on_side(F, o)) v[o] = X[off[o]];
 #pragma unroll
   for (int o = 0; o < 15; ++o)
+    if (on_side(F, o))
+      v[o] = iterate<T, MODE>(M, support_mask(3, N, x + ST.off[o][0], y + ST.off[o][1], z + ST.off[o][2]), omega, v[o]);
+#pragma unroll
+  for (int o = 0; o < 15; ++o)
     if (on_side(F, o)) acc = fma(uniform(w[o]), v[o], acc);
   return acc;
 }
 
-// Storage index in copy C of the face point with weights wa, wb (and its y, z).
-__device__ __forceinline__ int64_t face_index(const MacroDev* md, const FaceCopy& C, int N, int wa, int wb, int& y,
-                                              int& z) {
-  const int x = C.n[0] * N + C.a[0] * wa + C.b[0] * wb;
+// Storage index in copy C of the face point with weights wa, wb (and its x, y, z).
+__device__ __forceinline__ int64_t face_index(const MacroDev* md, const FaceCopy& C, int N, int wa, int wb, int& x,
+                                              int& y, int& z) {
+  x = C.n[0] * N + C.a[0] * wa + C.b[0] * wb;
   y = C.n[1] * N + C.a[1] * wa + C.b[1] * wb;
   z = C.n[2] * N + C.a[2] * wa + C.b[2] * wb;
   return uniform(md[C.macro].base) + idx3(N, x, y, z);
@@ -283,7 +318,7 @@ __device__ __forceinline__ int64_t face_index(const MacroDev* md, const FaceCopy
 template <typename T, int MODE>
 __device__ __forceinline__ void face_copies(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
   constexpr bool kX = MODE != kNormB;
-  constexpr bool kB = MODE == kResidual || MODE == kNormB;
+  constexpr bool kB = MODE == kResidual || MODE == kNormB || MODE == kJacobi2;
   constexpr int U = 4;
   const FaceDev& F = a.faces[t.z];
   for (int i0 = threadIdx.x & (kWave - 1); i0 < t.y0; i0 += U * kWave) {
@@ -291,9 +326,9 @@ __device__ __forceinline__ void face_copies(const StencilArgs<T>& a, const Tile&
     T xc[U], bv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int ia, ib, y, z;
+      int ia, ib, x, y, z;
       slice_xy3(F.N - 3, t.x0 + min(i0 + u * kWave, t.y0 - 1), ia, ib);
-      at[u] = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, y, z);
+      at[u] = face_index(a.md, F.cp[0], F.N, ia + 1, ib + 1, x, y, z);
       xc[u] = kX ? a.X[at[u]] : T(0);
       bv[u] = kB ? a.B[at[u]] : T(0);
     }
@@ -322,25 +357,27 @@ __device__ __forceinline__ void face_rows(const StencilArgs<T>& a, const Tile& t
     int ia, ib;
     slice_xy3(N - 3, t.x0 + i, ia, ib);
     int64_t at[2];
-    int y[2], z[2];
+    int x[2], y[2], z[2];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) at[c] = face_index(a.md, F.cp[c], N, ia + 1, ib + 1, y[c], z[c]);
-    const T xc = kX ? a.X[at[0]] : T(0), bv = kB ? a.B[at[0]] : T(0);
+    for (int c = 0; c < 2; ++c) at[c] = face_index(a.md, F.cp[c], N, ia + 1, ib + 1, x[c], y[c], z[c]);
+    const T bv = kB ? a.B[at[0]] : T(0);
+    const T inv = sizeof(T) == 8 ? (T)F.inv : (T)F.invf;
+    const T xc = MODE == kJacobi2 ? (a.omega * inv) * bv : (kX ? a.X[at[0]] : T(0));
     T acc = T(0);
     if (kX) {
       for (int c = 0; c < F.copies; ++c) {
         const MacroDev& M = a.md[F.cp[c].macro];
         const T* Xc = a.X + (c == 0 ? at[0] : at[1]);
-        const int yc = c == 0 ? y[0] : y[1], zc = c == 0 ? z[0] : z[1];
+        const int xp = c == 0 ? x[0] : x[1], yp = c == 0 ? y[0] : y[1], zp = c == 0 ? z[0] : z[1];
         switch (F.cp[c].face) {
-          case 0: acc += face_partial<T, 0>(M, Xc, N, yc, zc); break;
-          case 1: acc += face_partial<T, 1>(M, Xc, N, yc, zc); break;
-          case 2: acc += face_partial<T, 2>(M, Xc, N, yc, zc); break;
-          default: acc += face_partial<T, 3>(M, Xc, N, yc, zc); break;
+          case 0: acc += face_partial<T, 0, MODE>(M, Xc, N, xp, yp, zp, a.omega); break;
+          case 1: acc += face_partial<T, 1, MODE>(M, Xc, N, xp, yp, zp, a.omega); break;
+          case 2: acc += face_partial<T, 2, MODE>(M, Xc, N, xp, yp, zp, a.omega); break;
+          default: acc += face_partial<T, 3, MODE>(M, Xc, N, xp, yp, zp, a.omega); break;
         }
       }
     }
-    const T out = row_value<T, MODE>(acc, xc, bv, a.omega, sizeof(T) == 8 ? (T)F.inv : (T)F.invf);
+    const T out = row_value<T, MODE>(acc, xc, bv, a.omega, inv);
     if (MODE != kNormB) {
       a.Y[at[0]] = out;
       if (F.copies == 2) a.Y[at[1]] = out;
@@ -352,8 +389,8 @@ __device__ __forceinline__ void face_rows(const StencilArgs<T>& a, const Tile& t
 // ------------------------------------------------------------------ edges, vertices
 // Partial row of one copy of a macro edge or vertex DoF: the partial stencil
 // of its support mask, neighbours outside the macro dropped, table order.
-template <typename T>
-__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X) {
+template <typename T, int MODE>
+__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X, T omega) {
   constexpr StencilTable ST = stencil_table(3);
   const MacroDev& M = md[k.macro];
   const int N = M.N;
@@ -364,7 +401,7 @@ __device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k,
   for (int o = 0; o < ST.n; ++o) {
     const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
     const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
-    const T v = X[in ? k.idx + off[o] : k.idx];
+    const T v = iterate<T, MODE>(M, support_mask(3, N, nx, ny, nz), omega, X[in ? k.idx + off[o] : k.idx]);
     p = fma(Prec<T>::w(M, k.mask, o), in ? v : T(0), p);
   }
   return p;
@@ -385,10 +422,11 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
     if (kX && !L[0].dirichlet)
       for (int c0 = 0; c0 < t.y0; c0 += kWave) {
         const int n = min(kWave, t.y0 - c0);
-        const T p = lane < n ? copy_partial<T>(a.md, L[c0 + lane], a.X) : T(0);
+        const T p = lane < n ? copy_partial<T, MODE>(a.md, L[c0 + lane], a.X, a.omega) : T(0);
         for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
       }
-    const T xh = kX ? a.X[L[0].idx] : T(0), bh = kB ? a.B[L[0].idx] : T(0);
+    const T bh = kB ? a.B[L[0].idx] : T(0);
+    const T xh = kX ? iterate<T, MODE>(a.md[L[0].macro], L[0].mask, a.omega, a.X[L[0].idx]) : T(0);
     T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
     if (MODE != kNormB)
       for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
@@ -398,7 +436,7 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
   const bool live = lane < t.y0;
   const EdgeCopy k = L[live ? lane : 0];
   T p = T(0);
-  if (kX && live && !k.dirichlet) p = copy_partial<T>(a.md, k, a.X);
+  if (kX && live && !k.dirichlet) p = copy_partial<T, MODE>(a.md, k, a.X, a.omega);
   T acc = T(0);
   if (kX) {
     const int n = live ? k.copies : 0;
@@ -407,7 +445,7 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
       acc += i < n ? v : T(0);
     }
   }
-  const T xo = kX ? a.X[k.idx] : T(0), bo = kB ? a.B[k.idx] : T(0);
+  const T xo = kX ? iterate<T, MODE>(a.md[k.macro], k.mask, a.omega, a.X[k.idx]) : T(0), bo = kB ? a.B[k.idx] : T(0);
   const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
   const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
   if (live) {

@@ -1,0 +1,90 @@
+"""V-cycles whose first two sweeps from a zero iterate are one launch (3D),
+against the same cycle put together from the smoother, residual and transfer
+calls (each held to the oracle by its own tests) and a dense solve on the
+oracle's matrix at the coarse level.
+
+The launch forms the first sweep's iterate with the operations of a full sweep
+from zero, so FP64 cycles agree within 1e-12 of the largest entry (the coarse
+solve, here by another elimination, has a condition of at most about 1e2), FP32
+cycles within 1e-5 of it.
+"""
+import numpy as np
+import pytest
+
+import harness
+import paper_2305_15116_amd as P
+from oracle.oracle import OracleMesh
+from paper_2305_15116_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+OMEGA = 2.0 / 3.0
+
+
+def _mesh(name):
+    if name == "tet":
+        return W.unit_tet()
+    if name == "cube":
+        return W.kuhn_cube("random", 5)
+    if name.startswith("fan"):  # n tets around one edge
+        n = int(name[3:])
+        ring = [[np.cos(2 * np.pi * i / n), np.sin(2 * np.pi * i / n), 0.5] for i in range(n)]
+        co = np.array([[0.0, 0.0, 0.0], [0.0, 0.0, 1.0]] + ring)
+        return co, W.shuffle_cell_orders(np.array([[0, 1, 2 + i, 2 + (i + 1) % n] for i in range(n)]), 2)
+    co, ce = W.strip_3d(int(name[5:]))
+    return W.apply_affine(co, *W.random_affine(3, 9)), W.shuffle_cell_orders(ce, 6)
+
+
+def _cycle(m, l, lc, b, dtype, pre, post, coarse):
+    x = torch.zeros_like(b)
+    if l == lc:
+        return coarse(b)
+    t, r = torch.empty_like(b), torch.empty_like(b)
+    P.smooth(m, l, OMEGA, pre, b, x, t)
+    P.residual(m, l, b, x, r)
+    bc = torch.empty(P.mesh_num_dofs(m, l - 1)[0], dtype=dtype, device="cuda")
+    P.restrict_residual(m, l, r, bc)
+    e = _cycle(m, l - 1, lc, bc, dtype, pre, post, coarse)
+    P.prolong_add(m, l, e, x)
+    P.smooth(m, l, OMEGA, post, b, x, t)
+    return x
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("name,L,pre", [("tet", 5, 2), ("tet", 6, 3), ("tet", 7, 2), ("tet", 8, 2), ("cube", 5, 2),
+                                        ("cube", 6, 4), ("strip11", 5, 2), ("strip7", 4, 3), ("fan70", 4, 2),
+                                        ("strip5", 5, 1)])
+def test_one_cycle(name, L, pre, mode):
+    co, ce = _mesh(name)
+    m = P.create_macro_mesh(co, ce, L)
+    lc = 2
+    om = OracleMesh(co, ce, lc)
+    s2u = harness.storage_to_unique(P.mesh_dof_keys(m, lc), om.keys())
+    A = om.csr(dirichlet=True).toarray()
+    dtype = torch.float64 if mode == 0 else torch.float32
+
+    def coarse(b):
+        bu = np.zeros(om.n)
+        bu[s2u] = b.cpu().numpy()
+        bu[om.boundary()] = 0.0
+        return torch.as_tensor(np.linalg.solve(A, bu)[s2u].astype(b.cpu().numpy().dtype), device="cuda")
+
+    s, _ = P.mesh_num_dofs(m, L)
+    b = torch.empty(s, dtype=torch.float64, device="cuda")
+    P.mesh_fill_random(m, L, 77, b)
+    x = torch.zeros_like(b)
+    ws = torch.empty(P.mesh_workspace_bytes(m, L, mode), dtype=torch.uint8, device="cuda")
+    P.vcycle_solve(m, L, b, x, ws, mode=mode, pre=pre, post=pre, coarse_level=lc, rtol=0.0, max_iter=1)
+    # the solver's start: Dirichlet values of x from b, then one correction
+    fixed = torch.zeros_like(b)
+    one = torch.ones_like(b)
+    P.smooth(m, L, OMEGA, 1, one, fixed, torch.empty_like(b))  # moves every free row off 0
+    x0 = torch.where(fixed == 0, b, torch.zeros_like(b))
+    r = torch.empty_like(b)
+    P.residual(m, L, b, x0, r)
+    c = r.abs().max() if mode == 1 else torch.ones((), dtype=torch.float64, device="cuda")
+    want = x0 + c * _cycle(m, L, lc, (r / c).to(dtype), dtype, pre, pre, coarse).to(torch.float64)
+    got, want = x.cpu().numpy(), want.cpu().numpy()
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= (1e-12 if mode == 0 else 1e-5) * np.abs(want).max()
