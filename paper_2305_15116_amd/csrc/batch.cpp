@@ -124,7 +124,7 @@ namespace {
 
 const Level& lev(const Member& M, int l) { return M.m->levels[l]; }
 
-// Ops of one stencil pass (interior walk + exchange) over the selected
+// Ops of one stencil pass over the selected
 // members: sel(M) fills level / vectors / part and returns false to skip M.
 struct Pass {
   int level;
@@ -136,9 +136,8 @@ struct Pass {
 template <typename T, class Sel>
 void stencil_pass(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int dtype, int mode, double omega,
                   Sel sel) {
-  // one stencil launch per 3D band height (levels differ in it), then one exchange launch (2D)
+  // one launch per 3D band height (levels differ in it)
   std::vector<std::pair<StencilArgs<T>, int>> sa[kMaxR3 + 1];
-  std::vector<std::pair<GroupArgs<T>, int>> ga;
   for (Member* M : ms) {
     if (M->m->dim != dim) continue;
     Pass p{};
@@ -146,10 +145,8 @@ void stencil_pass(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int d
     const Level& L = lev(*M, p.level);
     const StencilArgs<T> a = stencil_args<T>(L, p.x, p.y, p.b, omega, p.part);
     sa[dim == 3 ? shape3(L.N).R : 0].push_back({a, a.nwg});
-    if (!exchange_in_launch(L)) ga.push_back({exchange_args<T>(L, p.x, p.y, p.b, omega, p.part), exchange_blocks(L)});
   }
   for (int i = 0; i <= kMaxR3; ++i) P.add(kOpStencil, dtype, dim, mode, sa[i], i);
-  P.add(kOpExchange, dtype, dim, mode, ga);
 }
 
 template <class Sel>

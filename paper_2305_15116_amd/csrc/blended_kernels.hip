@@ -176,10 +176,10 @@ __global__ __launch_bounds__(kWG) void blended_kernel(const Tile* __restrict__ t
 int launch_blended_apply(const mf_mesh* m, const Level& L, const double* bubble, const double* x, double* y,
                          hipStream_t s) {
   static_assert(kBlH == kTileH2F, "the walk runs on the FP32 tile list");
-  const int nwg = (int)(L.tiles_f32.size() / kWavesPerWG);
+  const int nwg = (int)(L.tiles_f32.size() / kWavesPerWG) - L.ewgs;
   if (nwg > 0)
-    hipLaunchKernelGGL(blended_kernel, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s, L.dev.tiles_f32, nwg, L.dev.md,
-                       m->geo2_dev, bubble, x, y);
+    hipLaunchKernelGGL(blended_kernel, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s,
+                       L.dev.tiles_f32 + L.ewgs * kWavesPerWG, nwg, L.dev.md, m->geo2_dev, bubble, x, y);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));
   return launch_exchange_apply(L, MF_F64, y, s);

@@ -1,0 +1,117 @@
+// Device code of the macro edges and vertices (gfx950; in 2D the edges shared by
+// macros): rows summed over all copies of a DoF within one launch.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rows.hpp"
+
+namespace mf {
+
+// Row value of a DoF that is not Dirichlet, from its assembled sum acc; inv = 1
+// / assembled diagonal.
+template <typename T, int MODE>
+__device__ __forceinline__ T row_value(T acc, T xc, T bv, T omega, T inv) {
+  if (MODE == kApply || MODE == kApplyDot) return acc;
+  if (MODE == kJacobi || MODE == kJacobi2) return fma(omega * inv, bv - acc, xc);
+  if (MODE == kResidual) return bv - acc;
+  return bv;
+}
+template <typename T, int MODE>
+__device__ __forceinline__ T dirichlet_row(T xc, T bv) {
+  if (MODE == kJacobi2) return T(0);
+  return MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : xc);
+}
+
+// The iterate at a point with support `mask` whose stored value is v: v, or
+// (kJacobi2, whose X is b) the first sweep's omega D^-1 b.
+template <typename T, int MODE>
+__device__ __forceinline__ T iterate(const MacroDev& M, int mask, T omega, T v) {
+  return MODE == kJacobi2 ? (omega * Prec<T>::zinv(M, mask)) * v : v;
+}
+
+// Partial row of one copy of a macro edge or vertex DoF: the partial stencil
+// of its support mask, neighbours outside the macro dropped, table order.
+template <typename T, int DIM, int MODE>
+__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X, T omega) {
+  constexpr StencilTable ST = stencil_table(DIM);
+  const MacroDev& M = md[k.macro];
+  const int N = M.N;
+  int off[15];
+  if constexpr (DIM == 3) {
+    nbr_offsets3(N, k.y, k.z, off);
+  } else {
+    const int l = N + 1 - k.y;  // the row's length
+#pragma unroll
+    for (int o = 0; o < ST.n; ++o) off[o] = ST.off[o][0] + (ST.off[o][1] > 0 ? l : ST.off[o][1] < 0 ? -l - 1 : 0);
+  }
+  T p = T(0);
+#pragma unroll
+  for (int o = 0; o < ST.n; ++o) {
+    const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
+    const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
+    const T v = iterate<T, MODE>(M, support_mask(DIM, N, nx, ny, nz), omega, X[in ? k.idx + off[o] : k.idx]);
+    p = fma(Prec<T>::w(M, k.mask, o), in ? v : T(0), p);
+  }
+  return p;
+}
+
+// Copies of macro edge and vertex DoFs, one per lane; the copies of a DoF sit in
+// consecutive lanes from its head (kEdgeTile: t.y0 copies, then t.z in a second
+// step), or, with more than 64 copies, one DoF fills the tile in steps of 64
+// (kEdgeBigTile).  The copies' partial rows are summed in list order by every
+// lane of the DoF.
+//
+// Bound: latency.  In 2D this replaces an exchange launch after every pass, of
+// partial rows that the walk wrote: seven triangles at level 8, FP64 apply / Jacobi
+// / residual 8.7 / 9.6 / 9.5 -> 5.1 / 5.9 / 5.6 us, FP32 10.6 / 11.8 / 11.9 -> 7.0 / 7.6 / 7.7;
+// two at level 12 FP32 39.5 / 49.5 / 51.9 -> 33.3 / 43.2 / 45.5.
+template <typename T, int DIM, int MODE>
+__device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
+  constexpr bool kX = MODE != kNormB;
+  constexpr bool kB = MODE != kApply && MODE != kApplyDot;
+  const int lane = threadIdx.x & (kWave - 1);
+  const EdgeCopy* L = a.edges + t.x0;
+  if (t.macro == kEdgeBigTile) {
+    T acc = T(0);
+    if (kX && !L[0].dirichlet)
+      for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+        const int n = min(kWave, t.y0 - c0);
+        const T p = lane < n ? copy_partial<T, DIM, MODE>(a.md, L[c0 + lane], a.X, a.omega) : T(0);
+        for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
+      }
+    const T bh = kB ? a.B[L[0].idx] : T(0);
+    const T xh = kX ? iterate<T, MODE>(a.md[L[0].macro], L[0].mask, a.omega, a.X[L[0].idx]) : T(0);
+    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
+    if (MODE != kNormB)
+      for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
+    if (lane == 0) accum<T, MODE>(ss, mx, out, xh);
+    return;
+  }
+  for (int step = 0; step < 2; ++step) {
+    const int n = step == 0 ? t.y0 : t.z;
+    if (n == 0) break;
+    const bool live = lane < n;
+    const EdgeCopy k = L[live ? lane : 0];
+    T p = T(0);
+    if (kX && live && !k.dirichlet) p = copy_partial<T, DIM, MODE>(a.md, k, a.X, a.omega);
+    T acc = T(0);
+    if (kX) {
+      const int nc = live ? k.copies : 0;
+      for (int i = 0; __builtin_amdgcn_ballot_w64(i < nc); ++i) {
+        const T v = __shfl(p, (k.head + i) & (kWave - 1), kWave);
+        acc += i < nc ? v : T(0);
+      }
+    }
+    const T xo = kX ? iterate<T, MODE>(a.md[k.macro], k.mask, a.omega, a.X[k.idx]) : T(0), bo = kB ? a.B[k.idx] : T(0);
+    const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
+    const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
+    if (live) {
+      if (MODE != kNormB) a.Y[k.idx] = out;
+      if (lane == k.head) accum<T, MODE>(ss, mx, out, xo);
+    }
+    L += t.y0;
+  }
+}
+
+}  // namespace mf

@@ -49,8 +49,8 @@ struct StencilArgs {
   T omega;
   double* part;  // sums at [0, np), maxima at [np, 2 np)
   int np;
-  const FaceDev* faces;   // 3D face and edge tiles
-  const EdgeCopy* edges;
+  const FaceDev* faces;   // 3D face tiles
+  const EdgeCopy* edges;  // edge tiles
 };
 
 // exchange_kernel / iface_kernel: groups of copies of macro-boundary DoFs.
@@ -259,27 +259,17 @@ StencilArgs<T> stencil_args(const Level& L, const void* x, void* y, const void* 
 }
 
 template <typename T>
-GroupArgs<T> exchange_args(const Level& L, const void* x, void* y, const void* b, double omega, double* part) {
-  GroupArgs<T> g;
+GroupArgs<T> exchange_args(const Level& L, void* y) {
+  GroupArgs<T> g{};
   g.ngroups = (int)L.nxgroups();
   g.gptr = L.dev.xgrp_ptr;
   g.copies = L.dev.xcopies;
   g.cidx = L.dev.xcpidx;
-  g.gflag = nullptr;
-  g.ginv = L.dev.xgrp_invdiag;
-  g.ginvf = L.dev.xgrp_invdiagf;
   g.md = L.dev.md;
-  g.X = (const T*)x;
   g.Y = (T*)y;
-  g.B = (const T*)b;
-  g.omega = (T)omega;
-  g.part = part ? part + L.tiles_for(dtype_of<T>()).size() / kWavesPerWG : nullptr;
-  g.np = (int)L.n_partials(dtype_of<T>());
   return g;
 }
-inline int exchange_blocks(const Level& L) { return (int)L.xgroup_blocks(); }
-// 3D stencil passes finish shared DoFs themselves: no exchange launch
-inline bool exchange_in_launch(const Level& L) { return L.xfused; }
+inline int exchange_blocks(const Level& L) { return (int)((L.nxgroups() + kIfaceWG - 1) / kIfaceWG); }
 
 template <typename T>
 GroupArgs<T> iface_args(const Level& L, const void* x, void* y, const void* b) {
@@ -409,8 +399,7 @@ inline int pcg_blocks(const Level& L) { return (int)L.lin_blocks(); }
 
 // ---------------------------------------------------------------- batch ops
 enum OpKind : int {
-  kOpStencil = 0,  // StencilArgs<T>, mode = kApply / kJacobi / kResidual / kNormB
-  kOpExchange,     // GroupArgs<T>, same modes
+  kOpStencil = 0,  // StencilArgs<T>, any Mode
   kOpIface,        // GroupArgs<T>, mode = kExchangeSum / kDirichletSet
   kOpReduce,       // ReduceArgs
   kOpRestrict,     // TransferArgs<T>

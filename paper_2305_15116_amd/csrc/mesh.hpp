@@ -54,7 +54,7 @@ struct LevelDev {
 struct Level {
   int level = 0;
   int N = 0;
-  bool xfused = false;  // 3D: the stencil launch finishes shared DoFs, no exchange launch follows
+  int ewgs = 0;  // 2D: workgroups of edge tiles, which lead both tile lists
   int64_t storage = 0, unique = 0;
   std::vector<int64_t> base;    // per macro storage offset
   std::vector<MacroDev> md;
@@ -82,15 +82,11 @@ struct Level {
   int64_t ngroups() const { return (int64_t)grp_ptr.size() - 1; }
   int64_t nxgroups() const { return (int64_t)xgrp_ptr.size() - 1; }
   int64_t iface_blocks() const { return (ngroups() + kIfaceWG - 1) / kIfaceWG; }
-  int64_t xgroup_blocks() const { return (nxgroups() + kIfaceWG - 1) / kIfaceWG; }
   const std::vector<Tile>& tiles_for(int dtype) const {
     return dtype == MF_F32 && !tiles_f32.empty() ? tiles_f32 : tiles;
   }
-  // norm / dot partials of one stencil pass: one per workgroup of tiles, then one per exchange block
-  // (levels whose stencil launch finishes shared DoFs have no exchange partials)
-  int64_t n_partials(int dtype) const {
-    return (int64_t)tiles_for(dtype).size() / kWavesPerWG + (xfused ? 0 : xgroup_blocks());
-  }
+  // norm / dot partials of one stencil pass: one per workgroup of tiles
+  int64_t n_partials(int dtype) const { return (int64_t)tiles_for(dtype).size() / kWavesPerWG; }
   int64_t n_partials() const { return std::max(n_partials(MF_F64), n_partials(MF_F32)); }  // buffer sizes
   // blocks of the linear (grid-stride) vector kernels with partials
   int64_t lin_blocks() const { return std::min<int64_t>(2048, std::max<int64_t>(1, (storage + 1023) / 1024)); }

@@ -270,6 +270,48 @@ static std::vector<Tile> column_tiles(int N, int64_t nc, const Shape3& sh) {
   return out;
 }
 
+// Tiles of a 2D level's DoFs that macros share (the exchange list), at the head
+// of both tile lists so that they start first: up to 64 copies per step, two
+// steps per tile.
+static void build_edge_tiles2(Level& L) {
+  std::vector<Tile>& out = L.tiles;
+  int32_t first = 0, n[2] = {0, 0}, step = 0;  // of the open tile
+  auto close = [&] {
+    if (n[0] > 0) out.push_back({kEdgeTile, first, n[0], n[1]});
+    first = (int32_t)L.edges.size();
+    n[0] = n[1] = step = 0;
+  };
+  L.edges.reserve(L.xcopies.size());
+  for (int64_t g = 0; g < L.nxgroups(); ++g) {
+    const int c0 = L.xgrp_ptr[g], nc = L.xgrp_ptr[g + 1] - c0;
+    if (nc <= kWave && n[step] + nc > kWave && ++step == 2) close();
+    if (nc > kWave) close();
+    const int head = n[step];
+    for (int c = c0; c < c0 + nc; ++c) {
+      const Copy& k = L.xcopies[c];
+      EdgeCopy e{};
+      e.idx = L.xcpidx[c];
+      e.inv = L.xgrp_invdiag[g];
+      e.macro = k.macro;
+      e.x = (uint16_t)k.x, e.y = (uint16_t)k.y;
+      e.mask = (uint8_t)support_mask(2, L.N, k.x, k.y, 0);
+      e.head = (uint8_t)(nc > kWave ? 0 : head);
+      e.copies = (uint8_t)(nc > kWave ? 0 : nc);
+      L.edges.push_back(e);
+    }
+    if (nc > kWave) {
+      out.push_back({kEdgeBigTile, first, nc, 0});
+      first = (int32_t)L.edges.size();
+    } else {
+      n[step] += nc;
+    }
+  }
+  close();
+  while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
+  L.ewgs = (int)(out.size() / kWavesPerWG);
+  L.tiles_f32 = out;
+}
+
 // Tiles of a 3D level: the interior walk's slabs of every macro, the inner
 // points of every macro face, and the copies of the edge and vertex DoFs.
 static void build_tiles3(const mf_mesh* m, Level& L) {
@@ -374,7 +416,7 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
       e.idx = L.base[k.macro] + idx3(N, k.x, k.y, k.z);
       e.inv = diag != 0.0 ? 1.0 / diag : 0.0;
       e.macro = k.macro;
-      e.x = (int16_t)k.x, e.y = (int16_t)k.y, e.z = (int16_t)k.z;
+      e.x = (uint16_t)k.x, e.y = (uint16_t)k.y, e.z = (uint16_t)k.z;
       e.mask = (uint8_t)support_mask(3, N, k.x, k.y, k.z);
       e.head = (uint8_t)(n > kWave ? 0 : head);
       e.copies = (uint8_t)(n > kWave ? 0 : n);
@@ -620,13 +662,14 @@ static int build_level(mf_mesh* m, int level, Level& L) {
       L.xcpidx[i] = storage_index(L.xcopies[i]);
   });
 
-  // wave tiles, natural order: 2D over every point of every macro (macro,
-  // band, strip); 3D over the interior points (macro, slab, columns), then the
+  // wave tiles, natural order: 2D the copies of shared DoFs, then every point
+  // of every macro (macro, band, strip); 3D over the interior points (macro, slab, columns), then the
   // macro faces and the edge and vertex copies
   L.tiles.clear();
-  L.xfused = dim == 3;
+  L.tiles_f32.clear();
   if (dim == 2) {
-    L.tiles.reserve((size_t)m->nc * (macro_points(dim, N) / (kTileW * kTileH2) * 2 + 64));
+    build_edge_tiles2(L);
+    L.tiles.reserve(L.tiles.size() + (size_t)m->nc * (macro_points(dim, N) / (kTileW * kTileH2) * 2 + 64));
     for (int64_t c = 0; c < m->nc; ++c)
       for (int y0 = 0; y0 <= N; y0 += kTileH2)
         for (int x0 = 0; x0 + y0 <= N; x0 += kTileW) L.tiles.push_back({(int32_t)c, x0, y0, 0});
@@ -634,7 +677,6 @@ static int build_level(mf_mesh* m, int level, Level& L) {
   } else {
     build_tiles3(m, L);
   }
-  L.tiles_f32.clear();
   if (dim == 2) {
     for (int64_t c = 0; c < m->nc; ++c)
       for (int y0 = 0; y0 <= N; y0 += kTileH2F)

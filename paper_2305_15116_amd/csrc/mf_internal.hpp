@@ -114,7 +114,7 @@ struct EdgeCopy {
   int64_t idx;  // storage index
   double inv;   // 1 / assembled diagonal
   int32_t macro;
-  int16_t x, y, z;
+  uint16_t x, y, z;
   uint8_t mask;          // support mask in its macro
   uint8_t head, copies;  // lane of the DoF's first copy in its tile, number of copies (kEdgeTile)
   uint8_t dirichlet;

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kWG) void stencil3_kernel(const Launch<StencilArgs<
   double ss = 0.0, mx = 0.0;
   if (t.macro >= 0) walk3<T, MODE, R>(t, a.md[t.macro], a.X, a.Y, a.B, a.omega, ss, mx);
   else if (t.macro == kFaceTile) face_rows<T, MODE>(a, t, ss, mx);
-  else if (t.macro != -1) edge_rows<T, MODE>(a, t, ss, mx);
+  else if (t.macro != -1) edge_rows<T, 3, MODE>(a, t, ss, mx);
   if (has_partials(MODE) && a.part != nullptr) wg_partial<kWavesPerWG>(ss, mx, a.part, a.np, n);
 }
 

@@ -18,13 +18,14 @@
 // Macro-boundary DoFs are handled in the same walk (the paper leaves them to
 // interface primitives, Performance Modeling, experiment description): a
 // point on a face, edge or vertex of its macro uses the partial stencil of
-// its support mask — only the micro-elements on its side — and a DoF shared
-// by several macros is finished by the exchange kernel, which sums the
-// copies' partial rows in fixed macro order and writes the result to every
-// copy.
+// its support mask — only the micro-elements on its side.  DoFs shared by
+// several macros are left to tiles of their own in the same launch (edges.hpp),
+// which sum the copies' partial rows in fixed macro order and write the result
+// to every copy.
 
 #include <hip/hip_runtime.h>
 
+#include "edges.hpp"
 #include "launch.hpp"
 #include "rows.hpp"
 #include "wave.hpp"
@@ -94,7 +95,8 @@ struct RowMasks {
 // rows a boundary lane is the row's first point (x = 0, only in tiles starting
 // at x0 = 0, tile_left), its last (on the far edge x + y = N), or both.  A row
 // without such a lane takes the interior stencil from scalar registers, and so
-// does a row whose boundary lanes are all Dirichlet points (they copy x).  Any
+// does a row whose boundary lanes are all Dirichlet (they copy x) or shared
+// points (written by the edge tiles).  Any
 // other row takes, in every lane, the partial stencil of the lane's own
 // support mask from the LDS table (interior lanes read the full stencil there,
 // the same weights); the neighbours such a lane lacks (x - 1 for x = 0, the
@@ -115,7 +117,8 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
     if (__builtin_amdgcn_ballot_w64(inside)) {
       const int mask = support_mask(2, N, x, y, 0);
       const T acc = partial_sum<T, 2>(W, inside ? mask : FM, N, x, y, 0, v);
-      if (inside) finish<T, 2, MODE>(M, W, mask, acc, xc, bv, omega, yp, ss, mx);
+      const bool shared = ((M.shared_mask & ~M.dir_mask) >> mask) & 1;
+      if (inside && !shared) finish<T, 2, MODE>(M, W, mask, acc, xc, bv, omega, yp, ss, mx);
     }
     return;
   }
@@ -131,10 +134,11 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
   const bool bnd = far || left;
   const int bm = FM & ~(far ? 1 : 0) & ~(left ? 2 : 0);
   const bool dir = bnd && ((M.dir_mask >> bm) & 1);
+  const bool shared = bnd && !dir && ((M.shared_mask >> bm) & 1);
   T a = T(0);
-  if (!__builtin_amdgcn_ballot_w64(bnd && !dir)) {
-    // the row's boundary lanes are all Dirichlet (they copy x): the others
-    // take the interior stencil
+  if (!__builtin_amdgcn_ballot_w64(bnd && !dir && !shared)) {
+    // the row's boundary lanes are all Dirichlet (they copy x) or shared (not
+    // written): the others take the interior stencil
     a = wi[0] * v[0];
 #pragma unroll
     for (int o = 1; o < NO; ++o) a = fma(wi[o], v[o], a);
@@ -148,22 +152,21 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
       a = o == 0 ? wr[0] * vo : fma(wr[o], vo, a);
     }
   }
-  const bool shared = bnd && !dir && ((M.shared_mask >> bm) & 1);
   const bool own = !bnd || ((M.own_mask >> bm) & 1);
   T out;
   if (MODE == kApply || MODE == kApplyDot) {
     out = dir ? xc : a;
   } else if (MODE == kJacobi) {
     const T id = !bnd ? Prec<T>::invd(M) : far ? (left ? bid[2] : bid[1]) : bid[0];
-    out = dir ? xc : (shared ? a : fma(omega * id, bv - a, xc));
+    out = dir ? xc : fma(omega * id, bv - a, xc);
   } else if (MODE == kResidual) {
-    out = dir ? bv - xc : (shared ? a : bv - a);
+    out = dir ? bv - xc : bv - a;
   } else {
     out = bv;
   }
-  if (inside) {
+  if (inside && !shared) {
     if (MODE != kNormB) st(yp, out);
-    if (dir ? own : !shared) accum<T, MODE>(ss, mx, out, xc);
+    if (!dir || own) accum<T, MODE>(ss, mx, out, xc);
   }
 }
 
@@ -367,27 +370,22 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
     WTab<T> W = wtab[same ? 0 : wv];
     if (tile2d_inner<T>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
     else tile2d<T, MODE>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
+  } else if (t.macro != -1) {
+    edge_rows<T, 2, MODE>(a, t, ss, mx);
   }
   if (has_partials(MODE) && a.part != nullptr) wg_partial<kWavesPerWG>(ss, mx, a.part, a.np, n);
 }
 
 // ------------------------------------------------------------------ exchange
 
-// One DoF shared by several macros and not Dirichlet: its copies hold
-// partial rows (written by stencil_kernel); sum them in fixed macro order,
-// finish the row, and write it to every copy.
-template <typename T, int DIM, int MODE>
-__global__ __launch_bounds__(kIfaceWG) void exchange_kernel(const Launch<GroupArgs<T>> L) {
-  GroupArgs<T> a;
-  const int blk = resolve(L, (int)blockIdx.x, a);
-  const int g = blk * kIfaceWG + threadIdx.x;
-  double ss = 0.0, mx = 0.0;
-  if (g < a.ngroups) {
-    int64_t i0;
-    const T out = exchange_row<T, DIM, MODE>(a, g, i0);
-    accum<T, MODE>(ss, mx, out, MODE == kApplyDot ? a.X[i0] : T(0));
-  }
-  if (has_partials(MODE) && a.part != nullptr) wg_partial<kIfaceWG / kWave>(ss, mx, a.part, a.np, blk);
+// One DoF shared by several macros and not Dirichlet: its copies hold partial
+// rows (of the P2, variable-coefficient and blended walks); sum them in fixed
+// macro order and write the row to every copy.
+template <typename T>
+__global__ __launch_bounds__(kIfaceWG) void exchange_kernel(const GroupArgs<T> a) {
+  const int g = blockIdx.x * kIfaceWG + threadIdx.x;
+  int64_t i0;
+  if (g < a.ngroups) exchange_row<T, 2, kApply>(a, g, i0);
 }
 
 // Every macro-boundary DoF: kExchangeSum (y = sum of x over the copies,
@@ -471,10 +469,6 @@ void run_stencil(const Level& L, const void* x, void* y, const void* b, double o
   if (a.nwg > 0)
     hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(a.nwg, wave::kRuns2)), dim3(kWG),
                        (stencil_lds<T, MODE>(a.nwg)), s, single(a, a.nwg));
-  const int nblk = exchange_blocks(L);
-  if (nblk == 0) return;
-  hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(nblk), dim3(kIfaceWG), 0, s,
-                     single(exchange_args<T>(L, x, y, b, omega, part), nblk));
 }
 
 template <typename T, int DIM, int MODE>
@@ -518,13 +512,8 @@ int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x,
 // ---------------------------------------------------------------- batched
 template <typename T, int MODE>
 void batch_stencil(const BatchOp& op, const char* table, hipStream_t s) {
-  if (op.kind == kOpStencil)
-    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(op.nwg, wave::kRuns2)), dim3(kWG),
-                       (stencil_lds<T, MODE>(op.nwg)), s,
-                       batched<StencilArgs<T>>(op, table));
-  else
-    hipLaunchKernelGGL((exchange_kernel<T, 2, MODE>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
-                       batched<GroupArgs<T>>(op, table));
+  hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(op.nwg, wave::kRuns2)), dim3(kWG),
+                     (stencil_lds<T, MODE>(op.nwg)), s, batched<StencilArgs<T>>(op, table));
 }
 
 template <typename T, int DIM>
@@ -574,11 +563,9 @@ int launch_exchange_apply(const Level& L, int dtype, void* y, hipStream_t s) {
   const int nblk = exchange_blocks(L);
   if (nblk == 0) return MF_OK;
   if (dtype == MF_F64)
-    hipLaunchKernelGGL((exchange_kernel<double, 2, kApply>), dim3(nblk), dim3(kIfaceWG), 0, s,
-                       single(exchange_args<double>(L, nullptr, y, nullptr, 0.0, nullptr), nblk));
+    hipLaunchKernelGGL((exchange_kernel<double>), dim3(nblk), dim3(kIfaceWG), 0, s, exchange_args<double>(L, y));
   else
-    hipLaunchKernelGGL((exchange_kernel<float, 2, kApply>), dim3(nblk), dim3(kIfaceWG), 0, s,
-                       single(exchange_args<float>(L, nullptr, y, nullptr, 0.0, nullptr), nblk));
+    hipLaunchKernelGGL((exchange_kernel<float>), dim3(nblk), dim3(kIfaceWG), 0, s, exchange_args<float>(L, y));
   return check_launch();
 }
 

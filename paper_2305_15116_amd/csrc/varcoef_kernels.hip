@@ -163,8 +163,8 @@ __global__ __launch_bounds__(kWG) void varcoef_kernel(const Tile* __restrict__ t
 template <typename T>
 int run_varcoef(const Level& L, const void* k, const void* x, void* y, hipStream_t s) {
   const bool f32 = sizeof(T) == 4 && !L.tiles_f32.empty();
-  const Tile* tiles = f32 ? L.dev.tiles_f32 : L.dev.tiles;
-  const int nwg = (int)((f32 ? L.tiles_f32.size() : L.tiles.size()) / kWavesPerWG);
+  const Tile* tiles = (f32 ? L.dev.tiles_f32 : L.dev.tiles) + L.ewgs * kWavesPerWG;
+  const int nwg = (int)((f32 ? L.tiles_f32.size() : L.tiles.size()) / kWavesPerWG) - L.ewgs;
   // five workgroups per CU on large launches (level 14: FP64 578.7 -> 560 us, FP32 301.7 -> 283; level 13 151 -> 149, 79.4
   // -> 78)
   if (nwg > 0)

@@ -1,11 +1,12 @@
 // Device code of the 3D stencil launches (gfx950): the interior walk of the
-// tetrahedral macros, the macro faces and the macro edges and vertices.  A
-// launch's tile list mixes the three kinds, so that every row of the level,
+// tetrahedral macros and the macro faces.  A launch's tile list mixes these and
+// the macro edges and vertices (edges.hpp), so that every row of the level,
 // shared DoFs included, is finished by one launch.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "edges.hpp"
 #include "rows.hpp"
 #include "wave.hpp"
 
@@ -46,28 +47,6 @@ __device__ __forceinline__ void st(Rsrc r, unsigned off, T v) {
 }
 
 }  // namespace buf
-
-// Row value of a DoF that is not Dirichlet, from its assembled sum acc; inv = 1
-// / assembled diagonal.
-template <typename T, int MODE>
-__device__ __forceinline__ T row_value(T acc, T xc, T bv, T omega, T inv) {
-  if (MODE == kApply || MODE == kApplyDot) return acc;
-  if (MODE == kJacobi || MODE == kJacobi2) return fma(omega * inv, bv - acc, xc);
-  if (MODE == kResidual) return bv - acc;
-  return bv;
-}
-template <typename T, int MODE>
-__device__ __forceinline__ T dirichlet_row(T xc, T bv) {
-  if (MODE == kJacobi2) return T(0);
-  return MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : xc);
-}
-
-// The iterate at a point with support `mask` whose stored value is v: v, or
-// (kJacobi2, whose X is b) the first sweep's omega D^-1 b.
-template <typename T, int MODE>
-__device__ __forceinline__ T iterate(const MacroDev& M, int mask, T omega, T v) {
-  return MODE == kJacobi2 ? (omega * Prec<T>::zinv(M, mask)) * v : v;
-}
 
 // ------------------------------------------------------------------ interior
 // Rows off the y = 0 and z = 0 faces, in a slab of nz slices from z0: the
@@ -383,74 +362,6 @@ __device__ __forceinline__ void face_rows(const StencilArgs<T>& a, const Tile& t
       if (F.copies == 2) a.Y[at[1]] = out;
     }
     accum<T, MODE>(ss, mx, out, xc);
-  }
-}
-
-// ------------------------------------------------------------------ edges, vertices
-// Partial row of one copy of a macro edge or vertex DoF: the partial stencil
-// of its support mask, neighbours outside the macro dropped, table order.
-template <typename T, int MODE>
-__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X, T omega) {
-  constexpr StencilTable ST = stencil_table(3);
-  const MacroDev& M = md[k.macro];
-  const int N = M.N;
-  int off[15];
-  nbr_offsets3(N, k.y, k.z, off);
-  T p = T(0);
-#pragma unroll
-  for (int o = 0; o < ST.n; ++o) {
-    const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
-    const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
-    const T v = iterate<T, MODE>(M, support_mask(3, N, nx, ny, nz), omega, X[in ? k.idx + off[o] : k.idx]);
-    p = fma(Prec<T>::w(M, k.mask, o), in ? v : T(0), p);
-  }
-  return p;
-}
-
-// t.y0 copies of macro edge and vertex DoFs, one per lane; the copies of a
-// DoF sit in consecutive lanes from its head (kEdgeTile), or, with more than
-// 64 copies, one DoF fills the tile in steps of 64 (kEdgeBigTile).  The
-// copies' partial rows are summed in list order by every lane of the DoF.
-template <typename T, int MODE>
-__device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
-  constexpr bool kX = MODE != kNormB;
-  constexpr bool kB = MODE != kApply && MODE != kApplyDot;
-  const int lane = threadIdx.x & (kWave - 1);
-  const EdgeCopy* L = a.edges + t.x0;
-  if (t.macro == kEdgeBigTile) {
-    T acc = T(0);
-    if (kX && !L[0].dirichlet)
-      for (int c0 = 0; c0 < t.y0; c0 += kWave) {
-        const int n = min(kWave, t.y0 - c0);
-        const T p = lane < n ? copy_partial<T, MODE>(a.md, L[c0 + lane], a.X, a.omega) : T(0);
-        for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
-      }
-    const T bh = kB ? a.B[L[0].idx] : T(0);
-    const T xh = kX ? iterate<T, MODE>(a.md[L[0].macro], L[0].mask, a.omega, a.X[L[0].idx]) : T(0);
-    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
-    if (MODE != kNormB)
-      for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
-    if (lane == 0) accum<T, MODE>(ss, mx, out, xh);
-    return;
-  }
-  const bool live = lane < t.y0;
-  const EdgeCopy k = L[live ? lane : 0];
-  T p = T(0);
-  if (kX && live && !k.dirichlet) p = copy_partial<T, MODE>(a.md, k, a.X, a.omega);
-  T acc = T(0);
-  if (kX) {
-    const int n = live ? k.copies : 0;
-    for (int i = 0; __builtin_amdgcn_ballot_w64(i < n); ++i) {
-      const T v = __shfl(p, (k.head + i) & (kWave - 1), kWave);
-      acc += i < n ? v : T(0);
-    }
-  }
-  const T xo = kX ? iterate<T, MODE>(a.md[k.macro], k.mask, a.omega, a.X[k.idx]) : T(0), bo = kB ? a.B[k.idx] : T(0);
-  const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
-  const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
-  if (live) {
-    if (MODE != kNormB) a.Y[k.idx] = out;
-    if (lane == k.head) accum<T, MODE>(ss, mx, out, xo);
   }
 }
 
