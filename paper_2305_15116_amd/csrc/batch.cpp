@@ -22,6 +22,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <new>
 #include <vector>
 
@@ -136,17 +137,17 @@ struct Pass {
 template <typename T, class Sel>
 void stencil_pass(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int dtype, int mode, double omega,
                   Sel sel) {
-  // one launch per 3D band height (levels differ in it)
-  std::vector<std::pair<StencilArgs<T>, int>> sa[kMaxR3 + 1];
+  // one launch per 3D band height or 2D tile height (levels differ in it)
+  std::map<int, std::vector<std::pair<StencilArgs<T>, int>>> sa;
   for (Member* M : ms) {
     if (M->m->dim != dim) continue;
     Pass p{};
     if (!sel(*M, p)) continue;
     const Level& L = lev(*M, p.level);
     const StencilArgs<T> a = stencil_args<T>(L, p.x, p.y, p.b, omega, p.part);
-    sa[dim == 3 ? shape3(L.N).R : 0].push_back({a, a.nwg});
+    sa[dim == 3 ? shape3(L.N).R : L.rows2(dtype)].push_back({a, a.nwg});
   }
-  for (int i = 0; i <= kMaxR3; ++i) P.add(kOpStencil, dtype, dim, mode, sa[i], i);
+  for (const auto& it : sa) P.add(kOpStencil, dtype, dim, mode, it.second, it.first);
 }
 
 template <class Sel>

@@ -241,10 +241,10 @@ constexpr int dtype_of() { return sizeof(T) == 4 ? MF_F32 : MF_F64; }
 template <typename T>
 StencilArgs<T> stencil_args(const Level& L, const void* x, void* y, const void* b, double omega, double* part) {
   constexpr int dt = dtype_of<T>();
-  const bool f32 = dt == MF_F32 && !L.tiles_f32.empty();
+  const std::vector<Tile>& tiles = L.tiles_for(dt);
   StencilArgs<T> a;
-  a.tiles = f32 ? L.dev.tiles_f32 : L.dev.tiles;
-  a.ntiles = (int)L.tiles_for(dt).size();
+  a.tiles = &tiles == &L.tiles ? L.dev.tiles : (&tiles == &L.tiles_f32 ? L.dev.tiles_f32 : L.dev.tiles_short);
+  a.ntiles = (int)tiles.size();
   a.nwg = a.ntiles / kWavesPerWG;
   a.md = L.dev.md;
   a.X = (const T*)x;
@@ -424,7 +424,7 @@ struct BatchOp {
   int kind, dtype, dim, mode;
   int nseg, nwg;
   int64_t args_off, wg0_off;
-  int variant;  // 3D stencil ops: rows per band (shape3); tail ops: dynamic LDS bytes
+  int variant;  // 3D stencil ops: rows per band (shape3); 2D: rows per tile; tail ops: dynamic LDS bytes
   int side;     // launched on the batch's second stream
 };
 

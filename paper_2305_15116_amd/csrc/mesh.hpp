@@ -21,6 +21,7 @@ struct LevelDev {
   MacroDev* md = nullptr;
   Tile* tiles = nullptr;       // interior wave tiles, padded to a multiple of kWavesPerWG
   Tile* tiles_f32 = nullptr;   // 2D FP32 wave tiles
+  Tile* tiles_short = nullptr;
   Tile* btiles = nullptr;      // 3D face and edge tiles
   Tile* vtiles[2] = {nullptr, nullptr};  // variable-coefficient column tiles (FP64, FP32)
   FaceDev* faces = nullptr;    // 3D macro faces
@@ -60,6 +61,8 @@ struct Level {
   std::vector<MacroDev> md;
   std::vector<Tile> tiles;      // interior wave tiles (natural order, padded)
   std::vector<Tile> tiles_f32;  // 2D FP32 wave tiles (kTileH2F rows); empty in 3D (same as tiles)
+  std::vector<Tile> tiles_short;  // 2D levels of few tiles: short_rows rows each, either type
+  int short_rows = 0;
   std::vector<Tile> btiles;     // 3D: the face and edge tiles by themselves, one per workgroup (kFaceRunsWG)
   std::vector<Tile> vtiles[2];  // 3D: column tiles of the variable-coefficient walk (FP64, FP32)
   std::vector<FaceDev> faces;   // 3D: macro faces, and the copies of the edge and vertex DoFs, that tiles name
@@ -82,8 +85,14 @@ struct Level {
   int64_t ngroups() const { return (int64_t)grp_ptr.size() - 1; }
   int64_t nxgroups() const { return (int64_t)xgrp_ptr.size() - 1; }
   int64_t iface_blocks() const { return (ngroups() + kIfaceWG - 1) / kIfaceWG; }
+  // rows per tile of the 2D stencil passes, and the passes' tiles
+  int rows2(int dtype) const {
+    if (short_rows) return short_rows;
+    return dtype == MF_F32 && tiles.size() > (size_t)kMidWGs * kWavesPerWG ? kTileH2F : kTileH2;
+  }
   const std::vector<Tile>& tiles_for(int dtype) const {
-    return dtype == MF_F32 && !tiles_f32.empty() ? tiles_f32 : tiles;
+    const int h = tiles_f32.empty() ? kTileH2 : rows2(dtype);  // (3D: one list)
+    return h < kTileH2 ? tiles_short : (h == kTileH2F ? tiles_f32 : tiles);
   }
   // norm / dot partials of one stencil pass: one per workgroup of tiles
   int64_t n_partials(int dtype) const { return (int64_t)tiles_for(dtype).size() / kWavesPerWG; }

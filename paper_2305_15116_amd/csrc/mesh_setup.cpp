@@ -312,6 +312,33 @@ static void build_edge_tiles2(Level& L) {
   L.tiles_f32 = out;
 }
 
+// The tiles of a 2D level that is small enough for short ones (edge tiles of
+// one step each).
+static void build_short_tiles2(Level& L, int64_t nc) {
+  constexpr size_t most = (size_t)kShortWGs * kWavesPerWG;
+  std::vector<Tile>& out = L.tiles_short;
+  L.short_rows = 0;
+  for (int rows : kTileShort) {
+    out.clear();
+    for (int i = 0; i < L.ewgs * kWavesPerWG && out.size() <= most; ++i) {
+      const Tile& t = L.tiles[i];
+      if (t.macro == -1) continue;
+      out.push_back({t.macro, t.x0, t.y0, 0});
+      if (t.z > 0) out.push_back({t.macro, t.x0 + t.y0, t.z, 0});
+    }
+    while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
+    for (int64_t c = 0; c < nc && out.size() <= most; ++c)
+      for (int y0 = 0; y0 <= L.N && out.size() <= most; y0 += rows)
+        for (int x0 = 0; x0 + y0 <= L.N; x0 += kTileW) out.push_back({(int32_t)c, x0, y0, 0});
+    while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
+    if (out.size() <= most) {
+      L.short_rows = rows;
+      return;
+    }
+  }
+  out.clear();
+}
+
 // Tiles of a 3D level: the interior walk's slabs of every macro, the inner
 // points of every macro face, and the copies of the edge and vertex DoFs.
 static void build_tiles3(const mf_mesh* m, Level& L) {
@@ -682,6 +709,7 @@ static int build_level(mf_mesh* m, int level, Level& L) {
       for (int y0 = 0; y0 <= N; y0 += kTileH2F)
         for (int x0 = 0; x0 + y0 <= N; x0 += kTileW) L.tiles_f32.push_back({(int32_t)c, x0, y0, 0});
     while (L.tiles_f32.size() % kWavesPerWG) L.tiles_f32.push_back({-1, 0, 0, 0});
+    build_short_tiles2(L, m->nc);
   }
 
   // row segments of 64 points over every storage point
@@ -731,6 +759,7 @@ int upload_level(mf_mesh* m, Level& L) {
   if ((rc = dev_upload(&D.md, L.md))) return rc;
   if ((rc = dev_upload(&D.tiles, L.tiles))) return rc;
   if ((rc = dev_upload(&D.tiles_f32, L.tiles_f32))) return rc;
+  if ((rc = dev_upload(&D.tiles_short, L.tiles_short))) return rc;
   if ((rc = dev_upload(&D.btiles, L.btiles))) return rc;
   for (int i = 0; i < 2; ++i)
     if ((rc = dev_upload(&D.vtiles[i], L.vtiles[i]))) return rc;
@@ -917,7 +946,7 @@ int build_mesh(mf_mesh* m) {
 void free_device(mf_mesh* m) {
   for (auto& L : m->levels) {
     LevelDev& D = L.dev;
-    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.btiles, D.vtiles[0], D.vtiles[1], D.faces, D.edges, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
+    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.tiles_short, D.btiles, D.vtiles[0], D.vtiles[1], D.faces, D.edges, D.segs, D.psegs, D.sbase, D.pruns, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
                     D.xgrp_invdiagf,
                     D.part, D.result, D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.own_bits, D.p2_tiles};
     for (void* p : ptrs)

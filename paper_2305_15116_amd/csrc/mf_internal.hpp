@@ -27,7 +27,14 @@ constexpr int kTileH2 = MF_TILE_H2;   // rows per 2D wave tile (FP64)
 // FP32 rows carry half the bytes: taller tiles with a deeper load ring keep
 // as many bytes in flight per wave.
 constexpr int kTileH2F = 16;
-constexpr int kRingU2F = 8;
+// A launch whose workgroups all run at once takes as long as one tile: levels
+// take the lowest tiles of which they need at most kShortWGs workgroups (four
+// per CU), FP32 levels of at most kMidWGs of kTileH2 rows take those.  FP64 and
+// FP32 Jacobi, us, against kTileH2 and kTileH2F rows: one triangle at level 8 5.3 ->
+// 3.3 and 7.3 -> 3.0, seven at level 7 5.8 -> 3.7 and 7.5 -> 3.4 (2 rows), seven at level
+// 8 5.9 -> 5.0 and 7.6 -> 4.1 (4 rows), 22 at level 8 FP32 9.4 -> 7.2.
+constexpr int kTileShort[2] = {2, 4};
+constexpr int kShortWGs = 1024, kMidWGs = 1024;
 // 3D: a wave takes 64 consecutive columns of a slab of PZ slices, cut into
 // bands of R rows, and walks them upward through the slices (walk3d.hpp).
 // Measured on the 6-tet cube (us per launch, FP64 apply / Jacobi / residual):

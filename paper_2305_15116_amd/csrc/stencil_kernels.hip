@@ -39,23 +39,10 @@ using wave::dn1;
 using wave::up1;
 
 
-#ifndef MF_RING_U2
-#define MF_RING_U2 8
-#endif
-constexpr int kU2 = MF_RING_U2;  // rows loaded ahead (2D)
-static_assert(kTileH2 % kU2 == 0, "ring depth must divide the tile height");
-static_assert(kTileH2F % kRingU2F == 0, "ring depth must divide the tile height");
+// Rows loaded ahead by a tile of H rows.
+constexpr int ring2(int H) { return H < 8 ? H : 8; }
 
-// 2D tile height and load-ring depth per precision.
-template <typename T>
-struct Tile2 {
-  static constexpr int H = kTileH2, U = kU2;
-};
-template <>
-struct Tile2<float> {
-  static constexpr int H = kTileH2F, U = kRingU2F;
-};
-
+static_assert(kTileH2 % ring2(kTileH2) == 0 && kTileH2F % ring2(kTileH2F) == 0, "ring depth must divide the tile height");
 
 // Copies the 16 x 16 partial-stencil table of macro M into W with `nthreads`
 // threads starting at `first` (a wave or the whole workgroup).
@@ -191,7 +178,7 @@ __device__ __forceinline__ T ldrow(const T* __restrict__ base, int S, int r, int
 }
 
 // ------------------------------------------------------------------ 2D tile
-template <typename T, int MODE>
+template <typename T, int MODE, int H>
 __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDev& M, WTab<T> W,
                                        const T* __restrict__ X, T* __restrict__ Y, const T* __restrict__ B,
                                        T omega, double& ss, double& mx) {
@@ -199,7 +186,7 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
   const int lane = threadIdx.x & (kWave - 1);
   const int N = M.N;
   const int x = x0 - 1 + lane;
-  constexpr int kH = Tile2<T>::H, kU = Tile2<T>::U;
+  constexpr int kH = H, kU = ring2(H);
   const int y1 = min(y0 + kH, N - x0 + 1);  // rows y0 .. y1-1 (x0 + y <= N)
   X += M.base;
   Y += M.base;
@@ -258,16 +245,16 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
 // addresses are then advanced incrementally (row y+1 starts N+1-y entries
 // after row y) with no clamping, and every output lane takes the interior
 // finish.
-template <typename T>
+template <int H>
 __device__ __forceinline__ bool tile2d_inner(int x0, int y0, int N) {
-  return x0 >= 1 && y0 >= 1 && x0 + y0 + kTileW + Tile2<T>::H <= N;
+  return x0 >= 1 && y0 >= 1 && x0 + y0 + kTileW + H <= N;
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int H>
 __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const MacroDev& M, const T* __restrict__ X,
                                             T* __restrict__ Y, const T* __restrict__ B, T omega, double& ss,
                                             double& mx) {
-  constexpr int kH = Tile2<T>::H, kU = Tile2<T>::U;
+  constexpr int kH = H, kU = ring2(H);
   const int lane = threadIdx.x & (kWave - 1);
   const int N = M.N;
   const bool out_lane = (unsigned)(lane - 1) < (unsigned)kTileW;
@@ -327,12 +314,12 @@ __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const Ma
 
 // Whether a wave tile has output points on its macro's boundary (x = 0, y = 0
 // or the far edge x + y = N).
-template <typename T>
+template <int H>
 __device__ __forceinline__ bool tile_on_boundary(const Tile& t, int N) {
-  return t.x0 == 0 || t.y0 == 0 || t.x0 + t.y0 + (kTileW - 1) + (Tile2<T>::H - 1) >= N;
+  return t.x0 == 0 || t.y0 == 0 || t.x0 + t.y0 + (kTileW - 1) + (H - 1) >= N;
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int H>
 __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T>> L) {
   const int g = wave::xcd_wg_runs(L.nwg, wave::kRuns2);
   if (g < 0) return;
@@ -354,13 +341,13 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
     if (m0 >= 0) {
       const int N0 = a.md[m0].N;
 #pragma unroll
-      for (int k = 0; k < kWavesPerWG; ++k) need = need || tile_on_boundary<T>(a.tiles[n * kWavesPerWG + k], N0);
+      for (int k = 0; k < kWavesPerWG; ++k) need = need || tile_on_boundary<H>(a.tiles[n * kWavesPerWG + k], N0);
     }
     if (need) {
       load_wtab<T>(a.md[m0], wtab[0], 0, kWG);
       __syncthreads();
     }
-  } else if (t.macro >= 0 && tile_on_boundary<T>(t, a.md[t.macro].N)) {
+  } else if (t.macro >= 0 && tile_on_boundary<H>(t, a.md[t.macro].N)) {
     load_wtab<T>(a.md[t.macro], wtab[wv], wv * kWave, kWave);
     __builtin_amdgcn_wave_barrier();
   }
@@ -368,8 +355,8 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (t.macro >= 0) {
     const MacroDev& M = a.md[t.macro];
     WTab<T> W = wtab[same ? 0 : wv];
-    if (tile2d_inner<T>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
-    else tile2d<T, MODE>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
+    if (tile2d_inner<H>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE, H>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
+    else tile2d<T, MODE, H>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
   } else if (t.macro != -1) {
     edge_rows<T, 2, MODE>(a, t, ss, mx);
   }
@@ -463,12 +450,30 @@ int stencil_lds(int nwg) {
 }
 
 template <typename T, int MODE>
-void run_stencil(const Level& L, const void* x, void* y, const void* b, double omega, double* part,
-                 hipStream_t s) {
-  const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
-  if (a.nwg > 0)
-    hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(a.nwg, wave::kRuns2)), dim3(kWG),
-                       (stencil_lds<T, MODE>(a.nwg)), s, single(a, a.nwg));
+void run_stencil(int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+  if (l.nwg <= 0) return;
+  const dim3 grid(wave::xcd_grid_runs(l.nwg, wave::kRuns2)), wg(kWG);
+  const int lds = stencil_lds<T, MODE>(l.nwg);
+  if (rows == kTileShort[0]) {
+    hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileShort[0]>), grid, wg, lds, s, l);
+  } else if (rows == kTileShort[1]) {
+    hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileShort[1]>), grid, wg, lds, s, l);
+  } else if (rows == kTileH2) {
+    hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileH2>), grid, wg, lds, s, l);
+  } else {
+    if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileH2F>), grid, wg, lds, s, l);
+  }
+}
+
+template <typename T>
+void run_stencil(int mode, int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+  switch (mode) {
+    case kApply: run_stencil<T, kApply>(rows, l, s); break;
+    case kJacobi: run_stencil<T, kJacobi>(rows, l, s); break;
+    case kResidual: run_stencil<T, kResidual>(rows, l, s); break;
+    case kNormB: run_stencil<T, kNormB>(rows, l, s); break;
+    default: run_stencil<T, kApplyDot>(rows, l, s); break;
+  }
 }
 
 template <typename T, int DIM, int MODE>
@@ -488,17 +493,10 @@ int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const vo
   } else if (mode == kDirichletSet) {
     if (dim == 2) run_iface<T, 2, kDirichletSet>(L, x, y, b, s);
     else run_iface<T, 3, kDirichletSet>(L, x, y, b, s);
-  } else if (dim == 3) {
-    const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
-    return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
   } else {
-    switch (mode) {
-      case kApply: run_stencil<T, kApply>(L, x, y, b, omega, part, s); break;
-      case kJacobi: run_stencil<T, kJacobi>(L, x, y, b, omega, part, s); break;
-      case kResidual: run_stencil<T, kResidual>(L, x, y, b, omega, part, s); break;
-      case kNormB: run_stencil<T, kNormB>(L, x, y, b, omega, part, s); break;
-      default: run_stencil<T, kApplyDot>(L, x, y, b, omega, part, s); break;
-    }
+    const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
+    if (dim == 3) return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
+    run_stencil<T>(mode, L.rows2(dtype_of<T>()), single(a, a.nwg), s);
   }
   return check_launch();
 }
@@ -510,12 +508,6 @@ int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x,
 }
 
 // ---------------------------------------------------------------- batched
-template <typename T, int MODE>
-void batch_stencil(const BatchOp& op, const char* table, hipStream_t s) {
-  hipLaunchKernelGGL((stencil_kernel<T, MODE>), dim3(wave::xcd_grid_runs(op.nwg, wave::kRuns2)), dim3(kWG),
-                     (stencil_lds<T, MODE>(op.nwg)), s, batched<StencilArgs<T>>(op, table));
-}
-
 template <typename T, int DIM>
 void batch_iface(const BatchOp& op, const char* table, hipStream_t s) {
   if (op.mode == kExchangeSum)
@@ -534,13 +526,7 @@ int batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
   } else if (op.dim == 3) {
     return launch_stencil3(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
   } else {
-    switch (op.mode) {
-      case kApply: batch_stencil<T, kApply>(op, table, s); break;
-      case kJacobi: batch_stencil<T, kJacobi>(op, table, s); break;
-      case kResidual: batch_stencil<T, kResidual>(op, table, s); break;
-      case kNormB: batch_stencil<T, kNormB>(op, table, s); break;
-      default: batch_stencil<T, kApplyDot>(op, table, s); break;
-    }
+    run_stencil<T>(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
   }
   return check_launch();
 }

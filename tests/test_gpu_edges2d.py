@@ -1,7 +1,8 @@
 """2D stencil launches against the oracle where macros share DoFs, which tiles
 of their own finish in the same launch: the smallest levels (vertices alone),
-strips in shuffled vertex orders, fans whose centre has up to 70 copies (one
-tile takes 64 per step), with and without Dirichlet rows.
+strips in shuffled vertex orders, up to the first level of every tile height,
+fans whose centre has up to 70 copies (one tile takes 64 per step), with and
+without Dirichlet rows.
 
 FP64 within 1e-12 of the largest entry; FP32 applies within 16 u32 (|A| |x|)_i
 per row (7 fused products with rounded weights and inputs per copy, and the
@@ -30,7 +31,7 @@ def _mesh(name):
     return W.apply_affine(co, *W.random_affine(2, 9)), W.shuffle_cell_orders(ce, 6)
 
 
-CASES = [("strip2", L) for L in (0, 1, 2, 3, 4, 6, 7, 9)] + [("strip7", 5), ("strip22", 6), ("strip64", 3), ("fan6", 5),
+CASES = [("strip2", L) for L in (0, 1, 2, 3, 4, 6, 7, 9, 10)] + [("strip7", 5), ("strip22", 6), ("strip64", 3), ("strip22", 8), ("strip44", 8), ("fan6", 5),
          ("fan64", 0), ("fan64", 2), ("fan70", 0), ("fan70", 1), ("fan70", 5)]
 
 
