@@ -249,7 +249,7 @@ void transfer_op(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int dt
       ta.push_back({restrict_args<T>(F, C, M->w.t[l], M->w.b[l - 1]), transfer_blocks((int)C.psegs.size())});
       ia.push_back({iface_args<T>(C, M->w.b[l - 1], M->w.b[l - 1], nullptr), iface_blocks(C)});
     } else {
-      ta.push_back({prolong_args<T>(F, C, M->w.x[l - 1], M->w.x[l]), transfer_blocks((int)F.psegs.size())});
+      ta.push_back({prolong_args<T>(F, C, M->w.x[l - 1], M->w.x[l]), transfer_blocks((int)C.psegs.size())});
     }
   }
   P.add(restrict_op ? kOpRestrict : kOpProlong, dtype, dim, 0, ta);

@@ -72,7 +72,7 @@ struct GroupArgs {
   int np;
 };
 
-// restrict_kernel / prolong_add_kernel: per-point segments of one level.
+// restrict_kernel / prolong_add_kernel: segments of 64 coarse points.
 template <typename T>
 struct TransferArgs {
   const Tile* segs;
@@ -306,11 +306,9 @@ TransferArgs<T> restrict_args(const Level& F, const Level& C, const void* rf, vo
 }
 template <typename T>
 TransferArgs<T> prolong_args(const Level& F, const Level& C, const void* ec, void* xf) {
-  // 3D prolongations walk runs of slice segments, 2D single segments
-  const bool runs = !F.pruns.empty();
-  const int n = (int)(runs ? F.pruns.size() : F.psegs.size());
-  return TransferArgs<T>{runs ? F.dev.pruns : F.dev.psegs, n, transfer_blocks(n), C.dev.md, F.dev.md,
-                         (const T*)ec, (T*)xf, C.dev.sbase, F.dev.sbase};
+  const int n = (int)C.psegs.size();
+  return TransferArgs<T>{C.dev.psegs, n, transfer_blocks(n), C.dev.md, F.dev.md, (const T*)ec, (T*)xf,
+                         C.dev.sbase, F.dev.sbase};
 }
 
 template <typename T>

@@ -76,9 +76,6 @@ struct FaceRuns {
 };
 constexpr FaceRuns kFaceRunsWG{1024, 256, 128};  // where a workgroup takes a tile
 MF_HD constexpr FaceRuns face_runs(int N) { return N >= 256 ? FaceRuns{2048, 1536, 128} : FaceRuns{256, 64, 64}; }
-// 3D prolongations walk runs of up to kTransferRun 64-point slice segments
-// (single segments below N = 256).
-constexpr int kTransferRun = 4;
 #ifndef MF_WAVES_PER_WG
 #define MF_WAVES_PER_WG 4
 #endif

@@ -294,15 +294,7 @@ __device__ __forceinline__ void slice_xy3(int S, int r, int& x, int& y) {
 // y^2 - (2S + 3) y + 2r = 0, rounded down and corrected by one step either
 // way.  Lanes past the slice's end get x = S + 1 (no point: x + y + z > N).
 template <int DIM>
-__device__ __forceinline__ void slice_point(const Tile& sg, int N, int& x, int& y, int& z) {
-  z = DIM == 3 ? sg.z : 0;
-  const int S = N - z;
-  const int r = sg.x0 + (int)(threadIdx.x & (kWave - 1));
-  if (r >= (S + 1) * (S + 2) / 2) {
-    x = S + 1;
-    y = 0;
-    return;
-  }
+__device__ __forceinline__ void slice_xy(int S, int r, int& x, int& y) {
   if (DIM == 3) {
     slice_xy3(S, r, x, y);
     return;
@@ -315,6 +307,18 @@ __device__ __forceinline__ void slice_point(const Tile& sg, int N, int& x, int& 
   else if (yy < S && row_start(S, yy + 1) <= r) ++yy;
   y = yy;
   x = r - row_start(S, yy);
+}
+template <int DIM>
+__device__ __forceinline__ void slice_point(const Tile& sg, int N, int& x, int& y, int& z) {
+  z = DIM == 3 ? sg.z : 0;
+  const int S = N - z;
+  const int r = sg.x0 + (int)(threadIdx.x & (kWave - 1));
+  if (r >= (S + 1) * (S + 2) / 2) {
+    x = S + 1;
+    y = 0;
+    return;
+  }
+  slice_xy<DIM>(S, r, x, y);
 }
 
 // Restriction over one 3D slice segment of coarse points: the same sum as
@@ -409,51 +413,101 @@ __device__ __forceinline__ void prolong_point(const TransferArgs<T>& a, int macr
   const T v = a.src[C.base + lidx<DIM>(Nc, (xl + sx) >> 1, (yl + sy) >> 1, (zl + sz) >> 1)];
   if (live && !dir) a.dst[F.base + lidx<DIM>(Nf, x, y, z)] += T(0.5) * (u + v);
 }
-// Prolongation over one 3D slice segment of fine points: prolong_point's
-// update, with the slice bases from the per-level tables and the coarse
-// points addressed by 32-bit offsets from the first point of coarse slice
-// z / 2 (the other coarse slice, (z + 1) / 2, follows it), the fine point by
-// its slice-local index.
-// The lane's fine point is slice-local index r of slice sg.z (in_run: inside
-// its run of points).
-template <typename T>
-__device__ __forceinline__ void prolong_seg3(const TransferArgs<T>& a, const Tile sg, int r, bool in_run,
-                                             int64_t& di, T& u, T& v, bool& wr) {
-  constexpr int full = 15;
-  const MacroC C = load_macro(a.mdc, sg.macro);
-  const MacroC F = load_macro(a.mdf, sg.macro);
-  const int Nc = C.N, Nf = F.N;
-  const int z = sg.z;
-  int x = Nf - z + 1, y = 0;  // lanes past the run or the slice: no point
-  if (in_run && r < (Nf - z + 1) * (Nf - z + 2) / 2) slice_xy3(Nf - z, r, x, y);
-  const bool live = x + y + z <= Nf;
-  const int mask = support_mask(3, Nf, x, y, z);
-  const bool dir = mask != full && ((F.dir_mask >> mask) & 1);
-  // dead lanes read the coarse points of (0, 0, z)
-  const int xl = live ? x : 0, yl = live ? y : 0;
-  const int px = xl & 1, py = yl & 1, pz = z & 1;
-  const int sx = px;
-  const int sy = (px && py) ? -1 : py;
-  const int sz = (pz && (px ^ py)) ? -1 : pz;
-  // coarse slices (z - sz) / 2 and (z + sz) / 2 are z / 2 or (z + 1) / 2
-  const int zl = z >> 1, zh = (z + 1) >> 1;
-  const T* __restrict__ Cl = a.src + C.base + as_const(a.sbc)[zl];
-  const int dh = as_const(a.sbc)[zh] - as_const(a.sbc)[zl];
-  const int zu = sz < 0 ? zh : zl, zv = sz > 0 ? zh : zl;
-  u = Cl[(unsigned)((sz < 0 ? dh : 0) + row_start(Nc - zu, (yl - sy) >> 1) + ((xl - sx) >> 1))];
-  v = Cl[(unsigned)((sz > 0 ? dh : 0) + row_start(Nc - zv, (yl + sy) >> 1) + ((xl + sx) >> 1))];
-  // dead lanes name the macro's first point (a valid address, never written)
-  di = F.base + (live ? as_const(a.sbf)[z] + r : 0);
-  wr = live && !dir;
-}
-
-// 2D: one 64-point segment of fine points.
+// Prolongation by cells: a lane takes coarse point P = (X, Y, Z) and the fine
+// points 2P + p, p in {0, 1}^DIM, that lie in the macro, two neighbours along x
+// at a time (8 or 16 bytes, consecutive lanes consecutive pairs).  Their
+// values need P and its neighbours along x, y, z and x + z; with room = N_c - |P|,
+// 2P + p is in the macro if |p| <= 2 room.  load() issues every load, store()
+// adds and writes; Dirichlet points are written back as they were.
 template <typename T, int DIM>
-__device__ __forceinline__ void prolong_segment(const TransferArgs<T>& a, const Tile sg) {
-  int x, y, z;
-  slice_point<DIM>(sg, load_macro(a.mdf, sg.macro).N, x, y, z);
-  prolong_point<T, DIM>(a, sg.macro, x, y, z);
-}
+struct ProlongCell {
+  typedef T Pair __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+  static constexpr int NP = 1 << (DIM - 1);  // pairs (y, z parities)
+  int room, X, Y, Z, dir;
+  bool live, apex;
+  T c, cx, cy, cz, cxz;
+  T* at[NP];
+  Pair old[NP];
+
+  __device__ __forceinline__ void load(const TransferArgs<T>& a, const Tile& sg) {
+    const MacroC C = load_macro(a.mdc, sg.macro);
+    const MacroC F = load_macro(a.mdf, sg.macro);
+    Z = DIM == 3 ? sg.z : 0;
+    const int S = C.N - Z, P = (S + 1) * (S + 2) / 2;
+    int r = sg.x0 + (int)(threadIdx.x & (kWave - 1));
+    live = r < P;
+    r = min(r, P - 1);
+    slice_xy<DIM>(S, r, X, Y);
+    room = S - X - Y;
+    dir = F.dir_mask & ~(1 << full_mask(DIM));
+    const T* p = a.src + C.base + (DIM == 3 ? as_const(a.sbc)[Z] : 0) + r;
+    const int l = S + 1 - Y, up = (S + 1) * (S + 2) / 2 - Y;
+    c = p[0];
+    cx = p[room >= 1 ? 1 : 0];
+    cy = p[room >= 1 ? l : 0];
+    if constexpr (DIM == 3) {
+      cz = p[room >= 1 ? up : 0];
+      cxz = p[room >= 2 ? up + 1 : 0];
+    }
+    const int Sf = 2 * S, lf = Sf + 1 - 2 * Y, uf = (Sf + 1) * (Sf + 2) / 2 - 2 * Y;
+    T* f = a.dst + F.base + (DIM == 3 ? as_const(a.sbf)[2 * Z] : 0) + row_start(Sf, 2 * Y) + 2 * X;
+    // the macro's last point has no successor: the pair from its predecessor on
+    apex = room == 0 && (DIM == 3 ? Z : Y) == C.N;
+    at[0] = f;
+    at[1] = f + (room >= 1 ? lf : 0);
+    if constexpr (DIM == 3) {
+      at[2] = f + (room >= 1 ? uf : 0);
+      at[3] = f + (room >= 1 ? uf + lf - 1 : 0);
+    }
+#pragma unroll
+    for (int k = 0; k < NP; ++k) old[k] = *(const Pair*)(at[k] - (apex ? 1 : 0));
+  }
+
+  __device__ __forceinline__ void store() const {
+    T add[NP][2] = {};
+    add[0][0] = T(0.5) * (c + c);
+    add[0][1] = T(0.5) * (c + cx);
+    add[1][0] = T(0.5) * (c + cy);
+    add[1][1] = T(0.5) * (cy + cx);
+    if constexpr (DIM == 3) {
+      add[2][0] = T(0.5) * (c + cz);
+      add[2][1] = T(0.5) * (cz + cx);
+      add[3][0] = T(0.5) * (cz + cy);
+      add[3][1] = T(0.5) * (cy + cxz);
+    }
+    const bool edge = X == 0 || Y == 0 || (DIM == 3 && Z == 0) || room <= 1;
+    bool keep[NP][2] = {};
+    if (dir != 0 && __builtin_amdgcn_ballot_w64(edge)) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k)
+#pragma unroll
+        for (int px = 0; px < 2; ++px) {
+          const int py = k & 1, pz = k >> 1;
+          const int mask = (2 * room != px + py + pz ? 1 : 0) | (X != 0 || px ? 2 : 0) | (Y != 0 || py ? 4 : 0) |
+                           (DIM == 3 && (Z != 0 || pz) ? 8 : 0);
+          keep[k][px] = (dir >> mask) & 1;
+        }
+    }
+    if (!live) return;
+    Pair v[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      v[k].x = apex ? old[k].y : old[k].x;
+      v[k].y = old[k].y;
+      if (!keep[k][0]) v[k].x += add[k][0];
+      if (!keep[k][1]) v[k].y += add[k][1];
+    }
+    if (room == 0) {
+      *at[0] = v[0].x;
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < NP - 1; ++k) *(Pair*)at[k] = v[k];
+    // |p| = DIM: outside the macro for room = 1 in 3D
+    if (DIM == 3 && room == 1) *at[NP - 1] = v[NP - 1].x;
+    else *(Pair*)at[NP - 1] = v[NP - 1];
+  }
+};
 
 // First Jacobi sweep of a V-cycle level.  The iterate is zero there, so
 // x' = x + omega D^-1 (b - A x) reduces to omega D^-1 b, with D the diagonal
