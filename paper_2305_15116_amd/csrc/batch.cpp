@@ -200,7 +200,7 @@ void jacobi_stage(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int v
     });
     return;
   }
-  const bool two = from_zero && two_from_zero(dim, sweeps);
+  const bool two = from_zero && two_from_zero(sweeps);
   if (two) {
     stencil_op(P, ms, dim, vdt, kJacobi2, o.omega, [&](const Member& M, Pass& p) {
       const int l = lof(M);

@@ -103,12 +103,12 @@ int jacobi_sweeps(const mf_mesh* m, const Level& L, int dtype, double omega, int
 
 // Jacobi sweeps from a zero iterate: the first sweep is y = omega D^-1 b (one
 // pass, no exchange), bitwise what a full sweep gives from x = 0; the rest as
-// jacobi_sweeps.  In 3D the first two are one launch (kJacobi2), which reads b
-// alone.  x need not be initialised.
+// jacobi_sweeps.  The first two are one launch (kJacobi2), which reads b alone.
+// x need not be initialised.
 int jacobi_sweeps_from_zero(const mf_mesh* m, const Level& L, int dtype, double omega, int sweeps, const void* b,
                             void* x, void* tmp, hipStream_t s) {
   if (sweeps == 0) return launch_fill(dtype, x, 0.0, L.storage, s);
-  const bool two = two_from_zero(m->dim, sweeps);
+  const bool two = two_from_zero(sweeps);
   void* cur = two ? x : tmp;
   void* oth = two ? tmp : x;
   int rc = two ? launch_stencil(m, L, dtype, kJacobi2, b, x, b, omega, nullptr, s)

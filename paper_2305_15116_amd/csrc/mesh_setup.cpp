@@ -270,6 +270,25 @@ static std::vector<Tile> column_tiles(int N, int64_t nc, const Shape3& sh) {
   return out;
 }
 
+// MacroDev::zinv: the assembled diagonals by macro and support.
+static void set_assembled_diagonals(const mf_mesh* m, Level& L) {
+  const StencilTable ST = stencil_table(m->dim);
+  for (int64_t c = 0; c < m->nc; ++c) L.md[c].zinv[full_mask(m->dim)] = L.md[c].inv_diag;
+  for (const Prim& P : m->prims) {
+    auto mask = [&](size_t k) {
+      int s = 0;
+      for (size_t j = 0; j < P.v.size(); ++j) s |= 1 << P.local[k][j];
+      return s;
+    };
+    double diag = 0.0;
+    for (size_t k = 0; k < P.cell.size(); ++k) diag += L.md[P.cell[k]].wm[mask(k)][ST.centre];
+    for (size_t k = 0; k < P.cell.size(); ++k)
+      L.md[P.cell[k]].zinv[mask(k)] = P.dirichlet || diag == 0.0 ? 0.0 : 1.0 / diag;
+  }
+  for (int64_t c = 0; c < m->nc; ++c)
+    for (int s = 0; s < 16; ++s) L.md[c].zinvf[s] = (float)L.md[c].zinv[s];
+}
+
 // Tiles of a 2D level's DoFs that macros share (the exchange list), at the head
 // of both tile lists so that they start first: up to 64 copies per step, two
 // steps per tile.
@@ -345,20 +364,6 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
   const int N = L.N;
   std::vector<Tile> bnd;
   const StencilTable ST = stencil_table(3);
-  for (int64_t c = 0; c < m->nc; ++c) L.md[c].zinv[full_mask(3)] = L.md[c].inv_diag;
-  for (const Prim& P : m->prims) {
-    auto mask = [&](size_t k) {
-      int s = 0;
-      for (size_t j = 0; j < P.v.size(); ++j) s |= 1 << P.local[k][j];
-      return s;
-    };
-    double diag = 0.0;
-    for (size_t k = 0; k < P.cell.size(); ++k) diag += L.md[P.cell[k]].wm[mask(k)][ST.centre];
-    for (size_t k = 0; k < P.cell.size(); ++k)
-      L.md[P.cell[k]].zinv[mask(k)] = P.dirichlet || diag == 0.0 ? 0.0 : 1.0 / diag;
-  }
-  for (int64_t c = 0; c < m->nc; ++c)
-    for (int s = 0; s < 16; ++s) L.md[c].zinvf[s] = (float)L.md[c].zinv[s];
   L.tiles = column_tiles(N, m->nc, shape3(N));
   for (int f32 = 0; f32 < 2; ++f32) L.vtiles[f32] = column_tiles(N, m->nc, shape3_varcoef(N, f32));
   // faces: weights a and b run over two of the face's vertices, with a along
@@ -692,6 +697,7 @@ static int build_level(mf_mesh* m, int level, Level& L) {
   // wave tiles, natural order: 2D the copies of shared DoFs, then every point
   // of every macro (macro, band, strip); 3D over the interior points (macro, slab, columns), then the
   // macro faces and the edge and vertex copies
+  set_assembled_diagonals(m, L);
   L.tiles.clear();
   L.tiles_f32.clear();
   if (dim == 2) {

@@ -145,7 +145,7 @@ struct MacroDev {
   float wmf[16][16];
   double K[6][16];      // element matrix of each micro-element type (row-major 4 x 4)
   float Kf[6][16];      // the same in FP32 (FP32 kernels read it without conversions)
-  double zinv[16];      // 3D: 1 / assembled diagonal of the points with support s, 0 on the Dirichlet boundary
+  double zinv[16];      // 1 / assembled diagonal of the points with support s, 0 on the Dirichlet boundary
   float zinvf[16];
 };
 
@@ -232,7 +232,7 @@ enum Mode : int {
   kResidual = 2,  // y = b - A x  (+ sum of squares and max |.| partials)
   kNormB = 3,     // no output; partials of b only (||b|| over unique DoFs)
   kApplyDot = 4,  // y = A x  (+ partials of x . y over unique DoFs)
-  kJacobi2 = 5,   // 3D: two Jacobi sweeps from a zero iterate, y = z + omega D^-1 (b - A z) with z = omega D^-1 b
+  kJacobi2 = 5,   // two Jacobi sweeps from a zero iterate, y = z + omega D^-1 (b - A z) with z = omega D^-1 b
 };
 
 // Modes whose kernels leave (sum, max) partials.

@@ -91,13 +91,13 @@ __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int m
   const bool dir = !full && ((M.dir_mask >> mask) & 1);
   const bool shared = !full && ((M.shared_mask >> mask) & 1);
   if (dir) {
-    const T out = MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : xc);
+    const T out = MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : (MODE == kJacobi2 ? T(0) : xc));
     if (MODE != kNormB) st(yp, out);
     if ((M.own_mask >> mask) & 1) accum<T, MODE>(ss, mx, out, xc);
   } else if (full || !shared) {
     T out;
     if (MODE == kApply || MODE == kApplyDot) out = acc;
-    else if (MODE == kJacobi) out = fma(omega * (full ? Prec<T>::invd(M) : T(1) / W[mask][ST.centre]), bv - acc, xc);
+    else if (MODE == kJacobi || MODE == kJacobi2) out = fma(omega * (full ? Prec<T>::invd(M) : T(1) / W[mask][ST.centre]), bv - acc, xc);
     else if (MODE == kResidual) out = bv - acc;
     else out = bv;
     if (MODE != kNormB) st(yp, out);

@@ -103,10 +103,11 @@ inline Workspace carve(const mf_mesh* m, int level, int mode, int lc, char* base
   return w;
 }
 
-// Whether the first two sweeps from a zero iterate are one launch (kJacobi2;
-// 2D has no such kernel).  Cube, FP32, against the three launches of a sweep
-// from zero and a full one: N = 256 88 -> 43 us, N = 128 25 -> 9.9, N = 32 16 -> 6.2.
-inline bool two_from_zero(int dim, int sweeps) { return dim == 3 && sweeps >= 2; }
+// Whether the first two sweeps from a zero iterate are one launch (kJacobi2).
+// Cube, FP32, against the three launches of a sweep from zero and a full one:
+// N = 256 88 -> 43 us, N = 128 25 -> 9.9, N = 32 16 -> 6.2; 2D levels of a few
+// macros, four microseconds a launch, three -> one.
+inline bool two_from_zero(int sweeps) { return sweeps >= 2; }
 
 inline int default_coarse(int level) { return std::min(2, level); }
 

@@ -61,7 +61,7 @@ __device__ __forceinline__ void finish_interior(const MacroDev& M, T acc, T xc, 
                                                 double& mx) {
   T out;
   if (MODE == kApply || MODE == kApplyDot) out = acc;
-  else if (MODE == kJacobi) out = fma(omega * Prec<T>::invd(M), bv - acc, xc);
+  else if (MODE == kJacobi || MODE == kJacobi2) out = fma(omega * Prec<T>::invd(M), bv - acc, xc);
   else if (MODE == kResidual) out = bv - acc;
   else out = bv;
   if (MODE != kNormB) st(yp, out);
@@ -143,9 +143,9 @@ __device__ __forceinline__ void point_row(const MacroDev& M, const WTab<T> W, co
   T out;
   if (MODE == kApply || MODE == kApplyDot) {
     out = dir ? xc : a;
-  } else if (MODE == kJacobi) {
+  } else if (MODE == kJacobi || MODE == kJacobi2) {
     const T id = !bnd ? Prec<T>::invd(M) : far ? (left ? bid[2] : bid[1]) : bid[0];
-    out = dir ? xc : fma(omega * id, bv - a, xc);
+    out = dir ? (MODE == kJacobi2 ? T(0) : xc) : fma(omega * id, bv - a, xc);
   } else if (MODE == kResidual) {
     out = dir ? bv - xc : bv - a;
   } else {
@@ -190,12 +190,14 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
   const int y1 = min(y0 + kH, N - x0 + 1);  // rows y0 .. y1-1 (x0 + y <= N)
   X += M.base;
   Y += M.base;
-  if (MODE != kApply) B += M.base;
+  constexpr bool kZ = MODE == kJacobi2;  // X is b: scaled to the iterate when its row is first used
+  constexpr bool kB = MODE != kApply && !kZ;
+  if (kB) B += M.base;
   T wi[7];
 #pragma unroll
   for (int o = 0; o < 7; ++o) wi[o] = Prec<T>::w(M, FM, o);
   T bid[3] = {T(0), T(0), T(0)};
-  if (MODE == kJacobi) {
+  if (MODE == kJacobi || MODE == kJacobi2) {
     constexpr int c = stencil_table(2).centre;
     bid[0] = T(1) / W[RowMasks::L][c];
     bid[1] = T(1) / W[RowMasks::F][c];
@@ -205,12 +207,22 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
   const int xc = max(x, 0);
   T am = ldrow(X, N, y0 - 1, y1, xc);
   T a0 = ldrow(X, N, y0, y1, xc);
+  // kJacobi2: omega / diagonal of the column's points inside and on the far
+  // edge, and on y = 0 (row y0 of a tile at y0 = 0); raw = b of row y0
+  T zi = T(0), zf = T(0), raw = a0;
+  if (kZ) {
+    const int mx = x <= 0 ? 0 : 2;
+    auto c = [&](int mask) { return omega * Prec<T>::zinv(M, mask); };
+    zi = c(5 | mx), zf = c(4 | mx);
+    am *= x + y0 - 1 == N ? zf : zi;
+    a0 *= y0 == 0 ? (x == N ? c(mx) : c(1 | mx)) : (x + y0 == N ? zf : zi);
+  }
   T am_r = dn1(am), a0_l = up1(a0), a0_r = dn1(a0);
   T q[kU], qb[kU];
 #pragma unroll
   for (int k = 0; k < kU; ++k) {
     q[k] = ldrow(X, N, y0 + 1 + k, y1, xc);                    // x rows y0+1 ..
-    if (MODE != kApply) qb[k] = ldrow(B, N, y0 + k, y1 - 1, xc);  // b rows = output rows
+    if (kB) qb[k] = ldrow(B, N, y0 + k, y1 - 1, xc);  // b rows = output rows
   }
   // The tile's rows are fully unrolled so that the load ring needs no
   // register copies at a loop back-edge (which would wait for every load in
@@ -220,12 +232,13 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
 #pragma unroll
   for (int k = 0; k < kH; ++k) {
     const int yy = y0 + k;
-    const T ap = q[k % kU];
-    const T bv = MODE != kApply ? qb[k % kU] : T(0);
+    const T rp = q[k % kU], ap = kZ ? rp * (x + yy + 1 == N ? zf : zi) : rp;
+    const T bv = kZ ? raw : (kB ? qb[k % kU] : T(0));
+    raw = rp;
     // (compile-time guards: a ring slot is refilled only if a later row of
     // this tile reads it)
     if (k + kU < kH) q[k % kU] = ldrow(X, N, y0 + 1 + k + kU, y1, xc);
-    if (MODE != kApply && k + kU < kH) qb[k % kU] = ldrow(B, N, y0 + k + kU, y1 - 1, xc);
+    if (kB && k + kU < kH) qb[k % kU] = ldrow(B, N, y0 + k + kU, y1 - 1, xc);
     if (k >= nrows) continue;
     const T ap_l = up1(ap), ap_r = dn1(ap);
     const T v[7] = {am, am_r, a0_l, a0, a0_r, ap_l, ap};
@@ -245,9 +258,11 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
 // addresses are then advanced incrementally (row y+1 starts N+1-y entries
 // after row y) with no clamping, and every output lane takes the interior
 // finish.
-template <int H>
+// (kJacobi2: nor does any row it reads hold such a point)
+template <int H, int MODE>
 __device__ __forceinline__ bool tile2d_inner(int x0, int y0, int N) {
-  return x0 >= 1 && y0 >= 1 && x0 + y0 + kTileW + H <= N;
+  constexpr int in = MODE == kJacobi2 ? 1 : 0;
+  return x0 >= 1 + in && y0 >= 1 + in && x0 + y0 + kTileW + H + in <= N;
 }
 
 template <typename T, int MODE, int H>
@@ -267,7 +282,9 @@ __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const Ma
   int sx = (N + 2 - y0) * (int)sizeof(T);
   char* py = (char*)(Y + M.base + rs32(N, y0));
   int sy = (N + 1 - y0) * (int)sizeof(T);
-  const char* pb = MODE != kApply ? (const char*)(B + M.base + rs32(N, y0)) : nullptr;
+  constexpr bool kZ = MODE == kJacobi2, kB = MODE != kApply && !kZ;
+  const T zi = kZ ? omega * Prec<T>::zinv(M, full_mask(2)) : T(1);
+  const char* pb = kB ? (const char*)(B + M.base + rs32(N, y0)) : nullptr;
   int sb = sy;
   auto ldx = [&]() -> T {
     const T v = *(const T*)(px + col);
@@ -282,20 +299,22 @@ __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const Ma
     return v;
   };
   T am = ldx();
-  T a0 = ldx();
+  T a0 = ldx(), raw = a0;
+  if (kZ) am *= zi, a0 *= zi;
   T am_r = dn1(am), a0_l = up1(a0), a0_r = dn1(a0);
   T q[kU], qb[kU];
 #pragma unroll
   for (int k = 0; k < kU; ++k) {
     q[k] = ldx();
-    if (MODE != kApply) qb[k] = ldb();
+    if (kB) qb[k] = ldb();
   }
 #pragma unroll
   for (int k = 0; k < kH; ++k) {
-    const T ap = q[k % kU];
-    const T bv = MODE != kApply ? qb[k % kU] : T(0);
+    const T rp = q[k % kU], ap = kZ ? rp * zi : rp;
+    const T bv = kZ ? raw : (kB ? qb[k % kU] : T(0));
+    raw = rp;
     if (k + 1 + kU <= kH) q[k % kU] = ldx();
-    if (MODE != kApply && k + kU < kH) qb[k % kU] = ldb();
+    if (kB && k + kU < kH) qb[k % kU] = ldb();
     const T ap_l = up1(ap), ap_r = dn1(ap);
     const T v[7] = {am, am_r, a0_l, a0, a0_r, ap_l, ap};
     T acc = wi[0] * v[0];
@@ -355,7 +374,7 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (t.macro >= 0) {
     const MacroDev& M = a.md[t.macro];
     WTab<T> W = wtab[same ? 0 : wv];
-    if (tile2d_inner<H>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE, H>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
+    if (tile2d_inner<H, MODE>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE, H>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
     else tile2d<T, MODE, H>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
   } else if (t.macro != -1) {
     edge_rows<T, 2, MODE>(a, t, ss, mx);
@@ -470,6 +489,7 @@ void run_stencil(int mode, int rows, const Launch<StencilArgs<T>>& l, hipStream_
   switch (mode) {
     case kApply: run_stencil<T, kApply>(rows, l, s); break;
     case kJacobi: run_stencil<T, kJacobi>(rows, l, s); break;
+    case kJacobi2: run_stencil<T, kJacobi2>(rows, l, s); break;
     case kResidual: run_stencil<T, kResidual>(rows, l, s); break;
     case kNormB: run_stencil<T, kNormB>(rows, l, s); break;
     default: run_stencil<T, kApplyDot>(rows, l, s); break;

@@ -1,5 +1,4 @@
-"""V-cycles whose first two sweeps from a zero iterate are one launch (3D),
-against the same cycle put together from the smoother, residual and transfer
+"""V-cycles whose first two sweeps from a zero iterate are one launch, against the same cycle put together from the smoother, residual and transfer
 calls (each held to the oracle by its own tests) and a dense solve on the
 oracle's matrix at the coarse level.
 
@@ -32,8 +31,12 @@ def _mesh(name):
         ring = [[np.cos(2 * np.pi * i / n), np.sin(2 * np.pi * i / n), 0.5] for i in range(n)]
         co = np.array([[0.0, 0.0, 0.0], [0.0, 0.0, 1.0]] + ring)
         return co, W.shuffle_cell_orders(np.array([[0, 1, 2 + i, 2 + (i + 1) % n] for i in range(n)]), 2)
-    co, ce = W.strip_3d(int(name[5:]))
-    return W.apply_affine(co, *W.random_affine(3, 9)), W.shuffle_cell_orders(ce, 6)
+    if name == "ring12":  # triangles around a point
+        co = np.array([[0.0, 0.0]] + [[np.cos(np.pi * i / 6), np.sin(np.pi * i / 6)] for i in range(12)])
+        return co, W.shuffle_cell_orders(np.array([[0, 1 + i, 1 + (i + 1) % 12] for i in range(12)]), 2)
+    dim = 2 if name.startswith("plane") else 3
+    co, ce = (W.strip_2d if dim == 2 else W.strip_3d)(int(name[5:]))
+    return W.apply_affine(co, *W.random_affine(dim, 9)), W.shuffle_cell_orders(ce, 6)
 
 
 def _cycle(m, l, lc, b, dtype, pre, post, coarse):
@@ -54,7 +57,9 @@ def _cycle(m, l, lc, b, dtype, pre, post, coarse):
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("name,L,pre", [("tet", 5, 2), ("tet", 6, 3), ("tet", 7, 2), ("tet", 8, 2), ("cube", 5, 2),
                                         ("cube", 6, 4), ("strip11", 5, 2), ("strip7", 4, 3), ("fan70", 4, 2),
-                                        ("strip5", 5, 1)])
+                                        ("strip5", 5, 1), ("plane1", 7, 2), ("plane1", 9, 3), ("plane1", 10, 2),
+                                        ("plane2", 7, 2), ("plane7", 8, 2), ("plane44", 8, 2), ("ring12", 6, 2),
+                                        ("plane3", 6, 1)])
 def test_one_cycle(name, L, pre, mode):
     co, ce = _mesh(name)
     m = P.create_macro_mesh(co, ce, L)
