@@ -18,6 +18,7 @@ namespace mf {
 
 // Device copies of one level's metadata.
 struct LevelDev {
+  std::vector<void*> allocs;   // of upload_level's tables
   MacroDev* md = nullptr;
   Tile* tiles = nullptr;       // interior wave tiles, padded to a multiple of kWavesPerWG
   Tile* tiles_f32 = nullptr;   // 2D FP32 wave tiles

@@ -746,36 +746,88 @@ static int build_level(mf_mesh* m, int level, Level& L) {
   return MF_OK;
 }
 
+namespace {
+// Device copies of a level's tables: the small ones share one allocation and
+// one copy (one each cost a mesh of ten levels some 250 of both).
+struct Upload {
+  struct Item {
+    void** dst;
+    const void* src;
+    size_t bytes;
+  };
+  static constexpr size_t kAlignment = 256, kSmall = 256 * 1024;
+  std::vector<Item> items;
+  template <class T>
+  void add(T** dst, const std::vector<T>& src) {
+    *dst = nullptr;
+    if (!src.empty()) items.push_back({(void**)dst, src.data(), sizeof(T) * src.size()});
+  }
+  int run(std::vector<void*>& allocs) {
+    auto padded = [](size_t n) { return (n + kAlignment - 1) / kAlignment * kAlignment; };
+    auto alloc = [&](size_t bytes, char** out) -> int {
+      const hipError_t e = hipMalloc((void**)out, bytes);
+      if (e != hipSuccess) return set_error(e == hipErrorOutOfMemory ? MF_ENOMEM : MF_EDEVICE, hipGetErrorString(e));
+      allocs.push_back(*out);
+      return MF_OK;
+    };
+    auto copy = [](void* dst, const void* src, size_t bytes) -> int {
+      const hipError_t e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+      return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
+    };
+    std::vector<char> small;
+    for (const Item& i : items)
+      if (i.bytes < kSmall) small.resize(small.size() + padded(i.bytes));
+    char* at = nullptr;
+    int rc = small.empty() ? MF_OK : alloc(small.size(), &at);
+    if (rc) return rc;
+    size_t off = 0;
+    for (const Item& i : items) {
+      char* dst = nullptr;
+      if (i.bytes < kSmall) {
+        dst = at + off;
+        std::memcpy(small.data() + off, i.src, i.bytes);
+        off += padded(i.bytes);
+      } else {
+        if ((rc = alloc(i.bytes, &dst)) || (rc = copy(dst, i.src, i.bytes))) return rc;
+      }
+      *i.dst = dst;
+    }
+    return small.empty() ? MF_OK : copy(at, small.data(), small.size());
+  }
+};
+}  // namespace
+
 int upload_level(mf_mesh* m, Level& L) {
   LevelDev& D = L.dev;
-  int rc;
-  if ((rc = dev_upload(&D.md, L.md))) return rc;
-  if ((rc = dev_upload(&D.tiles, L.tiles))) return rc;
-  if ((rc = dev_upload(&D.tiles_f32, L.tiles_f32))) return rc;
-  if ((rc = dev_upload(&D.tiles_short, L.tiles_short))) return rc;
-  if ((rc = dev_upload(&D.btiles, L.btiles))) return rc;
-  for (int i = 0; i < 2; ++i)
-    if ((rc = dev_upload(&D.vtiles[i], L.vtiles[i]))) return rc;
-  if ((rc = dev_upload(&D.faces, L.faces))) return rc;
-  if ((rc = dev_upload(&D.edges, L.edges))) return rc;
-  if ((rc = dev_upload(&D.segs, L.segs))) return rc;
-  if ((rc = dev_upload(&D.psegs, L.psegs))) return rc;
-  if ((rc = dev_upload(&D.sbase, L.sbase))) return rc;
-  if ((rc = dev_upload(&D.grp_ptr, L.grp_ptr))) return rc;
-  if ((rc = dev_upload(&D.copies, L.copies))) return rc;
-  if ((rc = dev_upload(&D.grp_flag, L.grp_flag))) return rc;
-  if ((rc = dev_upload(&D.xgrp_ptr, L.xgrp_ptr))) return rc;
-  if ((rc = dev_upload(&D.xcopies, L.xcopies))) return rc;
-  if ((rc = dev_upload(&D.cpidx, L.cpidx))) return rc;
-  if ((rc = dev_upload(&D.xcpidx, L.xcpidx))) return rc;
-  if ((rc = dev_upload(&D.xgrp_invdiag, L.xgrp_invdiag))) return rc;
-  if ((rc = dev_upload(&D.own_bits, L.own_bits))) return rc;
+  Upload up;
+  up.add(&D.md, L.md);
+  up.add(&D.tiles, L.tiles);
+  up.add(&D.tiles_f32, L.tiles_f32);
+  up.add(&D.tiles_short, L.tiles_short);
+  up.add(&D.btiles, L.btiles);
+  for (int i = 0; i < 2; ++i) up.add(&D.vtiles[i], L.vtiles[i]);
+  up.add(&D.faces, L.faces);
+  up.add(&D.edges, L.edges);
+  up.add(&D.segs, L.segs);
+  up.add(&D.psegs, L.psegs);
+  up.add(&D.sbase, L.sbase);
+  up.add(&D.grp_ptr, L.grp_ptr);
+  up.add(&D.copies, L.copies);
+  up.add(&D.grp_flag, L.grp_flag);
+  up.add(&D.xgrp_ptr, L.xgrp_ptr);
+  up.add(&D.xcopies, L.xcopies);
+  up.add(&D.cpidx, L.cpidx);
+  up.add(&D.xcpidx, L.xcpidx);
+  up.add(&D.xgrp_invdiag, L.xgrp_invdiag);
+  up.add(&D.own_bits, L.own_bits);
   std::vector<float> f(L.xgrp_invdiag.begin(), L.xgrp_invdiag.end());
-  if ((rc = dev_upload(&D.xgrp_invdiagf, f))) return rc;
+  up.add(&D.xgrp_invdiagf, f);
   std::vector<double> zeros(2 * (L.n_partials() + 1), 0.0);
-  if ((rc = dev_upload(&D.part, zeros))) return rc;
+  up.add(&D.part, zeros);
   std::vector<double> z2(2, 0.0);
-  if ((rc = dev_upload(&D.result, z2))) return rc;
+  up.add(&D.result, z2);
+  const int rc = up.run(D.allocs);
+  if (rc) return rc;
   hipError_t e = hipHostMalloc((void**)&D.host_result, 2 * sizeof(double), hipHostMallocDefault);
   if (e != hipSuccess) return set_error(MF_ENOMEM, hipGetErrorString(e));
   (void)m;
@@ -938,9 +990,8 @@ int build_mesh(mf_mesh* m) {
 void free_device(mf_mesh* m) {
   for (auto& L : m->levels) {
     LevelDev& D = L.dev;
-    void* ptrs[] = {D.md, D.tiles, D.tiles_f32, D.tiles_short, D.btiles, D.vtiles[0], D.vtiles[1], D.faces, D.edges, D.segs, D.psegs, D.sbase, D.grp_ptr, D.copies, D.grp_flag, D.xgrp_ptr, D.xcopies, D.cpidx, D.xcpidx, D.xgrp_invdiag,
-                    D.xgrp_invdiagf,
-                    D.part, D.result, D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.own_bits, D.p2_tiles};
+    for (void* p : D.allocs) (void)hipFree(p);
+    void* ptrs[] = {D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.p2_tiles};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
     if (D.host_result) (void)hipHostFree(D.host_result);
