@@ -239,21 +239,18 @@ void jacobi_stage(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int v
 template <typename T>
 void transfer_op(PlanBuilder& P, const std::vector<Member*>& ms, int dim, int dtype, bool restrict_op, int dl) {
   std::vector<std::pair<TransferArgs<T>, int>> ta;
-  std::vector<std::pair<GroupArgs<T>, int>> ia;
   for (Member* M : ms) {
     if (M->m->dim != dim || M->level - M->lc < dl || dl < M->tail) continue;
     const int l = M->lc + dl;
     const Level& F = lev(*M, l);
     const Level& C = lev(*M, l - 1);
     if (restrict_op) {
-      ta.push_back({restrict_args<T>(F, C, M->w.t[l], M->w.b[l - 1]), transfer_blocks((int)C.psegs.size())});
-      ia.push_back({iface_args<T>(C, M->w.b[l - 1], M->w.b[l - 1], nullptr), iface_blocks(C)});
+      ta.push_back({restrict_args<T>(F, C, M->w.t[l], M->w.b[l - 1]), restrict_blocks(C)});
     } else {
       ta.push_back({prolong_args<T>(F, C, M->w.x[l - 1], M->w.x[l]), transfer_blocks((int)C.psegs.size())});
     }
   }
   P.add(restrict_op ? kOpRestrict : kOpProlong, dtype, dim, 0, ta);
-  if (restrict_op) P.add(kOpIface, dtype, dim, kExchangeSum, ia);
 }
 
 template <typename T>
@@ -413,7 +410,7 @@ void build_plan(mf_batch* B, int dim) {
     std::vector<std::pair<GroupArgs<double>, int>> ia;
     for (Member* M : fresh) {
       const Level& L = lev(*M, M->level);
-      ia.push_back({iface_args<double>(L, M->x, M->x, M->b), iface_blocks(L)});
+      ia.push_back({iface_args<double>(L, M->x, M->b), iface_blocks(L)});
     }
     P.add(kOpIface, MF_F64, dim, kDirichletSet, ia);
     stencil_op(P, fresh, dim, MF_F64, kNormB, 0.0, [](const Member& M, Pass& p) {

@@ -58,18 +58,10 @@ template <typename T>
 struct GroupArgs {
   int ngroups;
   const int32_t* gptr;
-  const Copy* copies;
-  const int64_t* cidx;  // storage index of each copy
+  const int64_t* cidx;   // storage index of each copy
   const uint8_t* gflag;  // all-groups list only
-  const double* ginv;    // exchange list only
-  const float* ginvf;
-  const MacroDev* md;
-  const T* X;
   T* Y;
   const T* B;
-  T omega;
-  double* part;  // block partials at [0, nblk), maxima at [np, ...)
-  int np;
 };
 
 // restrict_kernel / prolong_add_kernel: segments of 64 coarse points.
@@ -82,8 +74,12 @@ struct TransferArgs {
   const MacroDev* mdf;
   const T* src;
   T* dst;
-  const int32_t* sbc;  // slice bases of the coarse and the fine level (3D segment kernels)
+  const int32_t* sbc;  // slice bases of the coarse and the fine level (3D)
   const int32_t* sbf;
+  int nb;  // restriction: workgroups of the coarse level's boundary tiles, before the others
+  const Tile* btiles;
+  const FaceDev* faces;
+  const EdgeCopy* edges;
 };
 
 // coarse_solve_kernel
@@ -114,7 +110,6 @@ struct Jacobi0Args {
   const Copy* acopies;
   int ngroups, nblk_grp;  // exchange list
   const int32_t* gptr;
-  const Copy* copies;
   const int64_t* gidx;  // storage index of each exchange-list copy
   const double* ginv;
   const float* ginvf;
@@ -148,15 +143,9 @@ template <typename T>
 struct TailLevel {
   int nx;  // exchange list: shared non-Dirichlet DoFs
   const int32_t* xptr;
-  const Copy* xcopies;
   const int64_t* xcidx;
   const double* xinv;
   const float* xinvf;
-  int ng;  // all macro-boundary DoFs
-  const int32_t* gptr;
-  const Copy* copies;
-  const int64_t* gcidx;
-  const uint8_t* gflag;
   const MacroDev* md;
   int64_t storage;  // nmac macros of side N, stored one after the other
   int N, nmac;
@@ -263,31 +252,21 @@ GroupArgs<T> exchange_args(const Level& L, void* y) {
   GroupArgs<T> g{};
   g.ngroups = (int)L.nxgroups();
   g.gptr = L.dev.xgrp_ptr;
-  g.copies = L.dev.xcopies;
   g.cidx = L.dev.xcpidx;
-  g.md = L.dev.md;
   g.Y = (T*)y;
   return g;
 }
 inline int exchange_blocks(const Level& L) { return (int)((L.nxgroups() + kIfaceWG - 1) / kIfaceWG); }
 
 template <typename T>
-GroupArgs<T> iface_args(const Level& L, const void* x, void* y, const void* b) {
-  GroupArgs<T> g;
+GroupArgs<T> iface_args(const Level& L, void* y, const void* b) {
+  GroupArgs<T> g{};
   g.ngroups = (int)L.ngroups();
   g.gptr = L.dev.grp_ptr;
-  g.copies = L.dev.copies;
   g.cidx = L.dev.cpidx;
   g.gflag = L.dev.grp_flag;
-  g.ginv = nullptr;
-  g.ginvf = nullptr;
-  g.md = L.dev.md;
-  g.X = (const T*)x;
   g.Y = (T*)y;
   g.B = (const T*)b;
-  g.omega = T(0);
-  g.part = nullptr;
-  g.np = 0;
   return g;
 }
 inline int iface_blocks(const Level& L) { return (int)L.iface_blocks(); }
@@ -301,14 +280,15 @@ inline int transfer_blocks(int nseg) {
 template <typename T>
 TransferArgs<T> restrict_args(const Level& F, const Level& C, const void* rf, void* bc) {
   const int n = (int)C.psegs.size();
-  return TransferArgs<T>{C.dev.psegs, n, transfer_blocks(n), C.dev.md, F.dev.md, (const T*)rf, (T*)bc,
-                         C.dev.sbase, F.dev.sbase};
+  return TransferArgs<T>{C.dev.psegs,  n, transfer_blocks(n),   C.dev.md,     F.dev.md,    (const T*)rf, (T*)bc, C.dev.sbase,
+                         F.dev.sbase, (int)C.btiles.size(), C.dev.btiles, C.dev.faces, C.dev.edges};
 }
+inline int restrict_blocks(const Level& C) { return transfer_blocks((int)C.psegs.size()) + (int)C.btiles.size(); }
 template <typename T>
 TransferArgs<T> prolong_args(const Level& F, const Level& C, const void* ec, void* xf) {
   const int n = (int)C.psegs.size();
-  return TransferArgs<T>{C.dev.psegs, n, transfer_blocks(n), C.dev.md, F.dev.md, (const T*)ec, (T*)xf,
-                         C.dev.sbase, F.dev.sbase};
+  return TransferArgs<T>{C.dev.psegs, n,           transfer_blocks(n), C.dev.md, F.dev.md, (const T*)ec, (T*)xf,
+                         C.dev.sbase, F.dev.sbase, 0,                  nullptr,  nullptr,  nullptr};
 }
 
 template <typename T>
@@ -338,7 +318,6 @@ Jacobi0Args<T> jacobi0_args(const Level& L, const void* b, void* y, double omega
   a.ngroups = (int)L.nxgroups();
   a.nblk_grp = (a.ngroups + kWG - 1) / kWG;
   a.gptr = L.dev.xgrp_ptr;
-  a.copies = L.dev.xcopies;
   a.gidx = L.dev.xcpidx;
   a.ginv = L.dev.xgrp_invdiag;
   a.ginvf = L.dev.xgrp_invdiagf;
@@ -358,15 +337,9 @@ TailLevel<T> tail_level(const Level& L, void* b, void* x, void* t) {
   TailLevel<T> v;
   v.nx = (int)L.nxgroups();
   v.xptr = L.dev.xgrp_ptr;
-  v.xcopies = L.dev.xcopies;
   v.xcidx = L.dev.xcpidx;
   v.xinv = L.dev.xgrp_invdiag;
   v.xinvf = L.dev.xgrp_invdiagf;
-  v.ng = (int)L.ngroups();
-  v.gptr = L.dev.grp_ptr;
-  v.copies = L.dev.copies;
-  v.gcidx = L.dev.cpidx;
-  v.gflag = L.dev.grp_flag;
   v.md = L.dev.md;
   v.storage = L.storage;
   v.N = L.N;
@@ -398,7 +371,7 @@ inline int pcg_blocks(const Level& L) { return (int)L.lin_blocks(); }
 // ---------------------------------------------------------------- batch ops
 enum OpKind : int {
   kOpStencil = 0,  // StencilArgs<T>, any Mode
-  kOpIface,        // GroupArgs<T>, mode = kExchangeSum / kDirichletSet
+  kOpIface,        // GroupArgs<T>, kDirichletSet
   kOpReduce,       // ReduceArgs
   kOpRestrict,     // TransferArgs<T>
   kOpProlong,      // TransferArgs<T>

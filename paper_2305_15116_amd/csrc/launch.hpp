@@ -46,8 +46,7 @@ int64_t stencil_partials(const Level& L, int dtype);
 int launch_stencil(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
                    double omega, double* part, hipStream_t s);
 
-// Interface groups only, for kExchangeSum (y = sum of x over copies;
-// Dirichlet -> 0) and kDirichletSet (y = b at Dirichlet DoFs).
+// kDirichletSet: y = b at the Dirichlet DoFs (b NULL: 0).
 int launch_iface(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
                  hipStream_t s);
 

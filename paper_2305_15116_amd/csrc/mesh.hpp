@@ -34,7 +34,6 @@ struct LevelDev {
   Copy* copies = nullptr;
   uint8_t* grp_flag = nullptr;  // bit0: Dirichlet
   int32_t* xgrp_ptr = nullptr;  // exchange groups: shared, non-Dirichlet DoFs
-  Copy* xcopies = nullptr;
   int64_t* cpidx = nullptr;   // storage index of every copy (all-groups list)
   int64_t* xcpidx = nullptr;  // storage index of every copy (exchange list)
   double* xgrp_invdiag = nullptr;
@@ -63,7 +62,7 @@ struct Level {
   std::vector<Tile> tiles_f32;  // 2D FP32 wave tiles (kTileH2F rows); empty in 3D (same as tiles)
   std::vector<Tile> tiles_short;  // 2D levels of few tiles: short_rows rows each, either type
   int short_rows = 0;
-  std::vector<Tile> btiles;     // 3D: the face and edge tiles by themselves, one per workgroup (kFaceRunsWG)
+  std::vector<Tile> btiles;     // the face and edge tiles by themselves, one per workgroup (kFaceRunsWG)
   std::vector<Tile> vtiles[2];  // 3D: column tiles of the variable-coefficient walk (FP64, FP32)
   std::vector<FaceDev> faces;   // 3D: macro faces, and the copies of the edge and vertex DoFs, that tiles name
   std::vector<EdgeCopy> edges;

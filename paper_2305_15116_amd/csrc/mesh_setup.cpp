@@ -326,6 +326,7 @@ static void build_edge_tiles2(Level& L) {
     }
   }
   close();
+  L.btiles = out;
   while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
   L.ewgs = (int)(out.size() / kWavesPerWG);
   L.tiles_f32 = out;
@@ -815,7 +816,6 @@ int upload_level(mf_mesh* m, Level& L) {
   up.add(&D.copies, L.copies);
   up.add(&D.grp_flag, L.grp_flag);
   up.add(&D.xgrp_ptr, L.xgrp_ptr);
-  up.add(&D.xcopies, L.xcopies);
   up.add(&D.cpidx, L.cpidx);
   up.add(&D.xcpidx, L.xcpidx);
   up.add(&D.xgrp_invdiag, L.xgrp_invdiag);

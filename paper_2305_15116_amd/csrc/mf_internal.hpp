@@ -240,7 +240,6 @@ MF_HD constexpr bool has_partials(int mode) { return mode == kResidual || mode =
 
 // Interface-kernel-only modes.
 enum IfaceMode : int {
-  kExchangeSum = 10,   // y(all copies) = sum of the copies' values of x; Dirichlet -> 0
   kDirichletSet = 11,  // y = b at Dirichlet DoFs only
 };
 

@@ -213,15 +213,15 @@ __device__ __forceinline__ Tile load_seg(const Tile* segs, int si) {
 struct MacroC {
   int64_t base;
   int32_t N;
-  uint16_t own_mask, dir_mask;
+  uint16_t own_mask, dir_mask, shared_mask;
 };
 
 __device__ __forceinline__ MacroC load_macro(const MacroDev* md, int m) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const auto* p = as_const(md) + m;
-  return MacroC{p->base, p->N, p->own_mask, p->dir_mask};
+  return MacroC{p->base, p->N, p->own_mask, p->dir_mask, p->shared_mask};
 #else
-  return MacroC{md[m].base, md[m].N, md[m].own_mask, md[m].dir_mask};
+  return MacroC{md[m].base, md[m].N, md[m].own_mask, md[m].dir_mask, md[m].shared_mask};
 #endif
 }
 
@@ -241,37 +241,28 @@ __device__ __forceinline__ void nbr_offsets3(int N, int y, int z, int (&o)[15]) 
 }
 
 template <typename T, int DIM>
-__device__ __forceinline__ void restrict_point(const TransferArgs<T>& a, int macro, int x, int y, int z) {
+__device__ __forceinline__ T restrict_partial(const TransferArgs<T>& a, int macro, int x, int y, int z) {
   constexpr StencilTable ST = stencil_table(DIM);
-  constexpr int full = DIM == 2 ? 7 : 15;
-  const MacroC C = load_macro(a.mdc, macro);
-  const MacroC F = load_macro(a.mdf, macro);
-  const int Nc = C.N, Nf = F.N;
-  const bool live = x + y + z <= Nc;
-  // 3D: the fine neighbours' indices as offsets from that of 2P
+  constexpr int full = full_mask(DIM);
+  const MacroDev& F = a.mdf[macro];
+  const int Nf = F.N, own = F.own_mask & ~F.dir_mask;
   int off[15];
-  int64_t fc = 0;
-  if constexpr (DIM == 3) {
-    nbr_offsets3(Nf, live ? 2 * y : 0, 2 * z, off);
-    fc = live ? lidx<3>(Nf, 2 * x, 2 * y, 2 * z) : 0;
-  }
-  // branch-free: every lane takes all offsets; fine points outside the macro
-  // read the centre instead and contribute nothing
+  if constexpr (DIM == 3) nbr_offsets3(Nf, 2 * y, 2 * z, off);
+  const T* p = a.src + F.base + lidx<DIM>(Nf, 2 * x, 2 * y, 2 * z);
   T acc = T(0);
 #pragma unroll
   for (int s = 0; s < ST.n; ++s) {
-    const int fx = 2 * x + ST.off[s][0], fy = 2 * y + ST.off[s][1], fz = DIM == 3 ? 2 * z + ST.off[s][2] : 0;
-    const bool in = live && fx >= 0 && fy >= 0 && fz >= 0 && fx + fy + fz <= Nf;
+    const int dx = ST.off[s][0], dy = ST.off[s][1], dz = ST.off[s][2];
+    const int fx = 2 * x + dx, fy = 2 * y + dy, fz = 2 * z + dz;
+    const bool in = fx >= 0 && fy >= 0 && fz >= 0 && fx + fy + fz <= Nf;
     const int mask = support_mask(DIM, Nf, fx, fy, fz);
-    const bool owned = mask == full || ((F.own_mask >> mask) & 1);
-    const bool dir = mask != full && ((F.dir_mask >> mask) & 1);
-    const bool use = in && owned && !dir;
-    const int64_t i = in ? (DIM == 3 ? fc + off[s] : lidx<DIM>(Nf, fx, fy, fz)) : 0;
-    const T r = a.src[F.base + i];
-    const T w = s == ST.centre ? T(1) : T(0.5);
-    acc += use ? w * r : T(0);
+    const bool use = in && (mask == full || ((own >> mask) & 1));
+    const int l = Nf + 1 - 2 * y;  // 2D: the row's length
+    const int o = DIM == 3 ? off[s] : dx + (dy > 0 ? l : dy < 0 ? -l - 1 : 0);
+    const T r = p[in ? o : 0];
+    acc += use ? (s == ST.centre ? T(1) : T(0.5)) * r : T(0);
   }
-  if (live) a.dst[C.base + lidx<DIM>(Nc, x, y, z)] = acc;
+  return acc;
 }
 // (x, y) of slice-local index r in a 3D slice of side S <= 2048, r <
 // (S+1)(S+2)/2: y is the smaller root of y^2 - (2S + 3) y + 2r = 0 (row y
@@ -288,11 +279,8 @@ __device__ __forceinline__ void slice_xy3(int S, int r, int& x, int& y) {
   x = r - row_start(S, yy);
 }
 
-// This lane's point of slice segment sg ({macro, first slice-local index, 0,
-// z}) in a macro of side N: the slice of side S = N - z holds (S+1)(S+2)/2
-// points, row y starting at y (2S + 3 - y) / 2, so y is the smaller root of
-// y^2 - (2S + 3) y + 2r = 0, rounded down and corrected by one step either
-// way.  Lanes past the slice's end get x = S + 1 (no point: x + y + z > N).
+// The same in either dimension: slice index r < (S + 1)(S + 2) / 2 of a slice of
+// side S (2D: the macro).
 template <int DIM>
 __device__ __forceinline__ void slice_xy(int S, int r, int& x, int& y) {
   if (DIM == 3) {
@@ -308,111 +296,90 @@ __device__ __forceinline__ void slice_xy(int S, int r, int& x, int& y) {
   y = yy;
   x = r - row_start(S, yy);
 }
-template <int DIM>
-__device__ __forceinline__ void slice_point(const Tile& sg, int N, int& x, int& y, int& z) {
-  z = DIM == 3 ? sg.z : 0;
-  const int S = N - z;
-  const int r = sg.x0 + (int)(threadIdx.x & (kWave - 1));
-  if (r >= (S + 1) * (S + 2) / 2) {
-    x = S + 1;
-    y = 0;
-    return;
-  }
-  slice_xy<DIM>(S, r, x, y);
-}
+// Restriction by segments of 64 coarse points: restrict_partial's sum, in its
+// order, for a lane's point P.  The fine points come in neighbouring pairs (8
+// or 16 bytes) of the rows around 2P: x and x + 1 where dx is 0 or 1, x - 1 and
+// x where it is -1 or 0.  Whether 2P + d lies in the macro, and its support,
+// follow from P's position: 2x + dx = 0 only for x = 0 and dx = 0, and N_f -
+// |2P + d| = 2 (N_c - |P|) - |d| vanishes only on P's far face with |d| = 0.
+// Rows outside the macro read the point itself.  load() issues every load,
+// store() sums and writes: 0 at Dirichlet points, nothing at shared ones.
+template <typename T, int DIM>
+struct RestrictCell {
+  typedef T Pair __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+  bool live, x0, y0, z0, far, first;
+  int own, mask, out;  // out: the coarse point's masks (dir, shared) as bits 0, 1
+  T* at;
+  Pair A, B, Cc, D, E, Ff, G;
+  T xp;
 
-// Restriction over one 3D slice segment of coarse points: the same sum as
-// restrict_point, in the same order, with cheaper index work.  Slice bases
-// come from the per-level tables; the storage index of fine point 2P + d is
-// formed from that of 2P (slice 2z of side S = Nf - 2z, row 2y of
-// l = S + 1 - 2y points): +-1 along the row, l after / l + 1 before it for
-// rows 2y +- 1, T(S) - 2y after and T(S + 1) - 2y before it for slices
-// 2z +- 1 (T(s) = (s + 1)(s + 2) / 2 points in a slice of side s), all as
-// 32-bit offsets from the first point of slice 2z - 1.  Whether 2P + d lies
-// in the macro, and its support mask, follow from P's position:
-// 2x + dx = 0 only for x = 0 and dx = 0, and Nf - |2P + d| =
-// 2 (Nc - |P|) - |d| vanishes only on P's far face with |d| = 0.
-// The lane's coarse point is slice-local index r of slice sg.z (in_run:
-// inside its run of points).
-template <typename T>
-__device__ __forceinline__ T restrict_seg3(const TransferArgs<T>& a, const Tile sg, int r, bool in_run, int64_t& di,
-                                           bool& wr) {
-  constexpr StencilTable ST = stencil_table(3);
-  constexpr int full = 15;
-  const MacroC C = load_macro(a.mdc, sg.macro);
-  const MacroC F = load_macro(a.mdf, sg.macro);
-  const int Nc = C.N, Nf = F.N;
-  const int z = sg.z;
-  int x = Nc - z + 1, y = 0;  // lanes past the run or the slice: no point
-  if (in_run && r < (Nc - z + 1) * (Nc - z + 2) / 2) slice_xy3(Nc - z, r, x, y);
-  const bool live = x + y + z <= Nc;
-  const bool x0 = x == 0, y0 = y == 0, z0 = z == 0, far = x + y + z == Nc;
-  const int zf = 2 * z, S = Nf - zf, yf = live ? 2 * y : 0, xf = live ? 2 * x : 0;
-  const int za = zf > 0 ? zf - 1 : 0;
-  const T* __restrict__ Fa = a.src + F.base + as_const(a.sbf)[za];  // anchor: slice 2z - 1 (slice 0 at z = 0)
-  const int tb = as_const(a.sbf)[zf] - as_const(a.sbf)[za];         // points of slice 2z - 1 (0 at z = 0)
-  const int c = tb + row_start(S, yf) + xf;
-  const int l = S + 1 - yf;
-  const int up = c + (S + 1) * (S + 2) / 2 - yf;
-  const int dn = c - tb + yf;
-  const int rel[15] = {dn,     dn + 1,     dn + l + 1, dn + l, c - l - 1, c - l, c - 1, c,
-                       c + 1,  c + l - 1,  c + l,      up - l, up - l + 1, up - 1, up};
-  T acc = T(0);
+  __device__ __forceinline__ void load(const TransferArgs<T>& a, const Tile& sg) {
+    const MacroC C = load_macro(a.mdc, sg.macro);
+    const MacroC F = load_macro(a.mdf, sg.macro);
+    const int z = DIM == 3 ? sg.z : 0, S = C.N - z, P = (S + 1) * (S + 2) / 2;
+    int r = sg.x0 + (int)(threadIdx.x & (kWave - 1)), x, y;
+    live = r < P;
+    r = min(r, P - 1);
+    slice_xy<DIM>(S, r, x, y);
+    x0 = x == 0, y0 = y == 0, z0 = DIM == 2 || z == 0, far = x + y == S;
+    own = F.own_mask & ~F.dir_mask;
+    mask = (far ? 0 : 1) | (x0 ? 0 : 2) | (y0 ? 0 : 4) | (DIM == 2 || z0 ? 0 : 8);
+    const bool full = mask == full_mask(DIM);
+    out = full ? 0 : ((C.dir_mask >> mask) & 1) | (((C.shared_mask >> mask) & 1) << 1);
+    at = a.dst + C.base + (DIM == 3 ? as_const(a.sbc)[z] : 0) + r;
+    // offsets from the first point of fine slice 2z - 1 (of slice 0 at z = 0)
+    const int zf = 2 * z, za = DIM == 3 && zf > 0 ? zf - 1 : 0, Sf = F.N - zf, yf = 2 * y;
+    const T* f = a.src + F.base + (DIM == 3 ? as_const(a.sbf)[za] : 0);
+    const int tb = DIM == 3 ? as_const(a.sbf)[zf] - as_const(a.sbf)[za] : 0;
+    const int c = tb + row_start(Sf, yf) + 2 * x, l = Sf + 1 - yf;
+    auto pair = [&](bool in, int i) { return *(const Pair*)(f + (unsigned)(in ? i : max(c - 1, 0))); };
+    first = x0 && !far;  // D starts at 2P
+    D = *(const Pair*)(f + (unsigned)(first ? c : c - 1));
+    xp = f[(unsigned)(far ? c : c + 1)];
+    Cc = pair(!y0, c - l - 1);
+    E = pair(!(far && x0), c + l - 1);
+    if constexpr (DIM == 3) {
+      const int dn = c - tb + yf, up = c + (Sf + 1) * (Sf + 2) / 2 - yf;
+      A = pair(!z0, dn);
+      B = pair(!z0, dn + l);
+      Ff = pair(!y0, up - l);
+      G = pair(!(far && x0), up - 1);
+    }
+  }
+
+  __device__ __forceinline__ void store() const {
+    constexpr StencilTable ST = stencil_table(DIM);
+    T v[ST.n];
+    const T xc = first ? D.x : D.y;
+    if constexpr (DIM == 3) {
+      const T t[15] = {A.x, A.y, B.y, B.x, Cc.x, Cc.y, D.x, xc, xp, E.x, E.y, Ff.x, Ff.y, G.x, G.y};
 #pragma unroll
-  for (int s = 0; s < ST.n; ++s) {
-    const int dx = ST.off[s][0], dy = ST.off[s][1], dz = ST.off[s][2], sd = dx + dy + dz;
-    const bool in = live && (dx >= 0 || !x0) && (dy >= 0 || !y0) && (dz >= 0 || !z0) && (sd <= 0 || !far);
-    const int mask = ((sd == 0 && far) ? 0 : 1) | ((dx == 0 && x0) ? 0 : 2) | ((dy == 0 && y0) ? 0 : 4) |
-                     ((dz == 0 && z0) ? 0 : 8);
-    const bool owned = mask == full || ((F.own_mask >> mask) & 1);
-    const bool dir = mask != full && ((F.dir_mask >> mask) & 1);
-    const bool use = in && owned && !dir;
-    // points outside the macro read the anchor (value unused)
-    const T r = Fa[in ? (unsigned)rel[s] : 0u];
-    const T w = s == ST.centre ? T(1) : T(0.5);
-    acc += use ? w * r : T(0);
+      for (int s = 0; s < ST.n; ++s) v[s] = t[s];
+    } else {
+      const T t[7] = {Cc.x, Cc.y, D.x, xc, xp, E.x, E.y};
+#pragma unroll
+      for (int s = 0; s < ST.n; ++s) v[s] = t[s];
+    }
+    T acc = T(0);
+#pragma unroll
+    for (int s = 0; s < ST.n; ++s) {
+      const int dx = ST.off[s][0], dy = ST.off[s][1], dz = ST.off[s][2], sd = dx + dy + dz;
+      const bool in = (dx >= 0 || !x0) && (dy >= 0 || !y0) && (dz >= 0 || !z0) && (sd <= 0 || !far);
+      const int m = ((sd == 0 && far) ? 0 : 1) | ((dx == 0 && x0) ? 0 : 2) | ((dy == 0 && y0) ? 0 : 4) |
+                    (DIM == 2 || (dz == 0 && z0) ? 0 : 8);
+      const bool use = in && (m == full_mask(DIM) || ((own >> m) & 1));
+      acc += use ? (s == ST.centre ? T(1) : T(0.5)) * v[s] : T(0);
+    }
+    if (live && (out & 3) != 2) *at = out & 1 ? T(0) : acc;
   }
-  di = C.base + as_const(a.sbc)[z] + r;
-  wr = live;
-  return acc;
-}
+};
 
-// 2D: one 64-point segment of coarse points.
-template <typename T, int DIM>
-__device__ __forceinline__ void restrict_segment(const TransferArgs<T>& a, const Tile sg) {
-  int x, y, z;
-  slice_point<DIM>(sg, load_macro(a.mdc, sg.macro).N, x, y, z);
-  restrict_point<T, DIM>(a, sg.macro, x, y, z);
-}
-
-// x_f += P e_c: even fine points take the coarse value, the others the mean
-// of the two coarse endpoints of the coarse micro-edge they bisect; the
-// edge direction follows from the coordinate parities.  Dirichlet points are
-// left unchanged.
-template <typename T, int DIM>
-__device__ __forceinline__ void prolong_point(const TransferArgs<T>& a, int macro, int x, int y, int z) {
-  constexpr int full = DIM == 2 ? 7 : 15;
-  const MacroC C = load_macro(a.mdc, macro);
-  const MacroC F = load_macro(a.mdf, macro);
-  const int Nc = C.N, Nf = F.N;
-  const bool live = x + y + z <= Nf;
-  const int mask = support_mask(DIM, Nf, x, y, z);
-  const bool dir = mask != full && ((F.dir_mask >> mask) & 1);
-  // direction s of the coarse micro-edge the point bisects: the parity
-  // pattern, with the middle odd coordinate negated for two or three odd
-  // coordinates ((1,1,0) -> e1 - e2, (1,0,1) -> e1 - e3, (0,1,1) -> e2 - e3,
-  // (1,1,1) -> e1 - e2 + e3); even points have s = 0 and take the coarse
-  // value itself (the two reads coincide)
-  // (lanes past the macro's far face read the coarse point (0, 0, 0))
-  const int xl = live ? x : 0, yl = live ? y : 0, zl = live ? z : 0;
-  const int px = xl & 1, py = yl & 1, pz = zl & 1;
-  const int sx = px;
-  const int sy = (px && py) ? -1 : py;
-  const int sz = (pz && (px ^ py)) ? -1 : pz;
-  const T u = a.src[C.base + lidx<DIM>(Nc, (xl - sx) >> 1, (yl - sy) >> 1, (zl - sz) >> 1)];
-  const T v = a.src[C.base + lidx<DIM>(Nc, (xl + sx) >> 1, (yl + sy) >> 1, (zl + sz) >> 1)];
-  if (live && !dir) a.dst[F.base + lidx<DIM>(Nf, x, y, z)] += T(0.5) * (u + v);
-}
+// x_f += P e_c: even fine points take the coarse value, the others the mean of
+// the two coarse endpoints of the coarse micro-edge they bisect.  Its direction
+// is the point's parities, with the middle odd coordinate negated for two or
+// three odd ones ((1,1,0): e1 - e2, (1,0,1): e1 - e3, (0,1,1): e2 - e3, (1,1,1): e1
+// - e2 + e3).  Dirichlet points are left unchanged.
+//
 // Prolongation by cells: a lane takes coarse point P = (X, Y, Z) and the fine
 // points 2P + p, p in {0, 1}^DIM, that lie in the macro, two neighbours along x
 // at a time (8 or 16 bytes, consecutive lanes consecutive pairs).  Their
@@ -523,59 +490,20 @@ __device__ __forceinline__ T centre_inv(const MacroDev& M, int mask, int full, i
   else return mask == full ? M.inv_diagf : 1.0f / M.wmf[mask][centre];
 }
 
-template <typename T, int DIM>
-__device__ __forceinline__ void jacobi0_point(const Jacobi0Args<T>& a, int macro, int x, int y, int z) {
-  constexpr int full = DIM == 2 ? 7 : 15;
-  constexpr int centre = stencil_table(DIM).centre;
-  const MacroDev& M = a.md[macro];
-  const MacroC C = load_macro(a.md, macro);
-  const int N = C.N;
-  if (x + y + z > N) return;
-  const int mask = support_mask(DIM, N, x, y, z);
-  const bool dir = mask != full && ((C.dir_mask >> mask) & 1);
-  const bool shared = mask != full && !dir && ((M.shared_mask >> mask) & 1);
-  if (shared) return;  // finished by the group part
-  const int64_t i = C.base + lidx<DIM>(N, x, y, z);
-  a.Y[i] = dir ? T(0) : fma(a.omega * centre_inv<T>(M, mask, full, centre), a.B[i], T(0));
-}
-
 template <int DIM>
 __device__ __forceinline__ int64_t copy_index(const MacroDev& M, const Copy& c) {
   return M.base + (DIM == 2 ? idx2(M.N, c.x, c.y) : idx3(M.N, c.x, c.y, c.z));
 }
 
 // One DoF shared by several macros and not Dirichlet (exchange list): its
-// copies in Y hold partial rows; sum them in fixed macro order, finish the
-// row and write it to every copy.  Returns the row value; i0 = index of the
-// first copy.
-template <typename T, int DIM, int MODE>
-__device__ __forceinline__ T exchange_row(const GroupArgs<T>& a, int g, int64_t& i0) {
+// copies in Y hold partial rows; sum them in fixed macro order and write the
+// row to every copy.
+template <typename T>
+__device__ __forceinline__ void exchange_row(const GroupArgs<T>& a, int g) {
   const int c0 = a.gptr[g], c1 = a.gptr[g + 1];
-  i0 = a.cidx[c0];
-  T out;
-  if (MODE == kNormB) {
-    out = a.B[i0];
-  } else {
-    T acc = T(0);
-    for (int c = c0; c < c1; ++c) acc += a.Y[a.cidx[c]];
-    if (MODE == kApply || MODE == kApplyDot) out = acc;
-    else if (MODE == kJacobi) out = fma(a.omega * Prec<T>::ginv(a.ginv, a.ginvf, g), a.B[i0] - acc, a.X[i0]);
-    else out = a.B[i0] - acc;
-    for (int c = c0; c < c1; ++c) a.Y[a.cidx[c]] = out;
-  }
-  return out;
-}
-
-// One macro-boundary DoF (all-groups list): y = the sum of x over its copies
-// (0 at Dirichlet DoFs), written to every copy (in place allowed).
-template <typename T, int DIM>
-__device__ __forceinline__ void iface_sum_row(const GroupArgs<T>& a, int g) {
-  const int c0 = a.gptr[g], c1 = a.gptr[g + 1];
-  const bool dir = a.gflag[g] & 1;
-  T out = T(0);
-  if (!dir)
-    for (int c = c0; c < c1; ++c) out += a.X[a.cidx[c]];
-  for (int c = c0; c < c1; ++c) a.Y[a.cidx[c]] = out;
+  T acc = T(0);
+  for (int c = c0; c < c1; ++c) acc += a.Y[a.cidx[c]];
+  for (int c = c0; c < c1; ++c) a.Y[a.cidx[c]] = acc;
 }
 
 // Coarse direct solve, unknown i, one wavefront (lane = its lane):

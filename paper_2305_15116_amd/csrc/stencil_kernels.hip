@@ -390,27 +390,20 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
 template <typename T>
 __global__ __launch_bounds__(kIfaceWG) void exchange_kernel(const GroupArgs<T> a) {
   const int g = blockIdx.x * kIfaceWG + threadIdx.x;
-  int64_t i0;
-  if (g < a.ngroups) exchange_row<T, 2, kApply>(a, g, i0);
+  if (g < a.ngroups) exchange_row(a, g);
 }
 
-// Every macro-boundary DoF: kExchangeSum (y = sum of x over the copies,
-// Dirichlet -> 0, in place allowed) or kDirichletSet (y = b at Dirichlet
-// DoFs; b == NULL sets them to 0).
-template <typename T, int DIM, int MODE>
+// y = b at the Dirichlet DoFs (b == NULL: 0).
+template <typename T>
 __global__ __launch_bounds__(kIfaceWG) void iface_kernel(const Launch<GroupArgs<T>> L) {
   GroupArgs<T> a;
   const int blk = resolve(L, (int)blockIdx.x, a);
   const int g = blk * kIfaceWG + threadIdx.x;
   if (g >= a.ngroups) return;
-  if (MODE == kDirichletSet) {
-    const int c0 = a.gptr[g], c1 = a.gptr[g + 1];
-    if (!(a.gflag[g] & 1)) return;
-    const T v = a.B ? a.B[a.cidx[c0]] : T(0);
-    for (int c = c0; c < c1; ++c) a.Y[a.cidx[c]] = v;
-    return;
-  }
-  iface_sum_row<T, DIM>(a, g);
+  const int c0 = a.gptr[g], c1 = a.gptr[g + 1];
+  if (!(a.gflag[g] & 1)) return;
+  const T v = a.B ? a.B[a.cidx[c0]] : T(0);
+  for (int c = c0; c < c1; ++c) a.Y[a.cidx[c]] = v;
 }
 
 // result = (sum of part[0, np), max of part[np, 2 np)) in a fixed order; one
@@ -496,23 +489,16 @@ void run_stencil(int mode, int rows, const Launch<StencilArgs<T>>& l, hipStream_
   }
 }
 
-template <typename T, int DIM, int MODE>
-void run_iface(const Level& L, const void* x, void* y, const void* b, hipStream_t s) {
-  const int nblk = iface_blocks(L);
-  if (nblk == 0) return;
-  hipLaunchKernelGGL((iface_kernel<T, DIM, MODE>), dim3(nblk), dim3(kIfaceWG), 0, s,
-                     single(iface_args<T>(L, x, y, b), nblk));
+template <typename T>
+void run_iface(const Launch<GroupArgs<T>>& l, hipStream_t s) {
+  if (l.nwg > 0) hipLaunchKernelGGL((iface_kernel<T>), dim3(l.nwg), dim3(kIfaceWG), 0, s, l);
 }
 
 template <typename T>
 int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const void* b, double omega, double* part,
              hipStream_t s) {
-  if (mode == kExchangeSum) {
-    if (dim == 2) run_iface<T, 2, kExchangeSum>(L, x, y, b, s);
-    else run_iface<T, 3, kExchangeSum>(L, x, y, b, s);
-  } else if (mode == kDirichletSet) {
-    if (dim == 2) run_iface<T, 2, kDirichletSet>(L, x, y, b, s);
-    else run_iface<T, 3, kDirichletSet>(L, x, y, b, s);
+  if (mode == kDirichletSet) {
+    run_iface<T>(single(iface_args<T>(L, y, b), iface_blocks(L)), s);
   } else {
     const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
     if (dim == 3) return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
@@ -528,21 +514,10 @@ int launch(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x,
 }
 
 // ---------------------------------------------------------------- batched
-template <typename T, int DIM>
-void batch_iface(const BatchOp& op, const char* table, hipStream_t s) {
-  if (op.mode == kExchangeSum)
-    hipLaunchKernelGGL((iface_kernel<T, DIM, kExchangeSum>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
-                       batched<GroupArgs<T>>(op, table));
-  else
-    hipLaunchKernelGGL((iface_kernel<T, DIM, kDirichletSet>), dim3(op.nwg), dim3(kIfaceWG), 0, s,
-                       batched<GroupArgs<T>>(op, table));
-}
-
 template <typename T>
 int batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
   if (op.kind == kOpIface) {
-    if (op.dim == 2) batch_iface<T, 2>(op, table, s);
-    else batch_iface<T, 3>(op, table, s);
+    run_iface<T>(batched<GroupArgs<T>>(op, table), s);
   } else if (op.dim == 3) {
     return launch_stencil3(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
   } else {

@@ -308,7 +308,7 @@ struct TailState {
       if (!live(k)) continue;
       int x, y, z;
       lattice(k, x, y, z);
-      // direction of the coarse micro-edge the point bisects (see prolong_point)
+      // direction of the coarse micro-edge the point bisects (rows.hpp)
       const int px = x & 1, py = y & 1, pz = z & 1;
       const int sx = px, sy = (px && py) ? -1 : py, sz = (pz && (px ^ py)) ? -1 : pz;
       const int c = (mm[k] >> 4) * Pc;

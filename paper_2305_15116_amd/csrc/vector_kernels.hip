@@ -11,6 +11,7 @@
 
 #include "launch.hpp"
 #include "rows.hpp"
+#include "walk3d.hpp"
 
 namespace mf {
 
@@ -74,42 +75,94 @@ __global__ __launch_bounds__(kWG) void fill_random_kernel(const Tile* __restrict
 
 
 
-// Each wave walks several segments of 64 coarse points.  In 3D all loads of a
-// step (kTransferU strided segments) are issued before any store.  2D walks
-// single segments.
-constexpr int kTransferU = 4;
+// b_c = P^T r_f.  Workgroups 0 .. a.nb - 1 take the coarse DoFs that macros
+// share, whose copies' parts they sum in list order and write to every copy:
+// an edge tile (a lane per copy; kEdgeBigTile: one DoF of more than 64) or a
+// face tile (waves 2 c and 2 c + 1: the two copies of 64 points).  The others
+// take every other coarse point, 64 per wave and step (two segments at a time
+// were slower: 37.8 us against 35.2 below, four 54).
+//
+// Bound: memory (r_f read).  Against 15 single gathers per point and a second
+// launch over the shared DoFs, level 8 of the cube: FP64 43.3 -> 35.2 us, FP32 26.0
+// -> 20.3; level 5 7.2 -> 4.8; one triangle at level 14 294 -> 267, 199 -> 155; seven
+// at level 8 5.9 -> 3.6.
 
 template <typename T, int DIM>
-__global__ __launch_bounds__(kWG) void restrict_kernel(const Launch<TransferArgs<T>> L) {
-  TransferArgs<T> a;
-  const int blk = resolve(L, (int)blockIdx.x, a);
-  const int stride = a.nblk * kWavesPerWG;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if constexpr (DIM == 3) {
-    const int lane = threadIdx.x & (kWave - 1);
-    for (int si = blk * kWavesPerWG + w; si < a.nseg; si += kTransferU * stride) {
-      T acc[kTransferU];
-      int64_t di[kTransferU];
-      bool wr[kTransferU];
-#pragma unroll
-      for (int k = 0; k < kTransferU; ++k) {
-        const int sk = si + k * stride;
-        const Tile sg = sk < a.nseg ? load_seg(a.segs, sk) : Tile{-1, 0, 0, 0};
-        wr[k] = false;
-        if (sg.macro >= 0) acc[k] = restrict_seg3<T>(a, sg, sg.x0 + lane, true, di[k], wr[k]);
+__device__ __forceinline__ void restrict_edges(const TransferArgs<T>& a, const Tile& t, int w) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const EdgeCopy* L = a.edges + t.x0;
+  if (t.macro == kEdgeBigTile) {
+    if (w != 0 || L[0].dirichlet) return;
+    T acc = T(0);
+    for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+      const int n = min(kWave, t.y0 - c0);
+      T p = T(0);
+      if (lane < n) {
+        const EdgeCopy& e = L[c0 + lane];
+        p = restrict_partial<T, DIM>(a, e.macro, e.x, e.y, e.z);
       }
-#pragma unroll
-      for (int k = 0; k < kTransferU; ++k)
-        if (wr[k]) a.dst[di[k]] = acc[k];
+      for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
     }
-  } else {
-    for (int si = blk * kWavesPerWG + w; si < a.nseg; si += stride) {
-      const Tile sg = load_seg(a.segs, si);
-      if (sg.macro >= 0) restrict_segment<T, DIM>(a, sg);
-    }
+    for (int c = lane; c < t.y0; c += kWave) a.dst[L[c].idx] = acc;
+    return;
+  }
+  // wave w: the tile's w-th step
+  const int n = w == 0 ? t.y0 : (w == 1 ? t.z : 0);
+  if (n == 0) return;
+  if (w == 1) L += t.y0;
+  const bool live = lane < n;
+  const EdgeCopy e = L[live ? lane : 0];
+  const bool sum = live && !e.dirichlet && e.copies > 1;  // (the others have been written with their macro)
+  const T p = sum ? restrict_partial<T, DIM>(a, e.macro, e.x, e.y, e.z) : T(0);
+  T acc = T(0);
+  const int nc = sum ? e.copies : 0;
+  for (int i = 0; __builtin_amdgcn_ballot_w64(i < nc); ++i) {
+    const T v = __shfl(p, (e.head + i) & (kWave - 1), kWave);
+    acc += i < nc ? v : T(0);
+  }
+  if (sum) a.dst[e.idx] = acc;
+}
+
+template <typename T>
+__device__ __forceinline__ void restrict_faces(const TransferArgs<T>& a, const Tile& t, int w, T* part) {
+  const FaceDev& F = a.faces[t.z];
+  if (F.dirichlet || F.copies != 2) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  const FaceCopy& C = F.cp[w & 1];
+  for (int i0 = 0; i0 < t.y0; i0 += kWG / 2) {
+    const int i = i0 + (w >> 1) * kWave + lane;
+    int ia, ib, x, y, z;
+    slice_xy3(F.N - 3, t.x0 + min(i, t.y0 - 1), ia, ib);
+    const int64_t p = face_index(a.mdc, C, F.N, ia + 1, ib + 1, x, y, z);
+    part[threadIdx.x] = restrict_partial<T, 3>(a, C.macro, x, y, z);
+    __syncthreads();
+    const T acc = part[(w & ~1) * kWave + lane] + part[(w | 1) * kWave + lane];
+    __syncthreads();
+    if (i < t.y0) a.dst[p] = acc;
   }
 }
 
+template <typename T, int DIM>
+__global__ __launch_bounds__(kWG) void restrict_kernel(const Launch<TransferArgs<T>> L) {
+  __shared__ T part[kWG];
+  TransferArgs<T> a;
+  const int blk = resolve(L, (int)blockIdx.x, a);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (blk < a.nb) {
+    const Tile t = load_seg(a.btiles, blk);
+    if (DIM == 3 && t.macro == kFaceTile) restrict_faces<T>(a, t, w, part);
+    else if (t.macro != -1) restrict_edges<T, DIM>(a, t, w);
+    return;
+  }
+  const int stride = a.nblk * kWavesPerWG;
+  for (int si = (blk - a.nb) * kWavesPerWG + w; si < a.nseg; si += stride) {
+    const Tile sg = load_seg(a.segs, si);
+    if (sg.macro < 0) continue;
+    RestrictCell<T, DIM> q;
+    q.load(a, sg);
+    q.store();
+  }
+}
 
 // x_f += P e_c, a wave per kProlongU segments of 64 coarse points at a time.
 //
@@ -168,8 +221,7 @@ __global__ __launch_bounds__(kWG) void jacobi0_stream_kernel(const Launch<Jacobi
   }
 }
 
-// Pass 2: the macro-boundary DoFs, as jacobi0_point and jacobi0_group finish
-// them (0 at Dirichlet DoFs, the partial stencil's centre at unshared ones,
+// Pass 2: the macro-boundary DoFs (0 at Dirichlet DoFs, the partial stencil's centre at unshared ones,
 // the assembled diagonal at shared ones).
 template <typename T, int DIM>
 __global__ __launch_bounds__(kWG) void jacobi0_fix_kernel(const Launch<Jacobi0Args<T>> L) {
@@ -380,13 +432,11 @@ int launch_fill_random(const mf_mesh* m, const Level& L, int dtype, uint64_t see
 
 int launch_restrict(const mf_mesh* m, const Level& F, const Level& C, int dtype, const void* rf, void* bc,
                     hipStream_t s) {
-  const int nwg = transfer_blocks((int)C.psegs.size());
+  const int nwg = restrict_blocks(C);
   if (nwg == 0) return MF_OK;
   if (dtype == MF_F64) run_transfer<double>(true, m->dim, single(restrict_args<double>(F, C, rf, bc), nwg), s);
   else run_transfer<float>(true, m->dim, single(restrict_args<float>(F, C, rf, bc), nwg), s);
-  int rc = check_launch();
-  if (rc) return rc;
-  return launch_iface(m, C, dtype, kExchangeSum, bc, bc, nullptr, s);
+  return check_launch();
 }
 
 int launch_prolong_add(const mf_mesh* m, const Level& F, const Level& C, int dtype, const void* ec, void* xf,
