@@ -114,4 +114,37 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
   }
 }
 
+// y = the sum over its copies of partial(copy) at the 2D shared DoFs of tile t,
+// laid out as for edge_rows.
+template <typename T, class Partial>
+__device__ __forceinline__ void shared_rows(const EdgeCopy* edges, const Tile& t, T* Y, Partial partial) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const EdgeCopy* L = edges + t.x0;
+  if (t.macro == kEdgeBigTile) {
+    T acc = T(0);
+    for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+      const int n = min(kWave, t.y0 - c0);
+      const T p = lane < n ? partial(L[c0 + lane]) : T(0);
+      for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
+    }
+    for (int c = lane; c < t.y0; c += kWave) Y[L[c].idx] = acc;
+    return;
+  }
+  for (int step = 0; step < 2; ++step) {
+    const int n = step == 0 ? t.y0 : t.z;
+    if (n == 0) break;
+    const bool live = lane < n;
+    const EdgeCopy e = L[live ? lane : 0];
+    const T p = live ? partial(e) : T(0);
+    T acc = T(0);
+    const int nc = live ? e.copies : 0;
+    for (int i = 0; __builtin_amdgcn_ballot_w64(i < nc); ++i) {
+      const T v = __shfl(p, (e.head + i) & (kWave - 1), kWave);
+      acc += i < nc ? v : T(0);
+    }
+    if (live) Y[e.idx] = acc;
+    L += t.y0;
+  }
+}
+
 }  // namespace mf
