@@ -222,8 +222,8 @@ def solve_bytes(P, m, L, mode, iters, lc=2):
     """Algorithmic HBM bytes of one vcycle_solve with V(2,2) cycles: every
     vector a kernel of the solve must read or write, once (interface and
     coarse-solve traffic excluded).  Per V-cycle level l above the coarse
-    level (storage S_l, precision e bytes: 8 FP64, 4 FP32 cycles): first
-    sweep from zero 2e, second sweep 3e, residual 3e, restriction e + e S_{l-1}/S_l,
+    level (storage S_l, precision e bytes: 8 FP64, 4 FP32 cycles): two sweeps
+    from zero 2e, residual 3e, restriction e + e S_{l-1}/S_l,
     prolongation e S_{l-1}/S_l + 2e, two post-sweeps 6e.  Outer step per fine
     DoF: refinement x += e and r = b - A x (FP64 48, mixed 56 with the
     scaled cast); CG r.z, direction, A p with p.Ap, x/r update (FP64 104,
@@ -239,7 +239,7 @@ def solve_bytes(P, m, L, mode, iters, lc=2):
     iteration (one cycle and v.z)."""
     S = [P.mesh_num_dofs(m, l)[0] for l in range(L + 1)]
     e = 4 if mode & 1 else 8
-    cycle = sum((17 * e + 2 * e * S[l - 1] / S[l]) * S[l] for l in range(lc + 1, L + 1))
+    cycle = sum((14 * e + 2 * e * S[l - 1] / S[l]) * S[l] for l in range(lc + 1, L + 1))
     outer = {0: 48, 1: 56, 2: 104, 3: 100, 4: 120, 5: 136}[mode] * S[L]
     setup = (32 + (24 if mode & 6 else 0) + (12 if mode == 3 else 0)) * S[L]
     if mode & 4:

@@ -1,11 +1,10 @@
 // extern "C" entry points (include/mf_stencil.h) and the multigrid solver.
 //
 // apply_stencil is the paper's "apply" (an operator applied to a function,
-// Performance Modeling section): the interior kernel covers every interior
-// row of every macro with its constant stencil, then the interface kernel
-// completes the rows of macro-boundary DoFs, which the paper leaves to
-// interface primitives rather than to the macro kernels (same section,
-// experiment description).  smooth and residual reuse the same kernels in
+// Performance Modeling section): one launch covers every interior row of every
+// macro with its constant stencil and the rows of macro-boundary DoFs, which
+// the paper leaves to interface primitives rather than to the macro kernels
+// (same section, experiment description).  smooth and residual reuse the same kernels in
 // their fused Jacobi and residual modes; vcycle_solve runs geometric
 // multigrid over the refinement levels (Intro: the levels are a natural
 // multigrid hierarchy) inside iterative refinement, conjugate gradients or
@@ -102,7 +101,7 @@ int jacobi_sweeps(const mf_mesh* m, const Level& L, int dtype, double omega, int
 }
 
 // Jacobi sweeps from a zero iterate: the first sweep is y = omega D^-1 b (one
-// pass, no exchange), bitwise what a full sweep gives from x = 0; the rest as
+// stream and the boundary), what a full sweep gives from x = 0; the rest as
 // jacobi_sweeps.  The first two are one launch (kJacobi2), which reads b alone.
 // x need not be initialised.
 int jacobi_sweeps_from_zero(const mf_mesh* m, const Level& L, int dtype, double omega, int sweeps, const void* b,

@@ -62,8 +62,8 @@ __device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k,
 // (kEdgeBigTile).  The copies' partial rows are summed in list order by every
 // lane of the DoF.
 //
-// Bound: latency.  In 2D this replaces an exchange launch after every pass, of
-// partial rows that the walk wrote: seven triangles at level 8, FP64 apply / Jacobi
+// Bound: latency.  In 2D this replaces a launch after every pass that summed
+// the partial rows that the walk wrote: seven triangles at level 8, FP64 apply / Jacobi
 // / residual 8.7 / 9.6 / 9.5 -> 5.1 / 5.9 / 5.6 us, FP32 10.6 / 11.8 / 11.9 -> 7.0 / 7.6 / 7.7;
 // two at level 12 FP32 39.5 / 49.5 / 51.9 -> 33.3 / 43.2 / 45.5.
 template <typename T, int DIM, int MODE>

@@ -38,8 +38,7 @@ int launch_stencil3(int mode, int R, const Launch<StencilArgs<double>>& l, hipSt
 int launch_stencil3(int mode, int R, const Launch<StencilArgs<float>>& l, hipStream_t s);
 
 // One launch of the whole operator: interior rows of every macro (wave
-// tiles) and macro-boundary rows (interface groups).  mode: kApply, kJacobi,
-// kResidual, kNormB.  part (nullable; kResidual / kNormB) receives sums of
+// tiles) and macro-boundary rows (face and edge tiles).  mode: any Mode.  part (nullable; kResidual / kNormB) receives sums of
 // squares at [0, np) and maxima at [np, 2 np), np = stencil_partials(L)
 // (at most L.n_partials(), which sizes the buffers).
 int64_t stencil_partials(const Level& L, int dtype);
@@ -50,17 +49,17 @@ int launch_stencil(const mf_mesh* m, const Level& L, int dtype, int mode, const 
 int launch_iface(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
                  hipStream_t s);
 
-// 2D only: y at every shared, non-Dirichlet DoF of L = the sum of its copies'
-// partial rows, written to every copy (the exchange step of an apply).
+// 2D variable-coefficient apply: y at every shared, non-Dirichlet DoF of L = the
+// sum of its copies' partial rows, written to every copy.
 int launch_exchange_apply(const Level& L, int dtype, void* y, hipStream_t s);
 
 // P2 operator of a 2D mesh at `level` (vector layout: storage of level + 1):
 // interior rows by fused wave tiles, macro-boundary rows from the element
-// matrices (identity at Dirichlet DoFs), then the exchange.
+// matrices (identity at Dirichlet DoFs), shared ones over their copies.
 int launch_p2_apply(const mf_mesh* m, int level, int dtype, const void* x, void* y, hipStream_t s);
 
 // Variable-coefficient apply y = A(k) x (k: nodal coefficient, same
-// layout as x), including the exchange of shared DoFs.
+// layout as x), shared DoFs included.
 int launch_varcoef_apply(const mf_mesh* m, const Level& L, int dtype, const void* k, const void* x, void* y,
                          hipStream_t s);
 
@@ -124,7 +123,7 @@ int launch_lin3(double* y, const double* x1, const double* x2, double a, double 
 int launch_reduce_shift(const double* part, int64_t np, double* result, hipStream_t s);
 
 // Batched launches (one kernel over many requests; table = device base of
-// the op's argument table).  Stencil, exchange, iface and reduce ops:
+// the op's argument table).  Stencil, iface and reduce ops:
 int launch_stencil_batch(const BatchOp& op, const char* table, hipStream_t s);
 // Transfer, coarse-solve and vector ops:
 int launch_vector_batch(const BatchOp& op, const char* table, hipStream_t s);

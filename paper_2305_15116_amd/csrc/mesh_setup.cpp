@@ -680,7 +680,7 @@ static int build_level(mf_mesh* m, int level, Level& L) {
   L.own_bits.resize(bits.size());
   for (size_t i = 0; i < bits.size(); ++i) L.own_bits[i] = bits[i].load(std::memory_order_relaxed);
 
-  // storage indices of the copies, so that exchange kernels index directly
+  // storage indices of the copies, so that kernels index directly
   auto storage_index = [&](const Copy& c) {
     return L.md[c.macro].base + (dim == 2 ? idx2(N, c.x, c.y) : idx3(N, c.x, c.y, c.z));
   };

@@ -78,10 +78,9 @@ __device__ __forceinline__ void accum(double& ss, double& mx, T out, T xc) {
 }
 
 // Finish the row of one point.  acc is its (partial) stencil value, xc and bv
-// its x and b entries.  Interior points, Dirichlet points (identity rows) and
-// points no other macro shares are finished here; shared non-Dirichlet points
-// get their partial row for the exchange.  Norm partials count each unique DoF
-// once (Dirichlet DoFs on shared primitives only in their owner).
+// its x and b entries; it is an interior or Dirichlet point (identity row), or one
+// that no other macro shares.  Norm partials count each unique DoF once
+// (Dirichlet DoFs on shared primitives only in their owner).
 template <typename T, int DIM, int MODE>
 __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int mask, T acc, T xc, T bv, T omega,
                                        T* yp, double& ss, double& mx) {
@@ -89,12 +88,11 @@ __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int m
   constexpr StencilTable ST = stencil_table(DIM);
   const bool full = mask == FM;
   const bool dir = !full && ((M.dir_mask >> mask) & 1);
-  const bool shared = !full && ((M.shared_mask >> mask) & 1);
   if (dir) {
     const T out = MODE == kResidual ? bv - xc : (MODE == kNormB ? bv : (MODE == kJacobi2 ? T(0) : xc));
     if (MODE != kNormB) st(yp, out);
     if ((M.own_mask >> mask) & 1) accum<T, MODE>(ss, mx, out, xc);
-  } else if (full || !shared) {
+  } else {
     T out;
     if (MODE == kApply || MODE == kApplyDot) out = acc;
     else if (MODE == kJacobi || MODE == kJacobi2) out = fma(omega * (full ? Prec<T>::invd(M) : T(1) / W[mask][ST.centre]), bv - acc, xc);
@@ -102,8 +100,6 @@ __device__ __forceinline__ void finish(const MacroDev& M, const WTab<T> W, int m
     else out = bv;
     if (MODE != kNormB) st(yp, out);
     accum<T, MODE>(ss, mx, out, xc);
-  } else if (MODE != kNormB) {
-    st(yp, acc);
   }
 }
 
@@ -198,7 +194,7 @@ __device__ __forceinline__ int64_t lidx(int N, int x, int y, int z) {
 // Restriction r_c = P^T r_f on one macro: a coarse point P gathers the fine
 // point 2P (weight 1) and the fine points 2P + d for the stencil offsets d
 // (weight 1/2) — the fine points whose interpolation uses P — counting only
-// fine points this macro owns, so that the later exchange sums each fine DoF
+// fine points this macro owns, so that the sum over the copies of P takes each fine DoF
 // once.  Dirichlet fine points are skipped.
 // Segment and macro records are read-only for the launch: read them through
 // the constant address space (scalar loads, scalar registers).
@@ -481,9 +477,8 @@ struct ProlongCell {
 // of the row the sweep would finish: the macro's interior centre weight, the
 // partial stencil's centre at a boundary point no other macro shares, the
 // assembled diagonal of a shared DoF (exchange list), and x' = x = 0 at
-// Dirichlet DoFs.  The arithmetic is that of the stencil and exchange
-// kernels with x = 0 (fma(omega d, b - 0, 0)), so the result is bitwise
-// the same, in one pass that reads b once and needs no exchange.
+// Dirichlet DoFs.  The arithmetic is that of the stencil kernels with x = 0
+// (fma(omega d, b - 0, 0)), in passes that read b once.
 template <typename T>
 __device__ __forceinline__ T centre_inv(const MacroDev& M, int mask, int full, int centre) {
   if constexpr (sizeof(T) == 8) return mask == full ? M.inv_diag : 1.0 / M.wm[mask][centre];

@@ -1,6 +1,6 @@
 // Constant-stencil kernels for CDNA4 (gfx950): the 2D operator's rows for every
 // point of every macro (apply, weighted Jacobi, residual + norm partials),
-// the exchange that completes rows of DoFs shared by several macros, and the
+// the sums over shared DoFs of the variable-coefficient walk, and the
 // deterministic norm reduction.
 //
 // The paper's vertex-to-vertex kernel (Performance Modeling section) walks

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kWG) void jacobi0_fix_kernel(const Launch<Jacobi0Ar
       const int mask = support_mask(DIM, M.N, k.x, k.y, k.z);
       const bool dir = mask != full && ((M.dir_mask >> mask) & 1);
       const bool shared = mask != full && !dir && ((M.shared_mask >> mask) & 1);
-      if (shared) continue;  // the exchange part below
+      if (shared) continue;  // the second part below
       const int64_t i = copy_index<DIM>(M, k);
       a.Y[i] = dir ? T(0) : fma(a.omega * centre_inv<T>(M, mask, full, centre), a.B[i], T(0));
     }

@@ -69,7 +69,7 @@ __device__ __forceinline__ void st(Rsrc r, unsigned off, T v) {
 // Bound: memory.  Against pencils of 62 columns x 4 rows x 8 slices whose lanes
 // past a row's end idled and whose boundary rows took per-lane weights from
 // LDS, this needs 8.2 million wave instructions instead of 23 at N = 256 (cube,
-// FP64 apply) and no exchange launch: 94.0 -> 70.5 us per apply (3.9 TB/s of x
+// FP64 apply) and no second launch over shared DoFs: 94.0 -> 70.5 us per apply (3.9 TB/s of x
 // and y; a copy that walks the same way runs at 4.0, a straight one at 6.1);
 // two FP32 sweeps 160 -> 92 us; N = 128 FP64 apply 28 -> 10.3 us.  Rows written
 // with holes (boundary points left to other tiles) cost 6 us more: a line
