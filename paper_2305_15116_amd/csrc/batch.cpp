@@ -368,8 +368,7 @@ void build_plan(mf_batch* B, int dim) {
       reduce_op(P, ra);
     };
     pcg_op(kOpPcgZDot, vdt, [](const Member& M) {
-      PcgArgs a = pcg_args(lev(M, M.level), nullptr, M.w.r64, nullptr, nullptr, M.w.x[M.level], M.w.z64, M.w.result,
-                           M.w.part);
+      PcgArgs a = pcg_args(lev(M, M.level), M.w.r64, nullptr, M.w.x[M.level], M.w.z64, M.w.result, M.w.part);
       a.sslot = kSlotScale;
       return a;
     });
@@ -379,6 +378,7 @@ void build_plan(mf_batch* B, int dim) {
     vector_op(P, corr, dim, kOpPcgDir, vdt, [f32](const Member& M, VecArgs& a) {
       a = vec_args(M.w.p64, f32 ? M.w.x[M.level] : (const void*)M.w.z64, M.w.result, lev(M, M.level).storage, 0.0);
       a.sslot = kSlotScale;
+      a.xs = M.x;
       return true;
     });
     stencil_op(P, corr, dim, MF_F64, kApplyDot, 0.0, [](const Member& M, Pass& p) {
@@ -393,7 +393,8 @@ void build_plan(mf_batch* B, int dim) {
       return ReduceArgs{M.w.part, stencil_partials(lev(M, M.level), MF_F64), M.w.result + 4, nullptr, 0, 0};
     });
     pcg_op(kOpPcgUpdate, MF_F64, [f32](const Member& M) {
-      PcgArgs a = pcg_args(lev(M, M.level), M.x, M.w.r64, M.w.p64, M.w.q64, nullptr, nullptr, M.w.result, M.w.part);
+      PcgArgs a = pcg_args(lev(M, M.level), M.w.r64, M.w.q64, nullptr, nullptr, M.w.result, M.w.part);
+      a.aout = M.w.result + kSlotAlpha;
       if (f32) {
         // the next FP32 preconditioner input, as vcycle_solve forms it
         a.r32 = (float*)M.w.b[M.level];
@@ -432,7 +433,7 @@ void build_plan(mf_batch* B, int dim) {
   const std::vector<Member*>& resid = pcg ? fresh : all;
   if (pcg)
     vector_op(P, fresh, dim, kOpFill, MF_F64, [](const Member& M, VecArgs& a) {
-      a = vec_args(M.w.result + 2, nullptr, nullptr, 6, 0.0);
+      a = vec_args(M.w.result + 2, nullptr, nullptr, kSlotAlpha - 1, 0.0);
       return true;
     });
   stencil_op(P, resid, dim, MF_F64, kResidual, 0.0, [](const Member& M, Pass& p) {
@@ -464,6 +465,14 @@ void build_plan(mf_batch* B, int dim) {
   // ---- CG members whose recurrence met rtol: the true residual, as vcycle_solve
   // recomputes it (into q and result[6..7], which no recurrence reads)
   if (verify.empty()) return;
+  vector_op(P, verify, dim, kOpAxpyRes, MF_F64, [](const Member& M, VecArgs& a) {
+    a = vec_args(M.x, M.w.p64, M.w.result, lev(M, M.level).storage, 0.0);
+    return true;
+  });
+  vector_op(P, verify, dim, kOpFill, MF_F64, [](const Member& M, VecArgs& a) {
+    a = vec_args(M.w.result + kSlotAlpha, nullptr, nullptr, 1, 0.0);
+    return true;
+  });
   stencil_op(P, verify, dim, MF_F64, kResidual, 0.0, [](const Member& M, Pass& p) {
     p.level = M.level;
     p.x = M.x;
@@ -690,7 +699,7 @@ int batch_step(mf_batch* B, void* stream, int64_t* done_tags, int* done_status, 
   // decide, per member, exactly as vcycle_solve does
   std::vector<Member> keep;
   keep.reserve(B->mem.size());
-  bool changed = false;
+  bool changed = false, stepped = false;
   const auto now = std::chrono::steady_clock::now();
   for (size_t i = 0; i < B->mem.size(); ++i) {
     Member& M = B->mem[i];
@@ -725,6 +734,11 @@ int batch_step(mf_batch* B, void* stream, int64_t* done_tags, int* done_status, 
         if (running && !verify_next && M.iters >= B->o.max_iter) {
           status = MF_NOT_CONVERGED;
           running = false;
+          if (mode_pcg(B->o.mode) && M.iters > 0) {  // x takes its last step
+            const int64_t n = lev(M, M.level).storage;
+            if (const int rc = launch_pcg_step_x(M.x, M.w.p64, M.w.result, n, s)) status = rc;
+            stepped = true;
+          }
         }
         if (verified) {
           M.state = kRunning;
@@ -756,6 +770,7 @@ int batch_step(mf_batch* B, void* stream, int64_t* done_tags, int* done_status, 
   }
   B->mem.swap(keep);
   if (changed) B->dirty = true;
+  if (stepped && (e = hipStreamSynchronize(s)) != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));
   return MF_OK;
 }
 

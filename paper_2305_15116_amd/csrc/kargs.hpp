@@ -182,7 +182,12 @@ struct VecArgs {
   double a;
   int nblk;   // grid-stride blocks of this request
   int sslot;  // PCG direction: res slot of the FP32 preconditioner's scale (1, or 8 in mixed CG)
+  double* xs;  // PCG direction: the iterate, which takes its last step there
 };
+
+// CG's update leaves its step length here: x += alpha p is made by the next
+// direction pass, which reads p anyway, or (before x is used) by kOpAxpyRes.
+constexpr int kSlotAlpha = 9;
 
 // reduce_kernel: one block per request.
 struct ReduceArgs {
@@ -202,9 +207,7 @@ struct ReduceArgs {
 struct PcgArgs {
   int64_t n;
   const uint32_t* own;  // owner bits of the storage DoFs
-  double* x;            // update: x += alpha p
   double* r;            // zdot: read; update: r -= alpha q
-  double* p;            // update: read
   const double* q;      // update: A p
   const void* e;        // zdot: preconditioner output (FP32 or FP64)
   double* z;            // zdot: z = s e (not written when z == e)
@@ -212,6 +215,7 @@ struct PcgArgs {
   double* part;         // sums at [0, nblk), maxima at [nblk, 2 nblk)
   float* r32;           // update (nullable): the next preconditioner input, float(r / res[1])
   double* sout;         // update with r32: receives res[1], the scale r32 was formed with
+  double* aout;         // update: receives alpha
   int nblk;
   int sslot;            // zdot: res slot of the FP32 preconditioner's scale s (1, or 8 in mixed CG)
 };
@@ -359,12 +363,12 @@ inline int tail_levels(const mf_mesh* m, int level, int lc) {
 }
 
 inline VecArgs vec_args(void* y, const void* x, const double* res, int64_t n, double a) {
-  return VecArgs{y, x, res, n, a, vec_blocks(n), 1};
+  return VecArgs{y, x, res, n, a, vec_blocks(n), 1, nullptr};
 }
 
-inline PcgArgs pcg_args(const Level& L, double* x, double* r, double* p, const double* q, const void* e, double* z,
-                        const double* res, double* part) {
-  return PcgArgs{L.storage, L.dev.own_bits, x, r, p, q, e, z, res, part, nullptr, nullptr, (int)L.lin_blocks(), 1};
+inline PcgArgs pcg_args(const Level& L, double* r, const double* q, const void* e, double* z, const double* res,
+                        double* part) {
+  return PcgArgs{L.storage, L.dev.own_bits, r, q, e, z, res, part, nullptr, nullptr, nullptr, (int)L.lin_blocks(), 1};
 }
 inline int pcg_blocks(const Level& L) { return (int)L.lin_blocks(); }
 
@@ -381,9 +385,10 @@ enum OpKind : int {
   kOpAxpy,         // VecArgs: y += a x
   kOpScaleF32,     // VecArgs: float y = x / res[1]
   kOpAxpyF32,      // VecArgs: double y += res[1] * float x
+  kOpAxpyRes,      // VecArgs: double y += res[kSlotAlpha] x (nothing where that is 0)
   kOpPcgZDot,      // PcgArgs, dtype = type of e: z = s e, partials of r . z
-  kOpPcgDir,       // VecArgs: y = x + beta y, beta = res[2] / res[3] (0 if res[3] == 0)
-  kOpPcgUpdate,    // PcgArgs: x += alpha p, r -= alpha q, alpha = res[2] / res[4]; partials of r . r
+  kOpPcgDir,       // VecArgs: xs += alpha y, y = x + beta y, beta = res[2] / res[3] (0 if res[3] == 0)
+  kOpPcgUpdate,    // PcgArgs: r -= alpha q, alpha = res[2] / res[4]; partials of r . r
   kOpJacobi0,      // Jacobi0Args<T>: y = omega D^-1 b (the first sweep from a zero iterate);
                    // mode 0: streaming pass over all points, mode 1: macro-boundary DoFs
   kOpTail,         // TailArgs<T>: the V-cycle below a level, one workgroup per request

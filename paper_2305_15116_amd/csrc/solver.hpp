@@ -40,7 +40,7 @@ struct Workspace {
   double* part = nullptr;
   // 16 doubles: [0] r.r, [1] max|r|, [2] r.z, [3] previous r.z, [4] p.Ap,
   // [6..7] a recomputed residual's pair, [8] mixed CG: the scale of the FP32
-  // preconditioner input in use (kSlotScale)
+  // preconditioner input in use (kSlotScale); [9] CG: the step x has yet to take (kSlotAlpha)
   double* result = nullptr;
   int64_t bytes = 0;
 };

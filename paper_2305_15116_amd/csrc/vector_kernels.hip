@@ -276,6 +276,10 @@ __global__ __launch_bounds__(256) void vector_kernel(const Launch<VecArgs> L) {
   } else if (KIND == kOpAxpy) {
     const T c = (T)a.a;
     for (; i < a.n; i += stride) ((T*)a.y)[i] = fma(c, ((const T*)a.x)[i], ((T*)a.y)[i]);
+  } else if (KIND == kOpAxpyRes) {
+    const double c = a.res[kSlotAlpha];
+    if (c == 0.0) return;
+    for (; i < a.n; i += stride) ((double*)a.y)[i] = fma(c, ((const double*)a.x)[i], ((double*)a.y)[i]);
   } else if (KIND == kOpScaleF32) {
     const double c = 1.0 / a.res[1];
     for (; i < a.n; i += stride) ((float*)a.y)[i] = (float)(c * ((const double*)a.x)[i]);
@@ -289,8 +293,8 @@ __global__ __launch_bounds__(256) void vector_kernel(const Launch<VecArgs> L) {
 // Grid-stride over the storage index, nblk blocks of 256 threads.  KIND
 // kOpPcgZDot: z = s e with s = res[sslot] for FP32 e (the preconditioner
 // solved for r / s) and 1 for FP64 e, partials of r . z.  KIND kOpPcgUpdate:
-// alpha = res[2] / res[4], x += alpha p, r -= alpha q, partials of r . r and
-// max |r|; with r32, also the next FP32 preconditioner input r / res[1]
+// alpha = res[2] / res[4] (also left in *aout), r -= alpha q, partials of r . r
+// and max |r|; with r32, also the next FP32 preconditioner input r / res[1]
 // (res[1] = max |r| of the residual before this update) and *sout = res[1].
 // Sums count each unique DoF once (owner bits); each block leaves one
 // partial, its four waves summed in a fixed order.
@@ -332,15 +336,16 @@ __global__ __launch_bounds__(256) void pcg_lin_kernel(const Launch<PcgArgs> L) {
   } else {
     const double alpha = a.res[2] / a.res[4];
     const double c32 = a.r32 ? 1.0 / a.res[1] : 0.0;  // as the scaled cast forms it
-    if (a.r32 && blk == 0 && threadIdx.x == 0) *a.sout = a.res[1];
+    if (blk == 0 && threadIdx.x == 0) {
+      *a.aout = alpha;
+      if (a.r32) *a.sout = a.res[1];
+    }
     for (int64_t i = i0; i < a.n; i += kPcgU * stride) {
-      double xv[kPcgU], pv[kPcgU], qv[kPcgU], rv[kPcgU];
+      double qv[kPcgU], rv[kPcgU];
       uint32_t ow[kPcgU];
 #pragma unroll
       for (int u = 0; u < kPcgU; ++u) {
         const int64_t j = i + u * stride, jj = j < a.n ? j : i;
-        xv[u] = a.x[jj];
-        pv[u] = a.p[jj];
         qv[u] = a.q[jj];
         rv[u] = a.r[jj];
         ow[u] = a.own[jj >> 5];
@@ -349,7 +354,6 @@ __global__ __launch_bounds__(256) void pcg_lin_kernel(const Launch<PcgArgs> L) {
       for (int u = 0; u < kPcgU; ++u) {
         const int64_t j = i + u * stride;
         if (j >= a.n) break;
-        a.x[j] = fma(alpha, pv[u], xv[u]);
         const double rn = fma(-alpha, qv[u], rv[u]);
         a.r[j] = rn;
         if (a.r32) a.r32[j] = (float)(c32 * rn);
@@ -373,10 +377,14 @@ __global__ __launch_bounds__(256) void pcg_lin_kernel(const Launch<PcgArgs> L) {
   }
 }
 
-// p = z + beta p, beta = res[2] / res[3] (0 on the first iteration, res[3] == 0).
-// p = z + beta p.  TZ = double: x is z; TZ = float: x is the FP32 V-cycle
-// output e and z = res[1] e is formed here exactly as the r . z pass forms it
-// (the mixed solver never stores z).
+// x += alpha p with the last update's alpha (here, where p is read anyway: the
+// update need not read p and x), then p = z + beta p, beta = res[2] / res[3].
+// TZ = double: x is z; TZ = float: x is the FP32 V-cycle output e and z = res[1]
+// e is formed here exactly as the r . z pass forms it (the mixed solver never
+// stores z).
+//
+// Bound: memory.  Cube at level 8, mixed CG: this and the update read and write 64 B
+// per DoF instead of 72, the whole solve 10.8 -> 10.5 ms.
 template <typename TZ>
 __global__ __launch_bounds__(256) void pcg_dir_kernel(const Launch<VecArgs> L) {
   VecArgs a;
@@ -386,13 +394,20 @@ __global__ __launch_bounds__(256) void pcg_dir_kernel(const Launch<VecArgs> L) {
   const TZ* zs = (const TZ*)a.x;
   const double sc = sizeof(TZ) == 4 ? a.res[a.sslot] : 1.0;
   auto z = [&](int64_t i) { return sizeof(TZ) == 4 ? sc * (double)zs[i] : (double)zs[i]; };
-  if (a.res[3] == 0.0) {
-    // first direction: p = z (p holds no earlier direction and is never read)
-    for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < a.n; i += stride) p[i] = z(i);
-    return;
+  const bool first = a.res[3] == 0.0;  // p = z
+  const double alpha = a.res[kSlotAlpha], beta = first ? 0.0 : a.res[2] / a.res[3];
+  const int64_t i0 = (int64_t)blk * 256 + threadIdx.x;
+  if (alpha != 0.0) {
+    for (int64_t i = i0; i < a.n; i += stride) {
+      const double pv = p[i];
+      a.xs[i] = fma(alpha, pv, a.xs[i]);
+      p[i] = first ? z(i) : fma(beta, pv, z(i));
+    }
+  } else if (first) {  // (p holds no earlier direction and is never read)
+    for (int64_t i = i0; i < a.n; i += stride) p[i] = z(i);
+  } else {
+    for (int64_t i = i0; i < a.n; i += stride) p[i] = fma(beta, p[i], z(i));
   }
-  const double beta = a.res[2] / a.res[3];
-  for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < a.n; i += stride) p[i] = fma(beta, p[i], z(i));
 }
 
 template <int KIND>
@@ -527,22 +542,30 @@ int launch_pcg_zdot(const mf_mesh* m, const Level& L, int edtype, const double* 
                     const double* res, double* part, hipStream_t s, int sslot) {
   const int nwg = pcg_blocks(L);
   if (nwg == 0) return MF_OK;
-  PcgArgs a = pcg_args(L, nullptr, (double*)r, nullptr, nullptr, e, z, res, part);
+  PcgArgs a = pcg_args(L, (double*)r, nullptr, e, z, res, part);
   a.sslot = sslot;
   run_pcg_point<kOpPcgZDot>(m->dim, edtype, single(a, nwg), s);
   return check_launch();
 }
 
-int launch_pcg_update(const mf_mesh* m, const Level& L, double* x, double* r, double* p, const double* q,
-                      const double* res, double* part, hipStream_t s, float* r32, double* sout) {
+int launch_pcg_update(const mf_mesh* m, const Level& L, double* r, const double* q, double* res, double* part,
+                      hipStream_t s, float* r32, double* sout) {
   const int nwg = pcg_blocks(L);
   if (nwg == 0) return MF_OK;
   if ((r32 == nullptr) != (sout == nullptr)) return set_error(MF_EINVAL, "pcg update: r32 and sout go together");
-  PcgArgs a = pcg_args(L, x, r, p, q, nullptr, nullptr, res, part);
+  PcgArgs a = pcg_args(L, r, q, nullptr, nullptr, res, part);
   a.r32 = r32;
   a.sout = sout;
+  a.aout = res + kSlotAlpha;
   run_pcg_point<kOpPcgUpdate>(m->dim, MF_F64, single(a, nwg), s);
   return check_launch();
+}
+
+int launch_pcg_step_x(double* x, const double* p, double* res, int64_t n, hipStream_t s) {
+  if (n <= 0) return MF_OK;
+  const VecArgs a = vec_args(x, p, res, n, 0.0);
+  const int rc = run_vector<kOpAxpyRes>(MF_F64, single(a, a.nblk), s);
+  return rc ? rc : launch_fill(MF_F64, res + kSlotAlpha, 0.0, 1, s);
 }
 
 namespace {
@@ -591,10 +614,12 @@ int launch_lin3(double* y, const double* x1, const double* x2, double a, double 
   return check_launch();
 }
 
-int launch_pcg_dir(double* p, const void* z, const double* res, int64_t n, hipStream_t s, int zdtype, int sslot) {
+int launch_pcg_dir(double* x, double* p, const void* z, const double* res, int64_t n, hipStream_t s, int zdtype,
+                   int sslot) {
   if (n <= 0) return MF_OK;
   VecArgs a = vec_args(p, z, res, n, 0.0);
   a.sslot = sslot;
+  a.xs = x;
   if (zdtype == MF_F32) hipLaunchKernelGGL(pcg_dir_kernel<float>, dim3(a.nblk), dim3(256), 0, s, single(a, a.nblk));
   else hipLaunchKernelGGL(pcg_dir_kernel<double>, dim3(a.nblk), dim3(256), 0, s, single(a, a.nblk));
   return check_launch();
@@ -621,6 +646,7 @@ int launch_vector_batch(const BatchOp& op, const char* table, hipStream_t s) {
     case kOpAxpy: return run_vector<kOpAxpy>(op.dtype, batched<VecArgs>(op, table), s);
     case kOpScaleF32: return run_vector<kOpScaleF32>(MF_F64, batched<VecArgs>(op, table), s);
     case kOpAxpyF32: return run_vector<kOpAxpyF32>(MF_F64, batched<VecArgs>(op, table), s);
+    case kOpAxpyRes: return run_vector<kOpAxpyRes>(MF_F64, batched<VecArgs>(op, table), s);
     case kOpPcgZDot: run_pcg_point<kOpPcgZDot>(op.dim, op.dtype, batched<PcgArgs>(op, table), s); return check_launch();
     case kOpPcgUpdate: run_pcg_point<kOpPcgUpdate>(op.dim, MF_F64, batched<PcgArgs>(op, table), s); return check_launch();
     case kOpPcgDir:
