@@ -93,20 +93,38 @@ def _check(rc, allow=(MF_OK,)):
     return rc
 
 
+# What a call does besides the library's own work is most of a small apply's
+# time (one triangle at level 8: 7.2 -> 4.7 us a
+# call, the kernel 3.2), so torch is looked up once, and the
+# current stream is asked for as a handle rather than as an object.
+_current_device = _raw_stream = None
+_DTYPES = {}
+
+
+def _load_torch():
+    global _current_device, _raw_stream
+    import torch
+    _DTYPES.update({torch.float64: MF_F64, torch.float32: MF_F32})
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda device: torch.cuda.current_stream(device).cuda_stream)
+    _current_device = torch.cuda.current_device
+
+
 def _stream(stream):
     if stream is not None:
         return C.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _current_device is None:
+        _load_torch()
+    return C.c_void_p(_raw_stream(_current_device()))
 
 
 def _dtype_code(t):
-    import torch
-    if t.dtype == torch.float64:
-        return MF_F64
-    if t.dtype == torch.float32:
-        return MF_F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    if not _DTYPES:
+        _load_torch()
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 class Mesh:
