@@ -117,7 +117,7 @@ struct mf_batch {
   bool forked = false;  // the plan has launches of both dimensions
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  double* dres = nullptr;  // per member: residual (ss, max), b norm (ss, max)
+  // per member: residual (ss, max), b norm (ss, max); pinned, written by the reductions themselves
   double* hres = nullptr;
 };
 
@@ -285,7 +285,7 @@ void build_plan(mf_batch* B, int dim) {
   const mf_solve_opts& o = B->o;
   const bool f32 = mode_f32(o.mode), pcg = mode_pcg(o.mode);
   const int vdt = f32 ? MF_F32 : MF_F64;
-  auto slot = [B](const Member& M) { return B->dres + 4 * (&M - B->mem.data()); };
+  auto slot = [B](const Member& M) { return B->hres + 4 * (&M - B->mem.data()); };
   std::vector<Member*> all, corr, fresh, verify;
   for (size_t i = 0; i < B->mem.size(); ++i) {
     Member* M = &B->mem[i];
@@ -592,17 +592,15 @@ int batch_create(const mf_solve_opts* opts, int capacity, mf_batch** out) {
   B->o = o;
   B->capacity = capacity;
   (void)hipGetDevice(&B->device);
-  hipError_t e = hipMalloc((void**)&B->dres, sizeof(double) * 4 * capacity);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&B->hres, sizeof(double) * 4 * capacity, hipHostMallocDefault);
+  const hipError_t e = hipHostMalloc((void**)&B->hres, sizeof(double) * 4 * capacity,
+                                     hipHostMallocPortable | hipHostMallocMapped);
   if (e != hipSuccess) {
-    if (B->dres) (void)hipFree(B->dres);
     delete B;
     return set_error(MF_ENOMEM, std::string("batch buffers: ") + hipGetErrorString(e));
   }
   try {
     B->mem.reserve(capacity);
   } catch (const std::bad_alloc&) {
-    (void)hipFree(B->dres);
     (void)hipHostFree(B->hres);
     delete B;
     return set_error(MF_ENOMEM, "host allocation failed");
@@ -616,7 +614,6 @@ int batch_destroy(mf_batch* B) {
   free_side(B);
   if (B->dtab) (void)hipFree(B->dtab);
   if (B->htab) (void)hipHostFree(B->htab);
-  if (B->dres) (void)hipFree(B->dres);
   if (B->hres) (void)hipHostFree(B->hres);
   delete B;
   return MF_OK;
@@ -693,8 +690,7 @@ int batch_step(mf_batch* B, void* stream, int64_t* done_tags, int* done_status, 
     }
   }
   if (rc) return rc;
-  hipError_t e = hipMemcpyAsync(B->hres, B->dres, sizeof(double) * 4 * B->mem.size(), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));
   // decide, per member, exactly as vcycle_solve does
   std::vector<Member> keep;

@@ -68,7 +68,8 @@ int launch_blended_apply(const mf_mesh* m, const Level& L, const double* bubble,
                          hipStream_t s);
 
 // result[0] = sum part[0..np), result[1] = max part[np..2np), fixed order.
-int launch_reduce(const double* part, int64_t np, double* result, hipStream_t s);
+// (copy: the pair once more, pinned host memory or nullptr)
+int launch_reduce(const double* part, int64_t np, double* result, hipStream_t s, double* copy = nullptr);
 
 int launch_fill_random(const mf_mesh* m, const Level& L, int dtype, uint64_t seed, void* x, hipStream_t s);
 int launch_restrict(const mf_mesh* m, const Level& fine, const Level& coarse, int dtype, const void* rf, void* bc,

@@ -40,7 +40,6 @@ struct LevelDev {
   float* xgrp_invdiagf = nullptr;
   double* part = nullptr;       // norm partials: ntiles + iface blocks, then the same again for max
   double* result = nullptr;     // 2 doubles: sum of squares, max |.|
-  double* host_result = nullptr;  // pinned host mirror of result
   // coarse direct solve (levels <= 2 only)
   double* cinv = nullptr;
   float* cinvf = nullptr;

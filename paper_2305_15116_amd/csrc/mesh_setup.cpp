@@ -826,12 +826,8 @@ int upload_level(mf_mesh* m, Level& L) {
   up.add(&D.part, zeros);
   std::vector<double> z2(2, 0.0);
   up.add(&D.result, z2);
-  const int rc = up.run(D.allocs);
-  if (rc) return rc;
-  hipError_t e = hipHostMalloc((void**)&D.host_result, 2 * sizeof(double), hipHostMallocDefault);
-  if (e != hipSuccess) return set_error(MF_ENOMEM, hipGetErrorString(e));
   (void)m;
-  return MF_OK;
+  return up.run(D.allocs);
 }
 
 // ---------------------------------------------------------------- coarse direct solve
@@ -994,7 +990,6 @@ void free_device(mf_mesh* m) {
     void* ptrs[] = {D.cinv, D.cinvf, D.cfirst, D.cptr, D.cidx, D.p2_tiles};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
-    if (D.host_result) (void)hipHostFree(D.host_result);
     D = LevelDev{};
   }
   if (m->p2_dev) (void)hipFree(m->p2_dev);

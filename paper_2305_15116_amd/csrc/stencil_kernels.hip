@@ -552,8 +552,8 @@ int launch_exchange_apply(const Level& L, int dtype, void* y, hipStream_t s) {
   return check_launch();
 }
 
-int launch_reduce(const double* part, int64_t np, double* result, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kRedT), 0, s, single(ReduceArgs{part, np, result, nullptr, 0, 0}, 1));
+int launch_reduce(const double* part, int64_t np, double* result, hipStream_t s, double* copy) {
+  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kRedT), 0, s, single(ReduceArgs{part, np, result, copy, 0, 0}, 1));
   return check_launch();
 }
 
