@@ -198,11 +198,11 @@ __device__ __forceinline__ double bl_partial(const MacroDev& M, const Geo2& G, d
   return acc;
 }
 
-__global__ __launch_bounds__(kWG) void blended_kernel(const Tile* __restrict__ tiles, int nwg, const MacroDev* md,
+__global__ __launch_bounds__(kWG) void blended_kernel(const Tile* __restrict__ tiles, int nwg, int lead, const MacroDev* md,
                                                       const EdgeCopy* edges, const Geo2* geo,
                                                       const double* __restrict__ bubble, const double* __restrict__ X,
                                                       double* __restrict__ Y) {
-  const int g = wave::xcd_wg(nwg);
+  const int g = wave::xcd_wg_lead(nwg, lead, 0, wave::kNoRuns);
   if (g < 0) return;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Tile t = load_seg(tiles, g * kWavesPerWG + wv);
@@ -229,7 +229,8 @@ int launch_blended_apply(const mf_mesh* m, const Level& L, const double* bubble,
   static_assert(kBlH == kTileH2F, "the walk runs on the FP32 tile list");
   const int nwg = (int)(L.tiles_f32.size() / kWavesPerWG);
   if (nwg > 0)
-    hipLaunchKernelGGL(blended_kernel, dim3(wave::xcd_grid(nwg)), dim3(kWG), 0, s, L.dev.tiles_f32, nwg, L.dev.md,
+    hipLaunchKernelGGL(blended_kernel, dim3(wave::xcd_grid(nwg, L.ewgs, 0, wave::kNoRuns)), dim3(kWG), 0, s, L.dev.tiles_f32, nwg,
+                       L.ewgs, L.dev.md,
                        L.dev.edges, m->geo2_dev, bubble, x, y);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));

@@ -22,6 +22,7 @@ struct Launch {
   const int32_t* wg0;  // nseg > 0: nseg + 1 workgroup offsets (device), wg0[0] = 0
   int nseg;
   int nwg;             // workgroups of the whole launch
+  int lead;            // nseg == 0: the first ones, of tiles of shared DoFs
 };
 
 // The request that owns workgroup g: the last r with wg0[r] <= g (requests

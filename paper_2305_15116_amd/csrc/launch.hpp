@@ -15,11 +15,12 @@ namespace mf {
 
 // A launch of one request (nwg workgroups), and one over a batch op's table.
 template <class A>
-Launch<A> single(const A& a, int nwg) {
+Launch<A> single(const A& a, int nwg, int lead = 0) {
   Launch<A> l{};
   l.one = a;
   l.nseg = 0;
   l.nwg = nwg;
+  l.lead = lead;
   return l;
 }
 template <class A>

@@ -53,7 +53,7 @@ struct LevelDev {
 struct Level {
   int level = 0;
   int N = 0;
-  int ewgs = 0;  // 2D: workgroups of edge tiles, which lead both tile lists
+  int ewgs = 0, ewgs_short = 0;  // 2D: workgroups of edge tiles, which lead the tile lists, and tiles_short
   int64_t storage = 0, unique = 0;
   std::vector<int64_t> base;    // per macro storage offset
   std::vector<MacroDev> md;
@@ -91,6 +91,8 @@ struct Level {
     const int h = tiles_f32.empty() ? kTileH2 : rows2(dtype);  // (3D: one list)
     return h < kTileH2 ? tiles_short : (h == kTileH2F ? tiles_f32 : tiles);
   }
+  // how many of its workgroups are edge tiles (2D)
+  int lead2(int dtype) const { return rows2(dtype) < kTileH2 ? ewgs_short : ewgs; }
   // norm / dot partials of one stencil pass: one per workgroup of tiles
   int64_t n_partials(int dtype) const { return (int64_t)tiles_for(dtype).size() / kWavesPerWG; }
   int64_t n_partials() const { return std::max(n_partials(MF_F64), n_partials(MF_F32)); }  // buffer sizes

@@ -347,6 +347,7 @@ static void build_short_tiles2(Level& L, int64_t nc) {
       if (t.z > 0) out.push_back({t.macro, t.x0 + t.y0, t.z, 0});
     }
     while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
+    L.ewgs_short = (int)(out.size() / kWavesPerWG);
     for (int64_t c = 0; c < nc && out.size() <= most; ++c)
       for (int y0 = 0; y0 <= L.N && out.size() <= most; y0 += rows)
         for (int x0 = 0; x0 + y0 <= L.N; x0 += kTileW) out.push_back({(int32_t)c, x0, y0, 0});

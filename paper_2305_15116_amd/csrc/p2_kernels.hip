@@ -252,7 +252,7 @@ __device__ __forceinline__ void p2_boundary(const P2Args<T>& a, int64_t t) {
 
 template <typename T>
 __global__ __launch_bounds__(kWG) void p2_kernel(const P2Args<T> a) {
-  int g = wave::xcd_wg_runs(a.nwg, wave::kRuns2);
+  int g = wave::xcd_wg_lead(a.nwg, a.ewg, a.bwg, wave::kRuns2);
   if (g < 0) return;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (g < a.ewg) {
@@ -274,7 +274,7 @@ int run_p2(const mf_mesh* m, const Level& F, const void* x, void* y, hipStream_t
   const int bwg = (int)((nb + kWG - 1) / kWG), nwg = F.ewgs + bwg + (int)(F.p2_tiles.size() / kWavesPerWG);
   const P2Args<T> a{F.dev.tiles, F.dev.edges, F.dev.p2_tiles, F.ewgs, bwg,        nwg,  (int)m->nc,
                     F.N,         F.dev.md,    m->p2_dev,      (const T*)x, (T*)y};
-  hipLaunchKernelGGL(p2_kernel<T>, dim3(wave::xcd_grid_runs(nwg, wave::kRuns2)), dim3(kWG), 0, s, a);
+  hipLaunchKernelGGL(p2_kernel<T>, dim3(wave::xcd_grid(nwg, F.ewgs, bwg, wave::kRuns2)), dim3(kWG), 0, s, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }

@@ -340,7 +340,7 @@ __device__ __forceinline__ bool tile_on_boundary(const Tile& t, int N) {
 
 template <typename T, int MODE, int H>
 __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T>> L) {
-  const int g = wave::xcd_wg_runs(L.nwg, wave::kRuns2);
+  const int g = wave::xcd_wg_lead(L.nwg, L.lead, 0, wave::kRuns2);
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
@@ -466,7 +466,7 @@ int stencil_lds(int nwg) {
 template <typename T, int MODE>
 void run_stencil(int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   if (l.nwg <= 0) return;
-  const dim3 grid(wave::xcd_grid_runs(l.nwg, wave::kRuns2)), wg(kWG);
+  const dim3 grid(wave::xcd_grid(l.nwg, l.lead, 0, wave::kRuns2)), wg(kWG);
   const int lds = stencil_lds<T, MODE>(l.nwg);
   if (rows == kTileShort[0]) {
     hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileShort[0]>), grid, wg, lds, s, l);
@@ -504,7 +504,7 @@ int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const vo
   } else {
     const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
     if (dim == 3) return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
-    run_stencil<T>(mode, L.rows2(dtype_of<T>()), single(a, a.nwg), s);
+    run_stencil<T>(mode, L.rows2(dtype_of<T>()), single(a, a.nwg, L.lead2(dtype_of<T>())), s);
   }
   return check_launch();
 }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mf_internal.hpp"
+#include "xcd.hpp"
 
 namespace mf {
 namespace wave {
@@ -34,38 +35,13 @@ __device__ __forceinline__ T up1(T v) { return dpp_move<kDppWaveShr1>(v); }  // 
 template <typename T>
 __device__ __forceinline__ T dn1(T v) { return dpp_move<kDppWaveShl1>(v); }  // value of lane + 1
 
-// Maps this block to its natural workgroup index so that each of the 8 XCDs
-// (which receive blocks round-robin) works through one contiguous chunk of
-// the natural order: neighbouring strips then share that XCD's L2.
-__device__ __forceinline__ int xcd_wg(int nwg) {
-  const int chunk = (nwg + kXCD - 1) / kXCD;
-  const int k = blockIdx.x % kXCD, j = blockIdx.x / kXCD;
-  if (j >= chunk) return -1;
-  const int n = k * chunk + j;
-  return n < nwg ? n : -1;
+// This block's natural workgroup under the mappings of xcd.hpp.
+__device__ __forceinline__ int xcd_wg(int nwg) { return xcd_wg_at(blockIdx.x, nwg); }
+__device__ __forceinline__ int xcd_wg_runs(int nwg, XcdRuns r) { return xcd_wg_at(blockIdx.x, nwg, r); }
+__device__ __forceinline__ int xcd_wg_lead(int nwg, int lead, int lead2, XcdRuns r) {
+  return xcd_wg_at(blockIdx.x, nwg, lead, lead2, r);
 }
 
-// Grid of an XCD-mapped launch of nwg workgroups.
-inline int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
-
-// The same for launches of at least `from` workgroups with runs of 2^shift
-// consecutive workgroups dealt to the XCDs in turn: neighbours still share an
-// L2, and the launch as a whole moves through memory in one front instead of
-// eight.  Smaller launches (whose data the caches hold) keep one chunk per XCD.
-struct XcdRuns {
-  int from, shift;
-};
-__device__ __forceinline__ int xcd_wg_runs(int nwg, XcdRuns r) {
-  if (nwg < r.from) return xcd_wg(nwg);
-  const int k = blockIdx.x % kXCD, j = blockIdx.x / kXCD;
-  const int n = (((j >> r.shift) * kXCD + k) << r.shift) + (j & ((1 << r.shift) - 1));
-  return n < nwg ? n : -1;
-}
-inline int xcd_grid_runs(int nwg, XcdRuns r) {
-  if (nwg < r.from) return xcd_grid(nwg);
-  const int per = kXCD << r.shift;
-  return (nwg + per - 1) / per * per;
-}
 // The 2D walks: runs of 32.  Level 14, FP64 apply / Jacobi: 380.7 / 565.6 us
 // with runs of 32, 399 / 586 with one chunk per XCD, 384.8 / 566 and 377 / 564
 // with 16 and 64 (two triangles at level 12: 58.0 / 82.3, 62.1 / 86.9, 58.3 /

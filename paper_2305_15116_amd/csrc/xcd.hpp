@@ -1,0 +1,74 @@
+// Which workgroup a block of a launch takes, for the 8 XCDs that receive blocks
+// in turn, and the launches' grids.  -1: none.
+#pragma once
+
+#include "mf_internal.hpp"
+
+namespace mf {
+namespace wave {
+
+// Each XCD works through one contiguous chunk of the natural order:
+// neighbouring strips then share that XCD's L2.
+MF_HD int xcd_wg_at(int block, int nwg) {
+  const int chunk = (nwg + kXCD - 1) / kXCD;
+  const int k = block % kXCD, j = block / kXCD;
+  if (j >= chunk) return -1;
+  const int n = k * chunk + j;
+  return n < nwg ? n : -1;
+}
+inline int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
+
+// The same for launches of at least `from` workgroups with runs of 2^shift
+// consecutive workgroups dealt to the XCDs in turn: neighbours still share an
+// L2, and the launch as a whole moves through memory in one front instead of
+// eight.  Smaller launches (whose data the caches hold) keep one chunk per XCD.
+struct XcdRuns {
+  int from, shift;
+};
+constexpr XcdRuns kNoRuns{0x7fffffff, 0};
+MF_HD int xcd_wg_at(int block, int nwg, XcdRuns r) {
+  if (nwg < r.from) return xcd_wg_at(block, nwg);
+  const int k = block % kXCD, j = block / kXCD;
+  const int n = (((j >> r.shift) * kXCD + k) << r.shift) + (j & ((1 << r.shift) - 1));
+  return n < nwg ? n : -1;
+}
+inline int xcd_grid_runs(int nwg, XcdRuns r) {
+  if (nwg < r.from) return xcd_grid(nwg);
+  const int per = kXCD << r.shift;
+  return (nwg + per - 1) / per * per;
+}
+
+// The same, and in smaller launches the first `lead` workgroups and the next
+// `lead2` in chunks of their own.  They hold tiles of other kinds (copies of shared
+// DoFs, other boundary points) that take longer than the walk's; at the head of the
+// first chunk they all fall to one XCD (512 triangles at level 6: FP64 apply 10.2
+// us, 14.9 so; P2 10.4 and 23; 32 at level 9, two FP32 sweeps 32.4 and 38.5).  Up
+// to kLeadMin of them, one for each CU of that XCD, stay there: they share their CUs with
+// fewer others than anywhere else (two triangles at level 11, eight of them:
+// FP32 P2 9.8 us, 11.4 dealt out).
+constexpr int kLeadMin = 32;
+MF_HD int xcd_head(int lead) { return lead > kLeadMin ? kXCD * ((lead + kXCD - 1) / kXCD) : 0; }
+MF_HD int xcd_wg_at(int block, int nwg, int lead, int lead2, XcdRuns r) {
+  if (nwg >= r.from) return xcd_wg_at(block, nwg, r);
+  int first = 0;
+  for (int l : {lead, lead2}) {
+    const int head = xcd_head(l);
+    if (block < head) {
+      const int n = xcd_wg_at(block, l);
+      return n < 0 ? -1 : first + n;
+    }
+    block -= head;
+    if (head > 0) first += l;
+    else if (l > 0) break;  // (it stays before what follows)
+  }
+  const int n = xcd_wg_at(block, nwg - first);
+  return n < 0 ? -1 : first + n;
+}
+inline int xcd_grid(int nwg, int lead, int lead2, XcdRuns r) {
+  if (nwg >= r.from) return xcd_grid_runs(nwg, r);
+  const int h = xcd_head(lead), h2 = lead == 0 || h > 0 ? xcd_head(lead2) : 0;
+  return h + h2 + xcd_grid(nwg - (h > 0 ? lead : 0) - (h2 > 0 ? lead2 : 0));
+}
+
+}  // namespace wave
+}  // namespace mf
