@@ -171,14 +171,8 @@ __device__ __forceinline__ double bl_partial(const MacroDev& M, const Geo2& G, d
     const double nb = (double)i * (double)(N - i - 2 * j - 1) * invN3;
     return {fma(nb, bx, G.e2[0] * invN), fma(nb, by, G.e2[1] * invN)};
   };
-  constexpr StencilTable ST = stencil_table(2);
-  double v[7];  // S, SE, W, C, E, NW, N (outside the macro: the point, without a triangle)
-#pragma unroll
-  for (int o = 0; o < 7; ++o) {
-    const int nx = x + ST.off[o][0], ny = y + ST.off[o][1];
-    const bool in = nx >= 0 && ny >= 0 && nx + ny <= N;
-    v[o] = X[M.base + idx2(N, in ? nx : x, in ? ny : y)];
-  }
+  double v[7];  // S, SE, W, C, E, NW, N (outside the macro: some point, without a triangle)
+  neighbours2(X + M.base + idx2(N, x, y), N, x, y, v);
   auto neg = [](V2 a) -> V2 { return {-a.x, -a.y}; };
   double acc = 0.0;
   // edge vectors a, b to neighbours i, j

@@ -9,7 +9,7 @@
 namespace mf {
 
 // Row value of a DoF that is not Dirichlet, from its assembled sum acc; inv = 1
-// / assembled diagonal.
+// / assembled diagonal (Jacobi).
 template <typename T, int MODE>
 __device__ __forceinline__ T row_value(T acc, T xc, T bv, T omega, T inv) {
   if (MODE == kApply || MODE == kApplyDot) return acc;
@@ -30,28 +30,52 @@ __device__ __forceinline__ T iterate(const MacroDev& M, int mask, T omega, T v) 
   return MODE == kJacobi2 ? (omega * Prec<T>::zinv(M, mask)) * v : v;
 }
 
+// The 2D stencil neighbours of point (x, y) of a macro of side N, stored at X
+// (table order): neighbours along x in pairs (8 or 16 bytes), four accesses
+// instead of seven, since the copies of an edge lie a row apart and each access
+// takes a cycle per lane.  Rows and points outside the macro read others of its
+// points, and their values are some point's: the caller drops them.
+template <typename T>
+__device__ __forceinline__ void neighbours2(const T* X, int N, int x, int y, T (&v)[7]) {
+  typedef T Pair __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+  const bool x0 = x == 0, y0 = y == 0, far = x + y == N, first = x0 && !far;  // first: its row's, with a successor
+  const int l = N + 1 - y;                                                     // the row's length
+  const int at = first ? 0 : -1;
+  const Pair m = *(const Pair*)(X + at);                                     // first: C, E; else W, C
+  const Pair s = *(const Pair*)(X + (y0 ? at : -l - 1));                     // S, SE
+  const Pair n = *(const Pair*)(X + (far ? (x0 ? at : l - 2) : l - 1));      // NW, N; far: its predecessor, NW
+  const T e = X[far ? 0 : 1];
+  v[0] = s.x, v[1] = s.y, v[2] = m.x, v[3] = first ? m.x : m.y, v[4] = e, v[5] = far ? n.y : n.x, v[6] = n.y;
+}
+
 // Partial row of one copy of a macro edge or vertex DoF: the partial stencil
-// of its support mask, neighbours outside the macro dropped, table order.
+// of its support mask, neighbours outside the macro dropped, table order.  xc:
+// the iterate at the copy.
 template <typename T, int DIM, int MODE>
-__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X, T omega) {
+__device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k, const T* X, T omega, T& xc) {
   constexpr StencilTable ST = stencil_table(DIM);
   const MacroDev& M = md[k.macro];
   const int N = M.N;
-  int off[15];
+  T v[ST.n];
   if constexpr (DIM == 3) {
+    int off[15];
     nbr_offsets3(N, k.y, k.z, off);
-  } else {
-    const int l = N + 1 - k.y;  // the row's length
 #pragma unroll
-    for (int o = 0; o < ST.n; ++o) off[o] = ST.off[o][0] + (ST.off[o][1] > 0 ? l : ST.off[o][1] < 0 ? -l - 1 : 0);
+    for (int o = 0; o < ST.n; ++o) {
+      const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
+      v[o] = X[nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N ? k.idx + off[o] : k.idx];
+    }
+  } else {
+    neighbours2(X + k.idx, N, k.x, k.y, v);
   }
   T p = T(0);
 #pragma unroll
   for (int o = 0; o < ST.n; ++o) {
     const int nx = k.x + ST.off[o][0], ny = k.y + ST.off[o][1], nz = k.z + ST.off[o][2];
     const bool in = nx >= 0 && ny >= 0 && nz >= 0 && nx + ny + nz <= N;
-    const T v = iterate<T, MODE>(M, support_mask(DIM, N, nx, ny, nz), omega, X[in ? k.idx + off[o] : k.idx]);
-    p = fma(Prec<T>::w(M, k.mask, o), in ? v : T(0), p);
+    const T vo = iterate<T, MODE>(M, support_mask(DIM, N, nx, ny, nz), omega, v[o]);
+    p = fma(Prec<T>::w(M, k.mask, o), in ? vo : T(0), p);
+    if (o == ST.centre) xc = vo;
   }
   return p;
 }
@@ -65,24 +89,39 @@ __device__ __forceinline__ T copy_partial(const MacroDev* md, const EdgeCopy& k,
 // Bound: latency.  In 2D this replaces a launch after every pass that summed
 // the partial rows that the walk wrote: seven triangles at level 8, FP64 apply / Jacobi
 // / residual 8.7 / 9.6 / 9.5 -> 5.1 / 5.9 / 5.6 us, FP32 10.6 / 11.8 / 11.9 -> 7.0 / 7.6 / 7.7;
-// two at level 12 FP32 39.5 / 49.5 / 51.9 -> 33.3 / 43.2 / 45.5.
+// two at level 12 FP32 39.5 / 49.5 / 51.9 -> 33.3 / 43.2 / 45.5.  Meshes of many
+// macros: the accesses, each lane's on a line of its own.  With 2D neighbours one by
+// one, x twice, b at every copy and 40-byte records, 3,200 triangles at level 7
+// took 176 us instead of 166 per FP64 apply, 512 at level 6 20.3 instead of 14.9.
 template <typename T, int DIM, int MODE>
 __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t, double& ss, double& mx) {
   constexpr bool kX = MODE != kNormB;
   constexpr bool kB = MODE != kApply && MODE != kApplyDot;
   const int lane = threadIdx.x & (kWave - 1);
   const EdgeCopy* L = a.edges + t.x0;
+  // (2D: the exchange list, without Dirichlet DoFs)
+  auto fixed = [](const EdgeCopy& k) { return DIM == 3 && k.dirichlet; };
+  // a copy's partial row p, x and b (b of the heads, and of Dirichlet copies)
+  auto load = [&](const EdgeCopy& k, bool live, bool head, T& p, T& xo, T& bo) {
+    p = xo = bo = T(0);
+    if (kB && live && (head || fixed(k))) bo = a.B[k.idx];
+    if (kX && live && fixed(k)) xo = iterate<T, MODE>(a.md[k.macro], k.mask, a.omega, a.X[k.idx]);
+    if (kX && live && !fixed(k)) p = copy_partial<T, DIM, MODE>(a.md, k, a.X, a.omega, xo);
+  };
+  auto inverse = [&](const EdgeCopy& k) {
+    return MODE == kJacobi || MODE == kJacobi2 ? Prec<T>::zinv(a.md[k.macro], k.mask) : T(0);
+  };
   if (t.macro == kEdgeBigTile) {
-    T acc = T(0);
-    if (kX && !L[0].dirichlet)
-      for (int c0 = 0; c0 < t.y0; c0 += kWave) {
-        const int n = min(kWave, t.y0 - c0);
-        const T p = lane < n ? copy_partial<T, DIM, MODE>(a.md, L[c0 + lane], a.X, a.omega) : T(0);
-        for (int i = 0; i < n; ++i) acc += __shfl(p, i, kWave);
-      }
-    const T bh = kB ? a.B[L[0].idx] : T(0);
-    const T xh = kX ? iterate<T, MODE>(a.md[L[0].macro], L[0].mask, a.omega, a.X[L[0].idx]) : T(0);
-    T out = L[0].dirichlet ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)L[0].inv);
+    T acc = T(0), xh = T(0), bh = T(0);
+    for (int c0 = 0; c0 < t.y0; c0 += kWave) {
+      const int n = min(kWave, t.y0 - c0);
+      T p, xo, bo;
+      load(L[c0 + min(lane, n - 1)], lane < n, c0 == 0 && lane == 0, p, xo, bo);
+      if (c0 == 0) xh = __shfl(xo, 0, kWave), bh = __shfl(bo, 0, kWave);
+      if (fixed(L[0])) break;
+      for (int i = 0; kX && i < n; ++i) acc += __shfl(p, i, kWave);
+    }
+    const T out = fixed(L[0]) ? dirichlet_row<T, MODE>(xh, bh) : row_value<T, MODE>(acc, xh, bh, a.omega, inverse(L[0]));
     if (MODE != kNormB)
       for (int c = lane; c < t.y0; c += kWave) a.Y[L[c].idx] = out;
     if (lane == 0) accum<T, MODE>(ss, mx, out, xh);
@@ -93,9 +132,9 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
     if (n == 0) break;
     const bool live = lane < n;
     const EdgeCopy k = L[live ? lane : 0];
-    T p = T(0);
-    if (kX && live && !k.dirichlet) p = copy_partial<T, DIM, MODE>(a.md, k, a.X, a.omega);
-    T acc = T(0);
+    const T inv = inverse(k);
+    T p, xo, bo, acc = T(0);
+    load(k, live, lane == k.head, p, xo, bo);
     if (kX) {
       const int nc = live ? k.copies : 0;
       for (int i = 0; __builtin_amdgcn_ballot_w64(i < nc); ++i) {
@@ -103,9 +142,8 @@ __device__ __forceinline__ void edge_rows(const StencilArgs<T>& a, const Tile& t
         acc += i < nc ? v : T(0);
       }
     }
-    const T xo = kX ? iterate<T, MODE>(a.md[k.macro], k.mask, a.omega, a.X[k.idx]) : T(0), bo = kB ? a.B[k.idx] : T(0);
     const T xh = __shfl(xo, k.head, kWave), bh = __shfl(bo, k.head, kWave);
-    const T out = k.dirichlet ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, (T)k.inv);
+    const T out = fixed(k) ? dirichlet_row<T, MODE>(xo, bo) : row_value<T, MODE>(acc, xh, bh, a.omega, inv);
     if (live) {
       if (MODE != kNormB) a.Y[k.idx] = out;
       if (lane == k.head) accum<T, MODE>(ss, mx, out, xo);

@@ -310,7 +310,6 @@ static void build_edge_tiles2(Level& L) {
       const Copy& k = L.xcopies[c];
       EdgeCopy e{};
       e.idx = L.xcpidx[c];
-      e.inv = L.xgrp_invdiag[g];
       e.macro = k.macro;
       e.x = (uint16_t)k.x, e.y = (uint16_t)k.y;
       e.mask = (uint8_t)support_mask(2, L.N, k.x, k.y, 0);
@@ -437,18 +436,12 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
     const int m0 = support_mask(3, N, k0.x, k0.y, k0.z);
     if (__builtin_popcount(m0) == 3 && N >= kMinFaceN) continue;  // a face point
     if ((m0 == 13 || m0 == 14) && (L.grp_flag[g] & 1)) continue;
-    double diag = 0.0;
-    for (int c = c0; c < c0 + n; ++c) {
-      const Copy& k = L.copies[c];
-      diag += L.md[k.macro].wm[support_mask(3, N, k.x, k.y, k.z)][ST.centre];
-    }
     if (n > kWave || (int32_t)L.edges.size() - first + n > kWave) close();
     const int head = (int)L.edges.size() - first;
     for (int c = c0; c < c0 + n; ++c) {
       const Copy& k = L.copies[c];
       EdgeCopy e{};
       e.idx = L.base[k.macro] + idx3(N, k.x, k.y, k.z);
-      e.inv = diag != 0.0 ? 1.0 / diag : 0.0;
       e.macro = k.macro;
       e.x = (uint16_t)k.x, e.y = (uint16_t)k.y, e.z = (uint16_t)k.z;
       e.mask = (uint8_t)support_mask(3, N, k.x, k.y, k.z);

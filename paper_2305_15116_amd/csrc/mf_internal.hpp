@@ -116,7 +116,6 @@ struct FaceDev {
 // A copy of a macro edge or vertex DoF (3D).
 struct EdgeCopy {
   int64_t idx;  // storage index
-  double inv;   // 1 / assembled diagonal
   int32_t macro;
   uint16_t x, y, z;
   uint8_t mask;          // support mask in its macro
