@@ -114,6 +114,9 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// LDS of a stencil kernel's partials
+constexpr int partials_lds(int mode) { return has_partials(mode) ? 2 * kWavesPerWG * (int)sizeof(double) : 0; }
+
 // One (sum, maximum) partial per workgroup of NW waves, summed in a fixed
 // order, into slot n of part (maxima at np).  Called by every thread.
 template <int NW>

@@ -40,7 +40,7 @@ constexpr int wgs_per_cu() {
 template <typename T, int MODE>
 void run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   const dim3 grid(R == kMaxR3 ? wave::xcd_grid_runs(l.nwg, wave::kRuns3) : wave::xcd_grid(l.nwg)), wg(kWG);
-  const int lds = R == kMaxR3 ? wave::lds_cap(l.nwg, wave::kRuns3, wgs_per_cu<T, MODE>()) : 0;
+  const int lds = R == kMaxR3 ? wave::lds_cap(l.nwg, wave::kRuns3.from, wgs_per_cu<T, MODE>(), partials_lds(MODE)) : 0;
   static_assert(kMaxR3 == 4, "one instance per band height");
   if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, lds, s, l);
   else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, lds, s, l);

@@ -460,7 +460,9 @@ int check_launch() {
 // 298.0 -> 290.6 us; the applies and FP64 lose or gain nothing).
 template <typename T, int MODE>
 int stencil_lds(int nwg) {
-  return wave::lds_cap(nwg, wave::kRuns2, sizeof(T) == 4 && MODE != kApply && MODE != kApplyDot ? 6 : 0);
+  constexpr bool pays = sizeof(T) == 4 && MODE != kApply && MODE != kApplyDot;
+  constexpr int own = sizeof(T) * kWavesPerWG * 256 + partials_lds(MODE);
+  return pays ? wave::lds_cap(nwg, wave::kRuns2.from, 5, own) : 0;
 }
 
 template <typename T, int MODE>

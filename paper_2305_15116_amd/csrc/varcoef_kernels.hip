@@ -169,7 +169,7 @@ int run_varcoef(const Level& L, const void* k, const void* x, void* y, hipStream
   // -> 78)
   if (nwg > 0)
     hipLaunchKernelGGL(varcoef_kernel<T>, dim3(wave::xcd_grid_runs(nwg, wave::kRuns2)), dim3(kWG),
-                       wave::lds_cap(nwg, wave::kRuns2, 5), s, tiles, nwg, L.dev.md,
+                       wave::lds_cap(nwg, wave::kRuns2.from, 5, 0), s, tiles, nwg, L.dev.md,
                        (const T*)k, (const T*)x, (T*)y);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));

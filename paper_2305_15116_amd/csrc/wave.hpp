@@ -54,16 +54,5 @@ constexpr XcdRuns kRuns2{3000, 5};
 // (runs of 4: 74.8 / 94.3 / 93.7, of 64: 76.8 / 98.9 / 98.7).
 constexpr XcdRuns kRuns3{1000, 4};
 
-// Dynamic LDS (unused) that lets at most n workgroups share a CU: fewer waves
-// at once keep the front of a launch that streams from memory compact, which
-// the memory rewards more than further loads in flight.  (LDS is granted in
-// steps of 1280 bytes and beside a kernel's own, so at the edge it may be one
-// fewer.)  Only for launches of
-// at least r.from workgroups.
-inline int lds_cap(int nwg, XcdRuns r, int n) {
-  constexpr int kLds = 160 * 1024;
-  return nwg < r.from || n <= 0 ? 0 : 2 * kLds / (2 * n + 1);
-}
-
 }  // namespace wave
 }  // namespace mf

@@ -70,5 +70,16 @@ inline int xcd_grid(int nwg, int lead, int lead2, XcdRuns r) {
   return h + h2 + xcd_grid(nwg - (h > 0 ? lead : 0) - (h2 > 0 ? lead2 : 0));
 }
 
+// Dynamic LDS (unused) that lets at most n workgroups of a kernel with `own` bytes
+// of LDS share a CU, in launches of at least `from` workgroups: fewer waves at once
+// keep the front of a launch that streams from memory compact, which the memory
+// rewards more than further loads in flight.  n workgroups and a half would fill
+// the CU, so that the steps LDS is granted in do not matter (up to n = 8).
+constexpr int kLdsPerCu = 160 * 1024, kLdsStep = 1280;
+inline int lds_cap(int nwg, int from, int n, int own) {
+  const int bytes = 2 * kLdsPerCu / (2 * n + 1);
+  return nwg < from || n <= 0 || own >= bytes ? 0 : bytes - own;
+}
+
 }  // namespace wave
 }  // namespace mf

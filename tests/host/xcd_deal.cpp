@@ -1,6 +1,7 @@
 // Which workgroups the blocks of a launch take (xcd.hpp), over launches of many
 // sizes: every workgroup exactly once, and no XCD more than its share of either
 // leading kind by more than one, where these are more than stay on one XCD.
+// Then the cap of workgroups per CU by unused LDS.
 #include <cstdio>
 #include <vector>
 
@@ -41,6 +42,13 @@ int main() {
               if (share[k][q] > (l + kXCD - 1) / kXCD) return fail("one XCD takes too many", nwg, lead, lead2);
           }
         }
+  for (int n = 1; n <= 8; ++n)
+    for (int own : {0, 64, 4096, 4160, 8192}) {
+      const int bytes = own + lds_cap(5000, 3000, n, own);
+      const int granted = (bytes + kLdsStep - 1) / kLdsStep * kLdsStep;
+      if (kLdsPerCu / granted != n) return printf("FAIL cap %d with %d bytes: %d\n", n, own, kLdsPerCu / granted), 1;
+    }
+  if (lds_cap(2999, 3000, 4, 0) != 0 || lds_cap(5000, 3000, 0, 0) != 0) return printf("FAIL no cap\n"), 1;
   printf("OK\n");
   return 0;
 }

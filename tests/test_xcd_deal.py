@@ -1,5 +1,5 @@
-"""The mapping of a launch's blocks to workgroups and XCDs (tests/host/xcd_deal.cpp;
-no GPU)."""
+"""The mapping of a launch's blocks to workgroups and XCDs, and the cap of
+workgroups per CU by unused LDS (tests/host/xcd_deal.cpp; no GPU)."""
 import os
 import subprocess
 
