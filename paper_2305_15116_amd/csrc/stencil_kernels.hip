@@ -456,20 +456,22 @@ int check_launch() {
   return MF_OK;
 }
 
-// Large FP32 launches that also read b: five workgroups per CU (level 14, Jacobi
-// 298.0 -> 290.6 us; the applies and FP64 lose or gain nothing).
+// FP32 launches that also read b, on levels whose tiles are mostly interior (N from
+// kCapN on; a batch passes 0): five workgroups per CU (one triangle at level 14,
+// Jacobi 298.0 -> 290.6 us; the applies and FP64 lose or gain nothing).  Tiles on a
+// macro's boundary wait for more than their rows (kCapN).
 template <typename T, int MODE>
-int stencil_lds(int nwg) {
+int stencil_lds(int nwg, int N) {
   constexpr bool pays = sizeof(T) == 4 && MODE != kApply && MODE != kApplyDot;
   constexpr int own = sizeof(T) * kWavesPerWG * 256 + partials_lds(MODE);
-  return pays ? wave::lds_cap(nwg, wave::kRuns2.from, 5, own) : 0;
+  return pays && N >= wave::kCapN ? wave::lds_cap(nwg, wave::kRuns2.from, 5, own) : 0;
 }
 
 template <typename T, int MODE>
-void run_stencil(int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+void run_stencil(int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   if (l.nwg <= 0) return;
   const dim3 grid(wave::xcd_grid(l.nwg, l.lead, 0, wave::kRuns2)), wg(kWG);
-  const int lds = stencil_lds<T, MODE>(l.nwg);
+  const int lds = stencil_lds<T, MODE>(l.nwg, N);
   if (rows == kTileShort[0]) {
     hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileShort[0]>), grid, wg, lds, s, l);
   } else if (rows == kTileShort[1]) {
@@ -482,14 +484,14 @@ void run_stencil(int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
 }
 
 template <typename T>
-void run_stencil(int mode, int rows, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+void run_stencil(int mode, int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   switch (mode) {
-    case kApply: run_stencil<T, kApply>(rows, l, s); break;
-    case kJacobi: run_stencil<T, kJacobi>(rows, l, s); break;
-    case kJacobi2: run_stencil<T, kJacobi2>(rows, l, s); break;
-    case kResidual: run_stencil<T, kResidual>(rows, l, s); break;
-    case kNormB: run_stencil<T, kNormB>(rows, l, s); break;
-    default: run_stencil<T, kApplyDot>(rows, l, s); break;
+    case kApply: run_stencil<T, kApply>(rows, N, l, s); break;
+    case kJacobi: run_stencil<T, kJacobi>(rows, N, l, s); break;
+    case kJacobi2: run_stencil<T, kJacobi2>(rows, N, l, s); break;
+    case kResidual: run_stencil<T, kResidual>(rows, N, l, s); break;
+    case kNormB: run_stencil<T, kNormB>(rows, N, l, s); break;
+    default: run_stencil<T, kApplyDot>(rows, N, l, s); break;
   }
 }
 
@@ -506,7 +508,7 @@ int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const vo
   } else {
     const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
     if (dim == 3) return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
-    run_stencil<T>(mode, L.rows2(dtype_of<T>()), single(a, a.nwg, L.lead2(dtype_of<T>())), s);
+    run_stencil<T>(mode, L.rows2(dtype_of<T>()), L.N, single(a, a.nwg, L.lead2(dtype_of<T>())), s);
   }
   return check_launch();
 }
@@ -525,7 +527,7 @@ int batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
   } else if (op.dim == 3) {
     return launch_stencil3(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
   } else {
-    run_stencil<T>(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
+    run_stencil<T>(op.mode, op.variant, 0, batched<StencilArgs<T>>(op, table), s);
   }
   return check_launch();
 }

@@ -165,11 +165,11 @@ int run_varcoef(const Level& L, const void* k, const void* x, void* y, hipStream
   const bool f32 = sizeof(T) == 4 && !L.tiles_f32.empty();
   const Tile* tiles = (f32 ? L.dev.tiles_f32 : L.dev.tiles) + L.ewgs * kWavesPerWG;
   const int nwg = (int)((f32 ? L.tiles_f32.size() : L.tiles.size()) / kWavesPerWG) - L.ewgs;
-  // five workgroups per CU on large launches (level 14: FP64 578.7 -> 560 us, FP32 301.7 -> 283; level 13 151 -> 149, 79.4
-  // -> 78)
+  // five workgroups per CU on large launches of long rows (level 14: FP64 578.7 -> 560 us, FP32 301.7 -> 283; level 13
+  // 151 -> 149, 79.4 -> 78)
   if (nwg > 0)
     hipLaunchKernelGGL(varcoef_kernel<T>, dim3(wave::xcd_grid_runs(nwg, wave::kRuns2)), dim3(kWG),
-                       wave::lds_cap(nwg, wave::kRuns2.from, 5, 0), s, tiles, nwg, L.dev.md,
+                       L.N >= wave::kCapN ? wave::lds_cap(nwg, wave::kRuns2.from, 5, 0) : 0, s, tiles, nwg, L.dev.md,
                        (const T*)k, (const T*)x, (T*)y);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(MF_EDEVICE, hipGetErrorString(e));
