@@ -50,8 +50,8 @@ int launch_stencil(const mf_mesh* m, const Level& L, int dtype, int mode, const 
 int launch_iface(const mf_mesh* m, const Level& L, int dtype, int mode, const void* x, void* y, const void* b,
                  hipStream_t s);
 
-// 2D variable-coefficient apply: y at every shared, non-Dirichlet DoF of L = the
-// sum of its copies' partial rows, written to every copy.
+// y at every shared, non-Dirichlet DoF of L = the sum of its copies, which hold the
+// macros' parts, written to every copy.
 int launch_exchange_apply(const Level& L, int dtype, void* y, hipStream_t s);
 
 // P2 operator of a 2D mesh at `level` (vector layout: storage of level + 1):

@@ -302,11 +302,12 @@ __device__ __forceinline__ void slice_xy(int S, int r, int& x, int& y) {
 // follow from P's position: 2x + dx = 0 only for x = 0 and dx = 0, and N_f -
 // |2P + d| = 2 (N_c - |P|) - |d| vanishes only on P's far face with |d| = 0.
 // Rows outside the macro read the point itself.  load() issues every load,
-// store() sums and writes: 0 at Dirichlet points, nothing at shared ones.
+// store() sums and writes: 0 at Dirichlet points, nothing at shared ones (without
+// boundary tiles, nb = 0: the macro's part).
 template <typename T, int DIM>
 struct RestrictCell {
   typedef T Pair __attribute__((ext_vector_type(2), aligned(sizeof(T))));
-  bool live, x0, y0, z0, far, first;
+  bool live, x0, y0, z0, far, first, parts;
   int own, mask, out;  // out: the coarse point's masks (dir, shared) as bits 0, 1
   T* at;
   Pair A, B, Cc, D, E, Ff, G;
@@ -316,6 +317,7 @@ struct RestrictCell {
     const MacroC C = load_macro(a.mdc, sg.macro);
     const MacroC F = load_macro(a.mdf, sg.macro);
     const int z = DIM == 3 ? sg.z : 0, S = C.N - z, P = (S + 1) * (S + 2) / 2;
+    parts = a.nb == 0;
     int r = sg.x0 + (int)(threadIdx.x & (kWave - 1)), x, y;
     live = r < P;
     r = min(r, P - 1);
@@ -369,7 +371,7 @@ struct RestrictCell {
       const bool use = in && (m == full_mask(DIM) || ((own >> m) & 1));
       acc += use ? (s == ST.centre ? T(1) : T(0.5)) * v[s] : T(0);
     }
-    if (live && (out & 3) != 2) *at = out & 1 ? T(0) : acc;
+    if (live && (parts || (out & 3) != 2)) *at = out & 1 ? T(0) : acc;
   }
 };
 

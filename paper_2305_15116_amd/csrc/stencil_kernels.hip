@@ -385,8 +385,8 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
 // ------------------------------------------------------------------ exchange
 
 // One DoF shared by several macros and not Dirichlet: its copies hold partial
-// rows of the variable-coefficient walk; sum them in fixed macro order and write
-// the row to every copy.  (With tiles of edge copies in the walk's own launch, as
+// rows of the variable-coefficient walk, or the macros' parts of a restriction; sum
+// them in fixed macro order and write the row to every copy.  (With tiles of edge copies in the walk's own launch, as
 // the other 2D passes have them, that walk was slower on large levels: five
 // triangles at level 11 54.0 -> 60.9 us, though seven at level 7 took 5.9 instead of 7.8.)
 template <typename T>

@@ -9,6 +9,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "launch.hpp"
 #include "rows.hpp"
 #include "walk3d.hpp"
@@ -75,8 +77,9 @@ __global__ __launch_bounds__(kWG) void fill_random_kernel(const Tile* __restrict
 
 
 
-// b_c = P^T r_f.  Workgroups 0 .. a.nb - 1 take the coarse DoFs that macros
-// share, whose copies' parts they sum in list order and write to every copy:
+// b_c = P^T r_f.  Workgroups 0 .. a.nb - 1 (none where a second launch sums the
+// copies) take
+// the coarse DoFs that macros share, whose copies' parts they sum in list order and write to every copy:
 // an edge tile (a lane per copy; kEdgeBigTile: one DoF of more than 64) or a
 // face tile (waves 2 c and 2 c + 1: the two copies of 64 points).  The others
 // take every other coarse point, 64 per wave and step (two segments at a time
@@ -445,13 +448,30 @@ int launch_fill_random(const mf_mesh* m, const Level& L, int dtype, uint64_t see
   return check_launch();
 }
 
+// Whether the copies of shared DoFs get their macro's part from the walk over all
+// coarse points and a second launch sums them: that reads each copy once where
+// the tiles gather 15 fine points per copy, each on a line of its own.  One launch /
+// two, us: 384 tets at level 6 (675,000 copies) FP64 70 / 58, FP32 46.5 / 42; 1,296 at
+// level 5 (594,000) 43.1 / 38.6, 33.0 / 34.7; 3,072 at level 4 (359,000) 26.8 / 30.5, 24.4 /
+// 26.2; 3,200 triangles at level 6 (302,000) 24.4 / 21.6, 18.4 / 17.6; 512 at level 8
+// (188,000) 37.7 / 38.1, 25.8 / 27.9.  The sums are the same, in the same order.
+static bool restrict_by_parts(int dim, int dtype, const Level& C) {
+  return (int64_t)C.xcopies.size() > (dim == 2 ? 1 << 18 : (dtype == MF_F64 ? 1 << 19 : 5 << 17));
+}
+
 int launch_restrict(const mf_mesh* m, const Level& F, const Level& C, int dtype, const void* rf, void* bc,
                     hipStream_t s) {
-  const int nwg = restrict_blocks(C);
+  const bool parts = restrict_by_parts(m->dim, dtype, C);
+  const int nwg = parts ? transfer_blocks((int)C.psegs.size()) : restrict_blocks(C);
   if (nwg == 0) return MF_OK;
-  if (dtype == MF_F64) run_transfer<double>(true, m->dim, single(restrict_args<double>(F, C, rf, bc), nwg), s);
-  else run_transfer<float>(true, m->dim, single(restrict_args<float>(F, C, rf, bc), nwg), s);
-  return check_launch();
+  auto run = [&](auto a) {
+    if (parts) a.nb = 0;
+    run_transfer<std::remove_pointer_t<decltype(a.dst)>>(true, m->dim, single(a, nwg), s);
+  };
+  if (dtype == MF_F64) run(restrict_args<double>(F, C, rf, bc));
+  else run(restrict_args<float>(F, C, rf, bc));
+  const int rc = check_launch();
+  return rc || !parts ? rc : launch_exchange_apply(C, dtype, bc, s);
 }
 
 int launch_prolong_add(const mf_mesh* m, const Level& F, const Level& C, int dtype, const void* ec, void* xf,
