@@ -342,10 +342,13 @@ __device__ __forceinline__ void vc_walk3(const Tile& t, const MacroDev& M, const
 // Macro-boundary points: one lane per point and copy, 24 element rows at most,
 // each the coefficient sum of its tet times its row of the element matrix.
 // Every vertex of a tet around a point is the point or one of its 15 stencil
-// neighbours.  Bound: the latency of the gathers (rows of a face lie a slice or
-// a row apart).  A workgroup per tile, with a face's two copies in two waves,
-// beside the walk's launch: in one kernel with it, the boundary's registers
-// made the walk spill.
+// neighbours.  Bound: the gathers (rows of a face lie a slice or a row apart, and
+// the copies of edges and vertices have a macro per lane).  A workgroup per tile,
+// with a face's two copies in two waves, beside the walk's launch: in one kernel with
+// it, the boundary's registers made the walk spill.  Against all 96 entries of
+// the six matrices (256 registers in FP64): cube at level 7 FP64 27.7 -> 24.6 us, level
+// 8 137 -> 129; 3,072 tets at level 3 FP64 109 -> 38, FP32 35.8 -> 28.4, 384 at level 5
+// FP64 87 -> 63.
 
 // Index into the 15 stencil offsets of lattice offset d (-1 if none).
 __host__ __device__ constexpr int stencil_slot(int dx, int dy, int dz) {
@@ -378,29 +381,83 @@ __host__ __device__ constexpr bool tet_on_side(int f, int t, int v) {
   return true;
 }
 
+// The element matrices' entries by type, vertex and vertex: a matrix is symmetric,
+// and type t's is that of type 0, 1 or 2 whose tet t is, or is the reflection of
+// through the cell's centre, so 18 entries off the diagonals serve all six
+// (like[t][v][u] among them; -1: v == u).
+struct LikeTable {
+  int8_t like[6][4][4];
+};
+__host__ __device__ constexpr LikeTable like_table() {
+  constexpr ElemTable E = elem_table(3);
+  LikeTable L{};
+  for (int t = 0; t < 6; ++t) {
+    int to[4] = {0, 1, 2, 3}, base = t;
+    for (int b = 0; b < 3 && t >= 3; ++b) {
+      int found = 0;
+      for (int v = 0; v < 4; ++v)
+        for (int u = 0; u < 4; ++u) {
+          bool same = true;
+          for (int d = 0; d < 3; ++d) same = same && E.off[b][u][d] == 1 - E.off[t][v][d];
+          if (same) to[v] = u, ++found;
+        }
+      if (found == 4) {
+        base = b;
+        break;
+      }
+    }
+    for (int v = 0; v < 4; ++v)
+      for (int u = 0; u < 4; ++u) {
+        const int lo = to[v] < to[u] ? to[v] : to[u], hi = to[v] < to[u] ? to[u] : to[v];
+        L.like[t][v][u] = (int8_t)(v == u ? -1 : 6 * base + (lo == 0 ? hi - 1 : lo + hi));
+      }
+  }
+  return L;
+}
+constexpr bool like_table_valid() {
+  constexpr LikeTable L = like_table();
+  for (int t = 0; t < 6; ++t)
+    for (int v = 0; v < 4; ++v)
+      for (int u = 0; u < 4; ++u)
+        if (L.like[t][v][u] >= 18 || (v != u && L.like[t][v][u] < 0)) return false;
+  return true;
+}
+static_assert(like_table_valid(), "18 entries serve all six types");
+
 // Four times the row of a point from the coefficients and values of its
-// stencil neighbours; in(t, v): its type-t tet with the point as vertex v is
-// in the macro; UNIFORM: all lanes have the same macro.
+// stencil neighbours (as the walk's, the sum over its tets' edges at the point);
+// in(t, v): its type-t tet with the point as vertex v is in the macro; UNIFORM:
+// all lanes have the same macro.
 template <bool UNIFORM, typename T, class In>
 __device__ __forceinline__ T vc3_row(const MacroDev& M, const T* kv, const T* xv, In in) {
-  auto entry = [](const T& v) { return UNIFORM ? uniform(v) : v; };
   constexpr ElemTable E = elem_table(3);
+  constexpr LikeTable L = like_table();
+  constexpr int centre = stencil_table(3).centre;
+  T w[18], d[15];
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+      for (int u = v + 1; u < 4; ++u) {
+        const T& e = Prec<T>::K(M, t)[4 * v + u];
+        w[L.like[t][v][u]] = UNIFORM ? uniform(e) : e;
+      }
+  __builtin_amdgcn_sched_barrier(0);  // every load before the sums
+#pragma unroll
+  for (int o = 0; o < 15; ++o) d[o] = xv[o] - xv[centre];
   T acc = T(0);
 #pragma unroll
   for (int t = 0; t < E.ntypes; ++t) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int s0 = tet_slot(t, v, 0), s1 = tet_slot(t, v, 1), s2 = tet_slot(t, v, 2), s3 = tet_slot(t, v, 3);
-      const T ks = kv[s0] + kv[s1] + kv[s2] + kv[s3];
-      const T* Kt = Prec<T>::K(M, t) + 4 * v;
-      T r = entry(Kt[0]) * xv[s0];
-      r = fma(entry(Kt[1]), xv[s1], r);
-      r = fma(entry(Kt[2]), xv[s2], r);
-      r = fma(entry(Kt[3]), xv[s3], r);
+      const T ks = kv[tet_slot(t, v, 0)] + kv[tet_slot(t, v, 1)] + kv[tet_slot(t, v, 2)] + kv[tet_slot(t, v, 3)];
+      T r = T(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u != v) r = fma(w[L.like[t][v][u]], d[tet_slot(t, v, u)], r);
       acc = in(t, v) ? fma(ks, r, acc) : acc;
     }
-    // per-lane matrices: one type's entries in registers at a time
-    if (!UNIFORM) __builtin_amdgcn_sched_barrier(0);
   }
   return acc;
 }
@@ -547,7 +604,11 @@ int run_varcoef3d(const Level& L, const void* k, const void* x, void* y, hipStre
     else run_vc3<T, 1>(a, nwg, s);
   }
   const int nb = (int)L.btiles.size();
-  if (nb > 0) hipLaunchKernelGGL((varcoef3d_boundary_kernel<T>), dim3(nb), dim3(kWG), 0, s, a);
+  // five workgroups per CU where there are face tiles (FP32, which seven would fit: 48 tets at level 6 32.5 -> 30.6 us, 3,072
+  // at level 4 62 -> 63.6; without face tiles, at level 3, 28.4 -> 31.4)
+  if (nb > 0)
+    hipLaunchKernelGGL((varcoef3d_boundary_kernel<T>), dim3(nb), dim3(kWG),
+                       L.N >= kMinFaceN ? wave::lds_cap(nb, 0, 5, kWG * (int)sizeof(T)) : 0, s, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }
