@@ -165,6 +165,13 @@ void parallel_for(size_t n, int64_t work, F&& fn) {
   for (auto& t : th) t.join();
 }
 
+// Points whose support is exactly a primitive of p vertices.
+int64_t prim_points(int N, int p) {
+  if (p == 1) return 1;
+  if (p == 2) return std::max(N - 1, 0);
+  return N >= 2 ? (int64_t)(N - 1) * (N - 2) / 2 : 0;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- topology
@@ -274,7 +281,8 @@ static std::vector<Tile> column_tiles(int N, int64_t nc, const Shape3& sh) {
 static void set_assembled_diagonals(const mf_mesh* m, Level& L) {
   const StencilTable ST = stencil_table(m->dim);
   for (int64_t c = 0; c < m->nc; ++c) L.md[c].zinv[full_mask(m->dim)] = L.md[c].inv_diag;
-  for (const Prim& P : m->prims) {
+  parallel_for(m->prims.size(), 512 * (int64_t)m->prims.size(), [&](size_t i) {
+    const Prim& P = m->prims[i];
     auto mask = [&](size_t k) {
       int s = 0;
       for (size_t j = 0; j < P.v.size(); ++j) s |= 1 << P.local[k][j];
@@ -284,47 +292,70 @@ static void set_assembled_diagonals(const mf_mesh* m, Level& L) {
     for (size_t k = 0; k < P.cell.size(); ++k) diag += L.md[P.cell[k]].wm[mask(k)][ST.centre];
     for (size_t k = 0; k < P.cell.size(); ++k)
       L.md[P.cell[k]].zinv[mask(k)] = P.dirichlet || diag == 0.0 ? 0.0 : 1.0 / diag;
-  }
+  });
   for (int64_t c = 0; c < m->nc; ++c)
     for (int s = 0; s < 16; ++s) L.md[c].zinvf[s] = (float)L.md[c].zinv[s];
 }
 
+// Cuts DoFs of n copies each, one after the other in Level::edges, into edge tiles
+// of up to 64 copies per step and `steps` steps (more than 64 copies: a tile of
+// its own, kEdgeBigTile), and notes the lane of each DoF's first copy.
+struct EdgeCutter {
+  int steps;
+  std::vector<Tile>& out;
+  std::vector<uint8_t> head;
+  int32_t first = 0, at = 0, n[2] = {0, 0}, step = 0;  // of the open tile; at: the next copy
+  void close() {
+    if (n[0] > 0) out.push_back({kEdgeTile, first, n[0], n[1]});
+    first = at;
+    n[0] = n[1] = step = 0;
+  }
+  void add(int nc) {
+    if (nc > kWave) {
+      close();
+      at += nc;
+      out.push_back({kEdgeBigTile, first, nc, 0});
+      first = at;
+      head.push_back(0);
+      return;
+    }
+    if (n[step] + nc > kWave && ++step == steps) close();
+    head.push_back((uint8_t)n[step]);
+    at += nc;
+    n[step] += nc;
+  }
+};
+
+// The records of a DoF's nc copies from e on.
+static void set_copies(EdgeCopy* e, int dim, int N, const Copy* k, const int64_t* idx, int nc, int head, bool dirichlet) {
+  for (int c = 0; c < nc; ++c) {
+    e[c].idx = idx[c];
+    e[c].macro = k[c].macro;
+    e[c].x = (uint16_t)k[c].x, e[c].y = (uint16_t)k[c].y, e[c].z = (uint16_t)k[c].z;
+    e[c].mask = (uint8_t)support_mask(dim, N, k[c].x, k[c].y, k[c].z);
+    e[c].head = (uint8_t)head;
+    e[c].copies = (uint8_t)(nc > kWave ? 0 : nc);
+    e[c].dirichlet = dirichlet ? 1 : 0;
+  }
+}
+
 // Tiles of a 2D level's DoFs that macros share (the exchange list), at the head
-// of both tile lists so that they start first: up to 64 copies per step, two
-// steps per tile.
+// of both tile lists so that they start first.
 static void build_edge_tiles2(Level& L) {
   std::vector<Tile>& out = L.tiles;
-  int32_t first = 0, n[2] = {0, 0}, step = 0;  // of the open tile
-  auto close = [&] {
-    if (n[0] > 0) out.push_back({kEdgeTile, first, n[0], n[1]});
-    first = (int32_t)L.edges.size();
-    n[0] = n[1] = step = 0;
-  };
-  L.edges.reserve(L.xcopies.size());
-  for (int64_t g = 0; g < L.nxgroups(); ++g) {
-    const int c0 = L.xgrp_ptr[g], nc = L.xgrp_ptr[g + 1] - c0;
-    if (nc <= kWave && n[step] + nc > kWave && ++step == 2) close();
-    if (nc > kWave) close();
-    const int head = n[step];
-    for (int c = c0; c < c0 + nc; ++c) {
-      const Copy& k = L.xcopies[c];
-      EdgeCopy e{};
-      e.idx = L.xcpidx[c];
-      e.macro = k.macro;
-      e.x = (uint16_t)k.x, e.y = (uint16_t)k.y;
-      e.mask = (uint8_t)support_mask(2, L.N, k.x, k.y, 0);
-      e.head = (uint8_t)(nc > kWave ? 0 : head);
-      e.copies = (uint8_t)(nc > kWave ? 0 : nc);
-      L.edges.push_back(e);
+  const int64_t ng = L.nxgroups();
+  EdgeCutter cut{2, out};
+  cut.head.reserve(ng);
+  for (int64_t g = 0; g < ng; ++g) cut.add(L.xgrp_ptr[g + 1] - L.xgrp_ptr[g]);
+  cut.close();
+  L.edges.resize(L.xcopies.size());
+  constexpr int64_t kChunk = 1 << 12;
+  parallel_for((size_t)((ng + kChunk - 1) / kChunk), 8 * (int64_t)L.edges.size(), [&](size_t k) {
+    for (int64_t g = (int64_t)k * kChunk; g < std::min(ng, (int64_t)(k + 1) * kChunk); ++g) {
+      const int c = L.xgrp_ptr[g];
+      set_copies(&L.edges[c], 2, L.N, &L.xcopies[c], &L.xcpidx[c], L.xgrp_ptr[g + 1] - c, cut.head[g], false);
     }
-    if (nc > kWave) {
-      out.push_back({kEdgeBigTile, first, nc, 0});
-      first = (int32_t)L.edges.size();
-    } else {
-      n[step] += nc;
-    }
-  }
-  close();
+  });
   L.btiles = out;
   while (out.size() % kWavesPerWG) out.push_back({-1, 0, 0, 0});
   L.ewgs = (int)(out.size() / kWavesPerWG);
@@ -419,44 +450,40 @@ static void build_tiles3(const mf_mesh* m, Level& L) {
     cut(bnd, face_runs(N));
     cut(L.btiles, kFaceRunsWG);
   }
-  // edge and vertex DoFs (the all-groups list's other groups; all of them on the smallest levels, except those
-  // that the walk writes)
-  int32_t first = 0;  // of the open tile
-  auto close = [&] {
-    const int32_t n = (int32_t)L.edges.size() - first;
-    if (n > 0) {
-      bnd.push_back({kEdgeTile, first, n, 0});
-      L.btiles.push_back(bnd.back());
-    }
-    first = (int32_t)L.edges.size();
+  // edge and vertex DoFs, and on the smallest levels the inner points of the faces that the walk
+  // does not write (whole primitives of the all-groups list)
+  struct Range {
+    size_t prim;
+    int64_t n, copies, dof, edge;  // its DoFs; its first of the list's copies, of the DoFs and of the edges
   };
-  for (int64_t g = 0; g < L.ngroups(); ++g) {
-    const int c0 = L.grp_ptr[g], n = L.grp_ptr[g + 1] - c0;
-    const Copy& k0 = L.copies[c0];
-    const int m0 = support_mask(3, N, k0.x, k0.y, k0.z);
-    if (__builtin_popcount(m0) == 3 && N >= kMinFaceN) continue;  // a face point
-    if ((m0 == 13 || m0 == 14) && (L.grp_flag[g] & 1)) continue;
-    if (n > kWave || (int32_t)L.edges.size() - first + n > kWave) close();
-    const int head = (int)L.edges.size() - first;
-    for (int c = c0; c < c0 + n; ++c) {
-      const Copy& k = L.copies[c];
-      EdgeCopy e{};
-      e.idx = L.base[k.macro] + idx3(N, k.x, k.y, k.z);
-      e.macro = k.macro;
-      e.x = (uint16_t)k.x, e.y = (uint16_t)k.y, e.z = (uint16_t)k.z;
-      e.mask = (uint8_t)support_mask(3, N, k.x, k.y, k.z);
-      e.head = (uint8_t)(n > kWave ? 0 : head);
-      e.copies = (uint8_t)(n > kWave ? 0 : n);
-      e.dirichlet = L.grp_flag[g] & 1;
-      L.edges.push_back(e);
+  std::vector<Range> ranges;
+  std::vector<Tile> etiles;
+  EdgeCutter cut{1, etiles};
+  int64_t c0 = 0;
+  for (size_t i = 0; i < m->prims.size(); ++i) {
+    const Prim& P = m->prims[i];
+    const int64_t n = prim_points(N, (int)P.v.size()), nc = (int64_t)P.cell.size();
+    int mask = 0;
+    for (size_t j = 0; j < P.v.size(); ++j) mask |= 1 << P.local[0][j];
+    const bool face = P.v.size() == 3;
+    if (n > 0 && !(face && N >= kMinFaceN) && !((mask == 13 || mask == 14) && P.dirichlet)) {
+      ranges.push_back({i, n, c0, (int64_t)cut.head.size(), cut.at});
+      for (int64_t g = 0; g < n; ++g) cut.add((int)nc);
     }
-    if (n > kWave) {
-      bnd.push_back({kEdgeBigTile, first, n, 0});
-      L.btiles.push_back(bnd.back());
-      first = (int32_t)L.edges.size();
-    }
+    c0 += n * nc;
   }
-  close();
+  cut.close();
+  L.edges.resize((size_t)cut.at);
+  parallel_for(ranges.size(), 8 * (int64_t)cut.at, [&](size_t r) {
+    const Range& R = ranges[r];
+    const Prim& P = m->prims[R.prim];
+    const int64_t nc = (int64_t)P.cell.size();
+    for (int64_t g = 0; g < R.n; ++g)
+      set_copies(&L.edges[R.edge + g * nc], 3, N, &L.copies[R.copies + g * nc], &L.cpidx[R.copies + g * nc], (int)nc,
+                 cut.head[R.dof + g], P.dirichlet);
+  });
+  bnd.insert(bnd.end(), etiles.begin(), etiles.end());
+  L.btiles.insert(L.btiles.end(), etiles.begin(), etiles.end());
   while (bnd.size() % kWavesPerWG) bnd.push_back({-1, 0, 0, 0});
   // the boundary's workgroups are spread evenly among the walk's (each XCD
   // takes a contiguous chunk of workgroups, so appended ones would all land on one)
@@ -559,14 +586,9 @@ static int build_level(mf_mesh* m, int level, Level& L) {
   // primitives are filled in parallel.
   const size_t np = m->prims.size();
   std::vector<int64_t> g_off(np + 1, 0), c_off(np + 1, 0), x_off(np + 1, 0), xc_off(np + 1, 0);
-  auto prim_points = [N](int p) -> int64_t {
-    if (p == 1) return 1;
-    if (p == 2) return std::max(N - 1, 0);
-    return N >= 2 ? (int64_t)(N - 1) * (N - 2) / 2 : 0;
-  };
   for (size_t i = 0; i < np; ++i) {
     const Prim& P = m->prims[i];
-    const int64_t n = prim_points((int)P.v.size()), nc = (int64_t)P.cell.size();
+    const int64_t n = prim_points(N, (int)P.v.size()), nc = (int64_t)P.cell.size();
     const bool xg = !P.dirichlet && nc >= 2;
     g_off[i + 1] = g_off[i] + n;
     c_off[i + 1] = c_off[i] + n * nc;

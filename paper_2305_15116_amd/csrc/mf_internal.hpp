@@ -121,6 +121,7 @@ struct EdgeCopy {
   uint8_t mask;          // support mask in its macro
   uint8_t head, copies;  // lane of the DoF's first copy in its tile, number of copies (kEdgeTile)
   uint8_t dirichlet;
+  EdgeCopy() {}  // (left unset: lists of them are filled by several threads)
 };
 
 // Per-macro, per-level constants.  wm[s] is the (partial) stencil of a point
