@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <string>
+
 #include "launch.hpp"
 #include "walk3d.hpp"
 
@@ -38,29 +40,30 @@ constexpr int wgs_per_cu() {
 }
 
 template <typename T, int MODE>
-void run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+int run(int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   const dim3 grid(R == kMaxR3 ? wave::xcd_grid_runs(l.nwg, wave::kRuns3) : wave::xcd_grid(l.nwg)), wg(kWG);
   const int lds = R == kMaxR3 ? wave::lds_cap(l.nwg, wave::kRuns3.from, wgs_per_cu<T, MODE>(), partials_lds(MODE)) : 0;
   static_assert(kMaxR3 == 4, "one instance per band height");
   if (R == 4) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 4>), grid, wg, lds, s, l);
   else if (R == 3) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 3>), grid, wg, lds, s, l);
   else if (R == 2) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 2>), grid, wg, lds, s, l);
-  else hipLaunchKernelGGL((stencil3_kernel<T, MODE, 1>), grid, wg, lds, s, l);
+  else if (R == 1) hipLaunchKernelGGL((stencil3_kernel<T, MODE, 1>), grid, wg, lds, s, l);
+  else return set_error(MF_EINVAL, "internal: no 3D walk over bands of " + std::to_string(R) + " rows");
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }
 
 template <typename T>
 int dispatch(int mode, int R, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   if (l.nwg <= 0) return MF_OK;
   switch (mode) {
-    case kApply: run<T, kApply>(R, l, s); break;
-    case kJacobi: run<T, kJacobi>(R, l, s); break;
-    case kJacobi2: run<T, kJacobi2>(R, l, s); break;
-    case kResidual: run<T, kResidual>(R, l, s); break;
-    case kNormB: run<T, kNormB>(R, l, s); break;
-    default: run<T, kApplyDot>(R, l, s); break;
+    case kApply: return run<T, kApply>(R, l, s);
+    case kJacobi: return run<T, kJacobi>(R, l, s);
+    case kJacobi2: return run<T, kJacobi2>(R, l, s);
+    case kResidual: return run<T, kResidual>(R, l, s);
+    case kNormB: return run<T, kNormB>(R, l, s);
+    default: return run<T, kApplyDot>(R, l, s);
   }
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }
 
 }  // namespace

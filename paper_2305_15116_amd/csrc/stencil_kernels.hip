@@ -25,6 +25,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <string>
+
 #include "edges.hpp"
 #include "launch.hpp"
 #include "rows.hpp"
@@ -468,8 +470,8 @@ int stencil_lds(int nwg, int N) {
 }
 
 template <typename T, int MODE>
-void run_stencil(int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
-  if (l.nwg <= 0) return;
+int run_stencil(int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+  if (l.nwg <= 0) return MF_OK;
   const dim3 grid(wave::xcd_grid(l.nwg, l.lead, 0, wave::kRuns2)), wg(kWG);
   const int lds = stencil_lds<T, MODE>(l.nwg, N);
   if (rows == kTileShort[0]) {
@@ -479,19 +481,26 @@ void run_stencil(int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s
   } else if (rows == kTileH2) {
     hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileH2>), grid, wg, lds, s, l);
   } else {
-    if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileH2F>), grid, wg, lds, s, l);
+    if constexpr (sizeof(T) == 4) {
+      if (rows == kTileH2F) {
+        hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileH2F>), grid, wg, lds, s, l);
+        return check_launch();
+      }
+    }
+    return set_error(MF_EINVAL, "internal: no 2D walk over tiles of " + std::to_string(rows) + " rows");
   }
+  return check_launch();
 }
 
 template <typename T>
-void run_stencil(int mode, int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
+int run_stencil(int mode, int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   switch (mode) {
-    case kApply: run_stencil<T, kApply>(rows, N, l, s); break;
-    case kJacobi: run_stencil<T, kJacobi>(rows, N, l, s); break;
-    case kJacobi2: run_stencil<T, kJacobi2>(rows, N, l, s); break;
-    case kResidual: run_stencil<T, kResidual>(rows, N, l, s); break;
-    case kNormB: run_stencil<T, kNormB>(rows, N, l, s); break;
-    default: run_stencil<T, kApplyDot>(rows, N, l, s); break;
+    case kApply: return run_stencil<T, kApply>(rows, N, l, s);
+    case kJacobi: return run_stencil<T, kJacobi>(rows, N, l, s);
+    case kJacobi2: return run_stencil<T, kJacobi2>(rows, N, l, s);
+    case kResidual: return run_stencil<T, kResidual>(rows, N, l, s);
+    case kNormB: return run_stencil<T, kNormB>(rows, N, l, s);
+    default: return run_stencil<T, kApplyDot>(rows, N, l, s);
   }
 }
 
@@ -508,7 +517,7 @@ int dispatch(int dim, int mode, const Level& L, const void* x, void* y, const vo
   } else {
     const StencilArgs<T> a = stencil_args<T>(L, x, y, b, omega, part);
     if (dim == 3) return launch_stencil3(mode, shape3(L.N).R, single(a, a.nwg), s);
-    run_stencil<T>(mode, L.rows2(dtype_of<T>()), L.N, single(a, a.nwg, L.lead2(dtype_of<T>())), s);
+    return run_stencil<T>(mode, L.rows2(dtype_of<T>()), L.N, single(a, a.nwg, L.lead2(dtype_of<T>())), s);
   }
   return check_launch();
 }
@@ -527,7 +536,7 @@ int batch_dispatch(const BatchOp& op, const char* table, hipStream_t s) {
   } else if (op.dim == 3) {
     return launch_stencil3(op.mode, op.variant, batched<StencilArgs<T>>(op, table), s);
   } else {
-    run_stencil<T>(op.mode, op.variant, 0, batched<StencilArgs<T>>(op, table), s);
+    return run_stencil<T>(op.mode, op.variant, 0, batched<StencilArgs<T>>(op, table), s);
   }
   return check_launch();
 }

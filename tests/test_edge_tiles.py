@@ -1,4 +1,4 @@
-"""The tiles of shared DoFs of host-only meshes (tests/host/edge_tiles.cpp, linked
+"""The tiles of host-only meshes (tests/host/edge_tiles.cpp, tile_shapes.cpp, linked
 with the library; no GPU): strips, grids of many macros, fans whose centre has
 64 and more copies, at the smallest levels and where the lists change kind."""
 import os
@@ -23,12 +23,12 @@ def fan(dim, n):
             W.shuffle_cell_orders(np.array([[0, 1, 2 + i, 2 + (i + 1) % n] for i in range(n)]), 2))
 
 
-def test_every_copy_in_one_tile(tmp_path):
+def _run(source, tmp_path):
     P.lib()
-    exe = str(tmp_path / "edge_tiles")
+    exe = str(tmp_path / "check")
     root = os.path.dirname(HERE)
     subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-                    "-I" + os.path.join(root, "include"), "-I" + build.CSRC, os.path.join(HERE, "host", "edge_tiles.cpp"),
+                    "-I" + os.path.join(root, "include"), "-I" + build.CSRC, os.path.join(HERE, "host", source),
                     build.LIB, "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath," + os.path.dirname(build.LIB),
                     "-Wl,-rpath,/opt/rocm/lib", "-o", exe], check=True)
     meshes = [(W.unit_triangle(), 8), (W.strip_2d(7), 8), (W.strip_2d(44), 8), (grid2(16), 6), (fan(2, 6), 6), (fan(2, 64), 4),
@@ -39,3 +39,11 @@ def test_every_copy_in_one_tile(tmp_path):
         text += [" ".join(repr(float(v)) for v in co.ravel()), " ".join(str(int(v)) for v in ce.ravel())]
     r = subprocess.run([exe], input="\n".join(text), capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "OK", r.stdout
+
+
+def test_every_copy_in_one_tile(tmp_path):
+    _run("edge_tiles.cpp", tmp_path)
+
+
+def test_tile_shapes_have_kernels(tmp_path):
+    _run("tile_shapes.cpp", tmp_path)
