@@ -20,6 +20,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <string>
+
 #include "launch.hpp"
 #include "rows.hpp"
 #include "walk3d.hpp"
@@ -586,9 +588,15 @@ __global__ __launch_bounds__(kWG) void varcoef3d_boundary_kernel(const VarcoefAr
   else if (t.macro != -1 && wv == 0) vc3_edges<T>(a, t);
 }
 
-template <typename T, int R>
-void run_vc3(const VarcoefArgs<T>& a, int nwg, hipStream_t s) {
-  hipLaunchKernelGGL((varcoef3d_kernel<T, R>), dim3(wave::xcd_grid_runs(nwg, wave::kRuns3)), dim3(kWG), 0, s, a, nwg);
+// Bands of R rows: those of shape3_varcoef (FP64 up to 2, FP32 up to 3).
+template <typename T, int R = sizeof(T) == 8 ? 2 : 3>
+int run_vc3(int rows, const VarcoefArgs<T>& a, int nwg, hipStream_t s) {
+  if (rows == R) {
+    hipLaunchKernelGGL((varcoef3d_kernel<T, R>), dim3(wave::xcd_grid_runs(nwg, wave::kRuns3)), dim3(kWG), 0, s, a, nwg);
+    return MF_OK;
+  }
+  if constexpr (R > 1) return run_vc3<T, R - 1>(rows, a, nwg, s);
+  else return set_error(MF_EINVAL, "internal: no variable-coefficient walk over bands of " + std::to_string(rows) + " rows");
 }
 
 template <typename T>
@@ -597,12 +605,8 @@ int run_varcoef3d(const Level& L, const void* k, const void* x, void* y, hipStre
   const int nwg = (int)(L.vtiles[i].size() / kWavesPerWG), R = shape3_varcoef(L.N, i == 1).R;
   const VarcoefArgs<T> a{L.dev.vtiles[i], L.dev.btiles, L.dev.md, L.dev.faces, L.dev.edges,
                          (const T*)k,      (const T*)x,   (T*)y};
-  if (nwg > 0) {
-    if (R == 4) run_vc3<T, 4>(a, nwg, s);
-    else if (R == 3) run_vc3<T, 3>(a, nwg, s);
-    else if (R == 2) run_vc3<T, 2>(a, nwg, s);
-    else run_vc3<T, 1>(a, nwg, s);
-  }
+  if (nwg > 0)
+    if (const int rc = run_vc3<T>(R, a, nwg, s)) return rc;
   const int nb = (int)L.btiles.size();
   // five workgroups per CU where there are face tiles (FP32, which seven would fit: 48 tets at level 6 32.5 -> 30.6 us, 3,072
   // at level 4 62 -> 63.6; without face tiles, at level 3, 28.4 -> 31.4)
