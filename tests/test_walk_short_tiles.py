@@ -27,7 +27,7 @@ def test_every_tile(L, H, U):
 
 
 @pytest.mark.parametrize("H", [2, 4, 8, 16])
-@pytest.mark.parametrize("L", [7, 8, 9])
+@pytest.mark.parametrize("L", [8, 9])  # (level 7 has no such tile)
 def test_two_sweeps_read_no_boundary_point_unclamped(L, H):
     N = 1 << L
     taken = 0
@@ -39,7 +39,7 @@ def test_two_sweeps_read_no_boundary_point_unclamped(L, H):
         for r, off in loads_tile2d_fast(x0, y0, N, H):
             x = off - rs32(N, r)
             assert r >= 1 and (x == x0 - 1 + LANES).all() and x.min() >= 1 and x.max() + r < N, (x0, y0, r)
-    assert taken > 0 or N < 2 * W62 + H
+    assert taken > 0
 
 
 def test_replay_catches_the_margin_of_one_sweep():
