@@ -592,8 +592,7 @@ int batch_create(const mf_solve_opts* opts, int capacity, mf_batch** out) {
   B->o = o;
   B->capacity = capacity;
   (void)hipGetDevice(&B->device);
-  const hipError_t e = hipHostMalloc((void**)&B->hres, sizeof(double) * 4 * capacity,
-                                     hipHostMallocPortable | hipHostMallocMapped);
+  const hipError_t e = hipHostMalloc((void**)&B->hres, sizeof(double) * 4 * capacity, kResultMemory);
   if (e != hipSuccess) {
     delete B;
     return set_error(MF_ENOMEM, std::string("batch buffers: ") + hipGetErrorString(e));

@@ -45,7 +45,7 @@ int check_dtype(int dtype) {
 // (nullptr: out of memory).  It lives until the process ends.
 double* pinned_pair() {
   static thread_local double* pinned = nullptr;
-  if (!pinned && hipHostMalloc((void**)&pinned, 2 * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+  if (!pinned && hipHostMalloc((void**)&pinned, 2 * sizeof(double), kResultMemory) != hipSuccess)
     pinned = nullptr;
   return pinned;
 }

@@ -109,6 +109,11 @@ inline Workspace carve(const mf_mesh* m, int level, int mode, int lc, char* base
 // macros, four microseconds a launch, three -> one.
 inline bool two_from_zero(int sweeps) { return sweeps >= 2; }
 
+// Host memory that reductions write and the host reads after a synchronisation.
+// Coherent whatever the environment says: a batch's second stream is joined by an
+// event, which need not write the device's caches back to the host.
+constexpr unsigned kResultMemory = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+
 inline int default_coarse(int level) { return std::min(2, level); }
 
 // Mixed CG keeps the scale of its FP32 preconditioner input here: the update
