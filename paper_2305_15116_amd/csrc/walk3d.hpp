@@ -224,14 +224,16 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
         T acc = T(0);
         if (kX) {
           // the terms with dx = -1 and dx = +1 are summed in the neighbour's
-          // lane and shifted once each (a shift is two moves in FP64)
+          // lane and shifted once each (a shift is two moves in FP64).  The
+          // point's own term, the largest, comes last: one rounding at its size
+          // (FP32 apply, cube at level 5, 1.5e-8 off; with the term in its place
+          // 2.3e-8, summed in the stencil's order 2.1e-8)
           T l = w[3] * a0[j + 1], r = w[1] * a0[j];
           acc = w[0] * a0[j];
           acc = fma(w[2], a0[j + 1], acc);
           acc = fma(w[4], a1[j - 1], acc);
           l = fma(w[6], a1[j], l);
           r = fma(w[5], a1[j - 1], r);
-          acc = fma(w[7], a1[j], acc);
           l = fma(w[9], a1[j + 1], l);
           r = fma(w[8], a1[j], r);
           acc = fma(w[10], a1[j + 1], acc);
@@ -239,7 +241,7 @@ __device__ __forceinline__ void walk3(const Tile& t, const MacroDev& M, const T*
           r = fma(w[12], a2[j - 1], r);
           acc = fma(w[11], a2[j - 1], acc);
           acc = fma(w[14], a2[j], acc);
-          acc = (acc + up1(l)) + dn1(r);
+          acc = fma(w[7], a1[j], (acc + up1(l)) + dn1(r));
         }
         const T bv = bq[i % 2][j - 1], xc = a1[j];
         const bool wr = wl.writes(j + k);
