@@ -348,9 +348,9 @@ __device__ __forceinline__ void vc_walk3(const Tile& t, const MacroDev& M, const
 // the copies of edges and vertices have a macro per lane).  A workgroup per tile,
 // with a face's two copies in two waves, beside the walk's launch: in one kernel with
 // it, the boundary's registers made the walk spill.  Against all 96 entries of
-// the six matrices (256 registers in FP64): cube at level 7 FP64 27.7 -> 24.6 us, level
-// 8 137 -> 129; 3,072 tets at level 3 FP64 109 -> 38, FP32 35.8 -> 28.4, 384 at level 5
-// FP64 87 -> 63.
+// the six matrices (256 registers in FP64): cube at level 7 FP64 27.7 -> 24.7 us, level
+// 8 137 -> 130; 3,072 tets at level 3 FP64 109 -> 43, FP32 35.8 -> 28.1, 384 at level 5
+// FP64 87 -> 65.
 
 // Index into the 15 stencil offsets of lattice offset d (-1 if none).
 __host__ __device__ constexpr int stencil_slot(int dx, int dy, int dz) {
@@ -385,8 +385,8 @@ __host__ __device__ constexpr bool tet_on_side(int f, int t, int v) {
 
 // The element matrices' entries by type, vertex and vertex: a matrix is symmetric,
 // and type t's is that of type 0, 1 or 2 whose tet t is, or is the reflection of
-// through the cell's centre, so 18 entries off the diagonals serve all six
-// (like[t][v][u] among them; -1: v == u).
+// through the cell's centre, so 30 entries serve all six (like[t][v][u] among
+// them).
 struct LikeTable {
   int8_t like[6][4][4];
 };
@@ -411,7 +411,7 @@ __host__ __device__ constexpr LikeTable like_table() {
     for (int v = 0; v < 4; ++v)
       for (int u = 0; u < 4; ++u) {
         const int lo = to[v] < to[u] ? to[v] : to[u], hi = to[v] < to[u] ? to[u] : to[v];
-        L.like[t][v][u] = (int8_t)(v == u ? -1 : 6 * base + (lo == 0 ? hi - 1 : lo + hi));
+        L.like[t][v][u] = (int8_t)(10 * base + (lo * (7 - lo)) / 2 + hi);
       }
   }
   return L;
@@ -421,43 +421,42 @@ constexpr bool like_table_valid() {
   for (int t = 0; t < 6; ++t)
     for (int v = 0; v < 4; ++v)
       for (int u = 0; u < 4; ++u)
-        if (L.like[t][v][u] >= 18 || (v != u && L.like[t][v][u] < 0)) return false;
+        if (L.like[t][v][u] < 0 || L.like[t][v][u] >= 30 || L.like[t][v][u] != L.like[t][u][v]) return false;
   return true;
 }
-static_assert(like_table_valid(), "18 entries serve all six types");
+static_assert(like_table_valid(), "30 entries serve all six types");
 
 // Four times the row of a point from the coefficients and values of its
-// stencil neighbours (as the walk's, the sum over its tets' edges at the point);
-// in(t, v): its type-t tet with the point as vertex v is in the macro; UNIFORM:
-// all lanes have the same macro.
+// stencil neighbours; in(t, v): its type-t tet with the point as vertex v is
+// in the macro; UNIFORM: all lanes have the same macro.  (The walk's differences
+// against the point would need 18 entries, FP64 3,072 tets at level 3 37 us, but make
+// FP32 rows up to 3 % less exact.)
 template <bool UNIFORM, typename T, class In>
 __device__ __forceinline__ T vc3_row(const MacroDev& M, const T* kv, const T* xv, In in) {
   constexpr ElemTable E = elem_table(3);
   constexpr LikeTable L = like_table();
-  constexpr int centre = stencil_table(3).centre;
-  T w[18], d[15];
+  T e[30];
 #pragma unroll
   for (int t = 0; t < 3; ++t)
 #pragma unroll
-    for (int v = 0; v < 3; ++v)
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
-      for (int u = v + 1; u < 4; ++u) {
-        const T& e = Prec<T>::K(M, t)[4 * v + u];
-        w[L.like[t][v][u]] = UNIFORM ? uniform(e) : e;
+      for (int u = v; u < 4; ++u) {
+        const T& k = Prec<T>::K(M, t)[4 * v + u];
+        e[L.like[t][v][u]] = UNIFORM ? uniform(k) : k;
       }
   __builtin_amdgcn_sched_barrier(0);  // every load before the sums
-#pragma unroll
-  for (int o = 0; o < 15; ++o) d[o] = xv[o] - xv[centre];
   T acc = T(0);
 #pragma unroll
   for (int t = 0; t < E.ntypes; ++t) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const T ks = kv[tet_slot(t, v, 0)] + kv[tet_slot(t, v, 1)] + kv[tet_slot(t, v, 2)] + kv[tet_slot(t, v, 3)];
-      T r = T(0);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u != v) r = fma(w[L.like[t][v][u]], d[tet_slot(t, v, u)], r);
+      const int s0 = tet_slot(t, v, 0), s1 = tet_slot(t, v, 1), s2 = tet_slot(t, v, 2), s3 = tet_slot(t, v, 3);
+      const T ks = kv[s0] + kv[s1] + kv[s2] + kv[s3];
+      T r = e[L.like[t][v][0]] * xv[s0];
+      r = fma(e[L.like[t][v][1]], xv[s1], r);
+      r = fma(e[L.like[t][v][2]], xv[s2], r);
+      r = fma(e[L.like[t][v][3]], xv[s3], r);
       acc = in(t, v) ? fma(ks, r, acc) : acc;
     }
   }
