@@ -45,10 +45,11 @@ inline int xcd_grid_runs(int nwg, XcdRuns r) {
 // DoFs, other boundary points) that take longer than the walk's; at the head of the
 // first chunk they all fall to one XCD (512 triangles at level 6: FP64 apply 10.2
 // us, 14.9 so; P2 10.4 and 23; 32 at level 9, two FP32 sweeps 32.4 and 38.5).  Up
-// to kLeadMin of them, one for each CU of that XCD, stay there: they share their CUs with
-// fewer others than anywhere else (two triangles at level 11, eight of them:
-// FP32 P2 9.8 us, 11.4 dealt out).
-constexpr int kLeadMin = 32;
+// to kLeadMin of them, one for each CU of that XCD, stay there, and so do up to one
+// in kLeadShare (a fifth of the chunk): they share their CUs with fewer others than
+// anywhere else (two triangles at level 11, eight of them: FP32 P2 9.8 us, 11.4 dealt
+// out; 13 at level 10, 48 of 2,100: 13.6 and 15.2).
+constexpr int kLeadMin = 32, kLeadShare = 40;
 // In larger launches, where runs deal them out, leading workgroups of one in
 // kLeadSpread or more are spread evenly among the others: the lines they share with
 // the walk are then in the caches (3,200 triangles at level 7, 4.9 %, FP64 apply 168 ->
@@ -59,7 +60,9 @@ MF_HD int xcd_spread(int p, int nwg, int lead) {
   const int before = (int)((int64_t)p * lead / nwg), upto = (int)((int64_t)(p + 1) * lead / nwg);
   return upto > before ? before : lead + p - before;
 }
-MF_HD int xcd_head(int lead) { return lead > kLeadMin ? kXCD * ((lead + kXCD - 1) / kXCD) : 0; }
+MF_HD int xcd_head(int nwg, int lead) {
+  return lead > kLeadMin && (int64_t)lead * kLeadShare > nwg ? kXCD * ((lead + kXCD - 1) / kXCD) : 0;
+}
 MF_HD int xcd_wg_at(int block, int nwg, int lead, int lead2, XcdRuns r) {
   if (nwg >= r.from) {
     const int p = xcd_wg_at(block, nwg, r);
@@ -67,7 +70,7 @@ MF_HD int xcd_wg_at(int block, int nwg, int lead, int lead2, XcdRuns r) {
   }
   int first = 0;
   for (int l : {lead, lead2}) {
-    const int head = xcd_head(l);
+    const int head = xcd_head(nwg, l);
     if (block < head) {
       const int n = xcd_wg_at(block, l);
       return n < 0 ? -1 : first + n;
@@ -81,7 +84,7 @@ MF_HD int xcd_wg_at(int block, int nwg, int lead, int lead2, XcdRuns r) {
 }
 inline int xcd_grid(int nwg, int lead, int lead2, XcdRuns r) {
   if (nwg >= r.from) return xcd_grid_runs(nwg, r);
-  const int h = xcd_head(lead), h2 = lead == 0 || h > 0 ? xcd_head(lead2) : 0;
+  const int h = xcd_head(nwg, lead), h2 = lead == 0 || h > 0 ? xcd_head(nwg, lead2) : 0;
   return h + h2 + xcd_grid(nwg - (h > 0 ? lead : 0) - (h2 > 0 ? lead2 : 0));
 }
 

@@ -37,7 +37,7 @@ int main() {
           if (nwg >= r.from) continue;
           for (int k = 0; k < 2; ++k) {
             const int l = k == 0 ? lead : lead2;
-            if (l <= kLeadMin || (k == 1 && lead > 0 && lead <= kLeadMin)) continue;
+            if (xcd_head(nwg, l) == 0 || (k == 1 && lead > 0 && xcd_head(nwg, lead) == 0)) continue;
             for (int q = 0; q < kXCD; ++q)
               if (share[k][q] > (l + kXCD - 1) / kXCD) return fail("one XCD takes too many", nwg, lead, lead2);
           }
