@@ -49,12 +49,13 @@ __device__ __forceinline__ int xcd_wg_lead(int nwg, int lead, int lead2, XcdRuns
 // 424 -> 415.  13 triangles at level 10: FP64 (3,600 workgroups) 31.6 -> 31.1,
 // FP32 (1,900) 19.4 -> 20.4, one triangle at level 10 5.5 -> 5.7.
 constexpr XcdRuns kRuns2{3000, 5};
-// From this side on the 2D launches that gain from it cap their workgroups per CU.
-// On shorter rows most tiles lie on a macro's boundary, whose latency needs the
-// waves: variable coefficient, FP32, 3,200 triangles at levels 6 and 7 39.5 and 103
-// us without, 43.5 and 116 with the cap (FP64 level 6 51.5 and 54.5); two FP32 sweeps
-// at level 7 278 and 304; 32 triangles at level 10 41.3 and 40.6.
-constexpr int kCapN = 1024;
+// From this side on the 2D launches that gain from it cap their workgroups per CU
+// (64 triangles at level 9, FP64 variable coefficient: 41.0 -> 39.0 us).  On shorter
+// rows most tiles lie on a macro's boundary, whose latency needs the waves: variable
+// coefficient, FP32, 3,200 triangles at levels 6 and 7 39.5 and 103 us without, 43.5
+// and 116 with the cap (FP64 level 6 51.5 and 54.5); two FP32 sweeps at level 7 225 and
+// 251.
+constexpr int kCapN = 512;
 // The 3D walks of fine levels: runs of 16.  N = 256, FP64 apply / Jacobi /
 // residual 73.6 / 94.0 / 93.2 us against 75.3 / 96 / 96 with one chunk per XCD
 // (runs of 4: 74.8 / 94.3 / 93.7, of 64: 76.8 / 98.9 / 98.7).
