@@ -46,6 +46,18 @@ constexpr int ring2(int H) { return H < 8 ? H : 8; }
 
 static_assert(kTileH2 % ring2(kTileH2) == 0 && kTileH2F % ring2(kTileH2F) == 0, "ring depth must divide the tile height");
 
+// A constant of the macro, the same for every lane.  Beside the shared DoFs' path
+// the compiler no longer reads it as a scalar by itself.  Held per lane, FP64 kernels
+// need 14 to 16 registers more and lose a wave per SIMD (one triangle at level 12:
+// residual 36.2 us, 33.5 as scalars; norm of a residual 55.0 and 49.5).  In FP32 they
+// reach eight waves either way, and the walk waits longer for the scalars (Jacobi at
+// level 11, two sweeps: 20.7 us and 21.6).
+template <typename T, class V>
+__device__ __forceinline__ V macro_const(const V& v) {
+  if constexpr (sizeof(T) == 8) return uniform(v);
+  else return v;
+}
+
 // Copies the 16 x 16 partial-stencil table of macro M into W with `nthreads`
 // threads starting at `first` (a wave or the whole workgroup).
 template <typename T>
@@ -63,7 +75,7 @@ __device__ __forceinline__ void finish_interior(const MacroDev& M, T acc, T xc, 
                                                 double& mx) {
   T out;
   if (MODE == kApply || MODE == kApplyDot) out = acc;
-  else if (MODE == kJacobi || MODE == kJacobi2) out = fma(omega * Prec<T>::invd(M), bv - acc, xc);
+  else if (MODE == kJacobi || MODE == kJacobi2) out = fma(omega * macro_const<T>(Prec<T>::invd(M)), bv - acc, xc);
   else if (MODE == kResidual) out = bv - acc;
   else out = bv;
   if (MODE != kNormB) st(yp, out);
@@ -186,18 +198,19 @@ __device__ __forceinline__ void tile2d(const int x0, const int y0, const MacroDe
                                        T omega, double& ss, double& mx) {
   constexpr int FM = full_mask(2);
   const int lane = threadIdx.x & (kWave - 1);
-  const int N = M.N;
+  const int N = macro_const<T>(M.N);
   const int x = x0 - 1 + lane;
   constexpr int kH = H, kU = ring2(H);
   const int y1 = min(y0 + kH, N - x0 + 1);  // rows y0 .. y1-1 (x0 + y <= N)
-  X += M.base;
-  Y += M.base;
+  const int64_t base = macro_const<T>(M.base);
+  X += base;
+  Y += base;
   constexpr bool kZ = MODE == kJacobi2;  // X is b: scaled to the iterate when its row is first used
   constexpr bool kB = MODE != kApply && !kZ;
-  if (kB) B += M.base;
+  if (kB) B += base;
   T wi[7];
 #pragma unroll
-  for (int o = 0; o < 7; ++o) wi[o] = Prec<T>::w(M, FM, o);
+  for (int o = 0; o < 7; ++o) wi[o] = macro_const<T>(Prec<T>::row(M, FM)[o]);
   T bid[3] = {T(0), T(0), T(0)};
   if (MODE == kJacobi || MODE == kJacobi2) {
     constexpr int c = stencil_table(2).centre;
@@ -273,20 +286,21 @@ __device__ __forceinline__ void tile2d_fast(const int x0, const int y0, const Ma
                                             double& mx) {
   constexpr int kH = H, kU = ring2(H);
   const int lane = threadIdx.x & (kWave - 1);
-  const int N = M.N;
+  const int N = macro_const<T>(M.N);
   const bool out_lane = (unsigned)(lane - 1) < (unsigned)kTileW;
   const unsigned col = (unsigned)(x0 - 1 + lane) * (unsigned)sizeof(T);
   T wi[7];
 #pragma unroll
-  for (int o = 0; o < 7; ++o) wi[o] = Prec<T>::w(M, full_mask(2), o);
+  for (int o = 0; o < 7; ++o) wi[o] = macro_const<T>(Prec<T>::row(M, full_mask(2))[o]);
   // cursors: byte address of the next row and the byte step to the one after
-  const char* px = (const char*)(X + M.base + rs32(N, y0 - 1));
+  const int64_t base = macro_const<T>(M.base);
+  const char* px = (const char*)(X + base + rs32(N, y0 - 1));
   int sx = (N + 2 - y0) * (int)sizeof(T);
-  char* py = (char*)(Y + M.base + rs32(N, y0));
+  char* py = (char*)(Y + base + rs32(N, y0));
   int sy = (N + 1 - y0) * (int)sizeof(T);
   constexpr bool kZ = MODE == kJacobi2, kB = MODE != kApply && !kZ;
   const T zi = kZ ? omega * Prec<T>::zinv(M, full_mask(2)) : T(1);
-  const char* pb = kB ? (const char*)(B + M.base + rs32(N, y0)) : nullptr;
+  const char* pb = kB ? (const char*)(B + base + rs32(N, y0)) : nullptr;
   int sb = sy;
   auto ldx = [&]() -> T {
     const T v = *(const T*)(px + col);
@@ -360,7 +374,7 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (same) {
     bool need = false;
     if (m0 >= 0) {
-      const int N0 = a.md[m0].N;
+      const int N0 = macro_const<T>(a.md[m0].N);
 #pragma unroll
       for (int k = 0; k < kWavesPerWG; ++k) need = need || tile_on_boundary<H>(a.tiles[n * kWavesPerWG + k], N0);
     }
@@ -368,7 +382,7 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
       load_wtab<T>(a.md[m0], wtab[0], 0, kWG);
       __syncthreads();
     }
-  } else if (t.macro >= 0 && tile_on_boundary<H>(t, a.md[t.macro].N)) {
+  } else if (t.macro >= 0 && tile_on_boundary<H>(t, macro_const<T>(a.md[t.macro].N))) {
     load_wtab<T>(a.md[t.macro], wtab[wv], wv * kWave, kWave);
     __builtin_amdgcn_wave_barrier();
   }
@@ -376,7 +390,7 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (t.macro >= 0) {
     const MacroDev& M = a.md[t.macro];
     WTab<T> W = wtab[same ? 0 : wv];
-    if (tile2d_inner<H, MODE>(t.x0, t.y0, M.N)) tile2d_fast<T, MODE, H>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
+    if (tile2d_inner<H, MODE>(t.x0, t.y0, macro_const<T>(M.N))) tile2d_fast<T, MODE, H>(t.x0, t.y0, M, a.X, a.Y, a.B, a.omega, ss, mx);
     else tile2d<T, MODE, H>(t.x0, t.y0, M, W, a.X, a.Y, a.B, a.omega, ss, mx);
   } else if (t.macro != -1) {
     edge_rows<T, 2, MODE>(a, t, ss, mx);
