@@ -58,6 +58,16 @@ __device__ __forceinline__ V macro_const(const V& v) {
   else return v;
 }
 
+// A single mesh without shared DoFs takes to runs later: one triangle at level 12, FP64
+// apply / two Jacobi sweeps / residual 22.5 / 64.3 / 32.4 us against 23.6 / 66.2 / 33.3
+// in runs.  With shared DoFs in the launch there is no one line: up to 6,000 workgroups
+// five triangles at level 11 would gain 4 %, 20 at level 10 would lose 2 % and 3,200
+// at level 6 in FP32 7 to 11 %.
+template <class A>
+MF_HD wave::XcdRuns runs2(const Launch<A>& l) {
+  return wave::XcdRuns{l.nseg > 0 || l.lead > 0 ? wave::kRuns2.from : 2 * wave::kRuns2.from, wave::kRuns2.shift};
+}
+
 // Copies the 16 x 16 partial-stencil table of macro M into W with `nthreads`
 // threads starting at `first` (a wave or the whole workgroup).
 template <typename T>
@@ -356,7 +366,7 @@ __device__ __forceinline__ bool tile_on_boundary(const Tile& t, int N) {
 
 template <typename T, int MODE, int H>
 __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T>> L) {
-  const int g = wave::xcd_wg_lead(L.nwg, L.lead, 0, wave::kRuns2);
+  const int g = wave::xcd_wg_lead(L.nwg, L.lead, 0, runs2(L));
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
@@ -486,7 +496,7 @@ int stencil_lds(int nwg, int N) {
 template <typename T, int MODE>
 int run_stencil(int rows, int N, const Launch<StencilArgs<T>>& l, hipStream_t s) {
   if (l.nwg <= 0) return MF_OK;
-  const dim3 grid(wave::xcd_grid(l.nwg, l.lead, 0, wave::kRuns2)), wg(kWG);
+  const dim3 grid(wave::xcd_grid(l.nwg, l.lead, 0, runs2(l))), wg(kWG);
   const int lds = stencil_lds<T, MODE>(l.nwg, N);
   if (rows == kTileShort[0]) {
     hipLaunchKernelGGL((stencil_kernel<T, MODE, kTileShort[0]>), grid, wg, lds, s, l);
