@@ -214,8 +214,8 @@ struct VarcoefArgs {
 // Bound: vector issue and memory about equally.  Cube, against a lane per
 // point that gathers 30 values and forms 24 element rows: N = 256 FP64 301 -> 138
 // us, FP32 143 -> 75 (24 and 12 B/DoF: 3.0 and 2.7 TB/s), N = 128 46 -> 30 and 27 ->
-// 20; of these the boundary launch takes 25 and 12 us.  More than two
-// workgroups per CU (launch bound 3) spill.
+// 20 (with the boundary in the same launch 126 and 62, 21.4 and 14.1).  More than two
+// workgroups per CU spill with bands of two rows in FP64.
 template <typename T, int R>
 __device__ __forceinline__ void vc_walk3(const Tile& t, const MacroDev& M, const T* __restrict__ K,
                                          const T* __restrict__ X, T* __restrict__ Y) {
@@ -346,8 +346,7 @@ __device__ __forceinline__ void vc_walk3(const Tile& t, const MacroDev& M, const
 // Every vertex of a tet around a point is the point or one of its 15 stencil
 // neighbours.  Bound: the gathers (rows of a face lie a slice or a row apart, and
 // the copies of edges and vertices have a macro per lane).  A workgroup per tile,
-// with a face's two copies in two waves, beside the walk's launch: in one kernel with
-// it, the boundary's registers made the walk spill.  Against all 96 entries of
+// with a face's two copies in two waves.  Against all 96 entries of
 // the six matrices (256 registers in FP64): cube at level 7 FP64 27.7 -> 24.7 us, level
 // 8 137 -> 130; 3,072 tets at level 3 FP64 109 -> 43, FP32 35.8 -> 28.1, 384 at level 5
 // FP64 87 -> 65.
@@ -569,49 +568,50 @@ __device__ __forceinline__ void vc3_edges(const VarcoefArgs<T>& a, const Tile& t
   if (live) a.Y[e.idx] = e.dirichlet ? a.X[e.idx] : acc * T(0.25);
 }
 
+// One launch: the boundary's workgroups first (its gathers wait while the walk
+// streams), then the walk's.  Against a launch each: a tet at levels 6 and 7 FP64 9.4 and
+// 9.9 -> 5.7 and 6.2 us, FP32 8.8 and 9.1 -> 5.2 and 5.4; the cube at level 7 24.8 ->
+// 21.4, at level 8 130 -> 126 and 65 -> 62.  In FP64 the boundary needs more registers
+// than bands of one row; held to 168 (none spill) both keep three workgroups per CU: 384
+// tets at level 5 54.4 us (64 as two launches, 67 at 170 registers and two workgroups),
+// 3,072 at level 3 33.2 (43).
 template <typename T, int R>
-__global__ __launch_bounds__(kWG, 2) void varcoef3d_kernel(const VarcoefArgs<T> a, int nwg) {
-  const int g = wave::xcd_wg_runs(nwg, wave::kRuns3);
+__global__ __launch_bounds__(kWG, R == 1 ? 3 : 2) void varcoef3d_kernel(const VarcoefArgs<T> a, int nb, int nwg) {
+  __shared__ T part[kWG];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), head = wave::xcd_grid(nb);
+  if ((int)blockIdx.x < head) {
+    if ((int)blockIdx.x >= nb) return;
+    const Tile t = load_seg(a.btiles, blockIdx.x);
+    if (t.macro == kFaceTile) vc3_faces<T>(a, t, wv, part);
+    else if (t.macro != -1 && wv == 0) vc3_edges<T>(a, t);
+    return;
+  }
+  const int g = wave::xcd_wg_at(blockIdx.x - head, nwg, wave::kRuns3);
   if (g < 0) return;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Tile t = load_seg(a.tiles, g * kWavesPerWG + wv);
   if (t.macro >= 0) vc_walk3<T, R>(t, a.md[t.macro], a.K, a.X, a.Y);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kWG) void varcoef3d_boundary_kernel(const VarcoefArgs<T> a) {
-  __shared__ T part[kWG];
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Tile t = load_seg(a.btiles, blockIdx.x);
-  if (t.macro == kFaceTile) vc3_faces<T>(a, t, wv, part);
-  else if (t.macro != -1 && wv == 0) vc3_edges<T>(a, t);
-}
-
 // Bands of R rows: those of shape3_varcoef (FP64 up to 2, FP32 up to 3).
 template <typename T, int R = sizeof(T) == 8 ? 2 : 3>
-int run_vc3(int rows, const VarcoefArgs<T>& a, int nwg, hipStream_t s) {
+int run_vc3(int rows, const VarcoefArgs<T>& a, int nb, int nwg, hipStream_t s) {
   if (rows == R) {
-    hipLaunchKernelGGL((varcoef3d_kernel<T, R>), dim3(wave::xcd_grid_runs(nwg, wave::kRuns3)), dim3(kWG), 0, s, a, nwg);
+    const dim3 grid(wave::xcd_grid(nb) + wave::xcd_grid_runs(nwg, wave::kRuns3));
+    hipLaunchKernelGGL((varcoef3d_kernel<T, R>), grid, dim3(kWG), 0, s, a, nb, nwg);
     return MF_OK;
   }
-  if constexpr (R > 1) return run_vc3<T, R - 1>(rows, a, nwg, s);
+  if constexpr (R > 1) return run_vc3<T, R - 1>(rows, a, nb, nwg, s);
   else return set_error(MF_EINVAL, "internal: no variable-coefficient walk over bands of " + std::to_string(rows) + " rows");
 }
 
 template <typename T>
 int run_varcoef3d(const Level& L, const void* k, const void* x, void* y, hipStream_t s) {
   constexpr int i = sizeof(T) == 8 ? 0 : 1;
-  const int nwg = (int)(L.vtiles[i].size() / kWavesPerWG), R = shape3_varcoef(L.N, i == 1).R;
+  const int nb = (int)L.btiles.size(), nwg = (int)(L.vtiles[i].size() / kWavesPerWG);
   const VarcoefArgs<T> a{L.dev.vtiles[i], L.dev.btiles, L.dev.md, L.dev.faces, L.dev.edges,
                          (const T*)k,      (const T*)x,   (T*)y};
-  if (nwg > 0)
-    if (const int rc = run_vc3<T>(R, a, nwg, s)) return rc;
-  const int nb = (int)L.btiles.size();
-  // five workgroups per CU where there are face tiles (FP32, which seven would fit: 48 tets at level 6 32.5 -> 30.6 us, 3,072
-  // at level 4 62 -> 63.6; without face tiles, at level 3, 28.4 -> 31.4)
-  if (nb > 0)
-    hipLaunchKernelGGL((varcoef3d_boundary_kernel<T>), dim3(nb), dim3(kWG),
-                       L.N >= kMinFaceN ? wave::lds_cap(nb, 0, 5, kWG * (int)sizeof(T)) : 0, s, a);
+  if (nb + nwg > 0)
+    if (const int rc = run_vc3<T>(shape3_varcoef(L.N, i == 1).R, a, nb, nwg, s)) return rc;
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? MF_OK : set_error(MF_EDEVICE, hipGetErrorString(e));
 }

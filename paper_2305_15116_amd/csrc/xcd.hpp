@@ -18,7 +18,7 @@ MF_HD int xcd_wg_at(int block, int nwg) {
   const int n = k * chunk + j;
   return n < nwg ? n : -1;
 }
-inline int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
+MF_HD int xcd_grid(int nwg) { return kXCD * ((nwg + kXCD - 1) / kXCD); }
 
 // The same for launches of at least `from` workgroups with runs of 2^shift
 // consecutive workgroups dealt to the XCDs in turn: neighbours still share an
