@@ -64,6 +64,9 @@ MF_HD int xcd_head(int nwg, int lead) {
   return lead > kLeadMin && (int64_t)lead * kLeadShare > nwg ? kXCD * ((lead + kXCD - 1) / kXCD) : 0;
 }
 MF_HD int xcd_wg_at(int block, int nwg, int lead, int lead2, XcdRuns r) {
+  // Few of them stay where they are under every rule (runs start at more than
+  // kLeadMin * kLeadSpread workgroups).  Asked first: 0.1 us of the smallest P2 applies.
+  if (lead <= kLeadMin && lead2 <= kLeadMin) return xcd_wg_at(block, nwg, r);
   if (nwg >= r.from) {
     const int p = xcd_wg_at(block, nwg, r);
     return p < 0 || lead2 > 0 || (int64_t)lead * kLeadSpread < nwg ? p : xcd_spread(p, nwg, lead);
