@@ -245,8 +245,8 @@ typedef struct {
  * to 5 after a miss that ends at max_iter: the last recomputed one; MINRES
  * recomputes it at max_iter).  Returns MF_OK, MF_NOT_CONVERGED (x = last
  * iterate) or an error (MF_ENUMERIC if MINRES meets a preconditioner that is
- * not positive definite).  Synchronous; one device-to-host copy of two
- * doubles per iteration (MINRES: two), plus one per recomputed residual in
+ * not positive definite).  Synchronous; the host waits for two doubles once
+ * per iteration (MINRES: twice), and once more per recomputed residual in
  * modes 2 to 5. */
 int vcycle_solve(const mf_mesh* mesh, int level, const double* b_dev, double* x_dev, void* workspace_dev,
                  const mf_solve_opts* opts, mf_solve_info* info, void* stream);

@@ -79,7 +79,7 @@ int reduce_sync(const double* part, int64_t np, double* result_dev, double out[2
   return MF_OK;
 }
 
-// r = b - A x with partials in `part`; reduces to result_dev and copies back.
+// r = b - A x with partials in `part`, reduced to result_dev and to the host.
 int residual_norm(const mf_mesh* m, const Level& L, int dtype, const void* b, const void* x, void* r, double* part,
                   double* result_dev, double* ss, double* mx, hipStream_t s) {
   const int64_t np = stencil_partials(L, dtype);

@@ -41,7 +41,7 @@ MF_HD int find_seg(const int32_t* wg0, int nseg, int g) {
 template <typename T>
 struct StencilArgs {
   const Tile* tiles;
-  int ntiles;  // wave tiles (one partial slot each)
+  int ntiles;  // wave tiles (kWavesPerWG per workgroup; one partial slot per workgroup)
   int nwg;     // workgroups of tiles (natural order)
   const MacroDev* md;
   const T* X;
@@ -276,7 +276,7 @@ GroupArgs<T> iface_args(const Level& L, void* y, const void* b) {
 }
 inline int iface_blocks(const Level& L) { return (int)L.iface_blocks(); }
 
-// restriction: coarse points gather fine values; prolongation: fine points.
+// Restriction and prolongation: both over segments of coarse points.
 // At most kTransferBlocks workgroups; each wave walks several segments.
 constexpr int kTransferBlocks = 8192;
 inline int transfer_blocks(int nseg) {

@@ -23,10 +23,10 @@ struct LevelDev {
   Tile* tiles = nullptr;       // interior wave tiles, padded to a multiple of kWavesPerWG
   Tile* tiles_f32 = nullptr;   // 2D FP32 wave tiles
   Tile* tiles_short = nullptr;
-  Tile* btiles = nullptr;      // 3D face and edge tiles
+  Tile* btiles = nullptr;      // face and edge tiles by themselves
   Tile* vtiles[2] = {nullptr, nullptr};  // variable-coefficient column tiles (FP64, FP32)
   FaceDev* faces = nullptr;    // 3D macro faces
-  EdgeCopy* edges = nullptr;   // 3D copies of macro edge and vertex DoFs
+  EdgeCopy* edges = nullptr;   // copies of macro edge and vertex DoFs (2D: of the shared ones)
   Tile* segs = nullptr;        // row segments of 64 points covering every storage point
   Tile* psegs = nullptr;       // slice segments: 64 consecutive storage points of one slice
   int32_t* sbase = nullptr;    // first macro-local index of each slice z = 0 .. N + 1 (3D)
@@ -38,7 +38,7 @@ struct LevelDev {
   int64_t* xcpidx = nullptr;  // storage index of every copy (exchange list)
   double* xgrp_invdiag = nullptr;
   float* xgrp_invdiagf = nullptr;
-  double* part = nullptr;       // norm partials: ntiles + iface blocks, then the same again for max
+  double* part = nullptr;       // norm partials: a sum per workgroup of tiles, then as many maxima
   double* result = nullptr;     // 2 doubles: sum of squares, max |.|
   // coarse direct solve (levels <= 2 only)
   double* cinv = nullptr;
@@ -63,8 +63,8 @@ struct Level {
   int short_rows = 0;
   std::vector<Tile> btiles;     // the face and edge tiles by themselves, one per workgroup (kFaceRunsWG)
   std::vector<Tile> vtiles[2];  // 3D: column tiles of the variable-coefficient walk (FP64, FP32)
-  std::vector<FaceDev> faces;   // 3D: macro faces, and the copies of the edge and vertex DoFs, that tiles name
-  std::vector<EdgeCopy> edges;
+  std::vector<FaceDev> faces;   // 3D: macro faces that tiles name
+  std::vector<EdgeCopy> edges;  // copies of edge and vertex DoFs (2D: of the shared ones) that tiles name
   std::vector<Tile> segs;       // per-point row segments
   // per-point slice segments {macro, first slice-local index, 0, z}: a
   // slice (the whole macro in 2D) is contiguous in storage, so its points

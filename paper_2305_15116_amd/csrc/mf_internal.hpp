@@ -113,7 +113,8 @@ struct FaceDev {
   float invf;
 };
 
-// A copy of a macro edge or vertex DoF (3D).
+// A copy of a macro edge or vertex DoF (2D: of a shared one; 3D below kMinFaceN: of
+// a face point too).
 struct EdgeCopy {
   int64_t idx;  // storage index
   int32_t macro;

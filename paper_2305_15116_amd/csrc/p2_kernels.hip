@@ -17,8 +17,8 @@
 // take a lane per copy and sum these over the copies; Dirichlet ones copy x.
 //
 // Bound: memory (x read, y written).  Against a launch each for the interior, the
-// boundary and the sums over shared DoFs: five triangles at level 11 FP64 159.7 ->
-// 147.3 us (4.6 TB/s), FP32 90.2 -> 84.5; seven at level 7 12.8 -> 6.4, 11.4 -> 5.9.
+// boundary and the sums over shared DoFs: five triangles at level 11 FP64 157.8 ->
+// 149.4 us (4.5 TB/s), FP32 90.2 -> 84.5; seven at level 7 12.8 -> 6.4, 11.4 -> 5.9.
 // Fewer workgroups at once (5, 4, 3 per CU) are slower: 149, 157, 179 us.
 
 #include <hip/hip_runtime.h>

@@ -194,11 +194,6 @@ __device__ __forceinline__ int64_t lidx(int N, int x, int y, int z) {
   return DIM == 2 ? idx2(N, x, y) : idx3(N, x, y, z);
 }
 
-// Restriction r_c = P^T r_f on one macro: a coarse point P gathers the fine
-// point 2P (weight 1) and the fine points 2P + d for the stencil offsets d
-// (weight 1/2) — the fine points whose interpolation uses P — counting only
-// fine points this macro owns, so that the sum over the copies of P takes each fine DoF
-// once.  Dirichlet fine points are skipped.
 // Segment and macro records are read-only for the launch: read them through
 // the constant address space (scalar loads, scalar registers).
 __device__ __forceinline__ Tile load_seg(const Tile* segs, int si) {
@@ -239,6 +234,11 @@ __device__ __forceinline__ void nbr_offsets3(int N, int y, int z, int (&o)[15]) 
   for (int k = 0; k < 15; ++k) o[k] = t[k];
 }
 
+// Restriction r_c = P^T r_f on one macro: a coarse point P gathers the fine
+// point 2P (weight 1) and the fine points 2P + d for the stencil offsets d
+// (weight 1/2) — the fine points whose interpolation uses P — counting only
+// fine points this macro owns, so that the sum over the copies of P takes each fine DoF
+// once.  Dirichlet fine points are skipped.
 template <typename T, int DIM>
 __device__ __forceinline__ T restrict_partial(const TransferArgs<T>& a, int macro, int x, int y, int z) {
   constexpr StencilTable ST = stencil_table(DIM);

@@ -36,10 +36,8 @@ namespace mf {
 
 namespace {
 
-
 using wave::dn1;
 using wave::up1;
-
 
 // Rows loaded ahead by a tile of H rows.
 constexpr int ring2(int H) { return H < 8 ? H : 8; }
@@ -75,9 +73,6 @@ __device__ __forceinline__ void load_wtab(const MacroDev& M, WTab<T> W, int firs
   for (int i = (int)threadIdx.x - first; i < 256; i += nthreads)
     if (i >= 0) W[i >> 4][i & 15] = Prec<T>::w(M, i >> 4, i & 15);
 }
-
-
-
 
 // Interior finish of one row value (full stencil, interior point).
 template <typename T, int MODE>

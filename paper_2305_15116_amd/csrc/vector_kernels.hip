@@ -33,7 +33,6 @@ __device__ __forceinline__ uint64_t splitmix(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-
 // x = 2u - 1 with u from the hash chained over (seed, sorted key pairs).
 template <typename T, int DIM>
 __global__ __launch_bounds__(kWG) void fill_random_kernel(const Tile* __restrict__ segs, int nseg,
@@ -71,11 +70,6 @@ __global__ __launch_bounds__(kWG) void fill_random_kernel(const Tile* __restrict
   const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
   X[M.base + lidx<DIM>(N, x, y, z)] = (T)(2.0 * u - 1.0);
 }
-
-
-
-
-
 
 // b_c = P^T r_f.  Workgroups 0 .. a.nb - 1 (none where a second launch sums the
 // copies) take
