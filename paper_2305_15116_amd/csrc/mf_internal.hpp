@@ -53,9 +53,10 @@ MF_HD constexpr Shape3 shape3(int N) {
 constexpr int kMaxR3 = 4;
 // The variable-coefficient walk's: it forms R + 1 rows and PZ + 1 layers of
 // cells for the R x PZ points of a column, and holds the rows of two vectors
-// (FP64 R = 3 spills).  Cube, us per apply: N = 256 FP64 R = 2, PZ = 8 / 12 / 6
-// 145 / 143 / 154, R = 1 159; FP32 R = 3, PZ = 12 / 8 77.0 / 78.5, R = 4, PZ = 8 81.3, R = 2
-// 79.5; N = 128 FP64 R = 2 29.8, R = 3 47.
+// (FP64 R = 3 spills).  Cube, us per apply with the boundary in a launch of its own
+// (in the walk's launch the shapes taken are at 126, 62 and 21): N = 256 FP64 R = 2, PZ = 8
+// / 12 / 6 145 / 143 / 154, R = 1 159; FP32 R = 3, PZ = 12 / 8 77.0 / 78.5, R = 4, PZ = 8
+// 81.3, R = 2 79.5; N = 128 FP64 R = 2 29.8, R = 3 47.
 MF_HD constexpr Shape3 shape3_varcoef(int N, bool f32) {
   return N >= 256 ? (f32 ? Shape3{3, 12} : Shape3{2, 12}) : N >= 64 ? Shape3{2, 4} : Shape3{1, 2};
 }
