@@ -100,7 +100,7 @@ struct RowMasks {
 // lie on the y = 0 edge: those go through the general per-lane path.  In other
 // rows a boundary lane is the row's first point (x = 0, only in tiles starting
 // at x0 = 0, tile_left), its last (on the far edge x + y = N), or both.  A row
-// without such a lane takes the interior stencil from scalar registers, and so
+// without such a lane takes the interior stencil (macro_const), and so
 // does a row whose boundary lanes are all Dirichlet (they copy x) or shared
 // points (written by the edge tiles).  Any
 // other row takes, in every lane, the partial stencil of the lane's own
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
   if (g < 0) return;
   StencilArgs<T> a;
   const int n = resolve(L, g, a);
-  // wave-uniform tile index: the tile and its macro constants load into scalar registers
+  // wave-uniform tile index: every lane reads the same tile and macro constants
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ti = n * kWavesPerWG + wv;
   const Tile t = a.tiles[ti];
@@ -407,9 +407,10 @@ __global__ __launch_bounds__(kWG) void stencil_kernel(const Launch<StencilArgs<T
 
 // One DoF shared by several macros and not Dirichlet: its copies hold partial
 // rows of the variable-coefficient walk, or the macros' parts of a restriction; sum
-// them in fixed macro order and write the row to every copy.  (With tiles of edge copies in the walk's own launch, as
-// the other 2D passes have them, that walk was slower on large levels: five
-// triangles at level 11 54.0 -> 60.9 us, though seven at level 7 took 5.9 instead of 7.8.)
+// them in fixed macro order and write the row to every copy.  (With tiles of edge
+// copies in the walk's own launch, as the other 2D passes have them, that walk was
+// slower on large levels: five triangles at level 11 54.0 -> 60.9 us, though seven at
+// level 7 took 5.9 instead of 7.8.)
 template <typename T>
 __global__ __launch_bounds__(kIfaceWG) void exchange_kernel(const GroupArgs<T> a) {
   const int g = blockIdx.x * kIfaceWG + threadIdx.x;
