@@ -385,7 +385,7 @@ def main():
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py measures one GPU only: the macro-parallel multi-GPU path is not built "
-              "(every GPU box here has one GPU); run with --gpus 1", file=sys.stderr)
+              "(measured on machines with one GPU); run with --gpus 1", file=sys.stderr)
         sys.exit(2)
     import torch
 
